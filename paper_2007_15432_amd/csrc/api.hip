@@ -91,8 +91,8 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   total += bytes(stmp, sizeof(int64_t));
   total += bytes(n2, sizeof(int32_t)) + bytes(n_cap, sizeof(int32_t));  // parent, visit
   total += bytes(n2, sizeof(WalkNode)) + bytes(n2, sizeof(CellMom));
-  total += bytes(n2, sizeof(int32_t)) + bytes(n2 + 1, sizeof(int64_t));  // group_flag, node_scan
-  total += bytes(n_cap, sizeof(int32_t));                               // group_node
+  total += bytes(n_cap, sizeof(int4)) + bytes(n2 + 1, sizeof(int64_t));  // topo, node_scan
+  total += 3 * bytes(n_cap, sizeof(int32_t));                             // chunk, top and group lists
   total += bytes(n_cap, sizeof(GroupList));
   total += bytes(n_cap, sizeof(int32_t));                                           // group order
   total += bytes(n_cap, sizeof(int32_t)) + bytes(n_cap + 1, sizeof(int64_t));       // row_cnt, csr_ptr
@@ -134,8 +134,10 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   c->visit = A.take<int32_t>(n_cap);
   c->wnode = A.take<WalkNode>(n2);
   c->cmom = A.take<CellMom>(n2);
-  c->group_flag = A.take<int32_t>(n2);
+  c->topo = A.take<int4>(n_cap);
   c->node_scan = A.take<int64_t>(n2 + 1);
+  c->chunk_list = A.take<int32_t>(n_cap);
+  c->top_list = A.take<int32_t>(n_cap);
   c->group_node = A.take<int32_t>(n_cap);
   c->glist = A.take<GroupList>(n_cap);
   c->group_order = A.take<int32_t>(n_cap);

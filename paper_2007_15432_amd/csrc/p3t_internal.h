@@ -60,6 +60,7 @@ struct DevCounters {
   unsigned long long n_near, n_far, n_cell;  // interaction counts
   unsigned long long n_clusters;
   unsigned long long n_chunks;     // subtree roots of the bottom-up moment pass
+  unsigned long long n_top;        // nodes above them
   unsigned long long queue[3];    // persistent queues of the split force kernels
   unsigned long long n_cand;      // neighbour candidates appended (split force)
   unsigned long long n_pairs_d;   // pairs of the parked members' direct terms (p3t_hard_evaluate)
@@ -279,8 +280,10 @@ struct p3t_ctx {
   int32_t *visit = nullptr;
   p3t::WalkNode *wnode = nullptr;
   p3t::CellMom *cmom = nullptr;
-  int32_t *group_flag = nullptr;
-  int64_t *node_scan = nullptr;     // exclusive scan over nodes (2n)
+  int4 *topo = nullptr;             // internal nodes: left, right, first, count (n - 1)
+  int32_t *chunk_list = nullptr;    // subtree roots of the bottom-up moments
+  int32_t *top_list = nullptr;      // nodes above them
+  int64_t *node_scan = nullptr;     // scan scratch (2n + 1)
   int32_t *group_node = nullptr;
   p3t::GroupList *glist = nullptr;
   int32_t *group_order = nullptr;   // groups sorted by work (longest first)

@@ -7,10 +7,11 @@
 //   2. stable radix sort of (key, index); gather of a Morton-ordered SoA copy;
 //   3. binary radix tree over the sorted keys (one thread per internal node,
 //      Karras 2012), ties broken by the sorted position;
-//   4. bottom-up pass (one thread per leaf, second arrival combines): tight
-//      bounding box, mass, centre of mass, traceless quadrupole, max reach;
-//   5. interaction groups: nodes with at most n_group_max particles whose
-//      parent has more.
+//      and the lists of interaction groups (nodes with at most n_group_max
+//      particles whose parent has more) and of the chunks of step 4;
+//   4. bottom-up pass (one thread per lowest node that the walk can reach,
+//      second arrival combines): tight bounding box, mass, centre of mass,
+//      traceless quadrupole, max reach.
 #include "p3t_internal.h"
 
 namespace p3t {
@@ -53,7 +54,8 @@ constexpr int PACK = 9;
 
 __global__ void k_pack(int64_t n, const double *__restrict__ pos, const double *__restrict__ vel,
                        const double *__restrict__ m, const double *__restrict__ ro, const double *__restrict__ rs,
-                       double *__restrict__ rec) {
+                       double *__restrict__ rec, p3t::DevCounters *cnt) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) cnt->n_chunks = cnt->n_top = cnt->n_groups = 0;  // listed by k_gather_tree
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     double *r = rec + PACK * i;
     r[0] = pos[i];
@@ -65,32 +67,6 @@ __global__ void k_pack(int64_t n, const double *__restrict__ pos, const double *
     r[6] = m[i];
     r[7] = ro[i];
     r[8] = rs[i];
-  }
-}
-
-__global__ void k_gather(int64_t n, const int32_t *__restrict__ perm, const double *__restrict__ rec,
-                         double *__restrict__ sx, double *__restrict__ sy, double *__restrict__ sz,
-                         double *__restrict__ svx, double *__restrict__ svy, double *__restrict__ svz,
-                         double *__restrict__ sm, double *__restrict__ sro, double *__restrict__ sinv,
-                         double *__restrict__ sreach, double *__restrict__ srs, int32_t *__restrict__ sid,
-                         unsigned long long *__restrict__ n_chunks) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *n_chunks = 0;  // the radix tree that follows lists the chunk roots
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = perm[k];
-    const double *r = rec + PACK * i;
-    sx[k] = r[0];
-    sy[k] = r[1];
-    sz[k] = r[2];
-    svx[k] = r[3];
-    svy[k] = r[4];
-    svz[k] = r[5];
-    sm[k] = r[6];
-    const double o = r[7], s = r[8];
-    sro[k] = o;
-    sinv[k] = 1.0 / o;
-    sreach[k] = fmax(o, s);
-    srs[k] = s;
-    sid[k] = (int32_t)i;
   }
 }
 
@@ -108,63 +84,160 @@ __global__ void k_regather_xm(int64_t n, const int32_t *__restrict__ sid, const 
 }
 
 // leaves per subtree of the bottom-up moments' first phase (see below)
-constexpr int CHUNK = 1024;
+constexpr int CHUNK = 2048;
 
-// common-prefix length of sorted keys i and j (positions break ties)
-__device__ __forceinline__ int prefix_len(const uint64_t *__restrict__ k, int n, int i, int j) {
-  if (j < 0 || j >= n) return -1;
-  const uint64_t a = k[i], b = k[j];
-  if (a == b) return 64 + __clz((unsigned)(i ^ j));
-  return __clzll(a ^ b);
-}
+// common-prefix length of sorted keys i and j (positions break ties); the
+// keys of [lo, lo + GT_KEYS) are in LDS
+constexpr int GT_T = 256, GT_TILE = 2 * GT_T, GT_HALO = 768, GT_KEYS = GT_TILE + 2 * GT_HALO;
+struct KeyView {
+  const uint64_t *k, *lds;
+  int n, lo;
+  __device__ __forceinline__ uint64_t at(int i) const {
+    const unsigned o = (unsigned)(i - lo);
+    return o < (unsigned)GT_KEYS ? lds[o] : k[i];
+  }
+  __device__ __forceinline__ int prefix(int i, uint64_t a, int j) const {
+    if (j < 0 || j >= n) return -1;
+    const uint64_t b = at(j);
+    if (a == b) return 64 + __clz((unsigned)(i ^ j));
+    return __clzll(a ^ b);
+  }
+};
 
-// Internal node i of the binary radix tree: its key range and split.
-// Also lists the chunk roots of the moments pass (nodes of at most CHUNK
-// leaves whose parent has more; the root if it has at most CHUNK; each is
-// appended by its parent, the root by node 0's thread, n_chunks zeroed
-// before the launch; their order does not matter) and clears the arrival
-// counter of every internal node.
-__global__ void k_radix_tree(int n, const uint64_t *__restrict__ k, p3t::WalkNode *__restrict__ wn,
-                             int32_t *__restrict__ parent, int32_t *__restrict__ chunk_list,
-                             unsigned long long *__restrict__ n_chunks, int32_t *__restrict__ visit) {
-  const int leaf0 = n - 1;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n - 1; i += gridDim.x * blockDim.x) {
-    const int d = (prefix_len(k, n, i, i + 1) - prefix_len(k, n, i, i - 1)) > 0 ? 1 : -1;
-    const int dmin = prefix_len(k, n, i, i - d);
-    int lmax = 2;
-    while (prefix_len(k, n, i, i + lmax * d) > dmin) lmax <<= 1;
-    int l = 0;
-    for (int t = lmax >> 1; t >= 1; t >>= 1)
-      if (prefix_len(k, n, i, i + (l + t) * d) > dmin) l += t;
-    const int j = i + l * d;
-    const int dnode = prefix_len(k, n, i, j);
-    int s = 0, t = l;
-    do {
-      t = (t + 1) >> 1;
-      if (prefix_len(k, n, i, i + (s + t) * d) > dnode) s += t;
-    } while (t > 1);
-    const int split = i + s * d + (d < 0 ? -1 : 0);
-    const int lo = i < j ? i : j, hi = i < j ? j : i;
-    const int left = (lo == split) ? leaf0 + split : split;
-    const int right = (hi == split + 1) ? leaf0 + split + 1 : split + 1;
-    wn[i].left = left;
-    wn[i].right = right;
-    wn[i].first = lo;
-    wn[i].count = hi - lo + 1;
-    parent[left] = i;
-    parent[right] = i;
-    if (i == 0) parent[0] = -1;  // node 0 is the root and never a child
-    visit[i] = 0;
-    const int count = hi - lo + 1;
-    const int cl = (lo == split) ? 1 : split - lo + 1, cr = (hi == split + 1) ? 1 : hi - split;
-    if (count > CHUNK) {
-      if (cl <= CHUNK) chunk_list[atomicAdd(n_chunks, 1ull)] = left;
-      if (cr <= CHUNK) chunk_list[atomicAdd(n_chunks, 1ull)] = right;
-    } else if (i == 0) {
-      chunk_list[atomicAdd(n_chunks, 1ull)] = 0;
+// Into Morton order, and the radix tree over the sorted keys, in one launch
+// (position k: sorted particle k and internal node k).
+//   The particle's record (k_pack) is read once, its rows written.
+//   The internal node's key range and split (Karras 2012) go to topo (left,
+// right, first, count: 16 B per node, so that every later pass over the
+// topology reads coalesced 16-B records).  Each node lists its children that
+// are chunk roots of the moments pass (at most CHUNK leaves, the parent more),
+// and groups (at most ng leaves, the parent more); a node of more than CHUNK
+// leaves lists itself as a top node.  The root is listed by node 0's thread.
+// The lists' order does not matter; a workgroup gathers its entries in LDS and
+// takes their slots with one atomic per list (one per entry queued up on the
+// counter: the flag, scan and compaction launches this replaces were no
+// slower at 2^20 particles).  The arrival counter of every internal node is cleared.
+//   Latency of the binary searches bounds the tree part, so the keys around
+// the tile are in LDS (nearly every search stays within GT_HALO keys); the
+// gather is bound by the scattered 72-B records.  2^20 particles: 75 us, the
+// two separate kernels 45 + 46 us, and 33 us of flag scan and compaction.
+__global__ __launch_bounds__(GT_T) void k_gather_tree(
+    int n, int ng, const int32_t *__restrict__ perm, const double *__restrict__ rec, const uint64_t *__restrict__ keys,
+    double *__restrict__ sx, double *__restrict__ sy, double *__restrict__ sz, double *__restrict__ svx,
+    double *__restrict__ svy, double *__restrict__ svz, double *__restrict__ sm, double *__restrict__ sro,
+    double *__restrict__ sinv, double *__restrict__ sreach, double *__restrict__ srs, int32_t *__restrict__ sid,
+    int4 *__restrict__ topo, int32_t *__restrict__ parent, int32_t *__restrict__ visit,
+    int32_t *__restrict__ chunk_list, int32_t *__restrict__ top_list, int32_t *__restrict__ group_node,
+    p3t::DevCounters *cnt) {
+  __shared__ uint64_t lk[GT_KEYS];
+  // a node lists itself or up to two children per list (the root's thread
+  // the root too, but then no child)
+  __shared__ int lchunk[2 * GT_TILE], lgroup[2 * GT_TILE], ltop[GT_TILE];
+  __shared__ int lcount[3];
+  __shared__ unsigned long long lbase[3];
+  const int t = threadIdx.x, leaf0 = n - 1;
+  for (int base = blockIdx.x * GT_TILE; base < n; base += gridDim.x * GT_TILE) {
+    __syncthreads();
+    if (t < 3) lcount[t] = 0;
+    KeyView K{keys, lk, n, base - GT_HALO};
+    for (int q = t; q < GT_KEYS; q += GT_T) {
+      const int i = base - GT_HALO + q;
+      lk[q] = (i >= 0 && i < n) ? keys[i] : 0ull;
     }
+    __syncthreads();
+    for (int k = base + t; k < min(n, base + GT_TILE); k += GT_T) {
+      {
+        const int i = perm[k];
+        const double *r = rec + (int64_t)PACK * i;
+        sx[k] = r[0];
+        sy[k] = r[1];
+        sz[k] = r[2];
+        svx[k] = r[3];
+        svy[k] = r[4];
+        svz[k] = r[5];
+        sm[k] = r[6];
+        const double o = r[7], s = r[8];
+        sro[k] = o;
+        sinv[k] = 1.0 / o;
+        sreach[k] = fmax(o, s);
+        srs[k] = s;
+        sid[k] = i;
+      }
+      if (k == 0) {
+        parent[0] = -1;  // node 0 is the root (the only particle's record if n = 1) and never a child
+        if (n <= CHUNK) lchunk[atomicAdd(&lcount[0], 1)] = 0;
+        if (n <= ng) lgroup[atomicAdd(&lcount[1], 1)] = 0;
+      }
+      if (k >= n - 1) continue;
+      const int i = k;
+      const uint64_t ki = K.at(i);
+      const int d = (K.prefix(i, ki, i + 1) - K.prefix(i, ki, i - 1)) > 0 ? 1 : -1;
+      const int dmin = K.prefix(i, ki, i - d);
+      int lmax = 2;
+      while (K.prefix(i, ki, i + lmax * d) > dmin) lmax <<= 1;
+      int l = 0;
+      for (int h = lmax >> 1; h >= 1; h >>= 1)
+        if (K.prefix(i, ki, i + (l + h) * d) > dmin) l += h;
+      const int j = i + l * d;
+      const int dnode = K.prefix(i, ki, j);
+      int s = 0, h = l;
+      do {
+        h = (h + 1) >> 1;
+        if (K.prefix(i, ki, i + (s + h) * d) > dnode) s += h;
+      } while (h > 1);
+      const int split = i + s * d + (d < 0 ? -1 : 0);
+      const int lo = i < j ? i : j, hi = i < j ? j : i;
+      const int left = (lo == split) ? leaf0 + split : split;
+      const int right = (hi == split + 1) ? leaf0 + split + 1 : split + 1;
+      const int count = hi - lo + 1;
+      topo[i] = make_int4(left, right, lo, count);
+      parent[left] = i;
+      parent[right] = i;
+      visit[i] = 0;
+      const int cl = split - lo + 1, cr = hi - split;
+      if (count > CHUNK) {
+        ltop[atomicAdd(&lcount[2], 1)] = i;
+        if (cl <= CHUNK) lchunk[atomicAdd(&lcount[0], 1)] = left;
+        if (cr <= CHUNK) lchunk[atomicAdd(&lcount[0], 1)] = right;
+      }
+      if (count > ng) {
+        if (cl <= ng) lgroup[atomicAdd(&lcount[1], 1)] = left;
+        if (cr <= ng) lgroup[atomicAdd(&lcount[1], 1)] = right;
+      }
+    }
+    __syncthreads();
+    if (t < 3 && lcount[t] > 0) {
+      unsigned long long *c = t == 0 ? &cnt->n_chunks : t == 1 ? &cnt->n_groups : &cnt->n_top;
+      lbase[t] = atomicAdd(c, (unsigned long long)lcount[t]);
+    }
+    __syncthreads();
+    for (int q = t; q < lcount[0]; q += GT_T) chunk_list[lbase[0] + q] = lchunk[q];
+    for (int q = t; q < lcount[1]; q += GT_T) group_node[lbase[1] + q] = lgroup[q];
+    for (int q = t; q < lcount[2]; q += GT_T) top_list[lbase[2] + q] = ltop[q];
   }
 }
+
+// Bottom-up moments in two phases so that every hand-over between threads
+// stays inside one workgroup (workgroup-scope fences only; device-scope
+// fences would write back and invalidate the L2 of every XCD per level).
+//   chunk roots: nodes with <= CHUNK leaves whose parent has more;
+//   phase 1: one workgroup per chunk, from its bottom nodes to its root;
+//   phase 2: one workgroup from every chunk root to the tree root.
+// Bottom nodes: nodes of at most `lim` = min(n_leaf, n_group) particles whose
+// parent holds more.  Nothing below them is read by the walk (it stops at
+// nodes of at most n_leaf particles; the groups are bottom nodes or above), so
+// one thread sums a bottom node over its particles directly and only the
+// bottom nodes and those above (one node in eight at 16 leaves) have a record.
+
+// What a parent needs of a child: box, centre of mass, mass, quadrupole,
+// reach, range.
+struct NodeRec {
+  double lo[3], hi[3], com[3];
+  double mass, reach;
+  double q[6];
+  int first, count;
+};
+static_assert(sizeof(NodeRec) == 144, "NodeRec layout");
 
 __device__ __forceinline__ void quad_shift(double q[6], double m, double dx, double dy, double dz) {
   // add m (3 d d^T - |d|^2 I) for a point mass m at offset d from the new centre
@@ -180,28 +253,95 @@ __device__ __forceinline__ void quad_shift(double q[6], double m, double dx, dou
 // Internal node from its two children: tight box, mass, centre of mass,
 // traceless quadrupole about the centre of mass (parallel-axis shift of each
 // child's moment), max reach.  Fixed order (left, right): deterministic.
-__device__ __forceinline__ void combine_node(int node, p3t::WalkNode *wn, p3t::CellMom *cm) {
-  const int a = wn[node].left, b = wn[node].right;
-  const p3t::WalkNode wa = wn[a], wb = wn[b];
-  const p3t::CellMom ca = cm[a], cb = cm[b];
-  p3t::WalkNode o;
-  p3t::CellMom co;
-  const double M = ca.mass + cb.mass;
-  co.mass = M;
+__device__ __forceinline__ NodeRec combine_rec(const NodeRec &a, const NodeRec &b) {
+  NodeRec o;
+  const double M = a.mass + b.mass;
+  o.mass = M;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    o.lo[d] = fmin(wa.lo[d], wb.lo[d]);
-    o.hi[d] = fmax(wa.hi[d], wb.hi[d]);
-    co.com[d] = M > 0.0 ? (ca.mass * ca.com[d] + cb.mass * cb.com[d]) / M : 0.5 * (o.lo[d] + o.hi[d]);
-    o.com[d] = co.com[d];
+    o.lo[d] = fmin(a.lo[d], b.lo[d]);
+    o.hi[d] = fmax(a.hi[d], b.hi[d]);
+    o.com[d] = M > 0.0 ? (a.mass * a.com[d] + b.mass * b.com[d]) / M : 0.5 * (o.lo[d] + o.hi[d]);
   }
 #pragma unroll
-  for (int q = 0; q < 6; ++q) co.q[q] = ca.q[q] + cb.q[q];
-  quad_shift(co.q, ca.mass, ca.com[0] - co.com[0], ca.com[1] - co.com[1], ca.com[2] - co.com[2]);
-  quad_shift(co.q, cb.mass, cb.com[0] - co.com[0], cb.com[1] - co.com[1], cb.com[2] - co.com[2]);
-  o.reach = fmax(wa.reach, wb.reach);
-  // range and children are already in the record (and may be read meanwhile)
-  p3t::WalkNode &w = wn[node];
+  for (int q = 0; q < 6; ++q) o.q[q] = a.q[q] + b.q[q];
+  quad_shift(o.q, a.mass, a.com[0] - o.com[0], a.com[1] - o.com[1], a.com[2] - o.com[2]);
+  quad_shift(o.q, b.mass, b.com[0] - o.com[0], b.com[1] - o.com[1], b.com[2] - o.com[2]);
+  o.reach = fmax(a.reach, b.reach);
+  o.first = a.first;
+  o.count = a.count + b.count;
+  return o;
+}
+
+// The children in the order (left, right), through one copy of the
+// arithmetic: whichever of them arrives second, the result has the same bits
+// (two inlined copies would be contracted differently).
+__device__ __forceinline__ NodeRec combine_pair(const NodeRec &cur, const NodeRec &other, bool cur_left) {
+  NodeRec a, b;
+  auto pick = [&](auto x, auto y, auto &p, auto &q) {
+    p = cur_left ? x : y;
+    q = cur_left ? y : x;
+  };
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    pick(cur.lo[d], other.lo[d], a.lo[d], b.lo[d]);
+    pick(cur.hi[d], other.hi[d], a.hi[d], b.hi[d]);
+    pick(cur.com[d], other.com[d], a.com[d], b.com[d]);
+  }
+#pragma unroll
+  for (int q = 0; q < 6; ++q) pick(cur.q[q], other.q[q], a.q[q], b.q[q]);
+  pick(cur.mass, other.mass, a.mass, b.mass);
+  pick(cur.reach, other.reach, a.reach, b.reach);
+  pick(cur.first, other.first, a.first, b.first);
+  pick(cur.count, other.count, a.count, b.count);
+  return combine_rec(a, b);
+}
+
+// Particles [first, first + count) summed in order: sums of m and m x, then
+// the quadrupole about the centre of mass.
+__device__ __forceinline__ NodeRec bottom_rec(int first, int count, const double *__restrict__ sx,
+                                              const double *__restrict__ sy, const double *__restrict__ sz,
+                                              const double *__restrict__ sm, const double *__restrict__ sreach) {
+  NodeRec o;
+  o.first = first;
+  o.count = count;
+  double p[3] = {sx[first], sy[first], sz[first]};
+  o.mass = sm[first];
+  o.reach = sreach[first];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    o.lo[d] = o.hi[d] = o.com[d] = p[d];
+  }
+#pragma unroll
+  for (int q = 0; q < 6; ++q) o.q[q] = 0.0;
+  if (count == 1) return o;
+  double s[3] = {o.mass * p[0], o.mass * p[1], o.mass * p[2]};
+#pragma unroll 4
+  for (int k = first + 1; k < first + count; ++k) {
+    const double x = sx[k], y = sy[k], z = sz[k], m = sm[k];
+    o.lo[0] = fmin(o.lo[0], x);
+    o.hi[0] = fmax(o.hi[0], x);
+    o.lo[1] = fmin(o.lo[1], y);
+    o.hi[1] = fmax(o.hi[1], y);
+    o.lo[2] = fmin(o.lo[2], z);
+    o.hi[2] = fmax(o.hi[2], z);
+    o.mass += m;
+    s[0] += m * x;
+    s[1] += m * y;
+    s[2] += m * z;
+    o.reach = fmax(o.reach, sreach[k]);
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) o.com[d] = o.mass > 0.0 ? s[d] / o.mass : 0.5 * (o.lo[d] + o.hi[d]);
+#pragma unroll 4
+  for (int k = first; k < first + count; ++k)
+    quad_shift(o.q, sm[k], sx[k] - o.com[0], sy[k] - o.com[1], sz[k] - o.com[2]);
+  return o;
+}
+
+__device__ __forceinline__ void write_node(p3t::WalkNode *wn, p3t::CellMom *cm, int node, int left, int right,
+                                           const NodeRec &o, bool moments) {
+  p3t::WalkNode w;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     w.lo[d] = o.lo[d];
@@ -209,285 +349,268 @@ __device__ __forceinline__ void combine_node(int node, p3t::WalkNode *wn, p3t::C
     w.com[d] = o.com[d];
   }
   w.reach = o.reach;
-  cm[node] = co;
+  w.first = o.first;
+  w.count = o.count;
+  w.left = left;
+  w.right = right;
+  wn[node] = w;
+  if (!moments) return;
+  p3t::CellMom c;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) c.com[d] = o.com[d];
+  c.mass = o.mass;
+#pragma unroll
+  for (int q = 0; q < 6; ++q) c.q[q] = o.q[q];
+  cm[node] = c;
 }
 
-// Bottom-up moments in two phases so that every hand-over between threads
-// stays inside one workgroup (workgroup-scope fences only; device-scope
-// fences would write back and invalidate the L2 of every XCD per level).
-//   chunk roots: nodes with <= CHUNK leaves whose parent has more;
-//   phase 1: one workgroup per chunk writes the leaf records and climbs to the
-//            chunk root (second arrival at a node combines its children);
-//   phase 2: one workgroup climbs from every chunk root to the tree root.
-// (CHUNK is defined with the radix tree, which flags the chunk roots.)
-
-__global__ void k_chunk_flag(int n, const p3t::WalkNode *__restrict__ wn, const int32_t *__restrict__ parent,
-                             int32_t *__restrict__ flag) {
-  const int n_nodes = 2 * n - 1, leaf0 = n - 1;
-  for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < n_nodes; g += gridDim.x * blockDim.x) {
-    const int c = g >= leaf0 ? 1 : wn[g].count;
-    const int p = (g == 0) ? -1 : parent[g];
-    flag[g] = (c <= CHUNK && (p < 0 || wn[p].count > CHUNK)) ? 1 : 0;
+__device__ __forceinline__ NodeRec read_node(const p3t::WalkNode *wn, const p3t::CellMom *cm, int node) {
+  const p3t::WalkNode w = wn[node];
+  const p3t::CellMom c = cm[node];
+  NodeRec o;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    o.lo[d] = w.lo[d];
+    o.hi[d] = w.hi[d];
+    o.com[d] = c.com[d];
   }
+  o.mass = c.mass;
+  o.reach = w.reach;
+#pragma unroll
+  for (int q = 0; q < 6; ++q) o.q[q] = c.q[q];
+  o.first = w.first;
+  o.count = w.count;
+  return o;
 }
 
-__global__ void k_chunk_compact(int n_nodes, const int32_t *__restrict__ flag, const int64_t *__restrict__ pos,
-                                int32_t *__restrict__ chunk, p3t::DevCounters *cnt) {
-  for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < n_nodes; g += gridDim.x * blockDim.x)
-    if (flag[g]) chunk[pos[g]] = g;
-  if (blockIdx.x == 0 && threadIdx.x == 0) cnt->n_chunks = (unsigned long long)pos[n_nodes];
-}
+// Phase 1.  A subtree of the radix tree over leaves [first, first + count)
+// numbers its count - 1 internal nodes inside [first, first + count), so
+// node - first indexes the chunk's slot map.  The chunk's wide nodes (more
+// than lim particles) and its internal bottom nodes take one of MOM_SLOTS LDS
+// records each (a full chunk of 2048 needs 300-400 at 16 leaves; nodes that
+// find none, with smaller leaves, hand over through their device-memory record
+// and arrival counter).  A thread takes a bottom node, writes its record and
+// climbs: the second arrival at a node combines its children, its own record
+// still in registers.
+// Bound by latency: the climb is a chain of about ten levels per chunk.  With
+// 73 KB of LDS two workgroups share a CU (the earlier climb from every
+// particle kept 1024 records, 152 KB).
+constexpr int MOM_T = 512, MOM_SLOTS = 384;
 
-// What a parent needs of a child: box, centre of mass, mass, quadrupole,
-// reach (136 B).  The chunk's internal nodes keep theirs in LDS while the
-// climb runs; a leaf's comes from the particle arrays.
-struct NodeRec {
-  double lo[3], hi[3], com[3];
-  double mass, reach;
-  double q[6];
-};
-static_assert(sizeof(NodeRec) == 136, "NodeRec layout");
-
-// Bottom-up within one chunk, the records of its internal nodes in LDS: a
-// subtree of the radix tree over leaves [first, first + count) numbers its
-// count - 1 internal nodes inside [first, first + count), so node - first
-// indexes a slot.  Same arithmetic, in the same order, as combine_node.
-//
-// Only the records that something reads are written to device memory: the
-// walk stops at the first node of at most n_leaf particles, so it reads a
-// node (box, centre, reach, range) only if the node's parent holds more than
-// n_leaf particles, and the force kernels read the moments of such nodes
-// when they are accepted as cells; the chunk roots are read by the top
-// climb.  Below that level the climb keeps its records in LDS only (most of
-// the 2n - 1 nodes: about 90% at n_leaf = 16).  A particle's moment record
-// is needed only when it is a chunk root itself.
-constexpr int MOM_T = 1024;
-
-__global__ __launch_bounds__(MOM_T) void k_moments_local(int n, const double *__restrict__ sx,
+__global__ __launch_bounds__(MOM_T) void k_moments_local(int n, int lim, const double *__restrict__ sx,
                                                          const double *__restrict__ sy, const double *__restrict__ sz,
                                                          const double *__restrict__ sm,
                                                          const double *__restrict__ sreach, p3t::WalkNode *wn,
-                                                         p3t::CellMom *cm, const int32_t *__restrict__ parent,
-                                                         int32_t *visit, const int32_t *__restrict__ chunk,
-                                                         p3t::DevCounters *cnt, int n_leaf) {
-  __shared__ __align__(16) NodeRec rec[CHUNK];
-  __shared__ int lvisit[CHUNK];
-  __shared__ int tleft[CHUNK], tright[CHUNK], tpar[CHUNK];  // the chunk's topology
-  __shared__ unsigned char wide[CHUNK];  // internal node first + t holds more than n_leaf particles
-  const int leaf0 = n - 1;
+                                                         p3t::CellMom *cm, const int4 *__restrict__ topo,
+                                                         const int32_t *__restrict__ parent, int32_t *visit,
+                                                         const int32_t *__restrict__ chunk, p3t::DevCounters *cnt) {
+  __shared__ NodeRec rec[MOM_SLOTS];
+  __shared__ int4 st[MOM_SLOTS];  // wide nodes: left, right, parent, arrivals
+  __shared__ short map[CHUNK];    // slot of internal node first + t, or -1
+  __shared__ int bot[CHUNK];      // bottom nodes
+  __shared__ int n_bot, n_slot;
+  const int leaf0 = n - 1, t0 = threadIdx.x;
   const int nch = (int)cnt->n_chunks;
-  auto child = [&](int c, int first, int count, NodeRec &o) -> bool {
-    if (c >= leaf0) {
-      const int k = c - leaf0;
-      o.lo[0] = o.hi[0] = o.com[0] = sx[k];
-      o.lo[1] = o.hi[1] = o.com[1] = sy[k];
-      o.lo[2] = o.hi[2] = o.com[2] = sz[k];
-      o.mass = sm[k];
-      o.reach = sreach[k];
-#pragma unroll
-      for (int q = 0; q < 6; ++q) o.q[q] = 0.0;
-      return true;
-    }
-    const unsigned off = (unsigned)(c - first);
-    if (off >= (unsigned)count) return false;
-    o = rec[off];
-    return true;
-  };
   for (int ci = blockIdx.x; ci < nch; ci += gridDim.x) {
     const int r = chunk[ci];
-    const int first = r >= leaf0 ? r - leaf0 : wn[r].first;
-    const int count = r >= leaf0 ? 1 : min(wn[r].count, CHUNK);
-    for (int t = threadIdx.x; t < CHUNK; t += blockDim.x) lvisit[t] = 0;
-    for (int t = threadIdx.x; t < count; t += blockDim.x) {
-      const int node = first + t;
-      if (node < leaf0) {  // one index of the range may be a node outside the subtree: loaded, never used
-        tleft[t] = wn[node].left;
-        tright[t] = wn[node].right;
-        tpar[t] = parent[node];
-        wide[t] = wn[node].count > n_leaf ? 1 : 0;
+    const int4 tr = r >= leaf0 ? make_int4(-1, -1, r - leaf0, 1) : topo[r];
+    const int first = tr.z, count = min(tr.w, CHUNK);
+    __syncthreads();
+    if (t0 == 0) {
+      n_bot = n_slot = 0;
+      if (count <= lim) {
+        bot[0] = r;
+        n_bot = 1;
       }
     }
     __syncthreads();
-    // is the record of node c (in this chunk) read later: the chunk root,
-    // or a node whose parent (then inside the chunk) is wider than a leaf
-    auto needed = [&](int c, int par) -> bool {
-      if (c == r) return true;
-      const unsigned po = (unsigned)(par - first);
-      return po < (unsigned)count && wide[po];
-    };
-    // leaf records, staged in the (still unused) record slots and written
-    // out as consecutive 16-B words: 96-B and 80-B records stored lane by
-    // lane would leave every store instruction on scattered partial lines
-    static_assert(CHUNK * sizeof(p3t::WalkNode) <= sizeof(rec) && CHUNK * sizeof(p3t::CellMom) <= sizeof(rec),
-                  "leaf records exceed the staging area");
-    p3t::WalkNode *lw = reinterpret_cast<p3t::WalkNode *>(rec);
-    const uint4 *stage = reinterpret_cast<const uint4 *>(rec);
-    // the leaves whose walk record is read (staged, then written as 16-B words)
-    for (int t = threadIdx.x; t < count; t += blockDim.x) {
-      const int k = first + t;
-      const int leaf = leaf0 + k;
-      lvisit[t] = needed(leaf, leaf == r ? -1 : parent[leaf]) ? 1 : 0;  // reset below, before the climb
-      p3t::WalkNode w;
-      w.lo[0] = w.hi[0] = w.com[0] = sx[k];
-      w.lo[1] = w.hi[1] = w.com[1] = sy[k];
-      w.lo[2] = w.hi[2] = w.com[2] = sz[k];
-      w.reach = sreach[k];
-      w.first = k;
-      w.count = 1;
-      w.left = -1;
-      w.right = -1;
-      lw[t] = w;
+    for (int t = t0; t < count && count > lim; t += MOM_T) {
+      const int node = first + t;
+      map[t] = -1;
+      if (node >= leaf0) continue;
+      const int4 tp = topo[node];
+      // (one index of the range may be a node that reaches outside it)
+      if (tp.w <= lim || tp.z < first || tp.z + tp.w > first + count) continue;
+      const int s = atomicAdd(&n_slot, 1);
+      if (s < MOM_SLOTS) {
+        map[t] = (short)s;
+        st[s] = make_int4(tp.x, tp.y, parent[node], 0);
+      }
+      // (a particle's or node's count: only wide nodes look at their children)
+      if (tp.x >= leaf0 || topo[tp.x].w <= lim) bot[atomicAdd(&n_bot, 1)] = tp.x;
+      if (tp.y >= leaf0 || topo[tp.y].w <= lim) bot[atomicAdd(&n_bot, 1)] = tp.y;
     }
     __syncthreads();
-    {
-      uint4 *dst = reinterpret_cast<uint4 *>(wn + leaf0 + first);
-      constexpr int WPR = (int)(sizeof(p3t::WalkNode) / sizeof(uint4));
-      const int words = count * WPR;
-      for (int q = threadIdx.x; q < words; q += blockDim.x)
-        if (lvisit[q / WPR]) dst[q] = stage[q];
-    }
+    const int nb = n_bot;
     __syncthreads();
-    for (int t = threadIdx.x; t < count; t += blockDim.x) lvisit[t] = 0;
-    if (r >= leaf0 && threadIdx.x == 0) {  // a chunk of one particle: the top climb reads its moments
-      const int k = r - leaf0;
-      p3t::CellMom c;
-      c.com[0] = sx[k];
-      c.com[1] = sy[k];
-      c.com[2] = sz[k];
-      c.mass = sm[k];
-#pragma unroll
-      for (int q = 0; q < 6; ++q) c.q[q] = 0.0;
-      cm[r] = c;
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < count; t += blockDim.x) {
-      const int leaf = leaf0 + first + t;
-      int node = (leaf == r) ? -1 : parent[leaf];
-      while (node >= 0) {
+    for (int b = t0; b < nb; b += MOM_T) {
+      int child = bot[b];
+      NodeRec cur;
+      {
+        const int4 tp = child >= leaf0 ? make_int4(-1, -1, child - leaf0, 1) : topo[child];
+        cur = bottom_rec(tp.z, tp.w, sx, sy, sz, sm, sreach);
+        // a particle is no cell: its moments are read only by the top climb
+        write_node(wn, cm, child, tp.x, tp.y, cur, tp.w > 1 || child == r);
+      }
+      if (child == r) break;
+      bool in_lds = true;  // the child's record is in LDS (a particle's is read from the arrays)
+      if (child < leaf0) {
+        const int s = atomicAdd(&n_slot, 1);
+        in_lds = s < MOM_SLOTS;
+        if (in_lds) rec[s] = cur;
+        map[child - first] = (short)(in_lds ? s : -1);
+      }
+      int node = parent[child];
+      for (;;) {
         const unsigned off = (unsigned)(node - first);
         if (off >= (unsigned)count) {  // not a radix subtree: reported, never indexed
           p3t::set_flag(cnt, P3T_FLAG_NAN);
           break;
         }
+        const int s = map[off];
+        if (in_lds)
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        else
+          __threadfence_block();
         // first arrival: the sibling will finish; only the second arrival
         // combines (a third would mean a malformed tree: stop, never loop)
-        if (atomicAdd(&lvisit[off], 1) != 1) break;
-        // the sibling's record is in LDS: order LDS only (the global
-        // records are read by later kernels)
+        const int prev = s >= 0 ? atomicAdd(&st[s].w, 1) : atomicAdd(&visit[node], 1);
+        if (prev != 1) break;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-        const int a = tleft[off], b = tright[off];
-        NodeRec ra, rb;
-        if (!child(a, first, count, ra) || !child(b, first, count, rb)) {
-          p3t::set_flag(cnt, P3T_FLAG_NAN);
-          break;
+        int left, right, up;
+        if (s >= 0) {
+          left = st[s].x;
+          right = st[s].y;
+          up = st[s].z;
+        } else {
+          left = topo[node].x;
+          right = topo[node].y;
+          up = parent[node];
         }
+        const int sib = left == child ? right : left;
         NodeRec o;
-        const double M = ra.mass + rb.mass;
-        o.mass = M;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          o.lo[d] = fmin(ra.lo[d], rb.lo[d]);
-          o.hi[d] = fmax(ra.hi[d], rb.hi[d]);
-          o.com[d] = M > 0.0 ? (ra.mass * ra.com[d] + rb.mass * rb.com[d]) / M : 0.5 * (o.lo[d] + o.hi[d]);
-        }
-#pragma unroll
-        for (int q = 0; q < 6; ++q) o.q[q] = ra.q[q] + rb.q[q];
-        quad_shift(o.q, ra.mass, ra.com[0] - o.com[0], ra.com[1] - o.com[1], ra.com[2] - o.com[2]);
-        quad_shift(o.q, rb.mass, rb.com[0] - o.com[0], rb.com[1] - o.com[1], rb.com[2] - o.com[2]);
-        o.reach = fmax(ra.reach, rb.reach);
-        rec[off] = o;
-        if (needed(node, tpar[off])) {
-          // the node's range and children are already in its record
-          p3t::WalkNode &wo = wn[node];
-          p3t::CellMom co;
-#pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            wo.lo[d] = o.lo[d];
-            wo.hi[d] = o.hi[d];
-            wo.com[d] = o.com[d];
-            co.com[d] = o.com[d];
+        if (sib >= leaf0) {
+          o = bottom_rec(sib - leaf0, 1, sx, sy, sz, sm, sreach);
+        } else {
+          const unsigned so = (unsigned)(sib - first);
+          if (so >= (unsigned)count) {
+            p3t::set_flag(cnt, P3T_FLAG_NAN);
+            break;
           }
-          wo.reach = o.reach;
-          co.mass = M;
-#pragma unroll
-          for (int q = 0; q < 6; ++q) co.q[q] = o.q[q];
-          cm[node] = co;
+          const int q = map[so];
+          if (q >= 0) {
+            o = rec[q];
+          } else {
+            __threadfence_block();
+            o = read_node(wn, cm, sib);
+          }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        cur = combine_pair(cur, o, left == child);
+        write_node(wn, cm, node, left, right, cur, true);
         if (node == r) break;
-        node = tpar[off];
+        in_lds = s >= 0;
+        if (in_lds) rec[s] = cur;
+        child = node;
+        node = up;
       }
     }
-    __syncthreads();
   }
 }
 
 constexpr int TOP_SLOTS = 4096;  // power of two
-constexpr int TOP_PROBES = 32;   // probes per node before it falls back to its counter in device memory
+constexpr int TOP_PROBES = 32;   // probes per node before it falls back to device memory
+constexpr int TOP_RECS = 768;
 
-// Workgroup 0 climbs from every chunk root to the root; the other
-// workgroups meanwhile flag the interaction groups, which need only the node
-// counts (group g: count(g) <= ng and g is the root or count(parent) > ng).
+// Phase 2: one workgroup climbs from every chunk root to the root.  The top
+// nodes' links, arrival counters and finished records are in LDS, found
+// through a hash table of `slots` entries (a power of two <= TOP_SLOTS; open
+// addressing on the node id), filled before the climb starts.  A top node
+// beyond the TOP_RECS records (2^20 particles have about 750), or that finds
+// no free entry within TOP_PROBES probes, goes through its record and counter
+// in device memory.
 __global__ __launch_bounds__(1024) void k_moments_top(p3t::WalkNode *wn, p3t::CellMom *cm,
+                                                      const int4 *__restrict__ topo,
                                                       const int32_t *__restrict__ parent, int32_t *visit,
-                                                      const int32_t *__restrict__ chunk, const p3t::DevCounters *cnt,
-                                                      int n_nodes, int ng, int32_t *__restrict__ flag,
-                                                      int slots) {
-  if (blockIdx.x > 0) {
-    // (a particle's record may not be written: its count is 1)
-    const int leaf0 = (n_nodes - 1) / 2;
-    for (int g = (blockIdx.x - 1) * blockDim.x + threadIdx.x; g < n_nodes; g += (gridDim.x - 1) * blockDim.x) {
-      const int c = g >= leaf0 ? 1 : wn[g].count;
-      const int p = (g == 0) ? -1 : parent[g];
-      flag[g] = (c <= ng && (p < 0 || wn[p].count > ng)) ? 1 : 0;
-    }
-    return;
-  }
-  // Arrival counters of the top nodes in an LDS hash table of `slots`
-  // entries (a power of two <= TOP_SLOTS; open addressing on the node id).
-  // A node that finds neither its key nor a free entry within TOP_PROBES
-  // probes uses its counter in device memory.  Keys are never removed, so the
-  // entries a node probes only ever fill: both arrivals at a node see the
-  // same probe sequence and make the same choice (the second finds the key
-  // the first stored, or the same entries taken by other nodes).
-  __shared__ int hkey[TOP_SLOTS], hcnt[TOP_SLOTS];
+                                                      const int32_t *__restrict__ chunk,
+                                                      const int32_t *__restrict__ top_list,
+                                                      const p3t::DevCounters *cnt, int slots) {
+  __shared__ NodeRec rec[TOP_RECS];
+  __shared__ int4 st[TOP_RECS];  // left, right, parent, arrivals
+  __shared__ int hkey[TOP_SLOTS];
+  __shared__ short hval[TOP_SLOTS];
   const unsigned mask = (unsigned)slots - 1u;
   const int probes = slots < TOP_PROBES ? slots : TOP_PROBES;
-  for (int q = threadIdx.x; q < slots; q += blockDim.x) {
-    hkey[q] = -1;
-    hcnt[q] = 0;
-  }
+  const int ntop = (int)cnt->n_top;
+  if (ntop == 0) return;  // the root is a chunk root
+  for (int q = threadIdx.x; q < slots; q += blockDim.x) hkey[q] = -1;
   __syncthreads();
-  const int nch = (int)cnt->n_chunks;
-  for (int ci = threadIdx.x; ci < nch; ci += blockDim.x) {
-    const int r = chunk[ci];
-    int node = r == 0 ? -1 : parent[r];
-    while (node >= 0) {
-      unsigned h = ((unsigned)node * 2654435761u) & mask;
-      int slot = -1;
-      for (int probe = 0; probe < probes; ++probe) {
-        const int k = atomicCAS(&hkey[h], -1, node);
-        if (k == -1 || k == node) {
-          slot = (int)h;
-          break;
-        }
-        h = (h + 1) & mask;
+  for (int q = threadIdx.x; q < min(ntop, TOP_RECS); q += blockDim.x) {
+    const int node = top_list[q];
+    const int4 tp = topo[node];
+    st[q] = make_int4(tp.x, tp.y, parent[node], 0);
+    unsigned h = ((unsigned)node * 2654435761u) & mask;
+    for (int probe = 0; probe < probes; ++probe) {
+      if (atomicCAS(&hkey[h], -1, node) == -1) {
+        hval[h] = (short)q;
+        break;
       }
-      const int prev = slot >= 0 ? atomicAdd(&hcnt[slot], 1) : atomicAdd(&visit[node], 1);
-      if (prev != 1) break;
-      __threadfence_block();
-      combine_node(node, wn, cm);
-      __threadfence_block();
-      node = parent[node];
+      h = (h + 1) & mask;
     }
   }
-}
-
-__global__ void k_group_compact(int n_nodes, const int32_t *__restrict__ flag, const int64_t *__restrict__ pos,
-                                int32_t *__restrict__ group_node, p3t::DevCounters *cnt) {
-  for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < n_nodes; g += gridDim.x * blockDim.x)
-    if (flag[g]) group_node[pos[g]] = g;
-  if (blockIdx.x == 0 && threadIdx.x == 0) cnt->n_groups = (unsigned long long)pos[n_nodes];
+  __syncthreads();
+  // the record index of a top node, -1 for every other node
+  auto find = [&](int node) -> int {
+    unsigned h = ((unsigned)node * 2654435761u) & mask;
+    for (int probe = 0; probe < probes; ++probe) {
+      const int k = hkey[h];
+      if (k == node) return hval[h];
+      if (k == -1) return -1;
+      h = (h + 1) & mask;
+    }
+    return -1;
+  };
+  const int nch = (int)cnt->n_chunks;
+  for (int ci = threadIdx.x; ci < nch; ci += blockDim.x) {
+    int child = chunk[ci];
+    NodeRec cur = read_node(wn, cm, child);
+    int node = parent[child];
+    bool in_lds = true;  // (a chunk root's record was written by the launch before)
+    while (node >= 0) {
+      const int q = find(node);
+      if (in_lds)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+      else
+        __threadfence_block();
+      const int prev = q >= 0 ? atomicAdd(&st[q].w, 1) : atomicAdd(&visit[node], 1);
+      if (prev != 1) break;
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+      int left, right, up;
+      if (q >= 0) {
+        left = st[q].x;
+        right = st[q].y;
+        up = st[q].z;
+      } else {
+        left = topo[node].x;
+        right = topo[node].y;
+        up = parent[node];
+      }
+      const int sib = left == child ? right : left;
+      const int qs = find(sib);
+      NodeRec o;
+      if (qs >= 0) {
+        o = rec[qs];
+      } else {  // a chunk root, or a top node without a record in LDS
+        __threadfence_block();
+        o = read_node(wn, cm, sib);
+      }
+      cur = combine_pair(cur, o, left == child);
+      write_node(wn, cm, node, left, right, cur, true);
+      in_lds = q >= 0;
+      if (in_lds) rec[q] = cur;
+      child = node;
+      node = up;
+    }
+  }
 }
 
 static inline unsigned g1d(int64_t n, int64_t cap = 65536) {
@@ -495,7 +618,19 @@ static inline unsigned g1d(int64_t n, int64_t cap = 65536) {
   return (unsigned)(b < 1 ? 1 : (b > cap ? cap : b));
 }
 
-static hipError_t moments_pass(p3t_ctx *c, int64_t n, bool chunks_ready);
+// Moments and boxes of the current topology (the bottom-up pass; the arrival
+// counters are clear).  2^20 particles, 16 leaves: local 63 us, top 38 us
+// (climbing from every particle in chunks of 1024: 190 and 80 us); 65,536
+// particles: 27 and 12 us (42 and 14).
+static hipError_t moments_pass(p3t_ctx *c, int64_t n) {
+  hipStream_t s = c->stream;
+  hipLaunchKernelGGL(k_moments_local, dim3(c->n_cu * 2), dim3(MOM_T), 0, s, (int)n,
+                     std::min(c->P.n_leaf_max, c->P.n_group_max), c->sx, c->sy, c->sz, c->sm, c->sreach, c->wnode,
+                     c->cmom, c->topo, c->parent, c->visit, c->chunk_list, c->cnt);
+  hipLaunchKernelGGL(k_moments_top, dim3(1), dim3(1024), 0, s, c->wnode, c->cmom, c->topo, c->parent, c->visit,
+                     c->chunk_list, c->top_list, c->cnt, c->top_slots);
+  return hipGetLastError();
+}
 
 hipError_t build_tree(p3t_ctx *c, int64_t n, const double *pos3, const double *vel3, const double *mass,
                       const double *r_out, const double *r_search) {
@@ -515,47 +650,19 @@ hipError_t build_tree(p3t_ctx *c, int64_t n, const double *pos3, const double *v
   // nodes) holds the packed rows until then.
   static_assert(PACK * sizeof(double) <= 2 * sizeof(WalkNode), "packed rows exceed the node storage");
   double *rec = reinterpret_cast<double *>(c->wnode);
-  hipLaunchKernelGGL(k_pack, dim3(g1d(n)), dim3(256), 0, s, n, pos3, vel3, mass, r_out, r_search, rec);
-  hipLaunchKernelGGL(k_gather, dim3(g1d(n)), dim3(256), 0, s, n, v, rec, c->sx, c->sy, c->sz, c->svx, c->svy, c->svz,
-                     c->sm, c->sro, c->sinv, c->sreach, c->srs, c->sid,
-                     &c->cnt->n_chunks);
-  if (n > 1) {
-    hipLaunchKernelGGL(k_radix_tree, dim3(g1d(n - 1)), dim3(256), 0, s, (int)n, k, c->wnode, c->parent,
-                       c->group_node, &c->cnt->n_chunks, c->visit);
-  }
-  return moments_pass(c, n, n > 1);
-}
-
-// Moments, boxes and groups of the current topology (the bottom-up pass);
-// chunks_ready: the radix tree has just listed the chunk roots and cleared
-// the arrival counters.
-static hipError_t moments_pass(p3t_ctx *c, int64_t n, bool chunks_ready) {
-  hipStream_t s = c->stream;
-  hipError_t e;
-  const int64_t n_nodes = 2 * n - 1;
-  if (!chunks_ready) {
-    if ((e = fill_i32(c->visit, 0, n > 1 ? n - 1 : 1, s)) != hipSuccess) return e;
-    // chunk roots (into group_node / node_scan, both free until the groups are formed)
-    hipLaunchKernelGGL(k_chunk_flag, dim3(g1d(n_nodes)), dim3(256), 0, s, (int)n, c->wnode, c->parent, c->group_flag);
-    if ((e = scan_i32_to_i64(c->group_flag, c->node_scan, n_nodes, c->scan_tmp, c->scan_tmp_cap, s)) != hipSuccess)
-      return e;
-    hipLaunchKernelGGL(k_chunk_compact, dim3(g1d(n_nodes)), dim3(256), 0, s, (int)n_nodes, c->group_flag,
-                       c->node_scan, c->group_node, c->cnt);
-  }
-  hipLaunchKernelGGL(k_moments_local, dim3(c->n_cu * 2), dim3(MOM_T), 0, s, (int)n, c->sx, c->sy, c->sz, c->sm,
-                     c->sreach, c->wnode, c->cmom, c->parent, c->visit, c->group_node, c->cnt, c->P.n_leaf_max);
-  const unsigned gflag = (unsigned)std::max<int64_t>(1, std::min<int64_t>(2048, (n_nodes + 1023) / 1024));
-  hipLaunchKernelGGL(k_moments_top, dim3(1 + gflag), dim3(1024), 0, s, c->wnode, c->cmom, c->parent, c->visit,
-                     c->group_node, c->cnt, (int)n_nodes, c->P.n_group_max, c->group_flag, c->top_slots);
-  if ((e = scan_i32_to_i64(c->group_flag, c->node_scan, n_nodes, c->scan_tmp, c->scan_tmp_cap, s)) != hipSuccess)
-    return e;
-  hipLaunchKernelGGL(k_group_compact, dim3(g1d(n_nodes)), dim3(256), 0, s, (int)n_nodes, c->group_flag, c->node_scan,
+  hipLaunchKernelGGL(k_pack, dim3(g1d(n)), dim3(256), 0, s, n, pos3, vel3, mass, r_out, r_search, rec, c->cnt);
+  hipLaunchKernelGGL(k_gather_tree, dim3((unsigned)((n + GT_TILE - 1) / GT_TILE)), dim3(GT_T), 0, s, (int)n,
+                     c->P.n_group_max, v, rec, k, c->sx, c->sy, c->sz, c->svx, c->svy, c->svz, c->sm, c->sro, c->sinv,
+                     c->sreach, c->srs, c->sid, c->topo, c->parent, c->visit, c->chunk_list, c->top_list,
                      c->group_node, c->cnt);
-  return hipGetLastError();
+  return moments_pass(c, n);
 }
 
-// the bottom-up pass over the current topology (its chunk roots flagged anew)
-hipError_t tree_moments(p3t_ctx *c, int64_t n) { return moments_pass(c, n, false); }
+// the bottom-up pass over the current topology, its chunks and groups
+hipError_t tree_moments(p3t_ctx *c, int64_t n) {
+  const hipError_t e = fill_i32(c->visit, 0, n > 1 ? n - 1 : 1, c->stream);
+  return e != hipSuccess ? e : moments_pass(c, n);
+}
 
 // Same topology, same lists: positions and masses replaced, moments redone.
 hipError_t refresh_tree(p3t_ctx *c, const double *pos3, const double *mass) {
