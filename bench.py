@@ -193,30 +193,20 @@ def kepler_leg(p3t, torch, disk, launches=20):
                 avg_ms=ms, bytes_per_launch=byt, n_unbound=nu)
 
 
-KERNEL_NAMES = {"near": "k_near", "far": "k_far", "cell": "k_cell"}
-
-
 def kernel_rooflines(out, stage, steps, precision):
-    """Achieved vs peak vector flop rate of each split force kernel: the
-    kernel's algorithmic flops per launch (interactions x flops per
-    interaction) over its event-timed average launch duration."""
+    """Achieved vs peak vector flop rate of the force kernel, one launch over
+    the near, far and cell lists: its algorithmic flops (interactions x flops
+    per interaction) over its event-timed average launch duration."""
     fp32 = precision == 1
-    spec = {
-        # mixed: mostly FP32 arithmetic on FP64 offsets, priced at the FP32 peak
-        "near": ((out["n_near"] * FLOPS_NEAR_MIXED, PEAK_FP32, "fp32+fp64") if fp32 else
-                 (out["n_near"] * FLOPS_NEAR, PEAK_FP64, "fp64")),
-        "far": (out["n_far"] * FLOPS_FAR, PEAK_FP32 if fp32 else PEAK_FP64, "fp32" if fp32 else "fp64"),
-        "cell": (out["n_cell"] * FLOPS_QUAD, PEAK_FP32 if fp32 else PEAK_FP64, "fp32" if fp32 else "fp64"),
-    }
-    ks = {}
-    for k, (flops, peak, dt) in spec.items():
-        ms = stage["ms_" + k] / steps
-        if ms <= 0.0:
-            continue
-        ach = flops / (ms * 1e-3)
-        ks[KERNEL_NAMES[k]] = dict(bound="alu", achieved=ach / 1e12, peak=peak / 1e12, unit="TFLOP/s",
-                                   frac=ach / peak, avg_ms=ms, flops_per_launch=flops, arith=dt)
-    return ks
+    ms = stage["ms_near"] / steps
+    if ms <= 0.0:
+        return {}
+    flops = (out["n_near"] * (FLOPS_NEAR_MIXED if fp32 else FLOPS_NEAR) + out["n_far"] * FLOPS_FAR +
+             out["n_cell"] * FLOPS_QUAD)
+    peak = PEAK_FP32 if fp32 else PEAK_FP64
+    ach = flops / (ms * 1e-3)
+    return {"k_force_all": dict(bound="alu", achieved=ach / 1e12, peak=peak / 1e12, unit="TFLOP/s", frac=ach / peak,
+                                avg_ms=ms, flops_per_launch=flops, arith="fp32+fp64" if fp32 else "fp64")}
 
 
 def source_digest():

@@ -72,7 +72,7 @@ def search(measure, group_cap: int = 128, groups=GROUPS, leaves=LEAVES, shapes=S
            default_kernel=None) -> TuneResult:
     """Coordinate search driven by measure(params: dict, kernel: dict) ->
     (ms, interactions).  Host logic only; see tune() for the GPU measure."""
-    kernel0 = dict(default_kernel or dict(force_split=1, force_unroll=4, force_persistent=1, waves_per_cu=8,
+    kernel0 = dict(default_kernel or dict(force_split=1, force_unroll=2, force_persistent=1, waves_per_cu=16,
                                           walk_waves_per_cu=8))
     trials = []
     s1 = []

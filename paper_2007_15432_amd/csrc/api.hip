@@ -99,7 +99,7 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   total += bytes(n_cap, sizeof(int32_t)) + 2 * bytes(n_cap, sizeof(uint64_t));      // uf, cl keys
   total += bytes(cut_part_need(n_cap), sizeof(double)) + bytes(n_cap, sizeof(int32_t));  // cut-off bins
   total += bytes(n_cap + 4, sizeof(uint8_t));                                                // close flags
-  total += 2 * bytes(3 * n_cap, sizeof(double));
+  total += bytes(3 * n_cap, sizeof(double));
   total += bytes(HERM_BC_WORDS, sizeof(int32_t)) + bytes(HERM_N_BUCKETS * n_cap, sizeof(int32_t));  // buckets
   total += bytes(n_cap, sizeof(int32_t)) + bytes(n_cap, sizeof(uint8_t));  // cluster buckets, slow flags
   total += 3 * bytes(n_cap + 1, sizeof(int32_t));                             // hard-step labels, clusters
@@ -150,7 +150,6 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   c->cut_bin = A.take<int32_t>(n_cap);
   c->close_flag = A.take<uint8_t>(n_cap + 4);
   c->tmp_d = A.take<double>(3 * n_cap);
-  c->acc_s = A.take<double>(3 * n_cap);
   c->herm_bcount = A.take<int32_t>(HERM_BC_WORDS);
   c->herm_blists = A.take<int32_t>(HERM_N_BUCKETS * n_cap);
   c->herm_clbk = A.take<int32_t>(n_cap);
@@ -732,10 +731,9 @@ bool eval_finish(p3t_ctx *c, const DevCounters &h, unsigned *num, p3t_status *st
       c->stats.ms_walk = ev_ms(c, 4, 5);
       c->stats.ms_force = ev_ms(c, 5, 6);
       if (c->fcfg.split) {
-        c->stats.ms_near = ev_ms(c, 5, 11);
-        c->stats.ms_far = ev_ms(c, 11, 12);
-        c->stats.ms_cell = ev_ms(c, 12, 13);
-        c->stats.ms_cand = ev_ms(c, 13, 14);
+        c->stats.ms_near = ev_ms(c, 5, 11);  // one launch for the three classes
+        c->stats.ms_far = c->stats.ms_cell = 0.0;
+        c->stats.ms_cand = ev_ms(c, 11, 12);
       } else {
         c->stats.ms_near = c->stats.ms_far = c->stats.ms_cell = c->stats.ms_cand = 0.0;
       }

@@ -426,7 +426,7 @@ hipError_t soft_force(p3t_ctx *c, int64_t n_groups_max, double *acc3, bool froze
   A.pair_cap = c->pair_cap;
   A.cands = c->cands;
   A.cand_cap = c->cand_cap;
-  A.cand_slab = c->force_persistent ? 512 : 0;
+  A.cand_slab = c->force_persistent ? 64 : 0;
   A.slow = c->slow_active ? c->slow_flag : nullptr;
   if (frozen) A.pair_cap = A.cand_cap = 0;
   // the close pairs of this evaluation (a kernel clears the flags: the

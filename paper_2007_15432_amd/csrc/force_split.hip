@@ -1,29 +1,39 @@
-// force_split.hip -- the soft force as one lean kernel per interaction class
-// (eq. (softforce) with the pair cut-off of eq. (rout2); neighbour pairs of
-// Section 2.3), an alternative to the fused kernel of force.hip.
+// force_split.hip -- the soft force (eq. (softforce) with the pair cut-off of
+// eq. (rout2); neighbour pairs of Section 2.3) in one launch over the groups'
+// lists and one over the neighbour candidates, an alternative to the fused
+// kernel of force.hip.
 //
-//   k_near   FP64 with the changeover K (mixed form: the pairs beyond both
+//   k_force_all  one workgroup of W wavefronts per group; the list's tiles of
+//            64 entries are dealt to the wavefronts, each class with a loop of
+//            its own:
+//     near   FP64 with the changeover K (mixed form: the pairs beyond both
 //            cut-offs, where K = 1, in FP32 from FP64 offsets, the few
 //            inside the changeover in FP64); while it runs, each lane
 //            records in a bit mask which j of the current tile are
 //            neighbour candidates
 //            (r^2 <= max reach^2, with a relative margin that covers the
 //            rounding of r^2) and appends them after the tile to a candidate
-//            buffer.  Writes the sorted-order accumulator (=).
+//            buffer.
+//     far    K = 1 particles, FP64 or (mixed) FP32 offsets from the group
+//            centre with compensated accumulation.
+//     cells  monopole or traceless-quadrupole cells, FP64 or FP32.
+//            The wavefronts' sums are added in LDS and written in the caller's
+//            order, with the NaN check.
 //   k_cand_test  the exact neighbour test of Section 2.3 on every candidate,
 //            one thread each; neighbours go to the pair buffer.  Coincident
 //            pairs (r = 0, i != j) are always candidates and are reported
 //            here.
-//   k_far    K = 1 particles, FP64 or (mixed) FP32 offsets from the group
-//            centre with compensated accumulation.  Adds (+=).
-//   k_cell   monopole or traceless-quadrupole cells, FP64 or FP32.  Adds.
-//   k_scatter  sorted-order accumulator -> caller's order, NaN check.
 //
-// Every kernel is one wavefront per group; a lane owns one i-particle, or
-// two when the group holds more than 64 (the choice is per group, so small
-// groups do not pay for an idle second slot).  j data are staged 64 at a
-// time in LDS and read back as broadcasts; the tile is padded to the unroll
-// width with massless dummies placed far from the group.
+// A lane owns one i-particle, or two when the group holds more than 64 (the
+// choice is per group, so small groups do not pay for an idle second slot).
+// j data are staged 64 at a time in the wavefront's own LDS tile and read back
+// as broadcasts; the tile is padded to the unroll width with massless dummies
+// placed far from the group.
+//
+// Bound by VALU issue.  One launch instead of one per class and a scatter:
+// the i-particles are read once, the sums written once, and the classes fill
+// each other's tails; tree + walk + force at 2^20 particles 2069 -> 1818 us
+// mixed, 2509 -> 2299 us FP64, at 65,536 592 -> 447 and 658 -> 473.
 #include "force_common.h"
 
 namespace p3t {
@@ -58,6 +68,15 @@ __device__ __forceinline__ bool group_header(const ForceArgs &A, int gi, GroupHd
 __device__ __forceinline__ int next_gi(const ForceArgs &A, int lane, int iter, int ngroups) {
   if (A.persistent) return next_group(A.queue, lane);
   return iter == 0 ? (int)blockIdx.x : ngroups;
+}
+
+// LDS ordering inside one wavefront (each wavefront has tiles of its own): a
+// wave's LDS operations execute in order, so a compiler fence is enough
+// between a write by one lane and a read by another.
+__device__ __forceinline__ void tile_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 constexpr double kDummyOffset = 1.0e3;  // distance of padding entries from the group centre
@@ -123,11 +142,13 @@ __device__ __forceinline__ void close_slab(const ForceArgs &A, const CandSlab &S
     if (q < A.cand_cap) A.cands[q] = make_int2(-1, -1);
 }
 
+// The near terms of the tiles from list position `from` on, every `step`
+// positions (multiples of WAVE), added to (ax, ay, az).
 template <bool MIXED, int IPL, int UNR>
-__device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h, NearTile &T, int lane,
-                                           CandSlab &S) {
+__device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h, NearTile &T, int lane, int from,
+                                           int step, CandSlab &S, double *ax, double *ay, double *az) {
   int ii[IPL];
-  double xi[IPL], yi[IPL], zi[IPL], invi[IPL], rch2[IPL], ax[IPL], ay[IPL], az[IPL];
+  double xi[IPL], yi[IPL], zi[IPL], invi[IPL], rch2[IPL];
   int ro2q[IPL], rch2q[IPL];  // MIXED: bit patterns of the widened FP32 squares
 #pragma unroll
   for (int s = 0; s < IPL; ++s) {
@@ -140,7 +161,6 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
     zi[s] = A.sz[i];
     invi[s] = A.sinv[i];
     rch2[s] = A.sreach[i] * A.sreach[i] * kCandMargin;
-    ax[s] = ay[s] = az[s] = 0.0;
     if constexpr (MIXED) {
       const double ro = A.sro[i], r = A.sreach[i];
       ro2q[s] = __float_as_int((float)(ro * ro * (1.0 + kMixMargin)));
@@ -175,19 +195,19 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
       nj = -2;
     }
   };
-  if (h.n_near > 0) fetch(0);
-  for (int t0 = 0; t0 < h.n_near; t0 += WAVE) {
+  if (h.n_near > from) fetch(from);
+  for (int t0 = from; t0 < h.n_near; t0 += step) {
     const int nt = min(WAVE, h.n_near - t0);
     const int ntp = min(WAVE, (nt + UNR - 1) / UNR * UNR);
-    __syncthreads();
+    tile_sync();
     if (lane < ntp) {
       T.a[lane] = na;
       T.b[lane] = nb;
       if constexpr (MIXED) T.f[lane] = nf;
       T.j[lane] = nj;
     }
-    __syncthreads();
-    if (t0 + WAVE < h.n_near) fetch(t0 + WAVE);
+    tile_sync();
+    if (t0 + step < h.n_near) fetch(t0 + step);
     unsigned cm[2][IPL], chg_m[2][IPL];
     float tx[IPL], ty[IPL], tz[IPL];
 #pragma unroll
@@ -299,38 +319,6 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
       S.base += total;
     }
   }
-  double *acc = A.acc;
-#pragma unroll
-  for (int s = 0; s < IPL; ++s) {
-    if (ii[s] >= 0) {
-      acc[ii[s]] = ax[s];
-      acc[A.n + ii[s]] = ay[s];
-      acc[2 * A.n + ii[s]] = az[s];
-    }
-  }
-}
-
-template <bool MIXED, int UNR>
-__global__ __launch_bounds__(WAVE) void k_near(ForceArgs A) {
-  __shared__ NearTile T;
-  const int lane = threadIdx.x;
-  const int ngroups = uniform_first(min((int)A.cnt->n_groups, A.ngroups_bound));
-  CandSlab S;
-  unsigned long long n_int = 0;  // this wavefront's interactions, added once at its end
-  for (int iter = 0;; ++iter) {
-    const int gi = next_gi(A, lane, iter, ngroups);
-    if (gi >= ngroups) break;
-    GroupHdr h;
-    if (!group_header(A, gi, h)) continue;
-    if (h.count > WAVE)
-      near_group<MIXED, 2, UNR>(A, h, T, lane, S);
-    else
-      near_group<MIXED, 1, UNR>(A, h, T, lane, S);
-    const unsigned long long ni = (unsigned long long)h.count;
-    n_int += ni * (unsigned long long)h.n_near - ni;
-  }
-  close_slab(A, S, lane);
-  if (lane == 0 && n_int) atomicAdd(&A.cnt->n_near, n_int);
 }
 
 // ------------------------------------------------------------------ far
@@ -340,32 +328,30 @@ union FarTile {
 };
 
 template <bool MIXED, int IPL, int UNR>
-__device__ __forceinline__ void far_group(const ForceArgs &A, const GroupHdr &h, FarTile &T, int lane) {
-  int ii[IPL];
-  double xi[IPL], yi[IPL], zi[IPL], ax[IPL], ay[IPL], az[IPL];
+__device__ __forceinline__ void far_group(const ForceArgs &A, const GroupHdr &h, FarTile &T, int lane, int from,
+                                          int step, double *ax, double *ay, double *az) {
+  double xi[IPL], yi[IPL], zi[IPL];
 #pragma unroll
   for (int s = 0; s < IPL; ++s) {
     const int k = lane + WAVE * s;
-    ii[s] = k < h.count ? h.first + k : -1;
-    const int i = ii[s] >= 0 ? ii[s] : h.first;
+    const int i = k < h.count ? h.first + k : h.first;
     xi[s] = A.sx[i];
     yi[s] = A.sy[i];
     zi[s] = A.sz[i];
-    ax[s] = ay[s] = az[s] = 0.0;
   }
   const int32_t *Lf = A.pool + h.off + h.n_cell + h.n_near;
   if (!MIXED) {
-    for (int t0 = 0; t0 < h.n_far; t0 += WAVE) {
+    for (int t0 = from; t0 < h.n_far; t0 += step) {
       const int nt = min(WAVE, h.n_far - t0);
       const int ntp = min(WAVE, (nt + UNR - 1) / UNR * UNR);
-      __syncthreads();
+      tile_sync();
       if (lane < nt) {
         const int j = Lf[t0 + lane];
         T.d[lane] = make_double4(A.sx[j], A.sy[j], A.sz[j], A.G * A.sm[j]);
       } else if (lane < ntp) {
         T.d[lane] = make_double4(h.cx + kDummyOffset, h.cy, h.cz, 0.0);
       }
-      __syncthreads();
+      tile_sync();
       for (int jj = 0; jj < ntp; jj += UNR) {
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
@@ -392,10 +378,10 @@ __device__ __forceinline__ void far_group(const ForceArgs &A, const GroupHdr &h,
       fzi[s] = (float)(zi[s] - h.cz);
       hx[s] = hy[s] = hz[s] = lx[s] = ly[s] = lz[s] = 0.0f;
     }
-    for (int t0 = 0; t0 < h.n_far; t0 += WAVE) {
+    for (int t0 = from; t0 < h.n_far; t0 += step) {
       const int nt = min(WAVE, h.n_far - t0);
       const int ntp = min(WAVE, (nt + UNR - 1) / UNR * UNR);
-      __syncthreads();
+      tile_sync();
       if (lane < nt) {
         const int j = Lf[t0 + lane];
         T.f[lane] = make_float4((float)(A.sx[j] - h.cx), (float)(A.sy[j] - h.cy), (float)(A.sz[j] - h.cz),
@@ -403,7 +389,7 @@ __device__ __forceinline__ void far_group(const ForceArgs &A, const GroupHdr &h,
       } else if (lane < ntp) {
         T.f[lane] = make_float4((float)kDummyOffset, 0.0f, 0.0f, 0.0f);
       }
-      __syncthreads();
+      tile_sync();
       float tx[IPL], ty[IPL], tz[IPL];
 #pragma unroll
       for (int s = 0; s < IPL; ++s) tx[s] = ty[s] = tz[s] = 0.0f;
@@ -432,41 +418,11 @@ __device__ __forceinline__ void far_group(const ForceArgs &A, const GroupHdr &h,
     }
 #pragma unroll
     for (int s = 0; s < IPL; ++s) {
-      ax[s] = (double)hx[s] + (double)lx[s];
-      ay[s] = (double)hy[s] + (double)ly[s];
-      az[s] = (double)hz[s] + (double)lz[s];
+      ax[s] += (double)hx[s] + (double)lx[s];
+      ay[s] += (double)hy[s] + (double)ly[s];
+      az[s] += (double)hz[s] + (double)lz[s];
     }
   }
-  double *acc = A.acc;
-#pragma unroll
-  for (int s = 0; s < IPL; ++s) {
-    if (ii[s] >= 0) {
-      acc[ii[s]] += ax[s];
-      acc[A.n + ii[s]] += ay[s];
-      acc[2 * A.n + ii[s]] += az[s];
-    }
-  }
-}
-
-template <bool MIXED, int UNR>
-__global__ __launch_bounds__(WAVE) void k_far(ForceArgs A) {
-  __shared__ FarTile T;
-  const int lane = threadIdx.x;
-  const int ngroups = uniform_first(min((int)A.cnt->n_groups, A.ngroups_bound));
-  unsigned long long n_int = 0;  // this wavefront's interactions, added once at its end
-  for (int iter = 0;; ++iter) {
-    const int gi = next_gi(A, lane, iter, ngroups);
-    if (gi >= ngroups) break;
-    GroupHdr h;
-    if (!group_header(A, gi, h)) continue;
-    if (h.n_far == 0) continue;
-    if (h.count > WAVE)
-      far_group<MIXED, 2, UNR>(A, h, T, lane);
-    else
-      far_group<MIXED, 1, UNR>(A, h, T, lane);
-    n_int += (unsigned long long)h.count * (unsigned long long)h.n_far;
-  }
-  if (lane == 0 && n_int) atomicAdd(&A.cnt->n_far, n_int);
 }
 
 // ------------------------------------------------------------------ cells
@@ -481,6 +437,13 @@ union CellTile {
     float4 qa[WAVE];
     float2 qb[WAVE];
   } f;
+};
+
+union ForceTile {
+  NearTile near;
+  FarTile far;
+  CellTile cell;
+  double sum[3][2 * WAVE];  // a wavefront's sums of the group
 };
 
 template <typename R>
@@ -520,26 +483,24 @@ __device__ __forceinline__ void cell_acc(R dx, R dy, R dz, R gm, R q0, R q1, R q
 }
 
 template <bool MIXED, bool QUAD, int IPL, int UNR>
-__device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h, CellTile &T, int lane) {
-  int ii[IPL];
-  double xi[IPL], yi[IPL], zi[IPL], ax[IPL], ay[IPL], az[IPL];
+__device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h, CellTile &T, int lane, int from,
+                                           int step, double *ax, double *ay, double *az) {
+  double xi[IPL], yi[IPL], zi[IPL];
 #pragma unroll
   for (int s = 0; s < IPL; ++s) {
     const int k = lane + WAVE * s;
-    ii[s] = k < h.count ? h.first + k : -1;
-    const int i = ii[s] >= 0 ? ii[s] : h.first;
+    const int i = k < h.count ? h.first + k : h.first;
     xi[s] = A.sx[i];
     yi[s] = A.sy[i];
     zi[s] = A.sz[i];
-    ax[s] = ay[s] = az[s] = 0.0;
   }
   const int32_t *Lc = A.pool + h.off;
   const double G = A.G;
   if (!MIXED) {
-    for (int t0 = 0; t0 < h.n_cell; t0 += WAVE) {
+    for (int t0 = from; t0 < h.n_cell; t0 += step) {
       const int nt = min(WAVE, h.n_cell - t0);
       const int ntp = min(WAVE, (nt + UNR - 1) / UNR * UNR);
-      __syncthreads();
+      tile_sync();
       if (lane < nt) {
         const CellMom c = A.cm[Lc[t0 + lane]];
         T.d.a[lane] = make_double4(c.com[0], c.com[1], c.com[2], G * c.mass);
@@ -554,7 +515,7 @@ __device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h
           T.d.qb[lane] = make_double2(0.0, 0.0);
         }
       }
-      __syncthreads();
+      tile_sync();
       for (int jj = 0; jj < ntp; jj += UNR) {
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
@@ -584,10 +545,10 @@ __device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h
       fzi[s] = (float)(zi[s] - h.cz);
       hx[s] = hy[s] = hz[s] = lx[s] = ly[s] = lz[s] = 0.0f;
     }
-    for (int t0 = 0; t0 < h.n_cell; t0 += WAVE) {
+    for (int t0 = from; t0 < h.n_cell; t0 += step) {
       const int nt = min(WAVE, h.n_cell - t0);
       const int ntp = min(WAVE, (nt + UNR - 1) / UNR * UNR);
-      __syncthreads();
+      tile_sync();
       if (lane < nt) {
         const CellMom c = A.cm[Lc[t0 + lane]];
         T.f.a[lane] = make_float4((float)(c.com[0] - h.cx), (float)(c.com[1] - h.cy), (float)(c.com[2] - h.cz),
@@ -604,7 +565,7 @@ __device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h
           T.f.qb[lane] = make_float2(0.0f, 0.0f);
         }
       }
-      __syncthreads();
+      tile_sync();
       float tx[IPL], ty[IPL], tz[IPL];
 #pragma unroll
       for (int s = 0; s < IPL; ++s) tx[s] = ty[s] = tz[s] = 0.0f;
@@ -636,41 +597,91 @@ __device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h
     }
 #pragma unroll
     for (int s = 0; s < IPL; ++s) {
-      ax[s] = (double)hx[s] + (double)lx[s];
-      ay[s] = (double)hy[s] + (double)ly[s];
-      az[s] = (double)hz[s] + (double)lz[s];
-    }
-  }
-  double *acc = A.acc;
-#pragma unroll
-  for (int s = 0; s < IPL; ++s) {
-    if (ii[s] >= 0) {
-      acc[ii[s]] += ax[s];
-      acc[A.n + ii[s]] += ay[s];
-      acc[2 * A.n + ii[s]] += az[s];
+      ax[s] += (double)hx[s] + (double)lx[s];
+      ay[s] += (double)hy[s] + (double)ly[s];
+      az[s] += (double)hz[s] + (double)lz[s];
     }
   }
 }
 
-template <bool MIXED, bool QUAD, int UNR>
-__global__ __launch_bounds__(WAVE) void k_cell(ForceArgs A) {
-  __shared__ CellTile T;
-  const int lane = threadIdx.x;
+// ------------------------------------------------------------------ one launch, W wavefronts per group
+// The three classes of a group's list in one launch: its tiles (near, then
+// far, then cells) are dealt round robin to the W wavefronts of a workgroup,
+// each with a tile of LDS of its own; the wavefronts' sums are added in
+// wavefront order and written in the caller's order.  Deterministic: the same
+// tiles in the same wavefronts whatever the grid.
+template <bool MIXED, bool QUAD, int IPL, int UNR, int W>
+__device__ __forceinline__ void all_group(const ForceArgs &A, const GroupHdr &h, ForceTile *T, int lane, int w,
+                                          CandSlab &S) {
+  double ax[IPL] = {}, ay[IPL] = {}, az[IPL] = {};
+  const int nt = (h.n_near + WAVE - 1) / WAVE, ft = (h.n_far + WAVE - 1) / WAVE;
+  // first far / cell tile of wavefront w: the tiles are numbered through
+  const int f0 = ((w - nt) % W + W) % W, c0 = ((w - nt - ft) % W + W) % W;
+  near_group<MIXED, IPL, UNR>(A, h, T[w].near, lane, WAVE * w, WAVE * W, S, ax, ay, az);
+  far_group<MIXED, IPL, UNR>(A, h, T[w].far, lane, WAVE * f0, WAVE * W, ax, ay, az);
+  cell_group<MIXED, QUAD, IPL, UNR>(A, h, T[w].cell, lane, WAVE * c0, WAVE * W, ax, ay, az);
+  tile_sync();
+#pragma unroll
+  for (int s = 0; s < IPL; ++s) {
+    T[w].sum[0][lane + WAVE * s] = ax[s];
+    T[w].sum[1][lane + WAVE * s] = ay[s];
+    T[w].sum[2][lane + WAVE * s] = az[s];
+  }
+  __syncthreads();
+  for (int k = WAVE * w + lane; k < h.count; k += WAVE * W) {
+    double v[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) v[d] += T[q].sum[d][k];
+    }
+    const int64_t o = A.sid[h.first + k];
+    A.acc[o] = v[0];
+    A.acc[A.n + o] = v[1];
+    A.acc[2 * A.n + o] = v[2];
+    if (!(isfinite(v[0]) && isfinite(v[1]) && isfinite(v[2]))) set_flag(A.cnt, P3T_FLAG_NAN);
+  }
+}
+
+// wavefronts per SIMD that the unroll's registers allow without spills
+constexpr int min_waves(int unr) { return unr <= 2 ? 4 : unr <= 4 ? 3 : 2; }
+
+template <bool MIXED, bool QUAD, int UNR, int W>
+__global__ __launch_bounds__(WAVE *W, min_waves(UNR)) void k_force_all(ForceArgs A) {
+  __shared__ ForceTile T[W];
+  __shared__ int next;
+  const int lane = threadIdx.x & (WAVE - 1), w = uniform_first(threadIdx.x / WAVE);
   const int ngroups = uniform_first(min((int)A.cnt->n_groups, A.ngroups_bound));
-  unsigned long long n_int = 0;  // this wavefront's interactions, added once at its end
+  CandSlab S;
+  unsigned long long nn = 0, nf = 0, nc = 0;  // this workgroup's interactions, added once at its end
   for (int iter = 0;; ++iter) {
-    const int gi = next_gi(A, lane, iter, ngroups);
+    int gi;
+    if (A.persistent) {
+      __syncthreads();  // also: the sums of the last group are read
+      if (threadIdx.x == 0) next = (int)atomicAdd(A.queue, 1ull);
+      __syncthreads();
+      gi = uniform_first(next);
+    } else {
+      gi = iter == 0 ? (int)blockIdx.x : ngroups;
+    }
     if (gi >= ngroups) break;
     GroupHdr h;
     if (!group_header(A, gi, h)) continue;
-    if (h.n_cell == 0) continue;
     if (h.count > WAVE)
-      cell_group<MIXED, QUAD, 2, UNR>(A, h, T, lane);
+      all_group<MIXED, QUAD, 2, UNR, W>(A, h, T, lane, w, S);
     else
-      cell_group<MIXED, QUAD, 1, UNR>(A, h, T, lane);
-    n_int += (unsigned long long)h.count * (unsigned long long)h.n_cell;
+      all_group<MIXED, QUAD, 1, UNR, W>(A, h, T, lane, w, S);
+    const unsigned long long ni = (unsigned long long)h.count;
+    nn += ni * (unsigned long long)h.n_near - ni;
+    nf += ni * (unsigned long long)h.n_far;
+    nc += ni * (unsigned long long)h.n_cell;
   }
-  if (lane == 0 && n_int) atomicAdd(&A.cnt->n_cell, n_int);
+  close_slab(A, S, lane);
+  if (threadIdx.x == 0) {
+    if (nn) atomicAdd(&A.cnt->n_near, nn);
+    if (nf) atomicAdd(&A.cnt->n_far, nf);
+    if (nc) atomicAdd(&A.cnt->n_cell, nc);
+  }
 }
 
 // exact neighbour test of every candidate (sorted indices) -> pairs in the
@@ -712,65 +723,53 @@ __global__ void k_cand_test(ForceArgs A) {
   }
 }
 
-// sorted-order accumulator -> caller's order
-__global__ void k_scatter(const double *__restrict__ acc_s, const int32_t *__restrict__ sid, int64_t n,
-                          double *__restrict__ acc, DevCounters *cnt) {
-  bool bad = false;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const double x = acc_s[i], y = acc_s[n + i], z = acc_s[2 * n + i];
-    const int64_t o = sid[i];
-    acc[o] = x;
-    acc[n + o] = y;
-    acc[2 * n + o] = z;
-    bad |= !(isfinite(x) && isfinite(y) && isfinite(z));
-  }
-  if (__ballot(bad) != 0ull && lane_id() == 0) set_flag(cnt, P3T_FLAG_NAN);
-}
+// Wavefronts per group.  A group's list holds about a dozen tiles, and a
+// wavefront's tile is 64 entries x 64 or 128 particles, so with one wavefront
+// per group a disk of 65,536 particles (750 groups) leaves a quarter of the
+// 1024 SIMDs idle and the others with one wavefront each.  Measured (tree +
+// walk + force, mixed quadrupole, us; groups counted as n / (2/3 n_group_max)):
+//   particles   groups   W = 2    4     8    16
+//     16,384      190      411   388   370     -
+//     65,536      750      503   467   447   478
+//    131,072     1500      599   581   594   634
+//  1,048,576   12,000     1829  1818  2236  2584
+// Above 1200 groups four are as good as any, below eight are.
+constexpr int64_t kGroupsWide = 1200;
 
-template <typename K>
-unsigned persistent_grid(K kernel, int n_cu, int waves_cap) {
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, WAVE, 0) != hipSuccess || nb <= 0) nb = 8;
-  return (unsigned)(n_cu * std::min(nb, waves_cap));
+template <int UNR, int W>
+void launch_all(p3t_ctx *c, const ForceArgs &A, unsigned nonpersistent_grid) {
+  const bool mixed = c->P.precision == 1, quad = c->P.multipole == 2;
+  auto go = [&](auto kernel) {
+    int nb = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, WAVE * W, 0) != hipSuccess || nb <= 0) nb = 1;
+    nb = std::min(nb, std::max(1, c->fcfg.waves_per_cu / W));
+    const unsigned g = A.persistent ? (unsigned)(c->n_cu * nb) : nonpersistent_grid;
+    hipLaunchKernelGGL(kernel, dim3(g), dim3(WAVE * W), 0, c->stream, A);
+  };
+  if (mixed && quad)
+    go(k_force_all<true, true, UNR, W>);
+  else if (mixed)
+    go(k_force_all<true, false, UNR, W>);
+  else if (quad)
+    go(k_force_all<false, true, UNR, W>);
+  else
+    go(k_force_all<false, false, UNR, W>);
 }
 
 template <int UNR>
 hipError_t launch_split(p3t_ctx *c, ForceArgs A, unsigned nonpersistent_grid, double *acc3) {
-  const bool mixed = c->P.precision == 1, quad = c->P.multipole == 2;
   const hipStream_t s = c->stream;
-  const int cap = c->fcfg.waves_per_cu;
-  A.acc = c->acc_s;
-  auto grid = [&](auto kernel) {
-    return A.persistent ? persistent_grid(kernel, c->n_cu, cap) : nonpersistent_grid;
-  };
+  A.acc = acc3;
   A.queue = &c->cnt->queue[0];
-  if (mixed)
-    hipLaunchKernelGGL((k_near<true, UNR>), dim3(grid(k_near<true, UNR>)), dim3(WAVE), 0, s, A);
+  const int64_t groups = c->n / std::max(1, 2 * c->P.n_group_max / 3);
+  if (groups < kGroupsWide)
+    launch_all<UNR, 8>(c, A, nonpersistent_grid);
   else
-    hipLaunchKernelGGL((k_near<false, UNR>), dim3(grid(k_near<false, UNR>)), dim3(WAVE), 0, s, A);
+    launch_all<UNR, 4>(c, A, nonpersistent_grid);
   ev_record(c, 11);
-  A.queue = &c->cnt->queue[1];
-  if (mixed)
-    hipLaunchKernelGGL((k_far<true, UNR>), dim3(grid(k_far<true, UNR>)), dim3(WAVE), 0, s, A);
-  else
-    hipLaunchKernelGGL((k_far<false, UNR>), dim3(grid(k_far<false, UNR>)), dim3(WAVE), 0, s, A);
-  ev_record(c, 12);
-  A.queue = &c->cnt->queue[2];
-  if (mixed && quad)
-    hipLaunchKernelGGL((k_cell<true, true, UNR>), dim3(grid(k_cell<true, true, UNR>)), dim3(WAVE), 0, s, A);
-  else if (mixed)
-    hipLaunchKernelGGL((k_cell<true, false, UNR>), dim3(grid(k_cell<true, false, UNR>)), dim3(WAVE), 0, s, A);
-  else if (quad)
-    hipLaunchKernelGGL((k_cell<false, true, UNR>), dim3(grid(k_cell<false, true, UNR>)), dim3(WAVE), 0, s, A);
-  else
-    hipLaunchKernelGGL((k_cell<false, false, UNR>), dim3(grid(k_cell<false, false, UNR>)), dim3(WAVE), 0, s, A);
-  ev_record(c, 13);
-  const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)c->n_cu * 8, (c->n + 255) / 256));
   const unsigned gc = (unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)c->n_cu * 8, (c->cand_cap + 255) / 256));
   if (A.cand_cap > 0) hipLaunchKernelGGL(k_cand_test, dim3(gc), dim3(256), 0, s, A);
-  ev_record(c, 14);
-  hipLaunchKernelGGL(k_scatter, dim3(g), dim3(256), 0, s, (const double *)c->acc_s, (const int32_t *)c->sid, c->n,
-                     acc3, c->cnt);
+  ev_record(c, 12);
   return hipGetLastError();
 }
 

@@ -257,8 +257,8 @@ struct p3t_ctx {
   int graphed = 0;            // the last evaluation replayed the captured graph
   struct {
     int split = 1;         // 1: one kernel per interaction class, 0: the fused kernel
-    int unroll = 4;        // j-loop unroll of the split kernels (1, 2, 4, 8)
-    int waves_per_cu = 8;  // persistent grid of the split kernels: waves per CU (capped by occupancy)
+    int unroll = 2;         // j-loop unroll of the split kernel (1, 2, 4, 8)
+    int waves_per_cu = 16;  // its persistent grid: waves per CU (capped by occupancy)
   } fcfg;
   int32_t *herm_bcount = nullptr;  // Hermite bucket counts (p3t::HERM_BC_WORDS)
   int32_t *herm_blists = nullptr;  // Hermite bucket lists (11 * n_cap)
@@ -300,7 +300,6 @@ struct p3t_ctx {
   int32_t *cut_bin = nullptr;       // cut-off radial bin of each particle (n; the cluster
                                     // preparation may use row_cnt at the same time)
   double *tmp_d = nullptr;          // per-particle FP64 scratch (3n)
-  double *acc_s = nullptr;          // soft acceleration in sorted order (3n)
   // second stream for the big Hermite clusters, fork / join events
   hipStream_t aux_stream = nullptr;
   hipEvent_t aux_ev[2] = {};

@@ -1,7 +1,9 @@
 """Tree moments at the sizes where the bottom-up pass changes its path: one
 particle, one chunk (2048 particles) and its neighbours, more nodes than a
 chunk's LDS records (leaves of one and two particles), leaves wider than the
-groups, several chunks with and without top records in LDS.
+groups, several chunks with and without top records in LDS; and the force
+launch with eight and (the many small groups of the last case) four wavefronts
+per group.
 
 The reference below builds the same tree (48-bit Morton keys, split at the
 highest differing bit), its moments by direct sums over each node's particles,
@@ -116,6 +118,7 @@ def reference(pos, m, ro, rs, n_leaf, n_group):
 @pytest.mark.parametrize("n,n_leaf,n_group,top_slots", [
     (1, 16, 128, 4096), (2, 1, 1, 4096), (3, 16, 2, 4096), (130, 16, 128, 4096), (2047, 1, 128, 4096),
     (2048, 16, 128, 4096), (2049, 2, 64, 4096), (4099, 200, 64, 4096), (9001, 16, 128, 4096), (9001, 4, 128, 2),
+    (6100, 8, 8, 4096),
 ])
 def test_moments_edges(gpu, orc, n, n_leaf, n_group, top_slots):
     d = diskgen.workload("disk2k_equal", n)
