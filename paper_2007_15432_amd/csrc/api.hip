@@ -83,7 +83,7 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   const int64_t stmp = scan_tmp_need(std::max<int64_t>(n2 + 1, hist));
   size_t total = 0;
   total += bytes(1, sizeof(DevCounters));
-  total += bytes(8 + 6 * 1024, sizeof(double));
+  total += bytes(6 * 1024, sizeof(double));
   total += 11 * bytes(n_cap, sizeof(double));
   total += bytes(n_cap, sizeof(int32_t));                          // sid
   total += 2 * bytes(n_cap, sizeof(uint64_t)) + 2 * bytes(n_cap, sizeof(int32_t));  // keys, perm
@@ -117,8 +117,7 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   c->arena.used = 0;
   Arena &A = c->arena;
   c->cnt = A.take<DevCounters>(1);
-  c->bbox = A.take<double>(8 + 6 * 1024);
-  c->bbox_part = c->bbox + 8;
+  c->bbox_part = A.take<double>(6 * 1024);
   double **soa[11] = {&c->sx, &c->sy, &c->sz, &c->svx, &c->svy, &c->svz, &c->sm, &c->sro, &c->sinv, &c->sreach, &c->srs};
   for (auto p : soa) *p = A.take<double>(n_cap);
   c->sid = A.take<int32_t>(n_cap);

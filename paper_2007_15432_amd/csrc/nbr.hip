@@ -249,8 +249,7 @@ hipError_t clusters_csr_dev(p3t_ctx *c, int64_t n, const int32_t *label, int32_t
   // label bits alone orders by (label, index)
   uint64_t *k = c->cl_keys, *ka = c->cl_keys_alt;
   int32_t *v = nullptr, *va = nullptr;
-  if ((e = radix_sort_pairs(k, v, ka, va, n, nullptr, 32, 32 + bits, c->radix_hist, c->radix_hist_cap, c->scan_tmp,
-                            c->scan_tmp_cap, s)) != hipSuccess)
+  if ((e = radix_sort_pairs(k, v, ka, va, n, 32, 32 + bits, c->radix_hist, c->radix_hist_cap, false, s)) != hipSuccess)
     return e;
   hipLaunchKernelGGL(k_cl_flags, dim3(g1d(n)), dim3(256), 0, s, n, k, cl_members, c->row_cnt);
   // (the node-scan buffer is free here; the neighbour CSR stays intact)

@@ -267,8 +267,7 @@ struct p3t_ctx {
 
   // arena pointers
   p3t::DevCounters *cnt = nullptr;
-  double *bbox = nullptr;       // 6 doubles (+ partials)
-  double *bbox_part = nullptr;
+  double *bbox_part = nullptr;  // bounding-box partials (6 doubles each)
   double *sx = nullptr, *sy = nullptr, *sz = nullptr, *svx = nullptr, *svy = nullptr, *svz = nullptr;
   double *sm = nullptr, *sro = nullptr, *sinv = nullptr, *sreach = nullptr, *srs = nullptr;
   int32_t *sid = nullptr;
@@ -354,14 +353,21 @@ void ev_record(p3t_ctx *c, int k);
 double ev_ms(p3t_ctx *c, int a, int b);
 void cut_timing_read(p3t_ctx *c);
 
-hipError_t radix_sort_pairs(uint64_t *&keys, int32_t *&vals, uint64_t *&keys_alt, int32_t *&vals_alt, int64_t n_static,
-                            const unsigned long long *n_dev, int bit_lo, int bit_hi, uint32_t *hist, int64_t hist_cap,
-                            int64_t *tmp, int64_t tmp_cap, hipStream_t s);
+// hist_ready: hist holds the first pass's tile histogram (tiles of
+// radix_plan(n), hist[tile][digit]) and zeros for the other passes
+constexpr int RADIX_PASSES = 6;
+struct RadixPlan {
+  int tile, ntiles;
+  bool chain;  // a pass counts the next one's tiles (else hist_ready does not matter)
+};
+RadixPlan radix_plan(int64_t n);
+hipError_t radix_sort_pairs(uint64_t *&keys, int32_t *&vals, uint64_t *&keys_alt, int32_t *&vals_alt, int64_t n,
+                            int bit_lo, int bit_hi, uint32_t *hist, int64_t hist_cap, bool hist_ready,
+                            hipStream_t s);
 int64_t radix_hist_need(int64_t n);
 hipError_t fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 hipError_t fill_f64(double *p, double v, int64_t n, hipStream_t s);
 hipError_t iota_i32(int32_t *p, int64_t n, hipStream_t s);
-hipError_t bbox_reduce(const double *pos3, int64_t n, double *part, double *out, hipStream_t s);
 hipError_t kick(int64_t n, double h, const double *acc3, double *vel3, hipStream_t s);
 hipError_t kepler_drift(int64_t n, int64_t n_list, const int32_t *list, double mu, double dt, double *pos3,
                         double *vel3, int32_t *iters, DevCounters *cnt, hipStream_t s);

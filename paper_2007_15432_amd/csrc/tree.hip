@@ -31,19 +31,41 @@ __device__ __forceinline__ uint64_t spread3(uint32_t v) {
 // radix passes
 constexpr int MORTON_BITS = 16;
 
-__global__ void k_morton(int64_t n, const double *__restrict__ pos, const double *__restrict__ box,
-                         uint64_t *__restrict__ keys, int32_t *__restrict__ perm) {
-  const double lx = box[0], ly = box[1], lz = box[2];
-  const double ext = fmax(fmax(box[3] - lx, box[4] - ly), box[5] - lz);
-  const double qmax = (double)((1 << MORTON_BITS) - 1);
-  const double scale = ext > 0.0 ? qmax / ext : 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    double q[3] = {(pos[i] - lx) * scale, (pos[n + i] - ly) * scale, (pos[2 * n + i] - lz) * scale};
-    uint32_t u[3];
+// Per-block bounding boxes of the positions.  Also clears the sort's
+// histograms and the lists' counters for the launches that follow.
+constexpr int BB_T = 256, BB_BLOCKS = 256;
+
+__global__ __launch_bounds__(BB_T) void k_bbox_part(const double *__restrict__ pos, int64_t n, double *__restrict__ part,
+                                                    uint32_t *__restrict__ hist, int64_t hist_words,
+                                                    p3t::DevCounters *cnt) {
+  __shared__ double sh[6][BB_T / p3t::WAVE];
+  const int64_t g0 = (int64_t)blockIdx.x * BB_T + threadIdx.x, gs = (int64_t)gridDim.x * BB_T;
+  if (g0 == 0) cnt->n_chunks = cnt->n_top = cnt->n_groups = 0;
+  for (int64_t q = g0; q < hist_words; q += gs) hist[q] = 0u;
+  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+  for (int64_t k = g0; k < n; k += gs) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) u[c] = (uint32_t)fmin(fmax(q[c], 0.0), qmax);
-    keys[i] = (spread3(u[0]) << 2) | (spread3(u[1]) << 1) | spread3(u[2]);
-    perm[i] = (int32_t)i;
+    for (int c = 0; c < 3; ++c) {
+      const double x = pos[c * n + k];
+      lo[c] = fmin(lo[c], x);
+      hi[c] = fmax(hi[c], x);
+    }
+  }
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    lo[c] = p3t::wave_min(lo[c]);
+    hi[c] = p3t::wave_max(hi[c]);
+    if ((t & (p3t::WAVE - 1)) == 0) {
+      sh[c][t / p3t::WAVE] = lo[c];
+      sh[3 + c][t / p3t::WAVE] = hi[c];
+    }
+  }
+  __syncthreads();
+  if (t < 6) {
+    double v = sh[t][0];
+    for (int w = 1; w < BB_T / p3t::WAVE; ++w) v = t < 3 ? fmin(v, sh[t][w]) : fmax(v, sh[t][w]);
+    part[t * gridDim.x + blockIdx.x] = v;
   }
 }
 
@@ -52,21 +74,65 @@ __global__ void k_morton(int64_t n, const double *__restrict__ pos, const double
 // it would read nine 8-B elements from nine scattered rows.
 constexpr int PACK = 9;
 
-__global__ void k_pack(int64_t n, const double *__restrict__ pos, const double *__restrict__ vel,
-                       const double *__restrict__ m, const double *__restrict__ ro, const double *__restrict__ rs,
-                       double *__restrict__ rec, p3t::DevCounters *cnt) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) cnt->n_chunks = cnt->n_top = cnt->n_groups = 0;  // listed by k_gather_tree
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    double *r = rec + PACK * i;
-    r[0] = pos[i];
-    r[1] = pos[n + i];
-    r[2] = pos[2 * n + i];
-    r[3] = vel[i];
-    r[4] = vel[n + i];
-    r[5] = vel[2 * n + i];
-    r[6] = m[i];
-    r[7] = ro[i];
-    r[8] = rs[i];
+// Morton keys, the tile histogram of their lowest digit for the sort
+// (nullable), and the packed rows.  Every block reduces the at most BB_T box partials itself.
+__global__ __launch_bounds__(BB_T) void k_morton(int64_t n, const double *__restrict__ pos,
+                                                 const double *__restrict__ vel, const double *__restrict__ m,
+                                                 const double *__restrict__ ro, const double *__restrict__ rs,
+                                                 const double *__restrict__ part, int nb, uint64_t *__restrict__ keys,
+                                                 int32_t *__restrict__ perm, double *__restrict__ rec,
+                                                 uint32_t *__restrict__ hist, int tile) {
+  __shared__ double sh[6][BB_T / p3t::WAVE];
+  __shared__ double lrec[PACK * BB_T];
+  double box[6];
+  {
+    const int t = threadIdx.x, w = t / p3t::WAVE;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      const double v = t < nb ? part[c * nb + t] : (c < 3 ? INFINITY : -INFINITY);
+      const double r = c < 3 ? p3t::wave_min(v) : p3t::wave_max(v);
+      if ((t & (p3t::WAVE - 1)) == 0) sh[c][w] = r;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      box[c] = sh[c][0];
+      for (int q = 1; q < BB_T / p3t::WAVE; ++q) box[c] = c < 3 ? fmin(box[c], sh[c][q]) : fmax(box[c], sh[c][q]);
+    }
+  }
+  const double lx = box[0], ly = box[1], lz = box[2];
+  const double ext = fmax(fmax(box[3] - lx, box[4] - ly), box[5] - lz);
+  const double qmax = (double)((1 << MORTON_BITS) - 1);
+  const double scale = ext > 0.0 ? qmax / ext : 0.0;
+  for (int64_t b0 = (int64_t)blockIdx.x * BB_T; b0 < n; b0 += (int64_t)gridDim.x * BB_T) {
+    const int64_t i = b0 + threadIdx.x;
+    __syncthreads();
+    if (i < n) {
+      const double x = pos[i], y = pos[n + i], z = pos[2 * n + i];
+      const double q[3] = {(x - lx) * scale, (y - ly) * scale, (z - lz) * scale};
+      uint32_t u[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) u[c] = (uint32_t)fmin(fmax(q[c], 0.0), qmax);
+      const uint64_t key = (spread3(u[0]) << 2) | (spread3(u[1]) << 1) | spread3(u[2]);
+      keys[i] = key;
+      perm[i] = (int32_t)i;
+      if (hist) atomicAdd(&hist[(i / tile) * 256 + (int64_t)(key & 255u)], 1u);
+      // the records through LDS: stored lane by lane, every instruction
+      // would leave 64 partial lines
+      double *r = lrec + PACK * threadIdx.x;
+      r[0] = x;
+      r[1] = y;
+      r[2] = z;
+      r[3] = vel[i];
+      r[4] = vel[n + i];
+      r[5] = vel[2 * n + i];
+      r[6] = m[i];
+      r[7] = ro[i];
+      r[8] = rs[i];
+    }
+    __syncthreads();
+    const int words = PACK * (int)(n - b0 < BB_T ? n - b0 : BB_T);
+    for (int q = threadIdx.x; q < words; q += BB_T) rec[PACK * b0 + q] = lrec[q];
   }
 }
 
@@ -636,21 +702,24 @@ hipError_t build_tree(p3t_ctx *c, int64_t n, const double *pos3, const double *v
                       const double *r_out, const double *r_search) {
   hipStream_t s = c->stream;
   hipError_t e;
-  if ((e = bbox_reduce(pos3, n, c->bbox_part, c->bbox, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_morton, dim3(g1d(n)), dim3(256), 0, s, n, pos3, c->bbox, c->keys, c->perm);
+  const RadixPlan rp = radix_plan(n);
+  const int nb = (int)std::min<int64_t>(BB_BLOCKS, (n + BB_T - 1) / BB_T);
+  // The node records are rebuilt below, so their storage (96 B per node,
+  // 2n - 1 nodes) holds the packed rows until then.
+  static_assert(PACK * sizeof(double) <= 2 * sizeof(WalkNode), "packed rows exceed the node storage");
+  double *rec = reinterpret_cast<double *>(c->wnode);
+  hipLaunchKernelGGL(k_bbox_part, dim3(nb), dim3(BB_T), 0, s, pos3, n, c->bbox_part, c->radix_hist,
+                     rp.chain ? (int64_t)RADIX_PASSES * rp.ntiles * 256 : 0, c->cnt);
+  hipLaunchKernelGGL(k_morton, dim3(g1d(n)), dim3(BB_T), 0, s, n, pos3, vel3, mass, r_out, r_search, c->bbox_part, nb,
+                     c->keys, c->perm, rec, rp.chain ? c->radix_hist : nullptr, rp.tile);
   uint64_t *k = c->keys, *ka = c->keys_alt;
   int32_t *v = c->perm, *va = c->perm_alt;
   ev_record(c, 17);
-  if ((e = radix_sort_pairs(k, v, ka, va, n, nullptr, 0, 3 * MORTON_BITS, c->radix_hist, c->radix_hist_cap, c->scan_tmp,
-                            c->scan_tmp_cap, s)) != hipSuccess)
+  static_assert(3 * MORTON_BITS <= 8 * RADIX_PASSES, "more sort passes than histograms");
+  if ((e = radix_sort_pairs(k, v, ka, va, n, 0, 3 * MORTON_BITS, c->radix_hist, c->radix_hist_cap, true, s)) !=
+      hipSuccess)
     return e;
   ev_record(c, 18);
-  // after an even number of passes the result is back in keys / perm.  The
-  // node records are rebuilt below, so their storage (96 B per node, 2n - 1
-  // nodes) holds the packed rows until then.
-  static_assert(PACK * sizeof(double) <= 2 * sizeof(WalkNode), "packed rows exceed the node storage");
-  double *rec = reinterpret_cast<double *>(c->wnode);
-  hipLaunchKernelGGL(k_pack, dim3(g1d(n)), dim3(256), 0, s, n, pos3, vel3, mass, r_out, r_search, rec, c->cnt);
   hipLaunchKernelGGL(k_gather_tree, dim3((unsigned)((n + GT_TILE - 1) / GT_TILE)), dim3(GT_T), 0, s, (int)n,
                      c->P.n_group_max, v, rec, k, c->sx, c->sy, c->sz, c->svx, c->svy, c->svz, c->sm, c->sro, c->sinv,
                      c->sreach, c->srs, c->sid, c->topo, c->parent, c->visit, c->chunk_list, c->top_list,

@@ -1,7 +1,7 @@
 // util.hip -- device-wide building blocks: exclusive scans, a stable LSD radix
-// sort of 64-bit keys with 32-bit values, bounding-box reduction, fills and
-// the soft kick.  All kernels take their element count either as a host value
-// or from a device counter (so data-dependent sizes need no host round trip).
+// sort of 64-bit keys with 32-bit values, fills and the soft kick.
+#include <algorithm>
+
 #include "p3t_internal.h"
 
 namespace p3t {
@@ -114,111 +114,143 @@ hipError_t scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, int64_t *
 }
 
 // ------------------------------------------------------------------ radix sort
-// Stable LSD radix sort, 8-bit digits.  One block sorts a tile of RS_TILE
-// keys per pass: a digit histogram per tile (hist[digit][tile]); one
-// workgroup per digit scans its row over the tiles (exclusive, in place) and
-// stores the row total; the stable scatter adds the exclusive scan of the
-// 256 row totals (done again by every scatter block, in LDS) and ranks equal
-// digits inside a wavefront with ballots and across wavefronts with
-// per-round counters.  Three launches per pass, no device-wide scan.
-constexpr int RS_T = 256;
-constexpr int RS_I = 8;  // tiles of 2048 keys: 512 workgroups per pass for 2^20 keys
-constexpr int RS_TILE = RS_T * RS_I;
-constexpr int RS_W = RS_T / WAVE;
+// Stable LSD radix sort, 8-bit digits, one launch per pass.  A workgroup of
+// 1024 threads takes a tile of 1024, 2048 or 4096 keys: every wavefront ranks
+// its own keys with ballots and counters of its own (no barrier per round),
+// the tile is ordered in LDS and written out in runs of equal digits.
+// The pass's tile histogram (hist[tile][digit]) is complete when it starts.
+// Up to RS_CHAIN keys the pass before, which knows where each key lands, adds
+// the key's next digit to it (the first one comes with the keys): one launch
+// per pass.  More keys make that an atomic per key too many (2^20 keys: 41 us a
+// pass), and a launch of its own counts each tile in LDS.  Up to RS_SELF tiles
+// every workgroup sums the histogram's columns itself (256 rows of 1 KB, 3 us);
+// more tiles take one launch more per pass that scans the columns.
+//   48-bit keys with values, all passes (one histogram, one column or row scan
+// and one scatter per pass of 2048-key tiles before): 2048 keys 82 -> 34 us,
+// 65,536 116 -> 47, 262,144 105 -> 85, 2^20 144 -> 119.
+constexpr int RS_T = 1024, RS_W = RS_T / WAVE;
+constexpr int RS_SELF = 256;
+constexpr int64_t RS_CHAIN = 1 << 18;
 
-__device__ __forceinline__ int64_t dev_count(int64_t n_static, const unsigned long long *n_dev) {
-  if (!n_dev) return n_static;
-  int64_t d = (int64_t)(*n_dev);
-  return d < n_static ? d : n_static;
+// keys per thread: tiles of 1024 keys keep 65,536 keys on 64 workgroups, tiles
+// of 4096 keep the columns of 2^20 keys at RS_SELF rows
+static int radix_items(int64_t n) { return n <= (1 << 16) ? 1 : n <= (1 << 18) ? 2 : 4; }
+
+RadixPlan radix_plan(int64_t n) {
+  RadixPlan p;
+  p.tile = RS_T * radix_items(n);
+  p.ntiles = (int)((n + p.tile - 1) / p.tile);
+  p.chain = n <= RS_CHAIN;
+  return p;
 }
 
-__global__ __launch_bounds__(RS_T) void k_radix_hist(const uint64_t *__restrict__ kin, int64_t n_static,
-                                                     const unsigned long long *n_dev, int shift,
-                                                     uint32_t *__restrict__ hist, int nblocks) {
+// one pass's histogram, a workgroup per tile (no clearing before)
+__global__ __launch_bounds__(RS_T) void k_radix_tile_hist(const uint64_t *__restrict__ kin, int64_t n, int shift,
+                                                          int tile, uint32_t *__restrict__ hist) {
   __shared__ uint32_t h[256];
   const int t = threadIdx.x;
-  h[t] = 0;
+  if (t < 256) h[t] = 0u;
   __syncthreads();
-  const int64_t n = dev_count(n_static, n_dev);
-  const int64_t base = (int64_t)blockIdx.x * RS_TILE;
+  const int64_t base = (int64_t)blockIdx.x * tile;
 #pragma unroll 4
-  for (int r = 0; r < RS_I; ++r) {
-    int64_t k = base + (int64_t)r * RS_T + t;
-    if (k < n) atomicAdd(&h[(unsigned)(kin[k] >> shift) & 255u], 1u);
-  }
+  for (int q = t; q < tile; q += RS_T)
+    if (base + q < n) atomicAdd(&h[(unsigned)(kin[base + q] >> shift) & 255u], 1u);
   __syncthreads();
-  hist[(int64_t)t * nblocks + blockIdx.x] = h[t];
+  if (t < 256) hist[(int64_t)blockIdx.x * 256 + t] = h[t];
 }
 
-// Row d of hist (nblocks tile counts of digit d) becomes its exclusive scan;
-// tot[d] receives the row total.  One workgroup per digit.
-constexpr int RR_I = 8;
-__global__ __launch_bounds__(RS_T) void k_radix_rowscan(uint32_t *__restrict__ hist, int nblocks,
-                                                        uint32_t *__restrict__ tot) {
-  __shared__ uint32_t ws[RS_W];
-  uint32_t *row = hist + (int64_t)blockIdx.x * nblocks;
-  const int t = threadIdx.x, w = t / WAVE, l = t & (WAVE - 1);
+// the first pass's histogram of up to RS_CHAIN keys that come without one (cleared before)
+__global__ __launch_bounds__(256) void k_radix_hist(const uint64_t *__restrict__ kin, int64_t n, int shift, int tile,
+                                                    uint32_t *__restrict__ hist) {
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
+    atomicAdd(&hist[(k / tile) * 256 + ((unsigned)(kin[k] >> shift) & 255u)], 1u);
+}
+
+// Column d of hist (tile counts of digit d) becomes its exclusive scan, tot[d]
+// its total: one wavefront per digit, 64 rows at a time.
+__global__ __launch_bounds__(256) void k_radix_colscan(uint32_t *__restrict__ hist, int ntiles,
+                                                       uint32_t *__restrict__ tot) {
+  const int d = blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE, l = threadIdx.x & (WAVE - 1);
   uint32_t carry = 0;
-  for (int c0 = 0; c0 < nblocks; c0 += RS_T * RR_I) {  // uniform
-    uint32_t v[RR_I], s = 0;
-#pragma unroll
-    for (int q = 0; q < RR_I; ++q) {
-      const int i = c0 + t * RR_I + q;
-      v[q] = i < nblocks ? row[i] : 0u;
-      s += v[q];
-    }
-    const uint32_t incl = (uint32_t)wave_incl_scan((int)s);
-    if (l == WAVE - 1) ws[w] = incl;
-    __syncthreads();
-    uint32_t run = carry + incl - s, chunk = 0;
-#pragma unroll
-    for (int q = 0; q < RS_W; ++q) {
-      run += q < w ? ws[q] : 0u;
-      chunk += ws[q];
-    }
-#pragma unroll
-    for (int q = 0; q < RR_I; ++q) {
-      const int i = c0 + t * RR_I + q;
-      if (i < nblocks) row[i] = run;
-      run += v[q];
-    }
-    carry += chunk;
-    __syncthreads();  // ws is rewritten by the next chunk
+  for (int r0 = 0; r0 < ntiles; r0 += WAVE) {  // uniform
+    const int r = r0 + l;
+    const uint32_t v = r < ntiles ? hist[(int64_t)r * 256 + d] : 0u;
+    const uint32_t incl = (uint32_t)wave_incl_scan((int)v);
+    if (r < ntiles) hist[(int64_t)r * 256 + d] = carry + incl - v;
+    carry += (uint32_t)uniform_lane((int)incl, WAVE - 1);
   }
-  if (t == 0) tot[blockIdx.x] = carry;
+  if (l == 0) tot[d] = carry;
 }
 
-__global__ __launch_bounds__(RS_T) void k_radix_scatter(const uint64_t *__restrict__ kin, const int32_t *__restrict__ vin,
-                                                        uint64_t *__restrict__ kout, int32_t *__restrict__ vout,
-                                                        int64_t n_static, const unsigned long long *n_dev, int shift,
-                                                        const uint32_t *__restrict__ offs, const uint32_t *__restrict__ tot,
-                                                        int nblocks) {
-  __shared__ uint32_t run[256];
-  __shared__ uint32_t wc[RS_W][256];
-  const int t = threadIdx.x, w = t / WAVE;
-  const int64_t n = dev_count(n_static, n_dev);
-  {
-    // first position of digit t: exclusive scan of the row totals
-    const uint32_t tv = tot[t];
-    const uint32_t incl = (uint32_t)wave_incl_scan((int)tv);
-    if ((t & (WAVE - 1)) == WAVE - 1) wc[0][w] = incl;
-    __syncthreads();
-    uint32_t base = incl - tv;
+// exclusive scan over the 256 values of threads 0..255 (every thread of the
+// workgroup calls it; ws: four words)
+__device__ __forceinline__ uint32_t scan256(uint32_t v, int t, uint32_t *ws) {
+  const uint32_t incl = (uint32_t)wave_incl_scan((int)v);
+  if (t < 256 && (t & (WAVE - 1)) == WAVE - 1) ws[t / WAVE] = incl;
+  __syncthreads();
+  uint32_t base = incl - v;
 #pragma unroll
-    for (int q = 0; q < RS_W; ++q) base += q < w ? wc[0][q] : 0u;
-    run[t] = base + offs[(int64_t)t * nblocks + blockIdx.x];
-    __syncthreads();  // wc is cleared below
+  for (int q = 0; q < 3; ++q) base += q < t / WAVE ? ws[q] : 0u;
+  __syncthreads();
+  return base;
+}
+
+template <int I, bool VALS, bool SELF>
+__global__ __launch_bounds__(RS_T) void k_radix_pass(const uint64_t *__restrict__ kin, const int32_t *__restrict__ vin,
+                                                     uint64_t *__restrict__ kout, int32_t *__restrict__ vout,
+                                                     int64_t n, int ntiles, int shift,
+                                                     const uint32_t *__restrict__ hist,
+                                                     const uint32_t *__restrict__ tot,
+                                                     uint32_t *__restrict__ hist_next) {
+  constexpr int TILE = RS_T * I;
+  __shared__ uint32_t wc[RS_W][256];  // the column sums, then each wavefront's digit counts
+  __shared__ uint32_t gbase[256], lstart[256], ws[4];
+  __shared__ uint64_t lk[TILE];
+  __shared__ int32_t lv[VALS ? TILE : 1];
+  const int t = threadIdx.x, w = t / WAVE, lane = t & (WAVE - 1), d0 = t & 255;
+  const int64_t base = (int64_t)blockIdx.x * TILE;
+  uint64_t key[I];
+  int32_t val[I];
+  // wavefront w owns the keys [w 64 I, (w + 1) 64 I) of the tile, in order
+#pragma unroll
+  for (int i = 0; i < I; ++i) {
+    const int64_t k = base + w * (WAVE * I) + i * WAVE + lane;
+    key[i] = k < n ? kin[k] : 0ull;
+    val[i] = VALS && k < n ? vin[k] : 0;
   }
-  const int64_t base = (int64_t)blockIdx.x * RS_TILE;
-  for (int r = 0; r < RS_I; ++r) {
+  {
+    uint32_t before = 0, all = 0;
+    if (SELF) {
+      const int b = blockIdx.x;
+#pragma unroll 16
+      for (int r = t >> 8; r < ntiles; r += RS_T / 256) {
+        const uint32_t c = hist[(int64_t)r * 256 + d0];
+        all += c;
+        before += r < b ? c : 0u;
+      }
+      wc[t >> 8][d0] = all;
+      wc[4 + (t >> 8)][d0] = before;
+      __syncthreads();
+      if (t < 256) {
+        all = wc[0][t] + wc[1][t] + wc[2][t] + wc[3][t];
+        before = wc[4][t] + wc[5][t] + wc[6][t] + wc[7][t];
+      }
+      __syncthreads();
+    } else if (t < 256) {
+      all = tot[t];
+      before = hist[(int64_t)blockIdx.x * 256 + t];
+    }
+    const uint32_t first = scan256(all, t, ws);
+    if (t < 256) gbase[t] = first + before;
+  }
 #pragma unroll
-    for (int q = 0; q < RS_W; ++q) wc[q][t] = 0;
-    __syncthreads();
-    const int64_t k = base + (int64_t)r * RS_T + t;
-    const bool valid = k < n;
-    const uint64_t key = valid ? kin[k] : 0ull;
-    const int32_t val = (valid && vin) ? vin[k] : 0;
-    const unsigned d = (unsigned)(key >> shift) & 255u;
+  for (int q = 0; q < RS_W / 4; ++q) wc[4 * q + (t >> 8)][d0] = 0u;
+  __syncthreads();
+  uint32_t rank[I];
+#pragma unroll
+  for (int i = 0; i < I; ++i) {
+    const bool valid = base + w * (WAVE * I) + i * WAVE + lane < n;
+    const unsigned d = (unsigned)(key[i] >> shift) & 255u;
     unsigned long long peers = __ballot(valid);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
@@ -226,47 +258,103 @@ __global__ __launch_bounds__(RS_T) void k_radix_scatter(const uint64_t *__restri
       const unsigned long long bal = __ballot(bit);
       peers &= bit ? bal : ~bal;
     }
-    const int rank = popc_below(peers);
-    if (valid && rank == 0) wc[w][d] = (uint32_t)__popcll(peers);
-    __syncthreads();
-    if (valid) {
-      uint32_t off = run[d] + (uint32_t)rank;
-      for (int q = 0; q < w; ++q) off += wc[q][d];
-      kout[off] = key;
-      if (vout) vout[off] = val;
-    }
-    __syncthreads();
-    uint32_t add = 0;
+    const int r = popc_below(peers);
+    const uint32_t c = wc[w][d];
+    rank[i] = c + (uint32_t)r;
+    // a wavefront's LDS operations execute in order: every peer has read c
+    __builtin_amdgcn_wave_barrier();
+    if (valid && r == 0) wc[w][d] = c + (uint32_t)__popcll(peers);
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  uint32_t cnt = 0;
+  if (t < 256) {
 #pragma unroll
-    for (int q = 0; q < RS_W; ++q) add += wc[q][t];
-    run[t] += add;
-    __syncthreads();
+    for (int q = 0; q < RS_W; ++q) {
+      const uint32_t c = wc[q][t];
+      wc[q][t] = cnt;
+      cnt += c;
+    }
+  }
+  const uint32_t ls = scan256(cnt, t, ws);
+  if (t < 256) lstart[t] = ls;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < I; ++i) {
+    if (base + w * (WAVE * I) + i * WAVE + lane >= n) continue;
+    const unsigned d = (unsigned)(key[i] >> shift) & 255u;
+    const uint32_t p = lstart[d] + wc[w][d] + rank[i];
+    lk[p] = key[i];
+    if (VALS) lv[p] = val[i];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < I; ++i) {
+    const int p = i * RS_T + t;
+    if (base + p >= n) break;
+    const uint64_t k = lk[p];
+    const unsigned d = (unsigned)(k >> shift) & 255u;
+    const uint32_t off = gbase[d] + (uint32_t)p - lstart[d];
+    kout[off] = k;
+    if (VALS) vout[off] = lv[p];
+    if (hist_next) atomicAdd(&hist_next[(off / TILE) * 256u + ((unsigned)(k >> (shift + 8)) & 255u)], 1u);
   }
 }
 
-int64_t radix_hist_need(int64_t n) { return 256 * ((n + RS_TILE - 1) / RS_TILE) + 256; }
+// histograms of up to RADIX_PASSES passes (one, above RS_CHAIN keys), and the
+// digit totals; at least the Hermite buckets' per-chunk counts (14 per 256)
+int64_t radix_hist_need(int64_t n) {
+  const int64_t tiles = (n + 4 * RS_T - 1) / (4 * RS_T);
+  return std::max<int64_t>(RADIX_PASSES * 128, tiles) * 256 + 256 + n / 16;
+}
 
-hipError_t radix_sort_pairs(uint64_t *&keys, int32_t *&vals, uint64_t *&keys_alt, int32_t *&vals_alt, int64_t n_static,
-                            const unsigned long long *n_dev, int bit_lo, int bit_hi, uint32_t *hist, int64_t hist_cap,
-                            int64_t *tmp, int64_t tmp_cap, hipStream_t s) {
-  if (n_static <= 0) return hipSuccess;
-  const int64_t nb64 = (n_static + RS_TILE - 1) / RS_TILE;
-  if (256 * nb64 + 256 > hist_cap || nb64 > (1 << 30)) return hipErrorInvalidValue;
-  const int nb = (int)nb64;
-  uint32_t *tot = hist + 256 * nb64;  // the 256 row totals follow the counters
-  (void)tmp;
-  (void)tmp_cap;
-  for (int shift = bit_lo; shift < bit_hi; shift += 8) {
-    hipLaunchKernelGGL(k_radix_hist, dim3(nb), dim3(RS_T), 0, s, keys, n_static, n_dev, shift, hist, nb);
-    hipLaunchKernelGGL(k_radix_rowscan, dim3(256), dim3(RS_T), 0, s, hist, nb, tot);
-    hipLaunchKernelGGL(k_radix_scatter, dim3(nb), dim3(RS_T), 0, s, keys, vals, keys_alt, vals_alt, n_static, n_dev,
-                       shift, hist, tot, nb);
-    uint64_t *tk = keys;
-    keys = keys_alt;
-    keys_alt = tk;
-    int32_t *tv = vals;
-    vals = vals_alt;
-    vals_alt = tv;
+hipError_t radix_sort_pairs(uint64_t *&keys, int32_t *&vals, uint64_t *&keys_alt, int32_t *&vals_alt, int64_t n,
+                            int bit_lo, int bit_hi, uint32_t *hist, int64_t hist_cap, bool hist_ready,
+                            hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  const RadixPlan p = radix_plan(n);
+  const int passes = (bit_hi - bit_lo + 7) / 8;
+  const int64_t words = (int64_t)p.ntiles * 256;
+  const int64_t used = p.chain ? passes * words : words;  // one histogram per pass, or one for all
+  if (passes > RADIX_PASSES || used + 256 > hist_cap) return hipErrorInvalidValue;
+  uint32_t *tot = hist + used;
+  if (p.chain && !hist_ready) {
+    const hipError_t e = fill_i32(reinterpret_cast<int32_t *>(hist), 0, passes * words, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)std::min<int64_t>(65536, (n + 255) / 256)), dim3(256), 0, s, keys,
+                       n, bit_lo, p.tile, hist);
+  }
+  for (int q = 0; q < passes; ++q) {
+    uint32_t *h = p.chain ? hist + q * words : hist, *hn = p.chain && q + 1 < passes ? h + words : nullptr;
+    const int shift = bit_lo + 8 * q;
+    if (!p.chain) hipLaunchKernelGGL(k_radix_tile_hist, dim3(p.ntiles), dim3(RS_T), 0, s, keys, n, shift, p.tile, h);
+    const bool self = p.ntiles <= RS_SELF;
+    if (!self) hipLaunchKernelGGL(k_radix_colscan, dim3(256 / (256 / WAVE)), dim3(256), 0, s, h, p.ntiles, tot);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(p.ntiles), dim3(RS_T), 0, s, keys, vals, keys_alt, vals_alt, n, p.ntiles, shift,
+                         h, tot, hn);
+    };
+    if (vals) {
+      if (p.tile == RS_T)
+        go(k_radix_pass<1, true, true>);
+      else if (p.tile == 2 * RS_T)
+        go(k_radix_pass<2, true, true>);
+      else if (self)
+        go(k_radix_pass<4, true, true>);
+      else
+        go(k_radix_pass<4, true, false>);
+    } else {
+      if (p.tile == RS_T)
+        go(k_radix_pass<1, false, true>);
+      else if (p.tile == 2 * RS_T)
+        go(k_radix_pass<2, false, true>);
+      else if (self)
+        go(k_radix_pass<4, false, true>);
+      else
+        go(k_radix_pass<4, false, false>);
+    }
+    std::swap(keys, keys_alt);
+    std::swap(vals, vals_alt);
   }
   return hipGetLastError();
 }
@@ -318,80 +406,6 @@ __global__ void k_kick(int64_t n3, double h, const double *__restrict__ a, doubl
 hipError_t kick(int64_t n, double h, const double *acc3, double *vel3, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_kick, dim3(grid_for(3 * n)), dim3(256), 0, s, 3 * n, h, acc3, vel3);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ bounding box
-constexpr int BB_BLOCKS = 1024;
-
-__global__ __launch_bounds__(256) void k_bbox_part(const double *__restrict__ pos, int64_t n, double *__restrict__ part) {
-  __shared__ double sh[6][256 / WAVE];
-  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      double x = pos[c * n + k];
-      lo[c] = fmin(lo[c], x);
-      hi[c] = fmax(hi[c], x);
-    }
-  }
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    lo[c] = wave_min(lo[c]);
-    hi[c] = wave_max(hi[c]);
-  }
-  if ((t & (WAVE - 1)) == 0) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      sh[c][t / WAVE] = lo[c];
-      sh[3 + c][t / WAVE] = hi[c];
-    }
-  }
-  __syncthreads();
-  if (t < 6) {
-    double v = sh[t][0];
-    for (int w = 1; w < 256 / WAVE; ++w) v = t < 3 ? fmin(v, sh[t][w]) : fmax(v, sh[t][w]);
-    part[blockIdx.x * 6 + t] = v;
-  }
-}
-
-// one 256-thread block: min / max over the per-block partials
-__global__ __launch_bounds__(256) void k_bbox_final(const double *__restrict__ part, int nb, double *__restrict__ out) {
-  __shared__ double sh[6][256 / WAVE];
-  const int t = threadIdx.x;
-  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int b = t; b < nb; b += 256) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      lo[c] = fmin(lo[c], part[b * 6 + c]);
-      hi[c] = fmax(hi[c], part[b * 6 + 3 + c]);
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    lo[c] = wave_min(lo[c]);
-    hi[c] = wave_max(hi[c]);
-  }
-  if ((t & (WAVE - 1)) == 0) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      sh[c][t / WAVE] = lo[c];
-      sh[3 + c][t / WAVE] = hi[c];
-    }
-  }
-  __syncthreads();
-  if (t < 6) {
-    double v = sh[t][0];
-    for (int w = 1; w < 256 / WAVE; ++w) v = t < 3 ? fmin(v, sh[t][w]) : fmax(v, sh[t][w]);
-    out[t] = v;
-  }
-}
-
-hipError_t bbox_reduce(const double *pos3, int64_t n, double *part, double *out, hipStream_t s) {
-  const int nb = (int)grid_for(n, 256, BB_BLOCKS);
-  hipLaunchKernelGGL(k_bbox_part, dim3(nb), dim3(256), 0, s, pos3, n, part);
-  hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(256), 0, s, part, nb, out);
   return hipGetLastError();
 }
 
