@@ -94,7 +94,8 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   total += bytes(n_cap, sizeof(int4)) + bytes(n2 + 1, sizeof(int64_t));  // topo, node_scan
   total += 3 * bytes(n_cap, sizeof(int32_t));                             // chunk, top and group lists
   total += bytes(n_cap, sizeof(GroupList));
-  total += bytes(n_cap, sizeof(int32_t));                                           // group order
+  total += 2 * bytes(n_cap, sizeof(int32_t));                                       // group order, classes
+  total += bytes(WALK_PARTS * WALK_QUEUE_STRIDE, sizeof(unsigned long long));       // walk queues
   total += bytes(n_cap, sizeof(int32_t)) + bytes(n_cap + 1, sizeof(int64_t));       // row_cnt, csr_ptr
   total += bytes(n_cap, sizeof(int32_t)) + 2 * bytes(n_cap, sizeof(uint64_t));      // uf, cl keys
   total += bytes(cut_part_need(n_cap), sizeof(double)) + bytes(n_cap, sizeof(int32_t));  // cut-off bins
@@ -140,6 +141,8 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   c->group_node = A.take<int32_t>(n_cap);
   c->glist = A.take<GroupList>(n_cap);
   c->group_order = A.take<int32_t>(n_cap);
+  c->group_cls = A.take<int32_t>(n_cap);
+  c->walk_q = A.take<unsigned long long>(WALK_PARTS * WALK_QUEUE_STRIDE);
   c->row_cnt = A.take<int32_t>(n_cap);
   c->csr_ptr = A.take<int64_t>(n_cap + 1);
   c->uf_parent = A.take<int32_t>(n_cap);

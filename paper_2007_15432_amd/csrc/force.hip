@@ -429,14 +429,9 @@ hipError_t soft_force(p3t_ctx *c, int64_t n_groups_max, double *acc3, bool froze
   A.cand_slab = c->force_persistent ? 64 : 0;
   A.slow = c->slow_active ? c->slow_flag : nullptr;
   if (frozen) A.pair_cap = A.cand_cap = 0;
-  // the close pairs of this evaluation (a kernel clears the flags: the
-  // evaluation may be captured into a graph)
+  // the close pairs of this evaluation (cleared with the queues before the walk)
   A.close = frozen ? nullptr : c->close_flag;
   A.close_k = P.G * P.dt_soft * P.dt_soft / (CLOSE_RATIO * CLOSE_RATIO);
-  if (A.close) {
-    const hipError_t e = fill_i32(reinterpret_cast<int32_t *>(c->close_flag), 0, (c->n + 3) / 4, c->stream);
-    if (e != hipSuccess) return e;
-  }
   A.acc = acc3;
   A.n = c->n;
   A.G = P.G;

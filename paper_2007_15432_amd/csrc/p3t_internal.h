@@ -55,7 +55,6 @@ struct DevCounters {
   unsigned long long pool_cursor;  // list pool allocation cursor
   unsigned long long n_pairs;      // neighbour pairs appended
   unsigned long long n_groups;     // interaction groups
-  unsigned long long walk_queue;   // persistent walk kernel queue head
   unsigned long long force_queue;  // persistent force kernel queue head
   unsigned long long n_near, n_far, n_cell;  // interaction counts
   unsigned long long n_clusters;
@@ -174,6 +173,8 @@ constexpr int HERM_N_BUCKETS = 11;
 // bound pairs), so the hard part dispatches such clusters first.  Only the
 // order of the work depends on it.
 constexpr double CLOSE_RATIO = 0.5;
+// the walk's parts of the group list and the words between their queue heads
+constexpr int WALK_PARTS = 8, WALK_QUEUE_STRIDE = 16;
 // parked members of one p3t_hard_evaluate call at most, and the chunks of
 // the direct sum over all particles for each of them
 constexpr int SLOW_CAP = 1024, SLOW_CHUNKS = 2048;
@@ -286,6 +287,8 @@ struct p3t_ctx {
   int32_t *group_node = nullptr;
   p3t::GroupList *glist = nullptr;
   int32_t *group_order = nullptr;   // groups sorted by work (longest first)
+  int32_t *group_cls = nullptr;     // work class of each group
+  unsigned long long *walk_q = nullptr;  // queue heads of the walk (WALK_PARTS, a cache line each)
   int64_t *scan_tmp = nullptr;
   int64_t scan_tmp_cap = 0;
   int32_t *row_cnt = nullptr;       // per-particle counters (n)

@@ -12,33 +12,94 @@
 // other opened nodes push their two children.  theta = 0 accepts nothing,
 // which reduces the tree force to the direct sum.
 //
-// One wavefront per group, persistent grid pulling groups from a counter.
-// The DFS stack and the three lists live in per-wave global scratch; the
-// finished lists are copied to a shared pool at an atomically reserved
-// offset.  Every write is bounds-checked; an overflow marks the group
-// (offset -1) and sets a status bit so that the host can grow and retry.
+// One wavefront per group, persistent grid.  The wavefront tests up to 64
+// nodes of its DFS stack at a time; the stack, the accepted cells and the
+// opened leaves (as ranges of particles, expanded only when the finished list
+// goes to the shared pool at an atomically reserved offset) live in LDS, with
+// per-wavefront device memory behind them for the groups that need more.  Every
+// write is bounds-checked; an overflow marks the group (offset -1) and sets a
+// status bit so that the host can grow and retry.
+//   Bound by a chain of about 30 frontiers per group, each the load of up to
+// 64 scattered node records and some 200 VALU instructions (more wavefronts
+// per CU than eight change nothing).  With the stack and lists in device
+// memory, a store waited for per frontier, and the particles written one by
+// one to a scratch list first, 2^20 particles took 359 us, 65,536 65, 2048
+// 43; now 199, 31 and 16.  The groups are dealt in eight contiguous
+// parts of the Morton order, a part to the workgroups of one XCD (blockIdx mod
+// 8), whose L2 then serves one region of the tree; a wavefront whose part is
+// done takes groups of the others.
 #include "p3t_internal.h"
 
 namespace p3t {
 
 constexpr int GROUP_CLASSES = 128;
+constexpr int WALK_STACK = 1536, WALK_CELLS = 768, WALK_NEAR = 256, WALK_FAR = 384;
+
+// Work of a group (its i-particles times its list entries, cells counted
+// twice), in classes of half an octave: the force kernels take the groups
+// in descending class, so the longest lists start first and the tail of
+// the launch is short.  Only the order of the work depends on it.
+__device__ __forceinline__ int group_class(int count, int n_cell, int n_near, int n_far) {
+  const uint64_t work = (uint64_t)count * (uint64_t)(n_near + n_far + 2 * n_cell) / 64 + 1;
+  const int msb = 63 - __clzll((long long)work);
+  const int half = msb > 0 ? (int)((work >> (msb - 1)) & 1ull) : 0;
+  return min(GROUP_CLASSES - 1, 2 * msb + half);
+}
+
+// the ranges of one class, expanded in order to out
+__device__ __forceinline__ void expand_ranges(const int2 *lds, int lds_cap, const int32_t *slot, int n_ranges,
+                                              int32_t *out, int lane) {
+  int base = 0;
+  for (int r0 = 0; r0 < n_ranges; r0 += WAVE) {  // uniform
+    const int r = r0 + lane;
+    int2 v = make_int2(0, 0);
+    if (r < n_ranges) v = r < lds_cap ? lds[r] : make_int2(slot[2 * r], slot[2 * r + 1]);
+    const int incl = wave_incl_scan(v.y);
+    int32_t *o = out + base + incl - v.y;
+    for (int q = 0; q < v.y; ++q) o[q] = v.x + q;
+    base += uniform_lane(incl, WAVE - 1);
+  }
+}
 
 __global__ __launch_bounds__(WAVE) void k_walk(const WalkNode *__restrict__ wn, const int32_t *__restrict__ group_node,
-                                               DevCounters *cnt, GroupList *__restrict__ gl, int32_t *__restrict__ pool,
-                                               int64_t pool_cap, int32_t *__restrict__ slot_lists, int cap,
+                                               DevCounters *cnt, unsigned long long *__restrict__ queues,
+                                               GroupList *__restrict__ gl, int32_t *__restrict__ group_cls,
+                                               int32_t *__restrict__ pool, int64_t pool_cap,
+                                               int32_t *__restrict__ slot_lists, int cap,
                                                int32_t *__restrict__ slot_stack, int stack_cap, double theta2,
                                                int n_leaf) {
+  __shared__ int lstk[WALK_STACK], lcell[WALK_CELLS];
+  __shared__ int2 lnear[WALK_NEAR], lfar[WALK_FAR];
   const int lane = threadIdx.x;
+  // device memory behind the LDS lists: entries (cells, stack) and ranges
+  // (two words each) beyond the LDS capacity, at their own index
   int32_t *Lc = slot_lists + (int64_t)blockIdx.x * 3 * cap;
   int32_t *Ln = Lc + cap;
   int32_t *Lf = Ln + cap;
   int32_t *stk = slot_stack + (int64_t)blockIdx.x * stack_cap;
   const int ngroups = uniform_first((int)cnt->n_groups);
+  int part = 0;  // parts finished so far
   for (;;) {
-    // every lane executes the atomic (lane 0 adds one, the others zero), so
-    // no divergent branch feeds the loop exit; lane 0's ticket goes to an SGPR
-    const int gi = (int)wave_fetch_add(&cnt->walk_queue, 1ull);
-    if (gi >= ngroups) break;
+    int gi = -1;
+    while (part < WALK_PARTS) {  // uniform
+      const int s = (blockIdx.x + part) % WALK_PARTS;
+      const int g0 = (int)((int64_t)ngroups * s / WALK_PARTS), g1 = (int)((int64_t)ngroups * (s + 1) / WALK_PARTS);
+      unsigned long long *q = queues + (int64_t)s * WALK_QUEUE_STRIDE;
+      // another part's queue is looked at first: the atomics of every
+      // wavefront that finds it empty would queue up behind each other
+      if (part > 0 &&
+          uniform_first((int)__hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >= g1 - g0) {
+        ++part;
+        continue;
+      }
+      const int k = (int)wave_fetch_add(q, 1ull);
+      if (k < g1 - g0) {
+        gi = g0 + k;
+        break;
+      }
+      ++part;
+    }
+    if (gi < 0) break;
     const int g = group_node[gi];
     double glo[3], ghi[3];
 #pragma unroll
@@ -47,13 +108,17 @@ __global__ __launch_bounds__(WAVE) void k_walk(const WalkNode *__restrict__ wn, 
       ghi[d] = wn[g].hi[d];
     }
     const double greach = wn[g].reach;
-    int top = 1, ncell = 0, nnear = 0, nfar = 0;
+    const int gcount = wn[g].count;
+    int top = 1, ncell = 0, nnear = 0, nfar = 0;  // entries, cells, near and far ranges
+    int tnear = 0, tfar = 0;                      // this lane's near and far particles
     bool ovf = false;
-    if (lane == 0) stk[0] = 0;  // root
+    __syncthreads();
+    if (lane == 0) lstk[0] = 0;  // root
     while (top > 0 && !ovf) {
       __syncthreads();
       const int npop = top < WAVE ? top : WAVE;
-      const int node = lane < npop ? stk[top - npop + lane] : -1;
+      const int p0 = top - npop + lane;
+      const int node = lane < npop ? (p0 < WALK_STACK ? lstk[p0] : stk[p0]) : -1;
       top -= npop;
       __syncthreads();
       int outcome = 0;  // 0 none, 1 cell, 2 near leaf, 3 far leaf, 4 open
@@ -83,40 +148,43 @@ __global__ __launch_bounds__(WAVE) void k_walk(const WalkNode *__restrict__ wn, 
         else
           outcome = 4;
       }
-      // cells
-      const unsigned long long mc = __ballot(outcome == 1);
+      const unsigned long long mc = __ballot(outcome == 1), mn = __ballot(outcome == 2), mf = __ballot(outcome == 3),
+                               mo = __ballot(outcome == 4);
       if (outcome == 1) {
         const int p = ncell + popc_below(mc);
-        if (p < cap) Lc[p] = node;
-      }
-      ncell += (int)__popcll(mc);
-      // near particles
-      {
-        const int cn = outcome == 2 ? count : 0;
-        const int incl = wave_incl_scan(cn);
-        const int start = nnear + incl - cn;
-        for (int q = 0; q < cn && start + q < cap; ++q) Ln[start + q] = first + q;
-        nnear += uniform_lane(incl, WAVE - 1);
-      }
-      // far particles
-      {
-        const int cf = outcome == 3 ? count : 0;
-        const int incl = wave_incl_scan(cf);
-        const int start = nfar + incl - cf;
-        for (int q = 0; q < cf && start + q < cap; ++q) Lf[start + q] = first + q;
-        nfar += uniform_lane(incl, WAVE - 1);
-      }
-      // opened internal nodes: push both children
-      const unsigned long long mo = __ballot(outcome == 4);
-      if (outcome == 4) {
+        if (p < WALK_CELLS)
+          lcell[p] = node;
+        else if (p < cap)
+          Lc[p] = node;
+      } else if (outcome == 2) {
+        const int p = nnear + popc_below(mn);
+        if (p < WALK_NEAR)
+          lnear[p] = make_int2(first, count);
+        else if (2 * p + 1 < cap)
+          Ln[2 * p] = first, Ln[2 * p + 1] = count;
+        tnear += count;
+      } else if (outcome == 3) {
+        const int p = nfar + popc_below(mf);
+        if (p < WALK_FAR)
+          lfar[p] = make_int2(first, count);
+        else if (2 * p + 1 < cap)
+          Lf[2 * p] = first, Lf[2 * p + 1] = count;
+        tfar += count;
+      } else if (outcome == 4) {  // both children
         const int p = top + 2 * popc_below(mo);
-        if (p + 1 < stack_cap) {
-          stk[p] = left;
+        if (p + 1 < WALK_STACK) {
+          lstk[p] = left;
+          lstk[p + 1] = right;
+        } else if (p + 1 < stack_cap) {
+          (p < WALK_STACK ? lstk : stk)[p] = left;
           stk[p + 1] = right;
         }
       }
+      ncell += (int)__popcll(mc);
+      nnear += (int)__popcll(mn);
+      nfar += (int)__popcll(mf);
       top += 2 * (int)__popcll(mo);
-      if (ncell > cap || nnear > cap || nfar > cap || top > stack_cap) ovf = true;
+      if (ncell > cap || 2 * nnear > cap || 2 * nfar > cap || top > stack_cap) ovf = true;
     }
     if (ovf) {
       if (lane == 0) {
@@ -126,40 +194,42 @@ __global__ __launch_bounds__(WAVE) void k_walk(const WalkNode *__restrict__ wn, 
         o.n_cell = o.n_near = o.n_far = 0;
         o.node = g;
         gl[gi] = o;
+        group_cls[gi] = 0;
       }
       continue;
     }
     __syncthreads();
-    const int total = ncell + nnear + nfar;
+    const int np = uniform_first(wave_sum(tnear)), nq = uniform_first(wave_sum(tfar));
+    const int total = ncell + np + nq;
     const long long off = (long long)wave_fetch_add(&cnt->pool_cursor, (unsigned long long)total);
-    if (off + total > pool_cap) {
-      if (lane == 0) {
-        set_flag(cnt, P3T_FLAG_LIST_OVERFLOW);
-        GroupList o;
-        o.off = -1;
-        o.n_cell = o.n_near = o.n_far = 0;
-        o.node = g;
-        gl[gi] = o;
-      }
-      continue;
-    }
-    for (int q = lane; q < ncell; q += WAVE) pool[off + q] = Lc[q];
-    for (int q = lane; q < nnear; q += WAVE) pool[off + ncell + q] = Ln[q];
-    for (int q = lane; q < nfar; q += WAVE) pool[off + ncell + nnear + q] = Lf[q];
+    const bool fits = off + total <= pool_cap;
     if (lane == 0) {
+      if (!fits) set_flag(cnt, P3T_FLAG_LIST_OVERFLOW);
       GroupList o;
-      o.off = off;
-      o.n_cell = ncell;
-      o.n_near = nnear;
-      o.n_far = nfar;
+      o.off = fits ? off : -1;
+      o.n_cell = fits ? ncell : 0;
+      o.n_near = fits ? np : 0;
+      o.n_far = fits ? nq : 0;
       o.node = g;
       gl[gi] = o;
+      group_cls[gi] = group_class(gcount, o.n_cell, o.n_near, o.n_far);
     }
+    if (!fits) continue;
+    for (int q = lane; q < ncell; q += WAVE) pool[off + q] = q < WALK_CELLS ? lcell[q] : Lc[q];
+    expand_ranges(lnear, WALK_NEAR, Ln, nnear, pool + off + ncell, lane);
+    expand_ranges(lfar, WALK_FAR, Lf, nfar, pool + off + ncell + np, lane);
   }
 }
 
-__global__ void k_reset_queues(DevCounters *cnt) {
-  cnt->walk_queue = 0;
+// Queue heads and per-evaluation counters; close: the close-pair flags to
+// clear (n4 words, nullable).
+__global__ void k_reset_queues(DevCounters *cnt, unsigned long long *__restrict__ queues, int32_t *__restrict__ close,
+                               int64_t n4) {
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (close)
+    for (int64_t k = t0; k < n4; k += (int64_t)gridDim.x * blockDim.x) close[k] = 0;
+  if (t0 < WALK_PARTS) queues[t0 * WALK_QUEUE_STRIDE] = 0;
+  if (t0 != 0) return;
   cnt->force_queue = 0;
   for (int k = 0; k < 3; ++k) cnt->queue[k] = 0;
   cnt->n_cand = 0;
@@ -170,29 +240,12 @@ __global__ void k_reset_queues(DevCounters *cnt) {
   cnt->n_cell = 0;
 }
 
-// Sort key of a group: (work descending, group index ascending).
-// A device count above n_static (the host's bound, from the last evaluation)
-// sets P3T_FLAG_GROUP_BOUND: the sort and the force then cover only the
-// first n_static groups and the host evaluates again with the bound n.
-// Work of a group (its i-particles times its list entries, cells counted
-// twice), in classes of half an octave: the force kernels take the groups
-// in descending class, so the longest lists start first and the tail of
-// the launch is short.  Only the order of the work depends on it.
-__device__ __forceinline__ int group_class(const GroupList &L, const WalkNode *__restrict__ wn) {
-  const uint64_t ni = (uint64_t)wn[L.node].count;
-  const uint64_t work = ni * (uint64_t)(L.n_near + L.n_far + 2 * L.n_cell) / 64 + 1;
-  const int msb = 63 - __clzll((long long)work);
-  const int half = msb > 0 ? (int)((work >> (msb - 1)) & 1ull) : 0;
-  return min(GROUP_CLASSES - 1, 2 * msb + half);
-}
-
 // One workgroup: a counting sort of the groups by class, largest first
 // (within a class in any order).  A device count above n_static (the host's
 // bound, from the last evaluation) sets P3T_FLAG_GROUP_BOUND: the order and
 // the force then cover only the first n_static groups and the host
 // evaluates again with the bound n.
-__global__ __launch_bounds__(1024) void k_group_order(const GroupList *__restrict__ gl,
-                                                      const WalkNode *__restrict__ wn, int n_static, DevCounters *cnt,
+__global__ __launch_bounds__(1024) void k_group_order(const int32_t *__restrict__ cls, int n_static, DevCounters *cnt,
                                                       int32_t *__restrict__ order) {
   __shared__ int hist[GROUP_CLASSES];
   const int t = threadIdx.x;
@@ -203,7 +256,7 @@ __global__ __launch_bounds__(1024) void k_group_order(const GroupList *__restric
   }
   for (int q = t; q < GROUP_CLASSES; q += blockDim.x) hist[q] = 0;
   __syncthreads();
-  for (int g = t; g < ng; g += blockDim.x) atomicAdd(&hist[group_class(gl[g], wn)], 1);
+  for (int g = t; g < ng; g += blockDim.x) atomicAdd(&hist[cls[g]], 1);
   __syncthreads();
   if (t == 0) {  // exclusive offsets, largest class first
     int acc = 0;
@@ -214,24 +267,34 @@ __global__ __launch_bounds__(1024) void k_group_order(const GroupList *__restric
     }
   }
   __syncthreads();
-  for (int g = t; g < ng; g += blockDim.x) order[atomicAdd(&hist[group_class(gl[g], wn)], 1)] = g;
+  for (int g = t; g < ng; g += blockDim.x) order[atomicAdd(&hist[cls[g]], 1)] = g;
+}
+
+static void reset(p3t_ctx *c, bool close) {
+  const int64_t n4 = (c->n + 3) / 4;
+  const unsigned g = close ? (unsigned)std::max<int64_t>(1, std::min<int64_t>(1024, (n4 + 255) / 256)) : 1u;
+  hipLaunchKernelGGL(k_reset_queues, dim3(g), dim3(256), 0, c->stream, c->cnt, c->walk_q,
+                     close ? reinterpret_cast<int32_t *>(c->close_flag) : nullptr, n4);
 }
 
 hipError_t walk_groups(p3t_ctx *c, int64_t n_groups_max) {
   hipStream_t s = c->stream;
-  hipLaunchKernelGGL(k_reset_queues, dim3(1), dim3(1), 0, s, c->cnt);
+  reset(c, true);
   const double th = c->P.theta;
-  hipLaunchKernelGGL(k_walk, dim3(c->walk_slots), dim3(WAVE), 0, s, c->wnode, c->group_node, c->cnt, c->glist, c->pool,
-                     c->pool_cap, c->slot_lists, (int)c->slot_cap_list, c->slot_stack, (int)c->slot_cap_stack, th * th,
-                     c->P.n_leaf_max);
+  // small disks have few groups (about n / 87): no more wavefronts than could find one
+  const unsigned g = (unsigned)std::min<int64_t>(c->walk_slots, std::max<int64_t>(64, c->n / 16));
+  hipLaunchKernelGGL(k_walk, dim3(g), dim3(WAVE), 0, s, c->wnode, c->group_node, c->cnt, c->walk_q, c->glist,
+                     c->group_cls, c->pool, c->pool_cap, c->slot_lists, (int)c->slot_cap_list, c->slot_stack,
+                     (int)c->slot_cap_stack, th * th, c->P.n_leaf_max);
   // longest-first order for the force kernels; the device-side group count
   // bounds it, so n_groups_max may be any upper bound (a captured graph
   // passes the particle count)
   const int ns = (int)std::min<int64_t>(n_groups_max, INT32_MAX);
-  hipLaunchKernelGGL(k_group_order, dim3(1), dim3(1024), 0, s, c->glist, c->wnode, ns, c->cnt, c->group_order);
+  hipLaunchKernelGGL(k_group_order, dim3(1), dim3(1024), 0, s, c->group_cls, ns, c->cnt, c->group_order);
   return hipGetLastError();
 }
 
-void reset_queues(p3t_ctx *c) { hipLaunchKernelGGL(k_reset_queues, dim3(1), dim3(1), 0, c->stream, c->cnt); }
+// (the frozen-list evaluation keeps the pairs, and the close flags, of the last one)
+void reset_queues(p3t_ctx *c) { reset(c, false); }
 
 }  // namespace p3t

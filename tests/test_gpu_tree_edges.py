@@ -32,7 +32,7 @@ def spread(v):
     return out
 
 
-def reference(pos, m, ro, rs, n_leaf, n_group):
+def reference(pos, m, ro, rs, n_leaf, n_group, theta=THETA):
     """(acc, sum of term magnitudes) over the tree's lists."""
     n = m.shape[0]
     lo, ext = pos.min(1, keepdims=True), (pos.max(1) - pos.min(1)).max()
@@ -75,7 +75,7 @@ def reference(pos, m, ro, rs, n_leaf, n_group):
             cg = np.maximum(np.maximum(glo - c, c - ghi), 0.0)
             sep = (gap * gap).sum() > (max(gr, cr) * (1.0 + 1e-12)) ** 2
             cnt = cb - ca + 1
-            if sep and cnt > 1 and (chi - clo).max() ** 2 < THETA ** 2 * (cg * cg).sum():
+            if sep and cnt > 1 and (chi - clo).max() ** 2 < theta ** 2 * (cg * cg).sum():
                 d = c - xi
                 r = np.sqrt((d * d).sum(1))[:, None]
                 Qd = d @ Q
@@ -156,4 +156,25 @@ def test_sort_sizes(gpu, orc, name, n):
     ref = orc.soft_acc(d.pos, d.mass, ro, p, idx=idx)
     num, den = ((acc[:, idx] - ref) ** 2).sum(0), (ref ** 2).sum(0)
     assert np.sqrt(np.mean(num / den)) < 2e-3 and np.sqrt(num.sum() / den.sum()) < 5e-4
+    ctx.close()
+
+
+@pytest.mark.parametrize("theta,n_leaf", [(0.0, 16), (0.1, 1)])
+def test_walk_lists_beyond_lds(gpu, orc, theta, n_leaf):
+    """Lists, stacks and ranges longer than the walk keeps in LDS (theta = 0
+    opens every node; leaves of one particle make a range each).  theta = 0 is the direct sum to rounding (1e-13
+    rms); at theta = 0.1 the numpy reference's terms, as above."""
+    d = diskgen.workload("disk2k_equal", 6000)
+    p = orc.Params()
+    ro, rs, _ = orc.cutoffs(d.pos, d.vel, d.mass, p)
+    ctx = gpu.Context(gparams(gpu, p, theta=theta, multipole=2, n_leaf_max=n_leaf))
+    ctx.build_tree(T(d.pos), T(d.vel), T(d.mass), T(ro), T(rs))
+    acc = ctx.compute_soft_force().cpu().numpy()
+    if theta == 0.0:
+        ref = orc.soft_acc(d.pos, d.mass, ro, p)
+        e = ((acc - ref) ** 2).sum(0) / (ref ** 2).sum(0)
+        assert np.sqrt(e.mean()) < 1e-13 and ctx.stats()["n_near"] + ctx.stats()["n_far"] == d.n * (d.n - 1)
+    else:
+        ref, mag = reference(d.pos, d.mass, ro, rs, n_leaf, 128, theta)
+        assert (np.sqrt(((acc - ref) ** 2).sum(0)) <= 1e-12 * mag).all()
     ctx.close()
