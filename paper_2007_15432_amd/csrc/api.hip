@@ -96,13 +96,14 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   total += bytes(n_cap, sizeof(GroupList));
   total += 2 * bytes(n_cap, sizeof(int32_t));                                       // group order, classes
   total += bytes(WALK_PARTS * WALK_QUEUE_STRIDE, sizeof(unsigned long long));       // walk queues
-  total += bytes(n_cap, sizeof(int32_t)) + bytes(n_cap + 1, sizeof(int64_t));       // row_cnt, csr_ptr
+  total += 4 * bytes(n_cap, sizeof(int32_t));                    // row_cnt, cl_cnt, cl_slot, cl_start
+  total += bytes(2, sizeof(int64_t)) + bytes(scan_sums_need(), sizeof(uint64_t));  // cluster count, scan sums
   total += bytes(n_cap, sizeof(int32_t)) + 2 * bytes(n_cap, sizeof(uint64_t));      // uf, cl keys
   total += bytes(cut_part_need(n_cap), sizeof(double)) + bytes(n_cap, sizeof(int32_t));  // cut-off bins
   total += bytes(n_cap + 4, sizeof(uint8_t));                                                // close flags
   total += bytes(3 * n_cap, sizeof(double));
   total += bytes(HERM_BC_WORDS, sizeof(int32_t)) + bytes(HERM_N_BUCKETS * n_cap, sizeof(int32_t));  // buckets
-  total += bytes(n_cap, sizeof(int32_t)) + bytes(n_cap, sizeof(uint8_t));  // cluster buckets, slow flags
+  total += bytes(n_cap, sizeof(uint8_t));                                     // slow flags
   total += 3 * bytes(n_cap + 1, sizeof(int32_t));                             // hard-step labels, clusters
   total += 4096;
   if (c->prep_state) {  // a cluster preparation may still use the old arena
@@ -144,7 +145,11 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   c->group_cls = A.take<int32_t>(n_cap);
   c->walk_q = A.take<unsigned long long>(WALK_PARTS * WALK_QUEUE_STRIDE);
   c->row_cnt = A.take<int32_t>(n_cap);
-  c->csr_ptr = A.take<int64_t>(n_cap + 1);
+  c->cl_cnt = A.take<int32_t>(n_cap);
+  c->cl_slot = A.take<int32_t>(n_cap);
+  c->cl_start = A.take<int32_t>(n_cap);
+  c->cl_nc = A.take<int64_t>(2);
+  c->cl_sums = A.take<uint64_t>(scan_sums_need());
   c->uf_parent = A.take<int32_t>(n_cap);
   c->cl_keys = A.take<uint64_t>(n_cap);
   c->cl_keys_alt = A.take<uint64_t>(n_cap);
@@ -154,13 +159,16 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   c->tmp_d = A.take<double>(3 * n_cap);
   c->herm_bcount = A.take<int32_t>(HERM_BC_WORDS);
   c->herm_blists = A.take<int32_t>(HERM_N_BUCKETS * n_cap);
-  c->herm_clbk = A.take<int32_t>(n_cap);
   c->slow_flag = A.take<uint8_t>(n_cap);
   c->hs_label = A.take<int32_t>(n_cap + 1);
   c->hs_cl_ptr = A.take<int32_t>(n_cap + 1);
   c->hs_cl_mem = A.take<int32_t>(n_cap + 1);
   if (!c->hs_cl_mem) return fail(c, P3T_ERR_HIP, "arena layout overflow (internal)");
   HIP_OK(c, hipMemsetAsync(c->cnt, 0, sizeof(DevCounters), c->stream));
+  // zero between calls: every pass that counts into them leaves them clear
+  HIP_OK(c, fill_i32(c->row_cnt, 0, n_cap, c->stream));
+  HIP_OK(c, fill_i32(c->cl_cnt, 0, n_cap, c->stream));
+  HIP_OK(c, fill_i32(reinterpret_cast<int32_t *>(c->cl_nc), 0, 4, c->stream));
   c->n_cap = n_cap;
   c->tree_valid = c->force_valid = false;
   c->park_flags_valid = 0;
@@ -188,7 +196,6 @@ p3t_status ensure_lists(p3t_ctx *c, int64_t n) {
   if (!c->pairs) {
     const int64_t cap = std::max<int64_t>(1 << 16, 2 * n);
     HIP_OK(c, dev_alloc(c->pairs, cap));
-    HIP_OK(c, dev_alloc(c->csr_col, cap));
     c->pair_cap = cap;
   }
   if (!c->cands) {
@@ -200,8 +207,10 @@ p3t_status ensure_lists(p3t_ctx *c, int64_t n) {
 }
 
 p3t_status sync_counters(p3t_ctx *c, DevCounters *h) {
-  HIP_OK(c, hipMemcpyAsync(h, c->cnt, sizeof(DevCounters), hipMemcpyDeviceToHost, c->stream));
+  // through pinned memory: a copy to pageable memory is staged by the runtime
+  HIP_OK(c, hipMemcpyAsync(c->host_words, c->cnt, sizeof(DevCounters), hipMemcpyDeviceToHost, c->stream));
   HIP_OK(c, hipStreamSynchronize(c->stream));
+  std::memcpy(h, c->host_words, sizeof(DevCounters));
   return P3T_OK;
 }
 
@@ -235,9 +244,8 @@ CloseSrc close_src(p3t_ctx *c) {
 
 // Enqueues on aux_stream, right behind the evaluation just enqueued on the
 // main stream and before its counters are read, the clusters of the next
-// hard part: labels straight from the pair list (its length read on the
-// device), the cluster CSR and the bucket words (copied to pinned host
-// memory).  It runs while the host reads the counters and enqueues the
+// hard part: labels from the union-find that the evaluation filled, the
+// cluster CSR and the bucket words (copied to pinned host memory).  It runs while the host reads the counters and enqueues the
 // kicks and radii that follow; eval_finish keeps it (prep_confirm) when the
 // evaluation needs no retry.  p3t_hard_step / p3t_hard_evaluate take the
 // result instead of computing it.
@@ -258,15 +266,14 @@ p3t_status prep_enqueue(p3t_ctx *c) {
   } swap{c, c->stream};
   c->stream = c->aux_stream;
   ev_record(c, 20);
-  HIP_OK(c, labels_pairs(c, n, c->hs_label));
-  HIP_OK(c, clusters_csr_dev(c, n, c->hs_label, c->hs_cl_ptr, c->hs_cl_mem, true));
+  HIP_OK(c, clusters_pairs(c, n, c->hs_label, c->hs_cl_ptr, c->hs_cl_mem, c->herm_bcount, HERM_BC_WORDS));
   // clusters with a close pair at this evaluation, or with a member parked
   // in the last hard part, are dispatched first
   const CloseSrc close = close_src(c);
   // the work counters of the hard part just finished are read after this
   // is enqueued: prep_take zeroes them instead
-  HIP_OK(c, herm_bucket_enqueue(c, c->aux_stream, n, n, c->hs_cl_ptr, c->hs_cl_mem, c->node_scan + n, c->hc_pinned,
-                                false, close));
+  HIP_OK(c, herm_bucket_enqueue(c, c->aux_stream, n, n, c->hs_cl_ptr, c->hs_cl_mem, c->cl_nc, c->hc_pinned,
+                                false, close, true));
   ev_record(c, 21);
   HIP_OK(c, hipEventRecord(c->prep_ev[1], c->aux_stream));
   c->prep_state = 2;
@@ -396,7 +403,7 @@ uint64_t mix(uint64_t h, uint64_t v) {
 uint64_t graph_key(const p3t_ctx *c, int64_t n, const void *const *ptrs, int np) {
   uint64_t h = mix(0x51ed270b27a1c3ull, (uint64_t)n);
   for (int k = 0; k < np; ++k) h = mix(h, (uint64_t)(uintptr_t)ptrs[k]);
-  const void *own[] = {c->arena.base, c->pool, c->slot_lists, c->slot_stack, c->pairs, c->cands, c->csr_col};
+  const void *own[] = {c->arena.base, c->pool, c->slot_lists, c->slot_stack, c->pairs, c->cands};
   for (const void *q : own) h = mix(h, (uint64_t)(uintptr_t)q);
   const int64_t caps[] = {c->n_cap, c->pool_cap, c->slot_cap_list, c->slot_cap_stack, c->pair_cap, c->cand_cap,
                           c->walk_slots, c->fcfg.split, c->fcfg.unroll, c->fcfg.waves_per_cu, c->force_persistent,
@@ -433,7 +440,8 @@ p3t_status p3t_create(const p3t_params *p, void *stream, p3t_ctx **out) {
       delete c;
       return P3T_ERR_HIP;
     }
-  if (alloc_arena(c, 1024) != P3T_OK) {
+  if (hipHostMalloc((void **)&c->host_words, sizeof(DevCounters)) != hipSuccess || alloc_arena(c, 1024) != P3T_OK) {
+    if (c->host_words) (void)hipHostFree(c->host_words);
     delete c;
     return P3T_ERR_HIP;
   }
@@ -456,8 +464,8 @@ p3t_status p3t_destroy(p3t_ctx *c) {
   for (auto &ev : c->slow_ev)
     if (ev) (void)hipEventDestroy(ev);
   void *bufs[] = {c->arena.base, c->pool,    c->slot_lists, c->slot_stack, c->pairs,
-                  c->csr_col,    c->cands,   c->adj_buf,    c->ov_buf,     c->pairs_d,
-                  c->huge_buf,   c->coll_buf, c->merge_st,  c->merge_i32};
+                  c->cands,      c->adj_buf, c->ov_buf,     c->pairs_d,    c->huge_buf,
+                  c->coll_buf,   c->merge_st, c->merge_i32};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
   for (auto &e : c->ev)
@@ -465,6 +473,7 @@ p3t_status p3t_destroy(p3t_ctx *c) {
   for (auto &e : c->prep_ev)
     if (e) (void)hipEventDestroy(e);
   if (c->hc_pinned) (void)hipHostFree(c->hc_pinned);
+  if (c->host_words) (void)hipHostFree(c->host_words);
   delete c;
   return P3T_OK;
 }
@@ -501,7 +510,6 @@ p3t_status p3t_reserve(p3t_ctx *c, int64_t n_max, int64_t nnz_max) {
   if ((st = ensure_lists(c, n_max)) != P3T_OK) return st;
   if (nnz_max > c->pair_cap) {
     HIP_OK(c, dev_alloc(c->pairs, nnz_max));
-    HIP_OK(c, dev_alloc(c->csr_col, nnz_max));
     c->pair_cap = nnz_max;
     c->force_valid = false;
   }
@@ -582,8 +590,7 @@ p3t_status grow_for_retry(p3t_ctx *c, const DevCounters &h) {
     if ((int64_t)h.n_pairs > c->pair_cap) {
       const int64_t cap = (int64_t)h.n_pairs + (int64_t)h.n_pairs / 4 + 1024;
       HIP_OK(c, dev_alloc(c->pairs, cap));
-      HIP_OK(c, dev_alloc(c->csr_col, cap));
-      c->pair_cap = cap;
+        c->pair_cap = cap;
     }
     if ((int64_t)h.n_cand > c->cand_cap) {
       const int64_t cap = (int64_t)h.n_cand + (int64_t)h.n_cand / 4 + 1024;
@@ -601,7 +608,6 @@ bool eval_finish(p3t_ctx *c, const DevCounters &h, unsigned *num, p3t_status *st
 p3t_status p3t_compute_soft_force(p3t_ctx *c, double *acc3) {
   if (!c) return P3T_ERR_ARG;
   prep_join(c);
-  c->uf_early = 0;  // a new pair list
   if (!c->tree_valid) return fail(c, P3T_ERR_STATE, "compute_soft_force: no tree (call p3t_build_tree)");
   if (bad_ptr(acc3, c->n)) return fail(c, P3T_ERR_ARG, "compute_soft_force: null pointer");
   c->force_valid = false;
@@ -641,7 +647,6 @@ namespace {
 p3t_status eval_enqueue(p3t_ctx *c, int64_t n, const double *pos3, const double *vel3, const double *mass,
                         const double *r_out, const double *r_search, double *acc3, int32_t use_graph) {
   p3t_status st;
-  c->uf_early = 0;  // a new pair list
   if (!use_graph) {
     if ((st = p3t_build_tree(c, n, pos3, vel3, mass, r_out, r_search)) != P3T_OK) return st;
     ev_record(c, 4);
@@ -799,15 +804,12 @@ p3t_status p3t_neighbour_list(p3t_ctx *c, int64_t *row_ptr, int32_t *col, int64_
     return P3T_OK;
   }
   ev_record(c, 7);
-  HIP_OK(c, build_csr(c, n, np));
   if (np > cap) {
     HIP_OK(c, hipStreamSynchronize(c->stream));
     return fail(c, P3T_ERR_CAPACITY, "neighbour_list: nnz %lld exceeds cap %lld", (long long)np, (long long)cap);
   }
   if (np > 0 && !col) return fail(c, P3T_ERR_ARG, "neighbour_list: null col");
-  HIP_OK(c, hipMemcpyAsync(row_ptr, c->csr_ptr, sizeof(int64_t) * (n + 1), hipMemcpyDeviceToDevice, c->stream));
-  if (np > 0) HIP_OK(c, hipMemcpyAsync(col, c->csr_col, sizeof(int32_t) * np, hipMemcpyDeviceToDevice, c->stream));
-  if (label) HIP_OK(c, labels_cc(c, n, label));
+  HIP_OK(c, neighbour_csr(c, n, np, row_ptr, col, label));
   ev_record(c, 8);
   HIP_OK(c, hipStreamSynchronize(c->stream));
   if (c->timing) c->stats.ms_neighbour = ev_ms(c, 7, 8);
@@ -951,13 +953,11 @@ p3t_status p3t_hard_step(p3t_ctx *c, double *pos3, double *vel3, const double *m
   const bool prepared = prep_take(c, n, hc);
   ev_record(c, 9);
   if (!prepared) {
-    HIP_OK(c, build_csr(c, n, c->n_pairs));
-    HIP_OK(c, labels_cc(c, n, c->hs_label));
-    HIP_OK(c, clusters_csr_dev(c, n, c->hs_label, c->hs_cl_ptr, c->hs_cl_mem));
+    HIP_OK(c, clusters_pairs(c, n, c->hs_label, c->hs_cl_ptr, c->hs_cl_mem, c->herm_bcount, HERM_BC_WORDS));
   }
   ev_record(c, 19);
   hipError_t e = prepared ? (hc[HERM_BC_BAD] ? hipErrorInvalidDevicePointer : hipSuccess)
-                          : herm_bucket(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, c->node_scan + n, hc, close_src(c));
+                          : herm_bucket(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, c->cl_nc, hc, close_src(c), true);
   HIP_OK(c, e);
   HIP_OK(c, aux_streams(c));
   HIP_OK(c, herm_launch(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, pos3, vel3, mass, r_out, dt_hard, nullptr, nullptr,
@@ -997,9 +997,7 @@ p3t_status p3t_hard_step_collide(p3t_ctx *c, double *pos3, double *vel3, const d
   const bool prepared = prep_take(c, n, hcw);
   ev_record(c, 9);
   if (!prepared) {
-    HIP_OK(c, build_csr(c, n, c->n_pairs));
-    HIP_OK(c, labels_cc(c, n, c->hs_label));
-    HIP_OK(c, clusters_csr_dev(c, n, c->hs_label, c->hs_cl_ptr, c->hs_cl_mem));
+    HIP_OK(c, clusters_pairs(c, n, c->hs_label, c->hs_cl_ptr, c->hs_cl_mem, c->herm_bcount, HERM_BC_WORDS));
   }
   ev_record(c, 19);
   HIP_OK(c, iota_i32(merged_into, n, c->stream));
@@ -1010,7 +1008,7 @@ p3t_status p3t_hard_step_collide(p3t_ctx *c, double *pos3, double *vel3, const d
   hc.merged = merged_into;
   hc.ceps = c->coll_buf;
   hipError_t e = prepared ? (hcw[HERM_BC_BAD] ? hipErrorInvalidDevicePointer : hipSuccess)
-                          : herm_bucket(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, c->node_scan + n, hcw, close_src(c));
+                          : herm_bucket(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, c->cl_nc, hcw, close_src(c), true);
   HIP_OK(c, e);
   HIP_OK(c, aux_streams(c));
   HIP_OK(c, herm_launch(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, pos3, vel3, mass, r_out, dt_hard, nullptr, nullptr,
@@ -1132,13 +1130,11 @@ p3t_status p3t_hard_evaluate(p3t_ctx *c, double *pos3, double *vel3, const doubl
   if (split && (st = ensure_overlap(c)) != P3T_OK) return st;
   ev_record(c, 9);
   if (!prepared) {
-    HIP_OK(c, build_csr(c, n, c->n_pairs));
-    HIP_OK(c, labels_cc(c, n, c->hs_label));
-    HIP_OK(c, clusters_csr_dev(c, n, c->hs_label, c->hs_cl_ptr, c->hs_cl_mem));
+    HIP_OK(c, clusters_pairs(c, n, c->hs_label, c->hs_cl_ptr, c->hs_cl_mem, c->herm_bcount, HERM_BC_WORDS));
   }
   ev_record(c, 19);
   hipError_t e = prepared ? (hc[HERM_BC_BAD] ? hipErrorInvalidDevicePointer : hipSuccess)
-                          : herm_bucket(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, c->node_scan + n, hc, close_src(c));
+                          : herm_bucket(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, c->cl_nc, hc, close_src(c), true);
   if (n_clusters_host) *n_clusters_host = hc[HERM_BC_NC];
   HIP_OK(c, e);
   HIP_OK(c, aux_streams(c));
@@ -1203,9 +1199,6 @@ p3t_status p3t_hard_evaluate(p3t_ctx *c, double *pos3, double *vel3, const doubl
     HIP_OK(c, slow_direct(c, pos3, vel3, mass, r_out, r_search, ns, c->slow_stream));
     HIP_OK(c, hipEventRecord(c->slow_ev[1], c->slow_stream));
   }
-  // the next hard part's union-find over the pairs written so far, while
-  // the main stream would wait for the second one anyway
-  if (ns > 0 && st == P3T_OK) HIP_OK(c, labels_pairs_early(c, n));
   // join: S's new state into pos3 / vel3, its terms into acc3
   if (ns > 0) HIP_OK(c, hipStreamWaitEvent(c->stream, c->slow_ev[1], 0));
   ev_record(c, 15);

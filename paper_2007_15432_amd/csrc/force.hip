@@ -163,6 +163,7 @@ __global__ __launch_bounds__(WAVE) void k_force(ForceArgs A) {
                                   A.srs[i], A.sx[j], A.sy[j], A.sz[j], A.svx[j], A.svy[j], A.svz[j], A.sm[j],
                                   A.sro[j], A.srs[j], A.G, A.rsch2, A.rsch3, A.dt)) {
               mark_close_pair(A, i, j);
+              join_pair(A, A.sid[i], A.sid[j]);
               const unsigned long long p = atomicAdd(&A.cnt->n_pairs, 1ull);
               if ((int64_t)p < A.pair_cap)
                 A.pairs[p] = make_int2(A.sid[i], A.sid[j]);
@@ -431,6 +432,7 @@ hipError_t soft_force(p3t_ctx *c, int64_t n_groups_max, double *acc3, bool froze
   if (frozen) A.pair_cap = A.cand_cap = 0;
   // the close pairs of this evaluation (cleared with the queues before the walk)
   A.close = frozen ? nullptr : c->close_flag;
+  A.uf = frozen ? nullptr : c->uf_parent;
   A.close_k = P.G * P.dt_soft * P.dt_soft / (CLOSE_RATIO * CLOSE_RATIO);
   A.acc = acc3;
   A.n = c->n;

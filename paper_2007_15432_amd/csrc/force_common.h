@@ -16,6 +16,7 @@ struct ForceArgs {
   DevCounters *cnt;
   int2 *pairs;
   int64_t pair_cap;
+  int32_t *uf;  // union-find parents, joined as pairs are found (nullable)
   int2 *cands;  // neighbour candidates (sorted indices), split form
   const uint8_t *slow;  // caller's order: pairs with a flagged member are not reported (nullable)
   int64_t cand_cap;
@@ -44,7 +45,13 @@ __device__ __forceinline__ void mark_close_pair(const ForceArgs &A, int i, int j
   }
 }
 
-// the split form (one kernel per interaction class), force_split.hip
+// Joins the clusters of a neighbour pair (caller's indices).  Every pair is
+// found from both sides (the test is symmetric): joined once.
+__device__ __forceinline__ void join_pair(const ForceArgs &A, int a, int b) {
+  if (A.uf && a < b) uf_union(A.uf, a, b);
+}
+
+// the split form (a loop per interaction class), force_split.hip
 hipError_t soft_force_split(p3t_ctx *c, const ForceArgs &A, unsigned nonpersistent_grid, double *acc3);
 
 // Neighbour test of Section 2.3 (closest approach over the step compared

@@ -715,8 +715,10 @@ __global__ void k_cand_test(ForceArgs A) {
     if (nb) {
       mark_close_pair(A, i, j);
       const unsigned long long q = o0 + popc_below(bal);
+      const int a = A.sid[i], b = A.sid[j];
+      join_pair(A, a, b);
       if ((int64_t)q < A.pair_cap)
-        A.pairs[q] = make_int2(A.sid[i], A.sid[j]);
+        A.pairs[q] = make_int2(a, b);
       else
         set_flag(A.cnt, P3T_FLAG_PAIR_OVERFLOW);
     }

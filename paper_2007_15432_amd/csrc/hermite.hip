@@ -1501,29 +1501,6 @@ __device__ __forceinline__ int bucket_of(int size, int cap) {
   return 10;
 }
 
-// Bucket the clusters by size with one atomic per bucket per wavefront; also
-// validate the caller's cluster arrays (offsets non-decreasing from >= 0,
-// members in [0, n)); a violation sets bcount[BC_BAD] and nothing is integrated.
-// Bucket lists.  Each workgroup owns a contiguous range of clusters: it
-// counts its clusters per bucket in LDS, reserves its share of every bucket
-// with one global atomic per bucket, then writes the entries in cluster
-// order.  (One atomic per wavefront and bucket contended on the same eleven
-// counters across the whole grid.)
-__device__ __forceinline__ int cluster_bucket(int64_t c, int64_t n, int cap, const int32_t *__restrict__ cl_ptr,
-                                              const int32_t *__restrict__ members, int32_t *__restrict__ bcount) {
-  const int a = cl_ptr[c], b = cl_ptr[c + 1];
-  bool ok = a >= 0 && b >= a;
-  for (int k = a; ok && k < b; ++k) {
-    const int g = members[k];
-    ok = g >= 0 && (int64_t)g < n;
-  }
-  if (!ok) {
-    atomicOr(&bcount[BC_BAD], 1);
-    return -1;
-  }
-  return b > a ? bucket_of(b - a, cap) : -1;
-}
-
 struct BucketArgs {
   int64_t nc_host;
   const int64_t *nc_dev;
@@ -1531,61 +1508,50 @@ struct BucketArgs {
   int cap;  // clusters above this many members take the percolated-cluster path
   const int32_t *cl_ptr, *members;
   int32_t *bcount, *blists;
-  int32_t *cl_bk;  // category chosen per cluster (between the sweeps)
   DevCounters *cnt;
   int reset_work;  // zero the Hermite work counters
   CloseSrc close;  // member flags that make a cluster of buckets 1..3 close
-  int32_t *wgc;    // per-chunk category counts, then their offsets (N_CATS rows)
 };
 
-__device__ bool cluster_close(int a, int b, const BucketArgs &B) {
-  for (int p = a; p < b; ++p) {
-    const int g = B.members[p];
-    if ((B.close.a && B.close.a[g]) || (B.close.b && B.close.b[g])) return true;
-  }
-  return false;
+// clusters of 2..8 members: all loads issued together (a loop that stops at
+// the first flag found is a chain of up to 16 of them)
+__device__ __forceinline__ bool cluster_close(int a, int b, const BucketArgs &B) {
+  int g[8];
+  unsigned f = 0;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) g[q] = B.members[a + q < b ? a + q : a];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) f |= (B.close.a ? B.close.a[g[q]] : 0) | (B.close.b ? B.close.b[g[q]] : 0);
+  return f != 0;
 }
 
 // Categories: the buckets 0..10, and N_BUCKETS + k - 1 for the clusters of
 // bucket k = 1..3 with a close pair.  The close ones are written from the
 // end of their bucket's list backwards (count in bcount[HERM_BC_CLOSE0 + k
-// - 1]), the others from its start.  Three launches, each over one
-// 256-cluster chunk per workgroup: the category counts of every chunk
-// (k_bucket_count), their exclusive scan over the chunks per category
-// (k_bucket_scan, one workgroup per category), and the entries in cluster
-// order (k_bucket_write).  B.wgc holds N_CATS rows of nchunk counts.
+// - 1]), the others from its start.
 constexpr int N_CATS = N_BUCKETS + 3;
 constexpr int BK_T = 256;
 
-__device__ __forceinline__ int64_t bucket_nc(const BucketArgs &B) {
-  return B.nc_dev ? *B.nc_dev : B.nc_host;  // clusters (at most stride)
-}
-
-// category of cluster c (-1: empty or beyond the count)
-__device__ __forceinline__ int cluster_category(const BucketArgs &B, int64_t c, int64_t nc) {
-  if (c >= nc) return -1;
-  int cat = cluster_bucket(c, B.n, B.cap, B.cl_ptr, B.members, B.bcount);
-  if (cat >= 1 && cat <= 3 && (B.close.a || B.close.b) && cluster_close(B.cl_ptr[c], B.cl_ptr[c + 1], B))
-    cat += N_BUCKETS - 1;
-  return cat;
-}
-
-// per wavefront: the mask of its lanes in category q, for every q (all lanes
-// take part); returns this lane's mask
-__device__ __forceinline__ unsigned long long cat_masks(int cat, int *wcount, int lane) {
-  unsigned long long mine = 0ull;
-  for (int q = 0; q < N_CATS; ++q) {
-    const unsigned long long mask = __ballot(cat == q);
-    if (lane == 0) wcount[q] = (int)__popcll(mask);
-    if (q == cat) mine = mask;
-  }
-  return mine;
-}
-
-__global__ __launch_bounds__(BK_T) void k_bucket_count(BucketArgs B, int nchunk) {
-  __shared__ int wc[BK_T / WAVE][N_CATS];
+// Bucket lists in one launch: a workgroup takes 256 BK_I clusters (one per
+// thread up to 2^18 clusters, so that a small batch still fills the chip; four
+// above, where the atomics on the counters add up), counts them
+// per category in LDS, reserves its share of every list with one atomic per
+// category and writes its entries (in cluster order within the chunk; the
+// order between chunks, on which nothing but the dispatch order depends, is
+// that of the atomics).  It also validates the caller's cluster arrays
+// (offsets non-decreasing from >= 0, members in [0, n)): a violation sets
+// bcount[BC_BAD] and nothing is integrated.  The members of a chunk with valid
+// offsets are contiguous, so the workgroup reads them coalesced (a thread per
+// cluster that walked its members took 27 us on 20,000 clusters of up to
+// 256).
+template <int BK_I>
+__global__ __launch_bounds__(BK_T) void k_bucket(BucketArgs B) {
+  constexpr int BK_CHUNK = BK_T * BK_I;
+  __shared__ int wc[BK_I * BK_T / WAVE][N_CATS];
+  __shared__ int base[N_CATS];
+  __shared__ int bad;
   const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE;
-  const int64_t nc = bucket_nc(B);
+  const int64_t nc = B.nc_dev ? *B.nc_dev : B.nc_host;  // clusters (at most stride)
   if (blockIdx.x == 0 && t == 0) {
     B.bcount[BC_NC] = (int32_t)nc;
     if (B.reset_work) {  // the work counters of this hard part
@@ -1594,64 +1560,67 @@ __global__ __launch_bounds__(BK_T) void k_bucket_count(BucketArgs B, int nchunk)
       B.cnt->n_coll = 0;
     }
   }
-  const int64_t c = (int64_t)blockIdx.x * BK_T + t;
-  const int cat = cluster_category(B, c, nc);
-  if (c < nc) B.cl_bk[c] = cat;
-  cat_masks(cat, wc[w], lane);
+  const int64_t c0 = (int64_t)blockIdx.x * BK_CHUNK;
+  if (c0 >= nc) return;  // uniform
+  const int64_t c1 = c0 + BK_CHUNK < nc ? c0 + BK_CHUNK : nc;
+  if (t == 0) bad = 0;
+  __syncthreads();
+  int a[BK_I], b[BK_I];
+#pragma unroll
+  for (int i = 0; i < BK_I; ++i) {
+    const int64_t c = c0 + i * BK_T + t;
+    a[i] = c < c1 ? B.cl_ptr[c] : 0;
+    b[i] = c < c1 ? B.cl_ptr[c + 1] : 0;
+    if (!(a[i] >= 0 && b[i] >= a[i])) bad = 1;
+  }
+  __syncthreads();
+  if (!bad) {  // uniform
+    const int64_t m1 = B.cl_ptr[c1];
+    for (int64_t k = (int64_t)B.cl_ptr[c0] + t; k < m1; k += BK_T) {
+      const int g = B.members[k];
+      if (!(g >= 0 && (int64_t)g < B.n)) bad = 1;
+    }
+  }
+  __syncthreads();
+  if (bad) {  // uniform
+    if (t == 0) atomicOr(&B.bcount[BC_BAD], 1);
+    return;
+  }
+  int cat[BK_I];
+  unsigned long long mine[BK_I];
+#pragma unroll
+  for (int i = 0; i < BK_I; ++i) {
+    cat[i] = b[i] > a[i] ? bucket_of(b[i] - a[i], B.cap) : -1;
+    if (cat[i] >= 1 && cat[i] <= 3 && (B.close.a || B.close.b) && cluster_close(a[i], b[i], B)) cat[i] += N_BUCKETS - 1;
+    // this lane's mask of its category, and the count of every category
+    mine[i] = 0ull;
+    for (int q = 0; q < N_CATS; ++q) {
+      const unsigned long long mask = __ballot(cat[i] == q);
+      if (lane == 0) wc[i * (BK_T / WAVE) + w][q] = (int)__popcll(mask);
+      if (q == cat[i]) mine[i] = mask;
+    }
+  }
   __syncthreads();
   if (t < N_CATS) {
     int tot = 0;
-    for (int u = 0; u < BK_T / WAVE; ++u) tot += wc[u][t];
-    B.wgc[(int64_t)t * nchunk + blockIdx.x] = tot;
-  }
-}
-
-// row q of wgc becomes its exclusive scan over the chunks; the row total is
-// the category's count
-__global__ __launch_bounds__(BK_T) void k_bucket_scan(BucketArgs B, int nchunk) {
-  __shared__ int ws[BK_T / WAVE];
-  const int q = blockIdx.x, t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE;
-  int32_t *row = B.wgc + (int64_t)q * nchunk;
-  int carry = 0;
-  for (int c0 = 0; c0 < nchunk; c0 += BK_T) {  // uniform
-    const int i = c0 + t;
-    const int v = i < nchunk ? row[i] : 0;
-    const int incl = wave_incl_scan(v);
-    if (lane == WAVE - 1) ws[w] = incl;
-    __syncthreads();
-    int before = 0, chunk = 0;
-    for (int u = 0; u < BK_T / WAVE; ++u) {
-      before += u < w ? ws[u] : 0;
-      chunk += ws[u];
+    for (int u = 0; u < BK_I * BK_T / WAVE; ++u) {
+      const int v = wc[u][t];
+      wc[u][t] = tot;
+      tot += v;
     }
-    if (i < nchunk) row[i] = carry + before + incl - v;
-    carry += chunk;
-    __syncthreads();  // ws is rewritten by the next chunk
+    const int word = t < N_BUCKETS ? t : HERM_BC_CLOSE0 + t - N_BUCKETS;
+    base[t] = tot > 0 ? atomicAdd(&B.bcount[word], tot) : 0;
   }
-  if (t == 0) {
-    if (q < N_BUCKETS)
-      B.bcount[q] = carry;
-    else
-      B.bcount[HERM_BC_CLOSE0 + q - N_BUCKETS] = carry;
-  }
-}
-
-__global__ __launch_bounds__(BK_T) void k_bucket_write(BucketArgs B, int nchunk) {
-  __shared__ int wc[BK_T / WAVE][N_CATS];
-  const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE;
-  const int64_t nc = bucket_nc(B);
-  const int64_t c = (int64_t)blockIdx.x * BK_T + t;
-  const int cat = c < nc ? B.cl_bk[c] : -1;  // as decided by k_bucket_count
-  const unsigned long long mine = cat_masks(cat, wc[w], lane);
   __syncthreads();
-  if (cat >= 0) {
-    int off = 0;
-    for (int u = 0; u < w; ++u) off += wc[u][cat];  // wavefronts take their slots in order
-    const int64_t k = (int64_t)B.wgc[(int64_t)cat * nchunk + blockIdx.x] + off + popc_below(mine);
-    if (cat < N_BUCKETS)
-      B.blists[(int64_t)cat * B.stride + k] = (int32_t)c;
+#pragma unroll
+  for (int i = 0; i < BK_I; ++i) {
+    if (cat[i] < 0) continue;
+    const int64_t k = (int64_t)base[cat[i]] + wc[i * (BK_T / WAVE) + w][cat[i]] + popc_below(mine[i]);
+    const int32_t c = (int32_t)(c0 + i * BK_T + t);
+    if (cat[i] < N_BUCKETS)
+      B.blists[(int64_t)cat[i] * B.stride + k] = c;
     else
-      B.blists[(int64_t)(cat - N_BUCKETS + 1) * B.stride + B.stride - 1 - k] = (int32_t)c;
+      B.blists[(int64_t)(cat[i] - N_BUCKETS + 1) * B.stride + B.stride - 1 - k] = c;
   }
 }
 
@@ -1677,8 +1646,8 @@ static void host_changeover_coeffs(double g, HermArgs &A) {
 // Bucket lists and counts (one host synchronisation); hc receives the
 // BC_WORDS words (the park counts are zero).
 hipError_t herm_bucket(p3t_ctx *c, int64_t n, int64_t nc, const int32_t *cl_ptr, const int32_t *cl_members,
-                       const int64_t *nc_dev, int32_t *hc, const CloseSrc &close) {
-  hipError_t e = herm_bucket_enqueue(c, c->stream, n, nc, cl_ptr, cl_members, nc_dev, hc, true, close);
+                       const int64_t *nc_dev, int32_t *hc, const CloseSrc &close, bool cleared) {
+  hipError_t e = herm_bucket_enqueue(c, c->stream, n, nc, cl_ptr, cl_members, nc_dev, hc, true, close, cleared);
   if (e != hipSuccess) return e;
   if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
   if (hc[BC_BAD]) return hipErrorInvalidDevicePointer;  // malformed cluster arrays
@@ -1689,9 +1658,11 @@ hipError_t herm_bucket(p3t_ctx *c, int64_t n, int64_t nc, const int32_t *cl_ptr,
 // stream s, without waiting.
 hipError_t herm_bucket_enqueue(p3t_ctx *c, hipStream_t s, int64_t n, int64_t nc, const int32_t *cl_ptr,
                                const int32_t *cl_members, const int64_t *nc_dev, int32_t *hc, bool reset_work,
-                               const CloseSrc &close) {
-  hipError_t e;
-  if ((e = fill_i32(c->herm_bcount, 0, BC_WORDS, s)) != hipSuccess) return e;
+                               const CloseSrc &close, bool cleared) {
+  if (!cleared) {
+    const hipError_t e = fill_i32(c->herm_bcount, 0, BC_WORDS, s);
+    if (e != hipSuccess) return e;
+  }
   BucketArgs B;
   B.nc_host = nc;
   B.nc_dev = nc_dev;
@@ -1702,18 +1673,16 @@ hipError_t herm_bucket_enqueue(p3t_ctx *c, hipStream_t s, int64_t n, int64_t nc,
   B.members = cl_members;
   B.bcount = c->herm_bcount;
   B.blists = c->herm_blists;
-  B.cl_bk = c->herm_clbk;
   B.cnt = c->cnt;
   B.reset_work = reset_work ? 1 : 0;
   B.close = close;
-  // the per-chunk counts use the radix sort's histogram buffer, which is
-  // free here (it holds 256 entries per 2048 keys, these N_CATS per 256)
-  const int64_t nchunk = std::max<int64_t>(1, (nc + BK_T - 1) / BK_T);
-  if (nchunk * N_CATS > c->radix_hist_cap || nchunk > INT32_MAX) return hipErrorInvalidValue;
-  B.wgc = reinterpret_cast<int32_t *>(c->radix_hist);
-  hipLaunchKernelGGL(k_bucket_count, dim3((unsigned)nchunk), dim3(BK_T), 0, s, B, (int)nchunk);
-  hipLaunchKernelGGL(k_bucket_scan, dim3(N_CATS), dim3(BK_T), 0, s, B, (int)nchunk);
-  hipLaunchKernelGGL(k_bucket_write, dim3((unsigned)nchunk), dim3(BK_T), 0, s, B, (int)nchunk);
+  auto go = [&](auto kernel, int chunk) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)std::max<int64_t>(1, (nc + chunk - 1) / chunk)), dim3(BK_T), 0, s, B);
+  };
+  if (nc <= (1 << 18))
+    go(k_bucket<1>, BK_T);
+  else
+    go(k_bucket<4>, 4 * BK_T);
   return hipMemcpyAsync(hc, c->herm_bcount, sizeof(int32_t) * BC_WORDS, hipMemcpyDeviceToHost, s);
 }
 

@@ -123,6 +123,38 @@ __device__ __forceinline__ unsigned long long wave_fetch_add(unsigned long long 
   return (unsigned long long)uniform_lane64((long long)r, from);
 }
 
+// Union-find over the neighbour pairs.  The larger root is hooked under the
+// smaller one, so every root stays its component's minimum index.
+__device__ __forceinline__ int uf_load(int32_t *p, int i) {
+  return __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ int uf_find(int32_t *p, int i) {
+  int r = uf_load(p, i);
+  while (r != i) {
+    i = r;
+    r = uf_load(p, i);
+  }
+  return i;
+}
+
+__device__ __forceinline__ void uf_union(int32_t *p, int a, int b) {
+  a = uf_find(p, a);
+  b = uf_find(p, b);
+  while (a != b) {
+    if (a < b) {
+      const int t = a;
+      a = b;
+      b = t;
+    }
+    // a > b: hook root a under b
+    const int old = atomicCAS(p + a, a, b);
+    if (old == a) break;
+    a = uf_find(p, old);
+    b = uf_find(p, b);
+  }
+}
+
 // inclusive wave scan of int
 __device__ __forceinline__ int wave_incl_scan(int v) {
   const int l = lane_id();
@@ -263,7 +295,6 @@ struct p3t_ctx {
   } fcfg;
   int32_t *herm_bcount = nullptr;  // Hermite bucket counts (p3t::HERM_BC_WORDS)
   int32_t *herm_blists = nullptr;  // Hermite bucket lists (11 * n_cap)
-  int32_t *herm_clbk = nullptr;    // bucket of each cluster (n_cap)
   uint8_t *slow_flag = nullptr;    // member of a slow cluster (n_cap), p3t_hard_evaluate
 
   // arena pointers
@@ -292,10 +323,13 @@ struct p3t_ctx {
   int64_t *scan_tmp = nullptr;
   int64_t scan_tmp_cap = 0;
   int32_t *row_cnt = nullptr;       // per-particle counters (n)
-  int64_t *csr_ptr = nullptr;       // internal CSR row pointer (n + 1)
-  int32_t *csr_col = nullptr;       // internal CSR columns (pair_cap)
-  int32_t *uf_parent = nullptr;     // union-find parents (n)
-  int64_t uf_early = 0;             // n if uf_parent holds the first pass of labels_pairs_early, else 0
+  int32_t *uf_parent = nullptr;     // union-find parents (n), complete with the pairs of the last evaluation
+  int32_t *cl_cnt = nullptr;        // members per label (n; zero between calls, as row_cnt is)
+  int32_t *cl_slot = nullptr;       // slot of each member in its cluster (n)
+  int32_t *cl_start = nullptr;      // first slot of each label's cluster (n)
+  int64_t *cl_nc = nullptr;         // cluster count, out-of-range flag of p3t_clusters
+  uint64_t *cl_sums = nullptr;      // scan scratch (scan_sums_need)
+  int64_t *host_words = nullptr;    // pinned host memory: the device counters, small results
   uint64_t *cl_keys = nullptr, *cl_keys_alt = nullptr;  // cluster sort keys (n)
   double *cut_part = nullptr;       // cut-off bin partial sums
   uint8_t *close_flag = nullptr;    // per particle: in a close neighbour pair at the last evaluation
@@ -407,14 +441,12 @@ hipError_t walk_groups(p3t_ctx *c, int64_t n_groups);
 hipError_t soft_force(p3t_ctx *c, int64_t n_groups, double *acc3, bool frozen = false);
 
 // nbr.hip
-hipError_t build_csr(p3t_ctx *c, int64_t n, int64_t n_pairs);
-hipError_t labels_cc(p3t_ctx *c, int64_t n, int32_t *label);
-hipError_t labels_pairs(p3t_ctx *c, int64_t n, int32_t *label);
-hipError_t labels_pairs_early(p3t_ctx *c, int64_t n);
+int64_t scan_sums_need();
+hipError_t neighbour_csr(p3t_ctx *c, int64_t n, int64_t np, int64_t *row_ptr, int32_t *col, int32_t *label);
+hipError_t clusters_pairs(p3t_ctx *c, int64_t n, int32_t *label, int32_t *cl_ptr, int32_t *cl_members,
+                          int32_t *clear, int n_clear);
 hipError_t clusters_csr(p3t_ctx *c, int64_t n, const int32_t *label, int32_t *cl_ptr, int32_t *cl_members,
                         int64_t *n_clusters);
-hipError_t clusters_csr_dev(p3t_ctx *c, int64_t n, const int32_t *label, int32_t *cl_ptr, int32_t *cl_members,
-                            bool keys_ready = false);
 
 // hermite.hip
 // nc_dev (nullable): the cluster count on the device, nc then only bounds it
@@ -423,8 +455,9 @@ hipError_t clusters_csr_dev(p3t_ctx *c, int64_t n, const int32_t *label, int32_t
 struct CloseSrc {
   const uint8_t *a = nullptr, *b = nullptr;
 };
+// cleared: the bucket words are clear (clusters_pairs cleared them)
 hipError_t herm_bucket(p3t_ctx *c, int64_t n, int64_t nc, const int32_t *cl_ptr, const int32_t *cl_members,
-                       const int64_t *nc_dev, int32_t *hc, const CloseSrc &close = CloseSrc());
+                       const int64_t *nc_dev, int32_t *hc, const CloseSrc &close = CloseSrc(), bool cleared = false);
 // perfect-accretion collisions in the hard part (hermite.hip, wave path)
 struct HermColl {
   double f;          // radius enhancement factor
@@ -437,7 +470,7 @@ struct HermColl {
 // read leaves them, and herm_reset_work zeroes them when the hard part starts
 hipError_t herm_bucket_enqueue(p3t_ctx *c, hipStream_t s, int64_t n, int64_t nc, const int32_t *cl_ptr,
                                const int32_t *cl_members, const int64_t *nc_dev, int32_t *hc, bool reset_work = true,
-                               const CloseSrc &close = CloseSrc());
+                               const CloseSrc &close = CloseSrc(), bool cleared = false);
 hipError_t herm_reset_work(p3t_ctx *c, hipStream_t s);
 hipError_t herm_launch(p3t_ctx *c, int64_t n, int64_t stride, const int32_t *cl_ptr, const int32_t *cl_members,
                        double *pos3, double *vel3, const double *mass, const double *r_out, double *dt_hard,

@@ -354,15 +354,18 @@ __global__ void k_slow_merge(int64_t n, const uint8_t *__restrict__ slow, const 
 // the pairs of the direct terms go behind those of the force kernels; a
 // second launch moves the counter (every thread of the first reads it).
 // Only the slots that were written are moved (at most cap_d); a count above
-// cap_d makes the host redo the evaluation.
+// cap_d makes the host redo the evaluation.  The pairs (found from both
+// sides) join their clusters.
 __global__ void k_slow_pairs(const int2 *__restrict__ pd, int64_t cap_d, int2 *__restrict__ pairs, int64_t cap,
-                             DevCounters *cnt) {
+                             int32_t *uf, DevCounters *cnt) {
   const unsigned long long nd = cnt->n_pairs_d, base = cnt->n_pairs;
   const unsigned long long m = nd < (unsigned long long)cap_d ? nd : (unsigned long long)cap_d;
   for (unsigned long long k = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x; k < m;
        k += (unsigned long long)gridDim.x * blockDim.x) {
+    const int2 e = pd[k];
+    if (e.x < e.y) uf_union(uf, e.x, e.y);
     if (base + k < (unsigned long long)cap)
-      pairs[base + k] = pd[k];
+      pairs[base + k] = e;
     else
       set_flag(cnt, P3T_FLAG_PAIR_OVERFLOW);
   }
@@ -448,7 +451,7 @@ hipError_t slow_merge(p3t_ctx *c, double *pos3, double *vel3, double *acc3, int 
                      (const double *)c->acc_d, acc3, c->cnt);
   const unsigned gp = (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (c->pairs_d_cap + 255) / 256));
   hipLaunchKernelGGL(k_slow_pairs, dim3(gp), dim3(256), 0, s, (const int2 *)c->pairs_d, c->pairs_d_cap, c->pairs,
-                     c->pair_cap, c->cnt);
+                     c->pair_cap, c->uf_parent, c->cnt);
   hipLaunchKernelGGL(k_slow_pairs_count, dim3(1), dim3(1), 0, s, c->cnt, c->pairs_d_cap);
   return hipGetLastError();
 }

@@ -302,10 +302,10 @@ __global__ __launch_bounds__(RS_T) void k_radix_pass(const uint64_t *__restrict_
 }
 
 // histograms of up to RADIX_PASSES passes (one, above RS_CHAIN keys), and the
-// digit totals; at least the Hermite buckets' per-chunk counts (14 per 256)
+// digit totals
 int64_t radix_hist_need(int64_t n) {
   const int64_t tiles = (n + 4 * RS_T - 1) / (4 * RS_T);
-  return std::max<int64_t>(RADIX_PASSES * 128, tiles) * 256 + 256 + n / 16;
+  return std::max<int64_t>(RADIX_PASSES * 128, tiles) * 256 + 256;
 }
 
 hipError_t radix_sort_pairs(uint64_t *&keys, int32_t *&vals, uint64_t *&keys_alt, int32_t *&vals_alt, int64_t n,

@@ -221,13 +221,16 @@ __global__ __launch_bounds__(WAVE) void k_walk(const WalkNode *__restrict__ wn, 
   }
 }
 
-// Queue heads and per-evaluation counters; close: the close-pair flags to
-// clear (n4 words, nullable).
-__global__ void k_reset_queues(DevCounters *cnt, unsigned long long *__restrict__ queues, int32_t *__restrict__ close,
-                               int64_t n4) {
-  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (close)
-    for (int64_t k = t0; k < n4; k += (int64_t)gridDim.x * blockDim.x) close[k] = 0;
+// Queue heads and per-evaluation counters; with a new pair list to come, the
+// close-pair flags are cleared and every particle becomes its own cluster
+// (close nullable).
+__global__ void k_reset_queues(DevCounters *cnt, unsigned long long *__restrict__ queues, int64_t n,
+                               int32_t *__restrict__ close, int32_t *__restrict__ uf) {
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, ts = (int64_t)gridDim.x * blockDim.x;
+  if (close) {
+    for (int64_t k = t0; k < (n + 3) / 4; k += ts) close[k] = 0;
+    for (int64_t k = t0; k < n; k += ts) uf[k] = (int32_t)k;
+  }
   if (t0 < WALK_PARTS) queues[t0 * WALK_QUEUE_STRIDE] = 0;
   if (t0 != 0) return;
   cnt->force_queue = 0;
@@ -270,11 +273,10 @@ __global__ __launch_bounds__(1024) void k_group_order(const int32_t *__restrict_
   for (int g = t; g < ng; g += blockDim.x) order[atomicAdd(&hist[cls[g]], 1)] = g;
 }
 
-static void reset(p3t_ctx *c, bool close) {
-  const int64_t n4 = (c->n + 3) / 4;
-  const unsigned g = close ? (unsigned)std::max<int64_t>(1, std::min<int64_t>(1024, (n4 + 255) / 256)) : 1u;
-  hipLaunchKernelGGL(k_reset_queues, dim3(g), dim3(256), 0, c->stream, c->cnt, c->walk_q,
-                     close ? reinterpret_cast<int32_t *>(c->close_flag) : nullptr, n4);
+static void reset(p3t_ctx *c, bool new_pairs) {
+  const unsigned g = new_pairs ? (unsigned)std::max<int64_t>(1, std::min<int64_t>(1024, (c->n + 255) / 256)) : 1u;
+  hipLaunchKernelGGL(k_reset_queues, dim3(g), dim3(256), 0, c->stream, c->cnt, c->walk_q, c->n,
+                     new_pairs ? reinterpret_cast<int32_t *>(c->close_flag) : nullptr, c->uf_parent);
 }
 
 hipError_t walk_groups(p3t_ctx *c, int64_t n_groups_max) {
