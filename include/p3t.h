@@ -93,9 +93,9 @@ typedef struct {
   int64_t list_entries; /* total interaction-list entries (near + far + cells) */
   double ms_cutoffs, ms_tree, ms_walk, ms_force, ms_neighbour, ms_hermite; /* event-timed phases */
   /* the force phase by launch (split form; zero for the fused kernel):
-     ms_near the launch over the near, far and cell lists (ms_far and ms_cell
-     are zero: the classes share it), ms_cand the exact neighbour test of the
-     candidates */
+     ms_near the launch over the near, far and cell lists with the exact
+     neighbour test of the candidates (ms_far, ms_cell and ms_cand are zero:
+     they share it) */
   double ms_near, ms_far, ms_cell, ms_cand;
   int32_t timing;       /* 1 if the phase times above were measured */
   int32_t n_slow;       /* members of slow clusters in the last p3t_hard_evaluate */
@@ -393,8 +393,8 @@ p3t_status p3t_set_timing(p3t_ctx *ctx, int32_t on);
    autotuner can pick the fastest shape for a workload.
      force_split      1: a loop per interaction class (near with the
                       changeover and neighbour candidates, far particles,
-                      cells), several wavefronts per group, plus an exact-test
-                      kernel over the candidates; 0: one fused kernel.
+                      cells), several wavefronts per group, the neighbour
+                      candidates tested 64 at a time; 0: one fused kernel.
      force_unroll     j-loop unroll of the split kernels: 1, 2, 4 or 8.
      force_persistent 1: persistent grids that take groups from a queue in
                       longest-list-first order; 0: one workgroup per group.

@@ -198,11 +198,6 @@ p3t_status ensure_lists(p3t_ctx *c, int64_t n) {
     HIP_OK(c, dev_alloc(c->pairs, cap));
     c->pair_cap = cap;
   }
-  if (!c->cands) {
-    const int64_t cap = std::max<int64_t>(1 << 16, 8 * n);
-    HIP_OK(c, dev_alloc(c->cands, cap));
-    c->cand_cap = cap;
-  }
   return P3T_OK;
 }
 
@@ -256,7 +251,6 @@ p3t_status prep_enqueue(p3t_ctx *c) {
   HIP_OK(c, aux_streams(c));
   if (!c->prep_ev[0])
     for (auto &ev : c->prep_ev) HIP_OK(c, hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-  if (!c->hc_pinned) HIP_OK(c, hipHostMalloc((void **)&c->hc_pinned, sizeof(int32_t) * HERM_BC_WORDS));
   HIP_OK(c, hipEventRecord(c->prep_ev[0], c->stream));
   HIP_OK(c, hipStreamWaitEvent(c->aux_stream, c->prep_ev[0], 0));
   struct Swap {  // the cluster functions enqueue on c->stream
@@ -403,9 +397,9 @@ uint64_t mix(uint64_t h, uint64_t v) {
 uint64_t graph_key(const p3t_ctx *c, int64_t n, const void *const *ptrs, int np) {
   uint64_t h = mix(0x51ed270b27a1c3ull, (uint64_t)n);
   for (int k = 0; k < np; ++k) h = mix(h, (uint64_t)(uintptr_t)ptrs[k]);
-  const void *own[] = {c->arena.base, c->pool, c->slot_lists, c->slot_stack, c->pairs, c->cands};
+  const void *own[] = {c->arena.base, c->pool, c->slot_lists, c->slot_stack, c->pairs};
   for (const void *q : own) h = mix(h, (uint64_t)(uintptr_t)q);
-  const int64_t caps[] = {c->n_cap, c->pool_cap, c->slot_cap_list, c->slot_cap_stack, c->pair_cap, c->cand_cap,
+  const int64_t caps[] = {c->n_cap, c->pool_cap, c->slot_cap_list, c->slot_cap_stack, c->pair_cap,
                           c->walk_slots, c->fcfg.split, c->fcfg.unroll, c->fcfg.waves_per_cu, c->force_persistent,
                           c->top_slots};
   for (int64_t v : caps) h = mix(h, (uint64_t)v);
@@ -440,8 +434,15 @@ p3t_status p3t_create(const p3t_params *p, void *stream, p3t_ctx **out) {
       delete c;
       return P3T_ERR_HIP;
     }
-  if (hipHostMalloc((void **)&c->host_words, sizeof(DevCounters)) != hipSuccess || alloc_arena(c, 1024) != P3T_OK) {
-    if (c->host_words) (void)hipHostFree(c->host_words);
+  // one pinned allocation: the device counters (and small results), the bucket words
+  constexpr size_t counters = (sizeof(DevCounters) + 63) & ~size_t(63);
+  if (hipHostMalloc((void **)&c->host_words, counters + sizeof(int32_t) * HERM_BC_WORDS) != hipSuccess) {
+    delete c;
+    return P3T_ERR_HIP;
+  }
+  c->hc_pinned = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(c->host_words) + counters);
+  if (alloc_arena(c, 1024) != P3T_OK) {
+    (void)hipHostFree(c->host_words);
     delete c;
     return P3T_ERR_HIP;
   }
@@ -464,15 +465,14 @@ p3t_status p3t_destroy(p3t_ctx *c) {
   for (auto &ev : c->slow_ev)
     if (ev) (void)hipEventDestroy(ev);
   void *bufs[] = {c->arena.base, c->pool,    c->slot_lists, c->slot_stack, c->pairs,
-                  c->cands,      c->adj_buf, c->ov_buf,     c->pairs_d,    c->huge_buf,
-                  c->coll_buf,   c->merge_st, c->merge_i32};
+                  c->adj_buf,    c->ov_buf,  c->pairs_d,    c->huge_buf,   c->coll_buf,
+                  c->merge_st,   c->merge_i32};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
   for (auto &e : c->ev)
     if (e) (void)hipEventDestroy(e);
   for (auto &e : c->prep_ev)
     if (e) (void)hipEventDestroy(e);
-  if (c->hc_pinned) (void)hipHostFree(c->hc_pinned);
   if (c->host_words) (void)hipHostFree(c->host_words);
   delete c;
   return P3T_OK;
@@ -591,11 +591,6 @@ p3t_status grow_for_retry(p3t_ctx *c, const DevCounters &h) {
       const int64_t cap = (int64_t)h.n_pairs + (int64_t)h.n_pairs / 4 + 1024;
       HIP_OK(c, dev_alloc(c->pairs, cap));
         c->pair_cap = cap;
-    }
-    if ((int64_t)h.n_cand > c->cand_cap) {
-      const int64_t cap = (int64_t)h.n_cand + (int64_t)h.n_cand / 4 + 1024;
-      HIP_OK(c, dev_alloc(c->cands, cap));
-      c->cand_cap = cap;
     }
   }
   return P3T_OK;
@@ -738,9 +733,9 @@ bool eval_finish(p3t_ctx *c, const DevCounters &h, unsigned *num, p3t_status *st
       c->stats.ms_walk = ev_ms(c, 4, 5);
       c->stats.ms_force = ev_ms(c, 5, 6);
       if (c->fcfg.split) {
-        c->stats.ms_near = ev_ms(c, 5, 11);  // one launch for the three classes
-        c->stats.ms_far = c->stats.ms_cell = 0.0;
-        c->stats.ms_cand = ev_ms(c, 11, 12);
+        // one launch for the three classes and the neighbour test
+        c->stats.ms_near = ev_ms(c, 5, 11);
+        c->stats.ms_far = c->stats.ms_cell = c->stats.ms_cand = 0.0;
       } else {
         c->stats.ms_near = c->stats.ms_far = c->stats.ms_cell = c->stats.ms_cand = 0.0;
       }

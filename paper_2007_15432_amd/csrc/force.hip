@@ -425,11 +425,9 @@ hipError_t soft_force(p3t_ctx *c, int64_t n_groups_max, double *acc3, bool froze
   A.cnt = c->cnt;
   A.pairs = c->pairs;
   A.pair_cap = c->pair_cap;
-  A.cands = c->cands;
-  A.cand_cap = c->cand_cap;
-  A.cand_slab = c->force_persistent ? 64 : 0;
+  A.collect = frozen ? 0 : 1;
   A.slow = c->slow_active ? c->slow_flag : nullptr;
-  if (frozen) A.pair_cap = A.cand_cap = 0;
+  if (frozen) A.pair_cap = 0;
   // the close pairs of this evaluation (cleared with the queues before the walk)
   A.close = frozen ? nullptr : c->close_flag;
   A.uf = frozen ? nullptr : c->uf_parent;

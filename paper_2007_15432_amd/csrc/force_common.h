@@ -17,10 +17,8 @@ struct ForceArgs {
   int2 *pairs;
   int64_t pair_cap;
   int32_t *uf;  // union-find parents, joined as pairs are found (nullable)
-  int2 *cands;  // neighbour candidates (sorted indices), split form
+  int collect;  // report neighbour pairs
   const uint8_t *slow;  // caller's order: pairs with a flagged member are not reported (nullable)
-  int64_t cand_cap;
-  int cand_slab;  // candidate slots a wavefront reserves at a time (0: exactly each tile's)
   double *acc;
   int64_t n;
   double G, gamma, inv1mg;

@@ -1,7 +1,6 @@
 // force_split.hip -- the soft force (eq. (softforce) with the pair cut-off of
-// eq. (rout2); neighbour pairs of Section 2.3) in one launch over the groups'
-// lists and one over the neighbour candidates, an alternative to the fused
-// kernel of force.hip.
+// eq. (rout2); neighbour pairs of Section 2.3) over the groups' lists, an
+// alternative to the fused kernel of force.hip.
 //
 //   k_force_all  one workgroup of W wavefronts per group; the list's tiles of
 //            64 entries are dealt to the wavefronts, each class with a loop of
@@ -12,17 +11,15 @@
 //            records in a bit mask which j of the current tile are
 //            neighbour candidates
 //            (r^2 <= max reach^2, with a relative margin that covers the
-//            rounding of r^2) and appends them after the tile to a candidate
-//            buffer.
+//            rounding of r^2); after the tile they queue up in LDS for the
+//            exact neighbour test of Section 2.3, one per lane, and neighbours
+//            go to the pair buffer.  Coincident pairs (r = 0, i != j) are
+//            always candidates and are reported there.
 //     far    K = 1 particles, FP64 or (mixed) FP32 offsets from the group
 //            centre with compensated accumulation.
 //     cells  monopole or traceless-quadrupole cells, FP64 or FP32.
 //            The wavefronts' sums are added in LDS and written in the caller's
 //            order, with the NaN check.
-//   k_cand_test  the exact neighbour test of Section 2.3 on every candidate,
-//            one thread each; neighbours go to the pair buffer.  Coincident
-//            pairs (r = 0, i != j) are always candidates and are reported
-//            here.
 //
 // A lane owns one i-particle, or two when the group holds more than 64 (the
 // choice is per group, so small groups do not pay for an idle second slot).
@@ -128,26 +125,57 @@ __device__ __forceinline__ void near_term64(const ForceArgs &A, double dx, doubl
 // FP32 and folded into the FP64 sums; the pairs inside the changeover
 // (y < 1, a fraction of a percent of the near lists) are flagged per lane
 // and evaluated in FP64 after the tile.  Without MIXED every pair is FP64.
-// Candidate slots reserved by one wavefront and not used yet: [base, end).
-// A wavefront reserves A.cand_slab slots at a time with one atomic (a
-// returning atomic per tile on the one counter queued behind those of every
-// other wavefront); slots it leaves unused are marked (-1, -1), which the
-// exact test skips.
-struct CandSlab {
-  long long base = 0, end = 0;
+// Neighbour candidates of a wavefront (sorted indices) waiting for the exact
+// test of Section 2.3, in LDS.  The tests run 64 at a time, one per lane, as
+// soon as that many wait: a candidate costs its lane 18 gathers of 8 bytes, which
+// overlap with the pair terms of the CU's other wavefronts.  (A buffer in
+// device memory and a launch of its own for the tests were bound by those
+// gathers' addresses: 159 us at 2^20 particles, 22 at 65,536; the tests here add
+// 60 and 11 us to the force launch.)
+struct CandQueue {
+  int2 e[2 * WAVE];
 };
 
-__device__ __forceinline__ void close_slab(const ForceArgs &A, const CandSlab &S, int lane) {
-  for (long long q = S.base + lane; q < S.end; q += WAVE)
-    if (q < A.cand_cap) A.cands[q] = make_int2(-1, -1);
+// tests the first min(n, 64) candidates and reports the neighbours (every
+// lane of the wavefront takes part)
+__device__ __forceinline__ void test_candidates(const ForceArgs &A, const CandQueue &Q, int n, int lane) {
+  bool nb = false;
+  int i = 0, j = 0, a = 0, b = 0;
+  if (lane < n) {
+    i = Q.e[lane].x;
+    j = Q.e[lane].y;
+    a = A.sid[i];
+    b = A.sid[j];
+    // a slow member sits at its pre-drift position here; its pairs are
+    // tested once its integration has finished
+    if (!(A.slow && (A.slow[a] | A.slow[b]))) {
+      const double xi = A.sx[i], yi = A.sy[i], zi = A.sz[i], xj = A.sx[j], yj = A.sy[j], zj = A.sz[j];
+      if (xi == xj && yi == yj && zi == zj) set_flag(A.cnt, P3T_FLAG_COINCIDENT);
+      nb = neighbour_test(xi, yi, zi, A.svx[i], A.svy[i], A.svz[i], A.sm[i], A.sro[i], A.srs[i], xj, yj, zj, A.svx[j],
+                          A.svy[j], A.svz[j], A.sm[j], A.sro[j], A.srs[j], A.G, A.rsch2, A.rsch3, A.dt);
+    }
+  }
+  const unsigned long long bal = __ballot(nb);
+  if (bal == 0ull) return;  // uniform
+  const unsigned long long o0 = wave_fetch_add(&A.cnt->n_pairs, (unsigned long long)__popcll(bal));
+  if (nb) {
+    mark_close_pair(A, i, j);
+    join_pair(A, a, b);
+    const unsigned long long q = o0 + popc_below(bal);
+    if ((int64_t)q < A.pair_cap)
+      A.pairs[q] = make_int2(a, b);
+    else
+      set_flag(A.cnt, P3T_FLAG_PAIR_OVERFLOW);
+  }
 }
 
 // The near terms of the tiles from list position `from` on, every `step`
 // positions (multiples of WAVE), added to (ax, ay, az).
 template <bool MIXED, int IPL, int UNR>
 __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h, NearTile &T, int lane, int from,
-                                           int step, CandSlab &S, double *ax, double *ay, double *az) {
+                                           int step, CandQueue &Q, double *ax, double *ay, double *az) {
   int ii[IPL];
+  int nq = 0;  // candidates waiting, fewer than 64 between tiles
   double xi[IPL], yi[IPL], zi[IPL], invi[IPL], rch2[IPL];
   int ro2q[IPL], rch2q[IPL];  // MIXED: bit patterns of the widened FP32 squares
 #pragma unroll
@@ -285,39 +313,39 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
         az[s] += (double)tz[s];
       }
     }
-    // hand this tile's candidates (sorted indices) to the exact test
-    int nc = 0;
-#pragma unroll
-    for (int s = 0; s < IPL; ++s) {
-      if (ii[s] < 0) cm[0][s] = cm[1][s] = 0u;
-      nc += __popc(cm[0][s]) + __popc(cm[1][s]);
-    }
-    const int incl = wave_incl_scan(nc);
-    const int total = uniform_lane(incl, WAVE - 1);
-    if (total > 0) {
-      if (S.base + total > S.end) {  // uniform
-        close_slab(A, S, lane);
-        const long long want = total > A.cand_slab ? total : A.cand_slab;
-        S.base = (long long)wave_fetch_add(&A.cnt->n_cand, (unsigned long long)want);
-        S.end = S.base + want;
-        if (S.end > A.cand_cap && lane == 0) set_flag(A.cnt, P3T_FLAG_PAIR_OVERFLOW);
-      }
-      long long o = S.base + incl - nc;
+    // hand this tile's candidates to the exact test: one of each lane a round
+    if (A.collect) {
 #pragma unroll
       for (int s = 0; s < IPL; ++s) {
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          unsigned m = cm[half][s];
-          while (m != 0u) {
-            const int b = __ffs(m) - 1;
-            m &= m - 1u;
-            if (o < A.cand_cap) A.cands[o] = make_int2(ii[s], T.j[32 * half + b]);
-            ++o;
+        unsigned m0 = ii[s] >= 0 ? cm[0][s] : 0u, m1 = ii[s] >= 0 ? cm[1][s] : 0u;
+        for (;;) {
+          const bool has = (m0 | m1) != 0u;
+          const unsigned long long bal = __ballot(has);
+          if (bal == 0ull) break;  // uniform
+          if (has) {
+            const int q = m0 ? __ffs(m0) - 1 : 31 + __ffs(m1);
+            if (m0)
+              m0 &= m0 - 1u;
+            else
+              m1 &= m1 - 1u;
+            Q.e[nq + popc_below(bal)] = make_int2(ii[s], T.j[q]);
+          }
+          nq += (int)__popcll(bal);
+          if (nq >= WAVE) {
+            tile_sync();
+            test_candidates(A, Q, WAVE, lane);
+            const int2 rest = Q.e[WAVE + lane];
+            tile_sync();
+            Q.e[lane] = rest;
+            nq -= WAVE;
           }
         }
       }
-      S.base += total;
     }
+  }
+  if (nq > 0) {
+    tile_sync();
+    test_candidates(A, Q, nq, lane);
   }
 }
 
@@ -611,13 +639,13 @@ __device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h
 // wavefront order and written in the caller's order.  Deterministic: the same
 // tiles in the same wavefronts whatever the grid.
 template <bool MIXED, bool QUAD, int IPL, int UNR, int W>
-__device__ __forceinline__ void all_group(const ForceArgs &A, const GroupHdr &h, ForceTile *T, int lane, int w,
-                                          CandSlab &S) {
+__device__ __forceinline__ void all_group(const ForceArgs &A, const GroupHdr &h, ForceTile *T, CandQueue *Q,
+                                          int lane, int w) {
   double ax[IPL] = {}, ay[IPL] = {}, az[IPL] = {};
   const int nt = (h.n_near + WAVE - 1) / WAVE, ft = (h.n_far + WAVE - 1) / WAVE;
   // first far / cell tile of wavefront w: the tiles are numbered through
   const int f0 = ((w - nt) % W + W) % W, c0 = ((w - nt - ft) % W + W) % W;
-  near_group<MIXED, IPL, UNR>(A, h, T[w].near, lane, WAVE * w, WAVE * W, S, ax, ay, az);
+  near_group<MIXED, IPL, UNR>(A, h, T[w].near, lane, WAVE * w, WAVE * W, Q[w], ax, ay, az);
   far_group<MIXED, IPL, UNR>(A, h, T[w].far, lane, WAVE * f0, WAVE * W, ax, ay, az);
   cell_group<MIXED, QUAD, IPL, UNR>(A, h, T[w].cell, lane, WAVE * c0, WAVE * W, ax, ay, az);
   tile_sync();
@@ -649,10 +677,10 @@ constexpr int min_waves(int unr) { return unr <= 2 ? 4 : unr <= 4 ? 3 : 2; }
 template <bool MIXED, bool QUAD, int UNR, int W>
 __global__ __launch_bounds__(WAVE *W, min_waves(UNR)) void k_force_all(ForceArgs A) {
   __shared__ ForceTile T[W];
+  __shared__ CandQueue Q[W];
   __shared__ int next;
   const int lane = threadIdx.x & (WAVE - 1), w = uniform_first(threadIdx.x / WAVE);
   const int ngroups = uniform_first(min((int)A.cnt->n_groups, A.ngroups_bound));
-  CandSlab S;
   unsigned long long nn = 0, nf = 0, nc = 0;  // this workgroup's interactions, added once at its end
   for (int iter = 0;; ++iter) {
     int gi;
@@ -668,60 +696,18 @@ __global__ __launch_bounds__(WAVE *W, min_waves(UNR)) void k_force_all(ForceArgs
     GroupHdr h;
     if (!group_header(A, gi, h)) continue;
     if (h.count > WAVE)
-      all_group<MIXED, QUAD, 2, UNR, W>(A, h, T, lane, w, S);
+      all_group<MIXED, QUAD, 2, UNR, W>(A, h, T, Q, lane, w);
     else
-      all_group<MIXED, QUAD, 1, UNR, W>(A, h, T, lane, w, S);
+      all_group<MIXED, QUAD, 1, UNR, W>(A, h, T, Q, lane, w);
     const unsigned long long ni = (unsigned long long)h.count;
     nn += ni * (unsigned long long)h.n_near - ni;
     nf += ni * (unsigned long long)h.n_far;
     nc += ni * (unsigned long long)h.n_cell;
   }
-  close_slab(A, S, lane);
   if (threadIdx.x == 0) {
     if (nn) atomicAdd(&A.cnt->n_near, nn);
     if (nf) atomicAdd(&A.cnt->n_far, nf);
     if (nc) atomicAdd(&A.cnt->n_cell, nc);
-  }
-}
-
-// exact neighbour test of every candidate (sorted indices) -> pairs in the
-// caller's indices
-__global__ void k_cand_test(ForceArgs A) {
-  const long long nc = (long long)A.cnt->n_cand;
-  const long long m = nc < A.cand_cap ? nc : A.cand_cap;
-  const int lane = lane_id();
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  // the loop runs wave by wave, so the ballot below sees every lane
-  for (long long p0 = blockIdx.x * (long long)blockDim.x + (threadIdx.x - lane); p0 < m; p0 += stride) {
-    const long long p = p0 + lane;
-    bool nb = false;
-    int i = 0, j = 0;
-    const int2 c = p < m ? A.cands[p] : make_int2(-1, -1);
-    if (c.x >= 0) {  // (-1, -1): a slot its wavefront left unused
-      i = c.x;
-      j = c.y;
-      // a slow member sits at its pre-drift position here; its pairs are
-      // tested once its integration has finished
-      const bool skip = A.slow && (A.slow[A.sid[i]] | A.slow[A.sid[j]]);
-      if (!skip && A.sx[i] == A.sx[j] && A.sy[i] == A.sy[j] && A.sz[i] == A.sz[j]) set_flag(A.cnt, P3T_FLAG_COINCIDENT);
-      nb = !skip && neighbour_test(A.sx[i], A.sy[i], A.sz[i], A.svx[i], A.svy[i], A.svz[i], A.sm[i], A.sro[i], A.srs[i],
-                          A.sx[j], A.sy[j], A.sz[j], A.svx[j], A.svy[j], A.svz[j], A.sm[j], A.sro[j], A.srs[j], A.G,
-                          A.rsch2, A.rsch3, A.dt);
-    }
-    const unsigned long long bal = __ballot(nb);
-    if (bal == 0ull) continue;
-    const int leader = __ffsll((long long)bal) - 1;
-    const unsigned long long o0 = wave_fetch_add(&A.cnt->n_pairs, (unsigned long long)__popcll(bal), leader);
-    if (nb) {
-      mark_close_pair(A, i, j);
-      const unsigned long long q = o0 + popc_below(bal);
-      const int a = A.sid[i], b = A.sid[j];
-      join_pair(A, a, b);
-      if ((int64_t)q < A.pair_cap)
-        A.pairs[q] = make_int2(a, b);
-      else
-        set_flag(A.cnt, P3T_FLAG_PAIR_OVERFLOW);
-    }
   }
 }
 
@@ -760,7 +746,6 @@ void launch_all(p3t_ctx *c, const ForceArgs &A, unsigned nonpersistent_grid) {
 
 template <int UNR>
 hipError_t launch_split(p3t_ctx *c, ForceArgs A, unsigned nonpersistent_grid, double *acc3) {
-  const hipStream_t s = c->stream;
   A.acc = acc3;
   A.queue = &c->cnt->queue[0];
   const int64_t groups = c->n / std::max(1, 2 * c->P.n_group_max / 3);
@@ -769,9 +754,6 @@ hipError_t launch_split(p3t_ctx *c, ForceArgs A, unsigned nonpersistent_grid, do
   else
     launch_all<UNR, 4>(c, A, nonpersistent_grid);
   ev_record(c, 11);
-  const unsigned gc = (unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)c->n_cu * 8, (c->cand_cap + 255) / 256));
-  if (A.cand_cap > 0) hipLaunchKernelGGL(k_cand_test, dim3(gc), dim3(256), 0, s, A);
-  ev_record(c, 12);
   return hipGetLastError();
 }
 

@@ -61,7 +61,6 @@ struct DevCounters {
   unsigned long long n_chunks;     // subtree roots of the bottom-up moment pass
   unsigned long long n_top;        // nodes above them
   unsigned long long queue[3];    // persistent queues of the split force kernels
-  unsigned long long n_cand;      // neighbour candidates appended (split force)
   unsigned long long n_pairs_d;   // pairs of the parked members' direct terms (p3t_hard_evaluate)
   unsigned long long n_unbound;   // orbits that are not bound (p3t_kepler_drift)
   unsigned long long n_bad_index; // list entries outside [0, n) (p3t_kepler_drift)
@@ -251,8 +250,6 @@ struct p3t_ctx {
   int32_t *slot_lists = nullptr;    // walk temp lists (walk_slots * 3 * slot_cap_list)
   int32_t *slot_stack = nullptr;    // walk stacks (walk_slots * slot_cap_stack)
   int2 *pairs = nullptr;            // neighbour pairs (i_orig, j_orig)
-  int2 *cands = nullptr;            // neighbour candidates (sorted indices)
-  int64_t cand_cap = 0;
   // The clusters of the next hard part (labels, cluster CSR, buckets) are
   // prepared on aux_stream right behind an evaluation's kernels, beside the
   // host's read of its counters and the kicks that follow; prep_state 2 =

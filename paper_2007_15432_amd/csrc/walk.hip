@@ -235,7 +235,6 @@ __global__ void k_reset_queues(DevCounters *cnt, unsigned long long *__restrict_
   if (t0 != 0) return;
   cnt->force_queue = 0;
   for (int k = 0; k < 3; ++k) cnt->queue[k] = 0;
-  cnt->n_cand = 0;
   cnt->pool_cursor = 0;
   cnt->n_pairs = 0;
   cnt->n_near = 0;
