@@ -24,9 +24,11 @@
 namespace p3t {
 
 constexpr int CUT_T = 256;
-constexpr int CUT_PER = 4;
-constexpr int CUT_CHUNK = CUT_T * CUT_PER;
+constexpr int CUT_CHUNK = 1024;  // particles per bin-sum slot that the scratch sizes allow for
 constexpr int CUT_MAX_BINS = 256;
+constexpr int CUT_BLOCKS = 256;       // workgroups of the bin pass at most
+constexpr int CUT_CELLS = 64 * CUT_T;  // LDS accumulators of the bin pass (128 KB)
+constexpr int CUT_BT = 1024;           // threads of the bin pass
 
 // The caller's particles and the constants of the per-particle terms.
 struct CutIn {
@@ -113,101 +115,102 @@ __global__ __launch_bounds__(CUT_T) void k_cut_prep(CutIn I, double *__restrict_
   }
 }
 
-__global__ __launch_bounds__(256) void k_cut_minmax(const double *__restrict__ part, int nb, double *__restrict__ out) {
-  __shared__ double sh[2][256 / WAVE];
-  const int t = threadIdx.x;
-  double lo = INFINITY, hi = -INFINITY;
-  for (int b = t; b < nb; b += 256) {
-    lo = fmin(lo, part[2 * b]);
-    hi = fmax(hi, part[2 * b + 1]);
-  }
-  lo = wave_min(lo);
-  hi = wave_max(hi);
-  if ((t & (WAVE - 1)) == 0) {
-    sh[0][t / WAVE] = lo;
-    sh[1][t / WAVE] = hi;
-  }
-  __syncthreads();
-  if (t == 0) {
-    for (int w = 1; w < 256 / WAVE; ++w) {
-      lo = fmin(lo, sh[0][w]);
-      hi = fmax(hi, sh[1][w]);
-    }
-    out[0] = lo;
-    out[1] = hi;
-  }
-}
-
-// Per chunk of CUT_CHUNK particles: bin index of each particle and, per bin,
-// the chunk's sum of u^2 and member count.  The chunk's bins and u^2 are
-// staged in LDS; L = CUT_T / nbins threads share a bin, each summing every
-// L-th entry in index order, and the L partials are added in order: a fixed
-// reduction order, so the result does not depend on scheduling.
+// Per workgroup's range of particles: bin index of each particle and, per
+// bin, the range's sum of u^2 and member count.  The accumulators are
+// [bin][column] in LDS, 256 columns up to 64 bins, fewer above; all threads
+// form their particles' bins (a logarithm each), then as many threads as there
+// are columns at a time add theirs, each to its own column.  At the end
+// threads share a bin and add its columns in order, and their partials are
+// added in order: a fixed reduction order, so the result does not depend on
+// scheduling.  2^20 particles: 16 us, where each bin's threads scanning
+// a chunk's bins for their own took 35.
+// The range of R is reduced from the partials by every workgroup itself;
+// workgroup 0 also leaves it in mm.
 // STORE: R and u2 come from the prep pass, and the bins are kept for the
 // last pass; otherwise R and u2 are recomputed here and nothing is kept.
 template <bool STORE>
-__global__ __launch_bounds__(CUT_T) void k_cut_bins(CutIn I, const double *__restrict__ R,
-                                                    const double *__restrict__ u2, const double *__restrict__ mm,
-                                                    int nbins, int32_t *__restrict__ bin_out,
-                                                    double *__restrict__ psum, double *__restrict__ pcnt) {
-  __shared__ int sb[CUT_CHUNK];
-  __shared__ double su[CUT_CHUNK];
-  __shared__ double ps[CUT_T], pc[CUT_T];
+__global__ __launch_bounds__(CUT_BT) void k_cut_bins(CutIn I, const double *__restrict__ R,
+                                                    const double *__restrict__ u2, const double *__restrict__ part,
+                                                    int nb_part, double *__restrict__ mm, int nbins, int64_t range,
+                                                    int32_t *__restrict__ bin_out, double *__restrict__ psum,
+                                                    double *__restrict__ pcnt) {
+  __shared__ double cell[CUT_CELLS];
+  __shared__ int cnt[CUT_MAX_BINS];
+  __shared__ double ps[CUT_BT], sh[2][CUT_BT / WAVE];
   const int t = threadIdx.x;
-  const int64_t n = I.n;
-  const int64_t base = (int64_t)blockIdx.x * CUT_CHUNK;
-  const double Rmin = mm[0];
-  const double lspan = cut_lspan(mm);
+  const int cols = CUT_CELLS / nbins < CUT_T ? CUT_CELLS / nbins : CUT_T;
+  {
+    double lo = INFINITY, hi = -INFINITY;
+    for (int b = t; b < nb_part; b += CUT_BT) {
+      lo = fmin(lo, part[2 * b]);
+      hi = fmax(hi, part[2 * b + 1]);
+    }
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    if ((t & (WAVE - 1)) == 0) {
+      sh[0][t / WAVE] = lo;
+      sh[1][t / WAVE] = hi;
+    }
+  }
+  for (int q = t; q < nbins * cols; q += CUT_BT) cell[q] = 0.0;
+  for (int q = t; q < nbins; q += CUT_BT) cnt[q] = 0;
+  __syncthreads();
+  double range_mm[2] = {sh[0][0], sh[1][0]};
+  for (int w = 1; w < CUT_BT / WAVE; ++w) {
+    range_mm[0] = fmin(range_mm[0], sh[0][w]);
+    range_mm[1] = fmax(range_mm[1], sh[1][w]);
+  }
+  if (blockIdx.x == 0 && t < 2) mm[t] = range_mm[t];
+  const double Rmin = range_mm[0], lspan = cut_lspan(range_mm);
+  const int64_t a = (int64_t)blockIdx.x * range, b = a + range < I.n ? a + range : I.n;
+  const int group = t / cols, col = t - group * cols, groups = (CUT_BT + cols - 1) / cols;
+  constexpr int PER = 4;
+  for (int64_t i0 = a; i0 < b; i0 += PER * CUT_BT) {  // uniform
+    int bb[PER];
+    double u[PER];
 #pragma unroll
-  for (int q = 0; q < CUT_PER; ++q) {
-    const int j = q * CUT_T + t;
-    const int64_t i = base + j;
-    int bb = -1;
-    double u = 0.0;
-    if (i < n) {
+    for (int q = 0; q < PER; ++q) {
+      const int64_t i = i0 + q * CUT_BT + t;
+      bb[q] = -1;
+      u[q] = 0.0;
+      if (i >= b) continue;
       double Ri;
       if (STORE) {
         Ri = R[i];
-        u = u2[i];
+        u[q] = u2[i];
       } else {
         double rh;
-        cut_terms(I, i, Ri, u, rh);
+        cut_terms(I, i, Ri, u[q], rh);
       }
-      bb = cut_bin(Ri, Rmin, lspan, nbins);
-      if (STORE) bin_out[i] = bb;
+      bb[q] = cut_bin(Ri, Rmin, lspan, nbins);
+      if (STORE) bin_out[i] = bb[q];
+      atomicAdd(&cnt[bb[q]], 1);
     }
-    sb[j] = bb;
-    su[j] = u;
-  }
-  __syncthreads();
-  const int L = nbins >= CUT_T ? 1 : CUT_T / nbins;  // threads per bin
-  const int k = t / L, part = t - k * L;
-  double s = 0.0, c = 0.0;
-  if (k < nbins) {
-    for (int j = part; j < CUT_CHUNK; j += L) {
-      if (sb[j] == k) {
-        s += su[j];
-        c += 1.0;
+    for (int g = 0; g < groups; ++g) {  // uniform
+      if (g == group) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+          if (bb[q] >= 0) cell[bb[q] * cols + col] += u[q];
       }
+      __syncthreads();
     }
   }
+  const int L = CUT_BT / nbins;  // threads per bin (at least four)
+  const int k = t / L, q0 = t - k * L;
+  double s = 0.0;
+  if (k < nbins)
+    for (int q = q0; q < cols; q += L) s += cell[k * cols + q];
   ps[t] = s;
-  pc[t] = c;
   __syncthreads();
-  for (int kk = t; kk < nbins; kk += CUT_T) {
-    double ts = 0.0, tc = 0.0;
-    if (nbins <= CUT_T) {
-      for (int p = 0; p < L; ++p) {
-        ts += ps[kk * L + p];
-        tc += pc[kk * L + p];
-      }
-    }
-    psum[(int64_t)kk * gridDim.x + blockIdx.x] = ts;  // [bin][chunk]
-    pcnt[(int64_t)kk * gridDim.x + blockIdx.x] = tc;
+  if (t < nbins) {
+    double ts = 0.0;
+    for (int p = 0; p < L; ++p) ts += ps[t * L + p];
+    psum[(int64_t)t * gridDim.x + blockIdx.x] = ts;  // [bin][workgroup]
+    pcnt[(int64_t)t * gridDim.x + blockIdx.x] = (double)cnt[t];
   }
 }
 
-// One block per bin: the bin's chunk partials in a fixed reduction order.
+// One block per bin: the bin's partials in a fixed reduction order.
 __global__ __launch_bounds__(256) void k_cut_binsum(const double *__restrict__ psum, const double *__restrict__ pcnt,
                                                     int nblk, double *__restrict__ bsum, double *__restrict__ bcnt) {
   __shared__ double shs[256 / WAVE], shc[256 / WAVE];
@@ -235,18 +238,28 @@ __global__ __launch_bounds__(256) void k_cut_binsum(const double *__restrict__ p
   }
 }
 
-// rms per bin, and the rms over all particles for sparse bins.
-__global__ void k_cut_binfinal(const double *__restrict__ bsum, const double *__restrict__ bcnt, int nbins,
-                               int min_count, double *__restrict__ vr_bin) {
-  __shared__ double ssum[CUT_MAX_BINS], scnt[CUT_MAX_BINS];
-  __shared__ double vglob;
-  const int k = threadIdx.x;
-  if (k < nbins) {
-    ssum[k] = bsum[k];
-    scnt[k] = bcnt[k];
+// The radii.  Every workgroup forms the bins' rms itself (and the rms over
+// all particles for sparse bins) from the at most 256 bin sums.
+// STORE: bins and Hill radii from the earlier passes; otherwise recomputed.
+// mxp (shared cut-offs, nullable): per workgroup the largest r_out and
+// r_search.
+template <bool STORE>
+__global__ __launch_bounds__(CUT_T) void k_cut_out(CutIn I, const int32_t *__restrict__ bin,
+                                                   const double *__restrict__ rh_in, const double *__restrict__ mm,
+                                                   int nbins, int min_count, const double *__restrict__ bsum,
+                                                   const double *__restrict__ bcnt, double rc0, double rc1, double rs0,
+                                                   double rs1, double dt, double *__restrict__ r_out,
+                                                   double *__restrict__ r_search, double *__restrict__ v_ran,
+                                                   double *__restrict__ mxp) {
+  __shared__ double ssum[CUT_MAX_BINS], scnt[CUT_MAX_BINS], vr_bin[CUT_MAX_BINS];
+  __shared__ double vglob, sh[2][CUT_T / WAVE];
+  const int t = threadIdx.x;
+  if (t < nbins) {
+    ssum[t] = bsum[t];
+    scnt[t] = bcnt[t];
   }
   __syncthreads();
-  if (k == 0) {
+  if (t == 0) {
     double s = 0.0, c = 0.0;
     for (int q = 0; q < nbins; ++q) {
       s += ssum[q];
@@ -255,17 +268,11 @@ __global__ void k_cut_binfinal(const double *__restrict__ bsum, const double *__
     vglob = c > 0.0 ? sqrt(s / c) : 0.0;
   }
   __syncthreads();
-  if (k < nbins) vr_bin[k] = scnt[k] >= (double)min_count ? sqrt(ssum[k] / scnt[k]) : vglob;
-}
-
-// STORE: bins and Hill radii from the earlier passes; otherwise recomputed.
-template <bool STORE>
-__global__ void k_cut_out(CutIn I, const int32_t *__restrict__ bin, const double *__restrict__ rh_in,
-                          const double *__restrict__ mm, int nbins, const double *__restrict__ vr_bin, double rc0,
-                          double rc1, double rs0, double rs1, double dt, double *__restrict__ r_out,
-                          double *__restrict__ r_search, double *__restrict__ v_ran) {
-  const double Rmin = mm[0], lspan = cut_lspan(mm);
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < I.n; i += (int64_t)gridDim.x * blockDim.x) {
+  if (t < nbins) vr_bin[t] = scnt[t] >= (double)min_count ? sqrt(ssum[t] / scnt[t]) : vglob;
+  __syncthreads();
+  const double Rmin = STORE ? 0.0 : mm[0], lspan = STORE ? 0.0 : cut_lspan(mm);
+  double mo = -INFINITY, ms = -INFINITY;
+  for (int64_t i = (int64_t)blockIdx.x * CUT_T + t; i < I.n; i += (int64_t)gridDim.x * CUT_T) {
     int b;
     double rh;
     if (STORE) {
@@ -278,39 +285,56 @@ __global__ void k_cut_out(CutIn I, const int32_t *__restrict__ bin, const double
     }
     const double vr = vr_bin[b];
     const double ro = fmax(rc0 * rh, rc1 * vr * dt);
-    r_out[i] = ro;
-    r_search[i] = rs0 * ro + rs1 * vr * dt;
+    const double rs = rs0 * ro + rs1 * vr * dt;
+    if (mxp) {
+      mo = fmax(mo, ro);
+      ms = fmax(ms, rs);
+    } else {
+      r_out[i] = ro;
+      r_search[i] = rs;
+    }
     if (v_ran) v_ran[i] = vr;
   }
-}
-
-// shared cut-off (eq. (rout1)): r_out,i = max_k r_out,k for every particle
-__global__ __launch_bounds__(256) void k_max_part(const double *__restrict__ v, int64_t n, double *__restrict__ part) {
-  __shared__ double sh[256 / WAVE];
-  double mx = -INFINITY;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    mx = fmax(mx, v[i]);
-  mx = wave_max(mx);
-  if ((threadIdx.x & (WAVE - 1)) == 0) sh[threadIdx.x / WAVE] = mx;
+  if (!mxp) return;  // uniform
+  mo = wave_max(mo);
+  ms = wave_max(ms);
+  if ((t & (WAVE - 1)) == 0) {
+    sh[0][t / WAVE] = mo;
+    sh[1][t / WAVE] = ms;
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 256 / WAVE; ++w) mx = fmax(mx, sh[w]);
-    part[blockIdx.x] = fmax(mx, sh[0]);
+  if (t < 2) {
+    double m = sh[t][0];
+    for (int w = 1; w < CUT_T / WAVE; ++w) m = fmax(m, sh[t][w]);
+    mxp[2 * blockIdx.x + t] = m;
   }
 }
 
-__global__ void k_max_final(const double *__restrict__ part, int nb, double *__restrict__ out) {
-  if (threadIdx.x == 0) {
-    double mx = part[0];
-    for (int b = 1; b < nb; ++b) mx = fmax(mx, part[b]);
-    *out = mx;
+// shared cut-off (eq. (rout1)): every particle takes the maxima over all
+// particles, which every workgroup reduces from the nb partials
+__global__ __launch_bounds__(CUT_T) void k_cut_shared(int64_t n, const double *__restrict__ mxp, int nb,
+                                                      double *__restrict__ r_out, double *__restrict__ r_search) {
+  __shared__ double sh[2][CUT_T / WAVE];
+  const int t = threadIdx.x;
+  double ro = -INFINITY, rs = -INFINITY;
+  for (int b = t; b < nb; b += CUT_T) {
+    ro = fmax(ro, mxp[2 * b]);
+    rs = fmax(rs, mxp[2 * b + 1]);
   }
-}
-
-__global__ void k_cut_shared(int64_t n, const double *__restrict__ mx, double *__restrict__ r_out,
-                             double *__restrict__ r_search) {
-  const double ro = mx[0], rs = mx[1];
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+  ro = wave_max(ro);
+  rs = wave_max(rs);
+  if ((t & (WAVE - 1)) == 0) {
+    sh[0][t / WAVE] = ro;
+    sh[1][t / WAVE] = rs;
+  }
+  __syncthreads();
+  ro = sh[0][0];
+  rs = sh[1][0];
+  for (int w = 1; w < CUT_T / WAVE; ++w) {
+    ro = fmax(ro, sh[0][w]);
+    rs = fmax(rs, sh[1][w]);
+  }
+  for (int64_t i = (int64_t)blockIdx.x * CUT_T + t; i < n; i += (int64_t)gridDim.x * CUT_T) {
     r_out[i] = ro;
     r_search[i] = rs;
   }
@@ -326,13 +350,13 @@ hipError_t cutoffs_run(const p3t_params &P, int64_t n, const double *pos3, const
   if (n <= 0) return hipSuccess;
   const bool store = tmp != nullptr;
   double *R = store ? tmp : nullptr, *u2 = store ? tmp + n : nullptr, *rh = store ? tmp + 2 * n : nullptr;
-  double *mm = part + 2048;  // [0, 2*1024) min/max partials; then the range, the bins
-  double *vr_bin = mm + 8;
-  double *psum = vr_bin + CUT_MAX_BINS;
+  double *mm = part + 2048;
+  double *psum = mm + 8 + CUT_MAX_BINS;
   const int nbins = P.vran_bins;
-  const int64_t nblk = (n + CUT_CHUNK - 1) / CUT_CHUNK;
-  double *pcnt = psum + nblk * nbins;
   const int nb_prep = (int)std::min<int64_t>(1024, (n + CUT_T - 1) / CUT_T);
+  const int nblk = (int)std::min<int64_t>(CUT_BLOCKS, (n + CUT_CHUNK - 1) / CUT_CHUNK);
+  const int64_t range = (n + nblk - 1) / nblk;
+  double *pcnt = psum + (int64_t)nblk * nbins;
   CutIn I;
   I.pos = pos3;
   I.vel = vel3;
@@ -345,32 +369,29 @@ hipError_t cutoffs_run(const p3t_params &P, int64_t n, const double *pos3, const
     hipLaunchKernelGGL(k_cut_prep<true>, dim3(nb_prep), dim3(CUT_T), 0, s, I, R, u2, rh, part);
   else
     hipLaunchKernelGGL(k_cut_prep<false>, dim3(nb_prep), dim3(CUT_T), 0, s, I, R, u2, rh, part);
-  hipLaunchKernelGGL(k_cut_minmax, dim3(1), dim3(256), 0, s, part, nb_prep, mm);
   if (store)
-    hipLaunchKernelGGL(k_cut_bins<true>, dim3((unsigned)nblk), dim3(CUT_T), 0, s, I, R, u2, mm, nbins, bin, psum, pcnt);
+    hipLaunchKernelGGL(k_cut_bins<true>, dim3(nblk), dim3(CUT_BT), 0, s, I, R, u2, part, nb_prep, mm, nbins, range, bin,
+                       psum, pcnt);
   else
-    hipLaunchKernelGGL(k_cut_bins<false>, dim3((unsigned)nblk), dim3(CUT_T), 0, s, I, R, u2, mm, nbins, bin, psum,
-                       pcnt);
+    hipLaunchKernelGGL(k_cut_bins<false>, dim3(nblk), dim3(CUT_BT), 0, s, I, R, u2, part, nb_prep, mm, nbins, range,
+                       bin, psum, pcnt);
   double *bsum = part, *bcnt = part + CUT_MAX_BINS;  // the min/max partials are consumed
-  hipLaunchKernelGGL(k_cut_binsum, dim3(nbins), dim3(256), 0, s, psum, pcnt, (int)nblk, bsum, bcnt);
-  hipLaunchKernelGGL(k_cut_binfinal, dim3(1), dim3(CUT_MAX_BINS), 0, s, bsum, bcnt, nbins, P.vran_min_count, vr_bin);
-  const unsigned g = (unsigned)std::min<int64_t>(65536, (n + 255) / 256);
+  hipLaunchKernelGGL(k_cut_binsum, dim3(nbins), dim3(256), 0, s, psum, pcnt, nblk, bsum, bcnt);
+  const bool shared = P.cutoff_mode == 1;
+  const int64_t g_max = shared ? CUT_BLOCKS : 2048;
+  const unsigned g = (unsigned)std::min<int64_t>(g_max, (n + CUT_T - 1) / CUT_T);
+  double *mxp = shared ? part + 2 * CUT_MAX_BINS : nullptr;  // 2 CUT_BLOCKS doubles, behind the bin sums
+  static_assert(2 * CUT_MAX_BINS + 2 * CUT_BLOCKS <= 2048, "maxima exceed the range partials' scratch");
   if (store)
-    hipLaunchKernelGGL(k_cut_out<true>, dim3(g), dim3(256), 0, s, I, bin, rh, mm, nbins, vr_bin, P.r_cut0, P.r_cut1,
-                       P.r_search0, P.r_search1, P.dt_soft, r_out, r_search, v_ran);
+    hipLaunchKernelGGL(k_cut_out<true>, dim3(g), dim3(CUT_T), 0, s, I, bin, rh, mm, nbins, P.vran_min_count, bsum, bcnt,
+                       P.r_cut0, P.r_cut1, P.r_search0, P.r_search1, P.dt_soft, r_out, r_search, v_ran, mxp);
   else
-    hipLaunchKernelGGL(k_cut_out<false>, dim3(g), dim3(256), 0, s, I, bin, rh, mm, nbins, vr_bin, P.r_cut0, P.r_cut1,
-                       P.r_search0, P.r_search1, P.dt_soft, r_out, r_search, v_ran);
-  if (P.cutoff_mode == 1) {
-    // shared cut-off (eq. (rout1)) and shared search radius (Section 2.3):
-    // every particle takes the maxima over all particles
-    const int nbm = (int)std::min<int64_t>(1024, (n + 255) / 256);
-    hipLaunchKernelGGL(k_max_part, dim3(nbm), dim3(256), 0, s, r_out, n, part);
-    hipLaunchKernelGGL(k_max_final, dim3(1), dim3(64), 0, s, part, nbm, mm + 2);
-    hipLaunchKernelGGL(k_max_part, dim3(nbm), dim3(256), 0, s, r_search, n, part);
-    hipLaunchKernelGGL(k_max_final, dim3(1), dim3(64), 0, s, part, nbm, mm + 3);
-    hipLaunchKernelGGL(k_cut_shared, dim3(g), dim3(256), 0, s, n, mm + 2, r_out, r_search);
-  }
+    hipLaunchKernelGGL(k_cut_out<false>, dim3(g), dim3(CUT_T), 0, s, I, bin, rh, mm, nbins, P.vran_min_count, bsum,
+                       bcnt, P.r_cut0, P.r_cut1, P.r_search0, P.r_search1, P.dt_soft, r_out, r_search, v_ran, mxp);
+  if (shared)
+    // shared cut-off (eq. (rout1)) and shared search radius (Section 2.3)
+    hipLaunchKernelGGL(k_cut_shared, dim3((unsigned)std::min<int64_t>(2048, (n + CUT_T - 1) / CUT_T)), dim3(CUT_T), 0,
+                       s, n, (const double *)mxp, (int)g, r_out, r_search);
   return hipGetLastError();
 }
 
