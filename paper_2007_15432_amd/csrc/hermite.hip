@@ -138,6 +138,16 @@ __device__ __forceinline__ void hard_pair(double dx, double dy, double dz, doubl
   jk[2] = fmad(-c2, dz, fmad(w, fmad(-c1, dz, uz), jk[2]));
 }
 
+// hard_pair for a partner that may be the member itself, which adds zeros
+// (unit distance, no mass) instead of a branch: a loop over all partners then
+// unrolls, and the roots and changeovers of several partners run side by side
+// while the sums keep their order.
+__device__ __forceinline__ void hard_pair_other(bool other, double dx, double dy, double dz, double ux, double uy,
+                                                double uz, double gmj, double invR, const HermArgs &A, double *a,
+                                                double *jk) {
+  hard_pair(other ? dx : 1.0, dy, dz, ux, uy, uz, other ? gmj : 0.0, invR, A, a, jk);
+}
+
 __device__ __forceinline__ void star_term(const double *x, const double *v, double GM, double *a, double *jk) {
   const double r2 = fmad(x[2], x[2], fmad(x[1], x[1], x[0] * x[0]));
   const double rinv = rsqrt_pos(r2);  // a particle away from the star
@@ -397,9 +407,11 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
   wave_sync();
   // forces at t = 0 and the initial energy (a resumed cluster reads them)
   double pa[3] = {0.0, 0.0, 0.0}, pj[3] = {0.0, 0.0, 0.0};
-  double e = lead ? 0.5 * m * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]) -
-                        A.GM * m * rsqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2])
-                  : 0.0;
+  // the energies are formed only where their error is asked for (uniform)
+  const bool energy = A.e_rel != nullptr;
+  double e = lead && energy ? 0.5 * m * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]) -
+                                  A.GM * m * rsqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2])
+                            : 0.0;
   if (mem && !RESUME) {
     for (int jj = sub; jj < size; jj += LPM) {
       if (jj == sl) continue;
@@ -407,7 +419,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
       const double dx = L.px[q] - x[0], dy = L.py[q] - x[1], dz = L.pz[q] - x[2];
       const double invR = fmin(invi, L.pinv[q]);
       hard_pair(dx, dy, dz, L.pvx[q] - v[0], L.pvy[q] - v[1], L.pvz[q] - v[2], L.pgm[q], invR, A, pa, pj);
-      if (jj > sl) {
+      if (energy && jj > sl) {
         const double r = sqrt(dx * dx + dy * dy + dz * dz);
         e -= m * L.pgm[q] * (1.0 - changeover_W(r * invR, A)) / r;
       }
@@ -419,7 +431,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
     a0[d] += lpm_sum(pa[d], ll2);
     j0[d] += lpm_sum(pj[d], ll2);
   }
-  double E0 = seg_sum(e, cl2);
+  double E0 = energy ? seg_sum(e, cl2) : 0.0;
   int lev = initial_level(a0, j0, mem, gid, A);  // every copy reads the carried step
   // two-member clusters: the partner's G m and 1 / r_out (lane ^ 1), and
   // the pair's 1 / max(r_out) as the LDS path forms it
@@ -560,28 +572,31 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
     }
   }
   // final energy
-  wave_sync();
-  if (lead) {
-    L.px[me] = x[0];
-    L.py[me] = x[1];
-    L.pz[me] = x[2];
-    L.pvx[me] = v[0];
-    L.pvy[me] = v[1];
-    L.pvz[me] = v[2];
-  }
-  wave_sync();
-  e = lead ? 0.5 * m * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]) -
-                 A.GM * m * rsqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2])
-           : 0.0;
-  if (mem) {
-    for (int jj = sl + 1 + sub; jj < size; jj += LPM) {
-      const int q = sb + jj;
-      const double dx = L.px[q] - x[0], dy = L.py[q] - x[1], dz = L.pz[q] - x[2];
-      const double r = sqrt(dx * dx + dy * dy + dz * dz);
-      e -= m * L.pgm[q] * (1.0 - changeover_W(r * fmin(invi, L.pinv[q]), A)) / r;
+  double E1 = 0.0;
+  if (energy) {
+    wave_sync();
+    if (lead) {
+      L.px[me] = x[0];
+      L.py[me] = x[1];
+      L.pz[me] = x[2];
+      L.pvx[me] = v[0];
+      L.pvy[me] = v[1];
+      L.pvz[me] = v[2];
     }
+    wave_sync();
+    e = lead ? 0.5 * m * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]) -
+                   A.GM * m * rsqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2])
+             : 0.0;
+    if (mem) {
+      for (int jj = sl + 1 + sub; jj < size; jj += LPM) {
+        const int q = sb + jj;
+        const double dx = L.px[q] - x[0], dy = L.py[q] - x[1], dz = L.pz[q] - x[2];
+        const double r = sqrt(dx * dx + dy * dy + dz * dz);
+        e -= m * L.pgm[q] * (1.0 - changeover_W(r * fmin(invi, L.pinv[q]), A)) / r;
+      }
+    }
+    E1 = seg_sum(e, cl2);
   }
-  const double E1 = seg_sum(e, cl2);
   if (PARK && parked) return;  // finished by the resume launch
   if (lead) {
     A.pos[gid] = x[0];
@@ -799,6 +814,7 @@ __device__ __forceinline__ void wave_body(const HermArgs &A, const int32_t *blis
   }
   if (mem) L.act[wbase + lane] = lane;  // every member: the forces at t = 0
   wave_sync();
+  const bool energy = A.e_rel != nullptr;  // formed only where asked for (uniform)
   double E0 = 0.0;
   int lev = 0;
   int64_t t = 0;
@@ -806,17 +822,17 @@ __device__ __forceinline__ void wave_body(const HermArgs &A, const int32_t *blis
   star_term(x, v, GM, a0, j0);
   if (!RESUME) {
     spread_sums<COLL>(A, L, wbase, size, size, lane, __ballot(mem));
-    double e = mem ? 0.5 * m * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]) -
-                         GM * m * rsqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2])
-                   : 0.0;
-    if (mem)
+    double e = mem && energy ? 0.5 * m * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]) -
+                                   GM * m * rsqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2])
+                             : 0.0;
+    if (mem && energy)
       for (int q = lane + 1; q < size; ++q) {
         const int sq = wbase + q;
         const double dx = L.px[sq] - x[0], dy = L.py[sq] - x[1], dz = L.pz[sq] - x[2];
         const double r = sqrt(dx * dx + dy * dy + dz * dz);
         e -= m * L.pgm[sq] * (1.0 - changeover_W(r * fmin(invi, L.pinv[sq]), A)) / r;
       }
-    E0 = seg_sum(e, 6);
+    if (energy) E0 = seg_sum(e, 6);
     wave_sync();
     if (mem) add_spread(L, wbase, lane, spread_lg(size, size), a0, j0);  // list position = lane
     lev = initial_level(a0, j0, mem, gid, A);
@@ -1072,26 +1088,29 @@ __device__ __forceinline__ void wave_body(const HermArgs &A, const int32_t *blis
     return;  // finished by the resume launch
   }
   // final energy (the pairs inside a composite left out)
-  wave_sync();
-  L.px[me] = x[0];
-  L.py[me] = x[1];
-  L.pz[me] = x[2];
-  L.pvx[me] = v[0];
-  L.pvy[me] = v[1];
-  L.pvz[me] = v[2];
-  wave_sync();
-  double e = mem ? 0.5 * m * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]) -
-                       GM * m * rsqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2])
-                 : 0.0;
-  if (mem)
-    for (int q = lane + 1; q < size; ++q) {
-      const int sq = wbase + q;
-      if (COLL && L.cid[sq] == mycid) continue;
-      const double dx = L.px[sq] - x[0], dy = L.py[sq] - x[1], dz = L.pz[sq] - x[2];
-      const double r = sqrt(dx * dx + dy * dy + dz * dz);
-      e -= m * L.pgm[sq] * (1.0 - changeover_W(r * fmin(invi, L.pinv[sq]), A)) / r;
-    }
-  const double E1 = seg_sum(e, 6);
+  double E1 = 0.0;
+  if (energy) {
+    wave_sync();
+    L.px[me] = x[0];
+    L.py[me] = x[1];
+    L.pz[me] = x[2];
+    L.pvx[me] = v[0];
+    L.pvy[me] = v[1];
+    L.pvz[me] = v[2];
+    wave_sync();
+    double e = mem ? 0.5 * m * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]) -
+                         GM * m * rsqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2])
+                   : 0.0;
+    if (mem)
+      for (int q = lane + 1; q < size; ++q) {
+        const int sq = wbase + q;
+        if (COLL && L.cid[sq] == mycid) continue;
+        const double dx = L.px[sq] - x[0], dy = L.py[sq] - x[1], dz = L.pz[sq] - x[2];
+        const double r = sqrt(dx * dx + dy * dy + dz * dz);
+        e -= m * L.pgm[sq] * (1.0 - changeover_W(r * fmin(invi, L.pinv[sq]), A)) / r;
+      }
+    E1 = seg_sum(e, 6);
+  }
   if (mem) {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -1114,16 +1133,6 @@ __device__ __forceinline__ void wave_body(const HermArgs &A, const int32_t *blis
 }
 
 // ---------------------------------------------------------------- big clusters
-__device__ __forceinline__ int64_t block_min_i64(int64_t v, int64_t *sh) {
-  v = wave_min(v);
-  const int w = threadIdx.x / WAVE;
-  __syncthreads();
-  if ((threadIdx.x & (WAVE - 1)) == 0) sh[w] = v;
-  __syncthreads();
-  int64_t r = sh[0];
-  for (int q = 1; q < BIG_T / WAVE; ++q) r = sh[q] < r ? sh[q] : r;
-  return r;
-}
 __device__ __forceinline__ double block_sum(double v, double *sh) {
   v = wave_sum(v);
   const int w = threadIdx.x / WAVE;
@@ -1135,28 +1144,49 @@ __device__ __forceinline__ double block_sum(double v, double *sh) {
   return r;
 }
 
-// exclusive scan of one int per thread over the workgroup; returns the total
-__device__ __forceinline__ int block_excl_scan_i32(int v, int &excl, int64_t *sh) {
-  const int w = threadIdx.x / WAVE, l = threadIdx.x & (WAVE - 1);
-  const int incl = wave_incl_scan(v);
-  __syncthreads();
-  if (l == WAVE - 1) sh[w] = incl;
-  __syncthreads();
-  int off = 0, tot = 0;
-  for (int q = 0; q < BIG_T / WAVE; ++q) {
-    const int s = (int)sh[q];
-    off += q < w ? s : 0;
-    tot += s;
-  }
-  excl = off + incl - v;
-  return tot;
+// The butterfly sums of six values over the wavefront, as wave_sum forms each
+// of them (partners 32, 16, 8, 4, 2 and 1 lanes away, added in that order: the
+// same bits), without LDS.  A swap of half wavefronts, then of rows, folds two
+// values in one addition; inside a row the rotations by 8 and 4 stand for the
+// partners 8 and 4 lanes away (the values repeat with that period by then).
+// Afterwards U holds a[0], a[1], j[0], j[1] in rows 0..3 and V holds a[2] in
+// rows 0 and 1, j[2] in rows 2 and 3.
+__device__ __forceinline__ double swap32_add(double a, double b) {
+  const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+  return __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])) +
+         __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
+}
+__device__ __forceinline__ double swap16_add(double a, double b) {
+  const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+  return __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])) +
+         __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
+}
+constexpr int DPP_ROR8 = 0x128, DPP_ROR4 = 0x124;
+__device__ __forceinline__ double row_butterfly(double v) {
+  v += dpp_f64<DPP_ROR8>(v);
+  v += dpp_f64<DPP_ROR4>(v);
+  v += dpp_f64<DPP_XOR2>(v);
+  v += dpp_f64<DPP_XOR1>(v);
+  return v;
+}
+__device__ __forceinline__ void wave_sum6(const double *a, const double *j, double &U, double &V) {
+  const double s0 = swap32_add(a[0], j[0]), s1 = swap32_add(a[1], j[1]), s2 = swap32_add(a[2], j[2]);
+  U = row_butterfly(swap16_add(s0, s1));
+  V = row_butterfly(swap16_add(s2, s2));
 }
 
 // One 256-thread workgroup per cluster c, MPT members per thread.
 template <int MPT, int MODE>
-__device__ __forceinline__ void big_body(const HermArgs &A, int c, int bk, const Lds &L, int64_t *shi, double *shd) {
+__device__ __forceinline__ void big_body(const HermArgs &A, int c, int bk, const Lds &L, int64_t *shi, double *shd,
+                                         unsigned long long *shm) {
   constexpr bool RESUME = MODE == 2, PARK = MODE == 1;
-  const int tid = threadIdx.x;
+  constexpr int NW = BIG_T / WAVE;
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = uniform_first(tid / WAVE);
+  const bool energy = A.e_rel != nullptr;  // formed only where asked for (uniform)
   const int b = A.cl_ptr[c];
   const int size = A.cl_ptr[c + 1] - b;
   const int64_t n = A.n;
@@ -1212,22 +1242,30 @@ __device__ __forceinline__ void big_body(const HermArgs &A, int c, int bk, const
       lev[u] = A.pk.lev[gid[u]];
       continue;
     }
-    e += 0.5 * m[u] * (v[u][0] * v[u][0] + v[u][1] * v[u][1] + v[u][2] * v[u][2]) -
-         A.GM * m[u] * rsqrt(x[u][0] * x[u][0] + x[u][1] * x[u][1] + x[u][2] * x[u][2]);
-    for (int q = 0; q < size; ++q) {
-      if (q == k) continue;
-      const double dx = L.px[q] - x[u][0], dy = L.py[q] - x[u][1], dz = L.pz[q] - x[u][2];
-      const double invR = fmin(invi[u], L.pinv[q]);
-      hard_pair(dx, dy, dz, L.pvx[q] - v[u][0], L.pvy[q] - v[u][1], L.pvz[q] - v[u][2], L.pgm[q], invR, A, a0[u],
-                j0[u]);
-      if (q > k) {
-        const double r = sqrt(dx * dx + dy * dy + dz * dz);
-        e -= m[u] * L.pgm[q] * (1.0 - changeover_W(r * invR, A)) / r;
+    if (energy)
+      e += 0.5 * m[u] * (v[u][0] * v[u][0] + v[u][1] * v[u][1] + v[u][2] * v[u][2]) -
+           A.GM * m[u] * rsqrt(x[u][0] * x[u][0] + x[u][1] * x[u][1] + x[u][2] * x[u][2]);
+    if (energy) {
+      for (int q = 0; q < size; ++q) {
+        if (q == k) continue;
+        const double dx = L.px[q] - x[u][0], dy = L.py[q] - x[u][1], dz = L.pz[q] - x[u][2];
+        const double invR = fmin(invi[u], L.pinv[q]);
+        hard_pair(dx, dy, dz, L.pvx[q] - v[u][0], L.pvy[q] - v[u][1], L.pvz[q] - v[u][2], L.pgm[q], invR, A, a0[u],
+                  j0[u]);
+        if (q > k) {
+          const double r = sqrt(dx * dx + dy * dy + dz * dz);
+          e -= m[u] * L.pgm[q] * (1.0 - changeover_W(r * invR, A)) / r;
+        }
       }
+    } else {
+#pragma unroll 4
+      for (int q = 0; q < size; ++q)
+        hard_pair_other(q != k, L.px[q] - x[u][0], L.py[q] - x[u][1], L.pz[q] - x[u][2], L.pvx[q] - v[u][0],
+                        L.pvy[q] - v[u][1], L.pvz[q] - v[u][2], L.pgm[q], fmin(invi[u], L.pinv[q]), A, a0[u], j0[u]);
     }
     lev[u] = initial_level(a0[u], j0[u], true, gid[u], A);
   }
-  double E0 = block_sum(e, shd);
+  double E0 = energy ? block_sum(e, shd) : 0.0;
   const int64_t T = (int64_t)1 << TICK_BITS;
   int it = 0;  // block steps taken
   if (RESUME) {
@@ -1244,7 +1282,17 @@ __device__ __forceinline__ void big_body(const HermArgs &A, int c, int bk, const
         const int64_t te = t[u] + ((int64_t)1 << (TICK_BITS - lev[u]));
         tel = te < tel ? te : tel;
       }
-    const int64_t tn = uniform_first64(block_min_i64(tel, shi));
+    // three barriers per step: the block time, the predicted states with the
+    // due members' masks, the partner sums.  (What a barrier separates: shi is
+    // rewritten after the states' barrier of this step, the states and masks
+    // after the next block time's, the partner sums after the next states'.)
+    const int64_t wmin = wave_min_uniform(tel);
+    if (lane == 0) shi[w] = wmin;
+    __syncthreads();
+    int64_t tn = shi[0];
+#pragma unroll
+    for (int q = 1; q < NW; ++q) tn = shi[q] < tn ? shi[q] : tn;
+    tn = uniform_first64(tn);
     if (tn > T) break;  // every member has reached T (see seg_body)
     if (its == budget) {  // uniform: park the cluster and stop
       __shared__ int pslot;
@@ -1285,7 +1333,7 @@ __device__ __forceinline__ void big_body(const HermArgs &A, int c, int bk, const
       const double d2 = dl * dl * 0.5, d3 = dl * dl * dl * (1.0 / 6.0);
       predict(x[u], v[u], a0[u], j0[u], dl, d2, d3, xp[u], vp[u]);
     }
-    __syncthreads();
+    bool act[MPT];
 #pragma unroll
     for (int u = 0; u < MPT; ++u) {
       const int k = tid + BIG_T * u;
@@ -1295,56 +1343,94 @@ __device__ __forceinline__ void big_body(const HermArgs &A, int c, int bk, const
       L.pvx[k] = vp[u][0];
       L.pvy[k] = vp[u][1];
       L.pvz[k] = vp[u][2];
+      act[u] = mem[u] && t[u] + ((int64_t)1 << (TICK_BITS - lev[u])) == tn;
+      const unsigned long long due = __ballot(act[u]);
+      if (lane == 0) shm[u * NW + w] = due;
     }
     __syncthreads();
     // Active members (due at tn).  With few of them, each active member's
     // partner loop is spread over the 64 lanes of a wavefront (wavefronts
     // take active members in turn) and reduced; otherwise every thread
     // loops over all partners of its own members.
-    bool act[MPT];
-    int slot[MPT];
-    int na_me = 0;
+    int na = 0, slot[MPT], first_w = 0;
 #pragma unroll
     for (int u = 0; u < MPT; ++u) {
-      act[u] = mem[u] && t[u] + ((int64_t)1 << (TICK_BITS - lev[u])) == tn;
-      na_me += act[u] ? 1 : 0;
+      slot[u] = -1;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) {
+        const unsigned long long due = (unsigned long long)uniform_first64((long long)shm[u * NW + q]);
+        if (q == w && act[u]) slot[u] = na + popc_below(due);
+        if (na == 0 && due != 0ull) first_w = q;
+        na += (int)__popcll(due);
+      }
     }
-    int base_me = 0;
-    const int na = block_excl_scan_i32(na_me, base_me, shi);
     const bool spread = L.act != nullptr && na <= BIG_ACT && 2 * na <= size;
     if (spread) {
-      int q = base_me;
+      // the members by their place among the due ones: up to two from the
+      // masks, more through a list
+      if (na > 2) {
 #pragma unroll
-      for (int u = 0; u < MPT; ++u) {
-        slot[u] = act[u] ? q : -1;
-        if (act[u]) L.act[q++] = tid + BIG_T * u;
+        for (int u = 0; u < MPT; ++u)
+          if (act[u]) L.act[slot[u]] = tid + BIG_T * u;
+        __syncthreads();
       }
-      __syncthreads();
-      const int w = tid / WAVE, lane = tid & (WAVE - 1);
-      for (int a = w; a < na; a += BIG_T / WAVE) {  // uniform per wavefront
-        const int k = L.act[a];
+      // (the sums of the first due member fall to the wavefront behind its
+      // own, which forms the star's term meanwhile)
+      for (int i = (w - first_w - 1 + 2 * NW) % NW; i < na; i += NW) {  // uniform per wavefront
+        int k = 0;
+        if (na > 2) {
+          k = L.act[i];
+        } else {
+          int left = i;
+#pragma unroll
+          for (int u = 0; u < MPT; ++u) {
+#pragma unroll
+            for (int q = 0; q < NW; ++q) {
+              unsigned long long due = (unsigned long long)uniform_first64((long long)shm[u * NW + q]);
+              const int cnt = (int)__popcll(due);
+              if (left >= 0 && left < cnt) {
+                if (left == 1) due &= due - 1ull;
+                k = BIG_T * u + WAVE * q + __ffsll((long long)due) - 1;
+              }
+              left -= cnt;
+            }
+          }
+        }
         const double xk = L.px[k], yk = L.py[k], zk = L.pz[k], vxk = L.pvx[k], vyk = L.pvy[k], vzk = L.pvz[k];
         const double ik = L.pinv[k];
         double pa[3] = {0.0, 0.0, 0.0}, pj[3] = {0.0, 0.0, 0.0};
-        for (int qq = lane; qq < size; qq += WAVE) {
-          if (qq == k) continue;
-          hard_pair(L.px[qq] - xk, L.py[qq] - yk, L.pz[qq] - zk, L.pvx[qq] - vxk, L.pvy[qq] - vyk, L.pvz[qq] - vzk,
-                    L.pgm[qq], fmin(ik, L.pinv[qq]), A, pa, pj);
-        }
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          pa[d] = wave_sum(pa[d]);
-          pj[d] = wave_sum(pj[d]);
-        }
-        if (lane == 0) {
-#pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            L.res[6 * a + d] = pa[d];
-            L.res[6 * a + 3 + d] = pj[d];
-          }
+#pragma unroll 2
+        for (int qq = lane; qq < size; qq += WAVE)
+          hard_pair_other(qq != k, L.px[qq] - xk, L.py[qq] - yk, L.pz[qq] - zk, L.pvx[qq] - vxk, L.pvy[qq] - vyk, L.pvz[qq] - vzk,
+                          L.pgm[qq], fmin(ik, L.pinv[qq]), A, pa, pj);
+        double U, V;
+        wave_sum6(pa, pj, U, V);
+        if ((lane & 15) == 0) {
+          const int r = lane >> 4;  // U: a[0], a[1], j[0], j[1]; V: a[2], -, j[2], -
+          double *o = L.res + 6 * i;
+          o[r < 2 ? r : r + 1] = U;
+          if ((r & 1) == 0) o[r == 0 ? 2 : 5] = V;
         }
       }
+      double a1[MPT][3], j1[MPT][3];
+#pragma unroll
+      for (int u = 0; u < MPT; ++u)
+        if (act[u]) star_term(xp[u], vp[u], A.GM, a1[u], j1[u]);
       __syncthreads();
+#pragma unroll
+      for (int u = 0; u < MPT; ++u) {
+        if (!act[u]) continue;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          a1[u][d] += L.res[6 * slot[u] + d];
+          j1[u][d] += L.res[6 * slot[u] + 3 + d];
+        }
+        const double h = (double)(tn - t[u]) * A.tick;
+        t[u] = tn;
+        correct(x[u], v[u], a0[u], j0[u], xp[u], vp[u], a1[u], j1[u], h, t[u], lev[u], A);
+        ++n_ev;
+      }
+      continue;
     }
 #pragma unroll
     for (int u = 0; u < MPT; ++u) {
@@ -1352,19 +1438,10 @@ __device__ __forceinline__ void big_body(const HermArgs &A, int c, int bk, const
       if (!act[u]) continue;
       double a1[3], j1[3];
       star_term(xp[u], vp[u], A.GM, a1, j1);
-      if (spread) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          a1[d] += L.res[6 * slot[u] + d];
-          j1[d] += L.res[6 * slot[u] + 3 + d];
-        }
-      } else {
-        for (int q = 0; q < size; ++q) {
-          if (q == k) continue;
-          hard_pair(L.px[q] - xp[u][0], L.py[q] - xp[u][1], L.pz[q] - xp[u][2], L.pvx[q] - vp[u][0],
-                    L.pvy[q] - vp[u][1], L.pvz[q] - vp[u][2], L.pgm[q], fmin(invi[u], L.pinv[q]), A, a1, j1);
-        }
-      }
+#pragma unroll 4
+      for (int q = 0; q < size; ++q)
+        hard_pair_other(q != k, L.px[q] - xp[u][0], L.py[q] - xp[u][1], L.pz[q] - xp[u][2], L.pvx[q] - vp[u][0],
+                        L.pvy[q] - vp[u][1], L.pvz[q] - vp[u][2], L.pgm[q], fmin(invi[u], L.pinv[q]), A, a1, j1);
       const double h = (double)(tn - t[u]) * A.tick;
       t[u] = tn;
       correct(x[u], v[u], a0[u], j0[u], xp[u], vp[u], a1, j1, h, t[u], lev[u], A);
@@ -1372,32 +1449,35 @@ __device__ __forceinline__ void big_body(const HermArgs &A, int c, int bk, const
     }
   }
   count_work(A, n_ev, size);
-  __syncthreads();
+  double E1 = 0.0;
+  if (energy) {
+    __syncthreads();
 #pragma unroll
-  for (int u = 0; u < MPT; ++u) {
-    const int k = tid + BIG_T * u;
-    L.px[k] = x[u][0];
-    L.py[k] = x[u][1];
-    L.pz[k] = x[u][2];
-    L.pvx[k] = v[u][0];
-    L.pvy[k] = v[u][1];
-    L.pvz[k] = v[u][2];
-  }
-  __syncthreads();
-  e = 0.0;
-#pragma unroll
-  for (int u = 0; u < MPT; ++u) {
-    const int k = tid + BIG_T * u;
-    if (!mem[u]) continue;
-    e += 0.5 * m[u] * (v[u][0] * v[u][0] + v[u][1] * v[u][1] + v[u][2] * v[u][2]) -
-         A.GM * m[u] * rsqrt(x[u][0] * x[u][0] + x[u][1] * x[u][1] + x[u][2] * x[u][2]);
-    for (int q = k + 1; q < size; ++q) {
-      const double dx = L.px[q] - x[u][0], dy = L.py[q] - x[u][1], dz = L.pz[q] - x[u][2];
-      const double r = sqrt(dx * dx + dy * dy + dz * dz);
-      e -= m[u] * L.pgm[q] * (1.0 - changeover_W(r * fmin(invi[u], L.pinv[q]), A)) / r;
+    for (int u = 0; u < MPT; ++u) {
+      const int k = tid + BIG_T * u;
+      L.px[k] = x[u][0];
+      L.py[k] = x[u][1];
+      L.pz[k] = x[u][2];
+      L.pvx[k] = v[u][0];
+      L.pvy[k] = v[u][1];
+      L.pvz[k] = v[u][2];
     }
+    __syncthreads();
+    e = 0.0;
+#pragma unroll
+    for (int u = 0; u < MPT; ++u) {
+      const int k = tid + BIG_T * u;
+      if (!mem[u]) continue;
+      e += 0.5 * m[u] * (v[u][0] * v[u][0] + v[u][1] * v[u][1] + v[u][2] * v[u][2]) -
+           A.GM * m[u] * rsqrt(x[u][0] * x[u][0] + x[u][1] * x[u][1] + x[u][2] * x[u][2]);
+      for (int q = k + 1; q < size; ++q) {
+        const double dx = L.px[q] - x[u][0], dy = L.py[q] - x[u][1], dz = L.pz[q] - x[u][2];
+        const double r = sqrt(dx * dx + dy * dy + dz * dz);
+        e -= m[u] * L.pgm[q] * (1.0 - changeover_W(r * fmin(invi[u], L.pinv[q]), A)) / r;
+      }
+    }
+    E1 = block_sum(e, shd);
   }
-  const double E1 = block_sum(e, shd);
 #pragma unroll
   for (int u = 0; u < MPT; ++u) {
     if (!mem[u]) continue;
@@ -1478,8 +1558,9 @@ __global__ __launch_bounds__(BIG_T) void k_herm_big(HermArgs A, int bk) {
   constexpr int NACT = MPT <= 2 ? BIG_ACT : 1;
   __shared__ int act[NACT];
   __shared__ double res[6 * NACT];
+  __shared__ unsigned long long shm[MPT * (BIG_T / WAVE)];  // due members
   const Lds L = {lds[0], lds[1], lds[2], lds[3], lds[4], lds[5], lds[6], lds[7], MPT <= 2 ? act : nullptr, res};
-  big_body<MPT, MODE>(A, A.blists[(int64_t)bk * A.nc + blockIdx.x], bk, L, shi, shd);
+  big_body<MPT, MODE>(A, A.blists[(int64_t)bk * A.nc + blockIdx.x], bk, L, shi, shd, shm);
 }
 
 // ---------------------------------------------------------------- bucketing
