@@ -14,12 +14,10 @@
 //   dX_c/dx_k = m_k / M_c,  dX_c/dm_k = (x_k - X_c) / M_c,  dM_c/dm_k = 1,
 // so the cell adjoints (dL/dX_c, dL/dM_c) are pushed down to every member.
 //
-// Kernels (one wavefront per group, i-particles in lanes as in the force):
-//   pass A: lane = i, loop over the tile's j / cells: the i-side terms -g_ij
-//     accumulate in registers and are written once per i;
-//   pass B: lane = tile entry j (or cell), loop over the group's i (staged in
-//     LDS): the j-side terms accumulate in registers and go to memory with one
-//     atomic add per (group, j) and component.
+// Every list entry is evaluated once: its term goes to both sides, into the
+// registers of the i-particle and, travelling round a row of lanes, into the
+// sums of the entry (k_adj_groups).  The i-side sums are written once per i,
+// the entry's with one atomic add per (group, entry) and component.
 // Then per node A_c = dL/dX_c / M_c, B_c = dL/dM_c - X_c . A_c, and per
 // particle the sums of A and B over its ancestors:
 //   dL/dx_k += m_k sum A,  dL/dm_k += sum B + x_k . sum A.
@@ -45,38 +43,42 @@ struct AdjArgs {
   DevCounters *cnt;
   const double *lam;  // cotangent in sorted order (3n)
   double *own;        // i-side terms, sorted order (3n), written once per particle
-  double *gx;         // j-side terms, sorted order (3n), atomic
-  double *gm;         // mass terms, sorted order (n), atomic
-  double *cx;         // cell adjoints dL/dX_c (3 n_nodes), atomic
-  double *cmass;      // cell adjoints dL/dM_c (n_nodes), atomic
+  double *g4;         // j-side terms and mass term, sorted order (n records of 4), atomic
+  double *c4;         // cell adjoints dL/dX_c, dL/dM_c (n_nodes records of 4), atomic
   int64_t n;
   int n_nodes;
   double G, gamma, inv1mg;
   unsigned long long *queue;
 };
 
-// g_ij and phi lambda . d for one entry; invR < 0 selects K = 1
-__device__ __forceinline__ void adj_term(double dx, double dy, double dz, double lx, double ly, double lz, double mj,
-                                         double invR, const AdjArgs &A, double &gx, double &gy, double &gz,
+// phi lambda + (phi'/r)(lambda . d) d (without the mass) and phi lambda . d
+// for one entry; lambda carries the factor g (1 where it holds G already).
+// `ok` false (the particle itself, a lane without a particle) gives zeros.
+template <bool NEAR>
+__device__ __forceinline__ void adj_term(double dx, double dy, double dz, double lx, double ly, double lz, double invR,
+                                         bool ok, double g, const AdjArgs &A, double &tx, double &ty, double &tz,
                                          double &s) {
+  if (NEAR) dx = ok ? dx : 1.0;
   const double r2 = dx * dx + dy * dy + dz * dz;
-  const double rinv = rsqrt(r2);
+  const double rinv = rsqrt_pos(r2);
   const double rinv2 = rinv * rinv;
-  double K = 1.0, Ky = 0.0;
-  if (invR >= 0.0) {
+  double phi = g * rinv * rinv2, dphi_r;  // phi, phi'(r) / r
+  if (NEAR) {
     const double y = r2 * rinv * invR;
     const double x = fmin(fmax((y - A.gamma) * A.inv1mg, 0.0), 1.0);
     const double x2 = x * x, omx = 1.0 - x;
-    K = x2 * x2 * (35.0 + x * (-84.0 + x * (70.0 - 20.0 * x)));
-    Ky = 140.0 * x2 * x * omx * omx * omx * A.inv1mg;
+    const double K = x2 * x2 * (35.0 + x * (-84.0 + x * (70.0 - 20.0 * x)));
+    const double Ky = 140.0 * x2 * x * omx * omx * omx * A.inv1mg;
+    dphi_r = ok ? phi * (Ky * invR - 3.0 * K * rinv) * rinv : 0.0;
+    phi = ok ? phi * K : 0.0;
+  } else {
+    dphi_r = -3.0 * phi * rinv2;
   }
-  const double phi = A.G * K * rinv * rinv2;
-  const double dphi_r = A.G * rinv2 * rinv2 * (Ky * invR - 3.0 * K * rinv);  // phi'(r) / r
   const double ld = lx * dx + ly * dy + lz * dz;
   const double c = dphi_r * ld;
-  gx = mj * (phi * lx + c * dx);
-  gy = mj * (phi * ly + c * dy);
-  gz = mj * (phi * lz + c * dz);
+  tx = phi * lx + c * dx;
+  ty = phi * ly + c * dy;
+  tz = phi * lz + c * dz;
   s = phi * ld;
 }
 
@@ -100,222 +102,233 @@ __device__ __forceinline__ void adj_term_f32(double dx, double dy, double dz, do
   s = (double)(phi * ld);
 }
 
-// one K = 1 term in the path's precision
-template <bool MIXED>
-__device__ __forceinline__ void adj_far(double dx, double dy, double dz, double lx, double ly, double lz, double mj,
-                                        const AdjArgs &A, double &gx, double &gy, double &gz, double &s) {
-  if (MIXED)
-    adj_term_f32(dx, dy, dz, lx, ly, lz, mj, (float)A.G, gx, gy, gz, s);
-  else
-    adj_term(dx, dy, dz, lx, ly, lz, mj, -1.0, A, gx, gy, gz, s);
-}
-
 __global__ void k_adj_prep(AdjArgs A, const double *__restrict__ lam_v3) {
   const int64_t n = A.n;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *A.queue = 0ull;
   double *lam = const_cast<double *>(A.lam);
   for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
     const int64_t o = A.sid[k];
     lam[k] = lam_v3[o];
     lam[n + k] = lam_v3[n + o];
     lam[2 * n + k] = lam_v3[2 * n + o];
-    A.gx[k] = A.gx[n + k] = A.gx[2 * n + k] = 0.0;
-    A.gm[k] = 0.0;
+    double2 *g = (double2 *)(A.g4 + 4 * k);
+    g[0] = g[1] = make_double2(0.0, 0.0);
   }
   for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < A.n_nodes;
        c += (int64_t)gridDim.x * blockDim.x) {
-    A.cx[c] = A.cx[A.n_nodes + c] = A.cx[2 * (int64_t)A.n_nodes + c] = 0.0;
-    A.cmass[c] = 0.0;
+    double2 *g = (double2 *)(A.c4 + 4 * c);
+    g[0] = g[1] = make_double2(0.0, 0.0);
   }
 }
 
+constexpr int ADJ_W = 4;       // wavefronts per group
+constexpr int ADJ_BLOCKS = 3;  // workgroups per CU
+enum { ADJ_NEAR, ADJ_FAR, ADJ_CELL };
+
+struct AdjTile {  // one wavefront's tile of particles or cells
+  double2 xy[WAVE], zm[WAVE];
+  double inv[WAVE];
+  int id[WAVE];
+};
 struct AdjLds {
-  // the group's i-particles (pass B)
-  double ix[2 * WAVE], iy[2 * WAVE], iz[2 * WAVE], ilx[2 * WAVE], ily[2 * WAVE], ilz[2 * WAVE], iinv[2 * WAVE];
-  int iid[2 * WAVE];
-  // one tile of j-particles or cells
-  double jx[WAVE], jy[WAVE], jz[WAVE], jm[WAVE], jinv[WAVE];
-  int jid[WAVE];
+  AdjTile tile[ADJ_W];
+  double own[3][ADJ_W][WAVE];
+  int gi;
 };
 
-// one tile of particles (near: K from the pair cut-off; far: K = 1)
-template <int IPL, bool MIXED>
-__device__ __forceinline__ void adj_tile(const AdjArgs &A, AdjLds &S, const int32_t *L, int t0, int nt, bool near,
-                                         int gcount, int lane, const int *ii, const double *xi, const double *yi,
-                                         const double *zi, const double *lxi, const double *lyi, const double *lzi,
-                                         const double *invi, double *ox, double *oy, double *oz) {
-  __syncthreads();
-  if (lane < nt) {
-    const int j = L[t0 + lane];
-    S.jx[lane] = A.sx[j];
-    S.jy[lane] = A.sy[j];
-    S.jz[lane] = A.sz[j];
-    S.jm[lane] = A.sm[j];
-    S.jinv[lane] = A.sinv[j];
-    S.jid[lane] = j;
-  }
-  __syncthreads();
-  // pass A: i in lanes
-  for (int jj = 0; jj < nt; ++jj) {
-    const double x = S.jx[jj], y = S.jy[jj], z = S.jz[jj], m = S.jm[jj], inv = S.jinv[jj];
-    const int jid = S.jid[jj];
-#pragma unroll
-    for (int s = 0; s < IPL; ++s) {
-      const bool ok = ii[s] >= 0 && ii[s] != jid;
-      const double dx = ok ? x - xi[s] : 1.0, dy = ok ? y - yi[s] : 0.0, dz = ok ? z - zi[s] : 0.0;
-      double gx, gy, gz, sc;
-      if (near)
-        adj_term(dx, dy, dz, lxi[s], lyi[s], lzi[s], m, fmin(invi[s], inv), A, gx, gy, gz, sc);
-      else
-        adj_far<MIXED>(dx, dy, dz, lxi[s], lyi[s], lzi[s], m, A, gx, gy, gz, sc);
-      if (ok) {
-        ox[s] -= gx;
-        oy[s] -= gy;
-        oz[s] -= gz;
-      }
-    }
-  }
-  // pass B: j in lanes, loop over the group's i
-  if (lane < nt) {
-    const double x = S.jx[lane], y = S.jy[lane], z = S.jz[lane], m = S.jm[lane], inv = S.jinv[lane];
-    const int jid = S.jid[lane];
-    double ax = 0.0, ay = 0.0, az = 0.0, am = 0.0;
-    for (int q = 0; q < gcount; ++q) {
-      if (S.iid[q] == jid) continue;
-      double gx, gy, gz, sc;
-      if (near)
-        adj_term(x - S.ix[q], y - S.iy[q], z - S.iz[q], S.ilx[q], S.ily[q], S.ilz[q], m, fmin(S.iinv[q], inv), A, gx,
-                 gy, gz, sc);
-      else
-        adj_far<MIXED>(x - S.ix[q], y - S.iy[q], z - S.iz[q], S.ilx[q], S.ily[q], S.ilz[q], m, A, gx, gy, gz, sc);
-      ax += gx;
-      ay += gy;
-      az += gz;
-      am += sc;
-    }
-    unsafeAtomicAdd(&A.gx[jid], ax);
-    unsafeAtomicAdd(&A.gx[A.n + jid], ay);
-    unsafeAtomicAdd(&A.gx[2 * A.n + jid], az);
-    unsafeAtomicAdd(&A.gm[jid], am);
-  }
+// LDS ordering inside one wavefront (its LDS operations execute in order)
+__device__ __forceinline__ void adj_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int IPL, bool MIXED>
-__device__ __forceinline__ void adj_group(const AdjArgs &A, AdjLds &S, int gi, int lane) {
-  const int q = uniform_first(A.order ? A.order[gi] : gi);
-  const GroupList Lh = A.gl[q];
-  const long long off = uniform_first64(Lh.off);
-  const int n_cell = uniform_first(Lh.n_cell), n_near = uniform_first(Lh.n_near), n_far = uniform_first(Lh.n_far);
-  const int node = uniform_first(Lh.node);
-  const int first = uniform_first(A.wn[node].first), gcount = uniform_first(A.wn[node].count);
-  const int64_t n = A.n;
-  int ii[IPL];
-  double xi[IPL], yi[IPL], zi[IPL], lxi[IPL], lyi[IPL], lzi[IPL], invi[IPL], ox[IPL], oy[IPL], oz[IPL];
-  __syncthreads();
-#pragma unroll
-  for (int s = 0; s < IPL; ++s) {
-    const int k = lane + WAVE * s;
-    ii[s] = k < gcount ? first + k : -1;
-    const int i = ii[s] >= 0 ? ii[s] : first;
-    xi[s] = A.sx[i];
-    yi[s] = A.sy[i];
-    zi[s] = A.sz[i];
-    lxi[s] = A.lam[i];
-    lyi[s] = A.lam[n + i];
-    lzi[s] = A.lam[2 * n + i];
-    invi[s] = A.sinv[i];
-    ox[s] = oy[s] = oz[s] = 0.0;
-    if (k < gcount) {
-      S.ix[k] = xi[s];
-      S.iy[k] = yi[s];
-      S.iz[k] = zi[s];
-      S.ilx[k] = lxi[s];
-      S.ily[k] = lyi[s];
-      S.ilz[k] = lzi[s];
-      S.iinv[k] = invi[s];
-      S.iid[k] = ii[s];
+// the value of the next lower lane of the row of 16 (row_ror:1)
+__device__ __forceinline__ double row_ror1(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x121, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x121, 0xF, 0xF, true);
+  return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+// a summed over rows 0, 1 (and 2, 3) in rows 0 (and 2), b's in rows 1 (and 3)
+__device__ __forceinline__ double row_pair_add(double a, double b) {
+  const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+  return __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])) +
+         __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
+}
+
+// the group's particles of one lane: number 32 s + (lane & 31) for slot s
+template <int IPL>
+struct AdjI {
+  int id[IPL];  // -1: none
+  double x[IPL], y[IPL], z[IPL], lx[IPL], ly[IPL], lz[IPL], inv[IPL], ox[IPL], oy[IPL], oz[IPL];
+};
+
+// One tile of up to 64 entries (list places t0 .. t0 + nt), 32 at a time: rows
+// 0 and 1 hold the group's particles and take the first 16 entries, rows 2 and
+// 3 hold the same particles and take the others.  In step s a lane meets entry
+// (lane - s) mod 16 of its half; the entry's sums move on one lane per step and
+// are home after 16.  The places behind nt repeat the first entry with no mass.
+template <int IPL, int KIND, bool MIXED>
+__device__ __forceinline__ void adj_tile(const AdjArgs &A, AdjTile &S, const int32_t *L, int nt, int lane,
+                                         AdjI<IPL> &I) {
+  constexpr bool F32 = MIXED && KIND != ADJ_NEAR;
+  const double g = MIXED ? A.G : 1.0;  // (FP64 throughout: lambda holds G)
+  {
+    const bool in = lane < nt;
+    const int j = L[in ? lane : 0];
+    double x, y, z, m;
+    if (KIND == ADJ_CELL) {
+      const CellMom &cm = A.cm[j];
+      x = cm.com[0];
+      y = cm.com[1];
+      z = cm.com[2];
+      m = cm.mass;
+    } else {
+      x = A.sx[j];
+      y = A.sy[j];
+      z = A.sz[j];
+      m = A.sm[j];
     }
+    adj_wave_sync();  // the last tile is read
+    S.xy[lane] = make_double2(x, y);
+    S.zm[lane] = make_double2(z, in ? m : 0.0);
+    if (KIND == ADJ_NEAR) S.inv[lane] = A.sinv[j];
+    S.id[lane] = j;
+    adj_wave_sync();
   }
-  const int32_t *Ln = A.pool + off + n_cell;
-  for (int t0 = 0; t0 < n_near; t0 += WAVE)
-    adj_tile<IPL, MIXED>(A, S, Ln, t0, min(WAVE, n_near - t0), true, gcount, lane, ii, xi, yi, zi, lxi, lyi, lzi, invi, ox,
-                  oy, oz);
-  const int32_t *Lf = Ln + n_near;
-  for (int t0 = 0; t0 < n_far; t0 += WAVE)
-    adj_tile<IPL, MIXED>(A, S, Lf, t0, min(WAVE, n_far - t0), false, gcount, lane, ii, xi, yi, zi, lxi, lyi, lzi, invi, ox,
-                  oy, oz);
-  // monopole cells
-  const int32_t *Lc = A.pool + off;
-  for (int t0 = 0; t0 < n_cell; t0 += WAVE) {
-    const int nt = min(WAVE, n_cell - t0);
-    __syncthreads();
-    if (lane < nt) {
-      const int c = Lc[t0 + lane];
-      const CellMom cm = A.cm[c];
-      S.jx[lane] = cm.com[0];
-      S.jy[lane] = cm.com[1];
-      S.jz[lane] = cm.com[2];
-      S.jm[lane] = cm.mass;
-      S.jid[lane] = c;
-    }
-    __syncthreads();
-    for (int jj = 0; jj < nt; ++jj) {
-      const double x = S.jx[jj], y = S.jy[jj], z = S.jz[jj], m = S.jm[jj];
+  const int row = lane >> 4, base = (lane >> 5) << 4;
+  for (int u = 0; u < nt; u += 32) {
+    double ax = 0.0, ay = 0.0, az = 0.0, am = 0.0;
+#pragma unroll 1
+    for (int s = 0; s < 16; ++s) {
+      const int e = u + base + ((lane - s) & 15);
+      const double2 xy = S.xy[e], zm = S.zm[e];
+      const double inv = KIND == ADJ_NEAR ? S.inv[e] : 0.0;
+      const int jid = KIND == ADJ_NEAR ? S.id[e] : 0;
 #pragma unroll
-      for (int s = 0; s < IPL; ++s) {
-        double gx, gy, gz, sc;
-        adj_far<MIXED>(x - xi[s], y - yi[s], z - zi[s], lxi[s], lyi[s], lzi[s], m, A, gx, gy, gz, sc);
-        if (ii[s] >= 0) {
-          ox[s] -= gx;
-          oy[s] -= gy;
-          oz[s] -= gz;
+      for (int q = 0; q < IPL; ++q) {
+        const double dx = xy.x - I.x[q], dy = xy.y - I.y[q], dz = zm.x - I.z[q];
+        double tx, ty, tz, sc;
+        if constexpr (F32) {  // (tx, ty, tz hold the mass)
+          adj_term_f32(dx, dy, dz, I.lx[q], I.ly[q], I.lz[q], zm.y, (float)A.G, tx, ty, tz, sc);
+          I.ox[q] -= tx;
+          I.oy[q] -= ty;
+          I.oz[q] -= tz;
+        } else {
+          const bool ok = KIND != ADJ_NEAR || (I.id[q] >= 0 && I.id[q] != jid);
+          adj_term<KIND == ADJ_NEAR>(dx, dy, dz, I.lx[q], I.ly[q], I.lz[q],
+                                     KIND == ADJ_NEAR ? fmin(I.inv[q], inv) : 0.0, ok, g, A, tx, ty, tz, sc);
+          I.ox[q] -= zm.y * tx;
+          I.oy[q] -= zm.y * ty;
+          I.oz[q] -= zm.y * tz;
         }
-      }
-    }
-    if (lane < nt) {
-      const double x = S.jx[lane], y = S.jy[lane], z = S.jz[lane], m = S.jm[lane];
-      const int c = S.jid[lane];
-      double ax = 0.0, ay = 0.0, az = 0.0, am = 0.0;
-      for (int q2 = 0; q2 < gcount; ++q2) {
-        double gx, gy, gz, sc;
-        adj_far<MIXED>(x - S.ix[q2], y - S.iy[q2], z - S.iz[q2], S.ilx[q2], S.ily[q2], S.ilz[q2], m, A, gx, gy, gz,
-                       sc);
-        ax += gx;
-        ay += gy;
-        az += gz;
+        ax += tx;
+        ay += ty;
+        az += tz;
         am += sc;
       }
-      const int64_t nn = A.n_nodes;
-      unsafeAtomicAdd(&A.cx[c], ax);
-      unsafeAtomicAdd(&A.cx[nn + c], ay);
-      unsafeAtomicAdd(&A.cx[2 * nn + c], az);
-      unsafeAtomicAdd(&A.cmass[c], am);
+      ax = row_ror1(ax);
+      ay = row_ror1(ay);
+      az = row_ror1(az);
+      am = row_ror1(am);
     }
-  }
-#pragma unroll
-  for (int s = 0; s < IPL; ++s) {
-    if (ii[s] >= 0) {
-      A.own[ii[s]] = ox[s];
-      A.own[n + ii[s]] = oy[s];
-      A.own[2 * n + ii[s]] = oz[s];
+    const int e = u + base + (lane & 15);
+    const double m = F32 ? 1.0 : S.zm[e].y;
+    // rows 0 and 2 add x and z of their entries, rows 1 and 3 y and the mass term
+    const double v0 = row_pair_add(ax, ay), v1 = row_pair_add(az, am);
+    if (e < nt) {
+      double *o = (KIND == ADJ_CELL ? A.c4 : A.g4) + 4 * (int64_t)S.id[e] + (row & 1);
+      unsafeAtomicAdd(o, m * v0);
+      unsafeAtomicAdd(o + 2, (row & 1) ? v1 : m * v1);
     }
   }
 }
 
+template <int IPL, bool MIXED>
+__device__ __forceinline__ void adj_group(const AdjArgs &A, AdjLds &S, const GroupList &Lh, int first, int gcount,
+                                          int lane, int w) {
+  const long long off = uniform_first64(Lh.off);
+  const int n_cell = uniform_first(Lh.n_cell), n_near = uniform_first(Lh.n_near), n_far = uniform_first(Lh.n_far);
+  const int64_t n = A.n;
+  AdjI<IPL> I;
+#pragma unroll
+  for (int s = 0; s < IPL; ++s) {
+    const int k = (lane & 31) + 32 * s;
+    const bool in = k < gcount;
+    const int i = in ? first + k : first;
+    const double f = !in ? 0.0 : MIXED ? 1.0 : A.G;
+    I.id[s] = in ? i : -1;
+    I.x[s] = A.sx[i];
+    I.y[s] = A.sy[i];
+    I.z[s] = A.sz[i];
+    I.lx[s] = f * A.lam[i];
+    I.ly[s] = f * A.lam[n + i];
+    I.lz[s] = f * A.lam[2 * n + i];
+    I.inv[s] = A.sinv[i];
+    I.ox[s] = I.oy[s] = I.oz[s] = 0.0;
+  }
+  // the tiles of the three lists in turn over the wavefronts
+  const int32_t *Lc = A.pool + off, *Ln = Lc + n_cell, *Lf = Ln + n_near;
+  const int tn = (n_near + WAVE - 1) / WAVE, tf = (n_far + WAVE - 1) / WAVE, tc = (n_cell + WAVE - 1) / WAVE;
+  int t = w;
+  for (; t < tn; t += ADJ_W)
+    adj_tile<IPL, ADJ_NEAR, MIXED>(A, S.tile[w], Ln + t * WAVE, min(WAVE, n_near - t * WAVE), lane, I);
+  for (t -= tn; t < tf; t += ADJ_W)
+    adj_tile<IPL, ADJ_FAR, MIXED>(A, S.tile[w], Lf + t * WAVE, min(WAVE, n_far - t * WAVE), lane, I);
+  for (t -= tf; t < tc; t += ADJ_W)
+    adj_tile<IPL, ADJ_CELL, MIXED>(A, S.tile[w], Lc + t * WAVE, min(WAVE, n_cell - t * WAVE), lane, I);
+  // the particles' sums: two copies in each of the wavefronts
+#pragma unroll
+  for (int s = 0; s < IPL; ++s) {
+    S.own[0][w][lane] = I.ox[s];
+    S.own[1][w][lane] = I.oy[s];
+    S.own[2][w][lane] = I.oz[s];
+    __syncthreads();
+    const int d = threadIdx.x >> 5, k = (threadIdx.x & 31) + 32 * s;
+    if (d < 3 && k < gcount) {
+      double v = 0.0;
+#pragma unroll
+      for (int q = 0; q < ADJ_W; ++q) v += S.own[d][q][threadIdx.x & 31] + S.own[d][q][(threadIdx.x & 31) + 32];
+      A.own[d * n + first + k] = v;
+    }
+    __syncthreads();
+  }
+}
+
+// One workgroup of four wavefronts per group, from a queue in the order of the
+// work.  Bound by FP64 arithmetic: about 40 operations per pair (60 with the
+// changeover).  Meeting each entry once with the sums passed along the row
+// costs 8 lane moves per step for up to four pairs, where a second loop with
+// the entries in lanes evaluated every pair again; rows of 16 leave less of a
+// group's 65 to 128 places empty than lanes of 64 do.  262,144 particles,
+// monopole cells: 1041 -> 422 us.
 template <bool MIXED>
-__global__ __launch_bounds__(WAVE) void k_adj_groups(AdjArgs A) {
+__global__ __launch_bounds__(ADJ_W *WAVE) void k_adj_groups(AdjArgs A) {
   __shared__ AdjLds S;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & (WAVE - 1), w = uniform_first((int)threadIdx.x / WAVE);
   const int ngroups = uniform_first((int)A.cnt->n_groups);
   for (;;) {
-    const int gi = (int)wave_fetch_add(A.queue, 1ull);
+    if (threadIdx.x == 0) S.gi = (int)atomicAdd(A.queue, 1ull);
+    __syncthreads();
+    const int gi = uniform_first(S.gi);
+    __syncthreads();
     if (gi >= ngroups) break;
     const int q = uniform_first(A.order ? A.order[gi] : gi);
-    if (uniform_first64(A.gl[q].off) < 0) continue;
-    const int cnt = uniform_first(A.wn[uniform_first(A.gl[q].node)].count);
-    if (cnt > WAVE)
-      adj_group<2, MIXED>(A, S, gi, lane);
+    const GroupList Lh = A.gl[q];
+    if (uniform_first64(Lh.off) < 0) continue;
+    const int node = uniform_first(Lh.node);
+    const int first = uniform_first(A.wn[node].first), cnt = uniform_first(A.wn[node].count);
+    if (cnt <= 32)
+      adj_group<1, MIXED>(A, S, Lh, first, cnt, lane, w);
+    else if (cnt <= 64)
+      adj_group<2, MIXED>(A, S, Lh, first, cnt, lane, w);
+    else if (cnt <= 96)
+      adj_group<3, MIXED>(A, S, Lh, first, cnt, lane, w);
     else
-      adj_group<1, MIXED>(A, S, gi, lane);
+      adj_group<4, MIXED>(A, S, Lh, first, cnt, lane, w);
   }
 }
 
@@ -323,38 +336,41 @@ __global__ __launch_bounds__(WAVE) void k_adj_groups(AdjArgs A) {
 __global__ void k_adj_cell_coeffs(AdjArgs A) {
   const int64_t nn = A.n_nodes;
   for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < nn; c += (int64_t)gridDim.x * blockDim.x) {
-    const double ax = A.cx[c], ay = A.cx[nn + c], az = A.cx[2 * nn + c];
-    if (ax == 0.0 && ay == 0.0 && az == 0.0 && A.cmass[c] == 0.0) continue;  // cell never used
+    double2 *r = (double2 *)(A.c4 + 4 * c);
+    const double2 xy = r[0], zm = r[1];
+    if (xy.x == 0.0 && xy.y == 0.0 && zm.x == 0.0 && zm.y == 0.0) continue;  // cell never used
     const double M = A.cm[c].mass;  // (the records of nodes no walk reaches are not written)
     const double iM = 1.0 / M;
-    const double px = ax * iM, py = ay * iM, pz = az * iM;
-    A.cx[c] = px;
-    A.cx[nn + c] = py;
-    A.cx[2 * nn + c] = pz;
-    A.cmass[c] -= A.cm[c].com[0] * px + A.cm[c].com[1] * py + A.cm[c].com[2] * pz;
+    const double px = xy.x * iM, py = xy.y * iM, pz = zm.x * iM;
+    r[0] = make_double2(px, py);
+    r[1] = make_double2(pz, zm.y - (A.cm[c].com[0] * px + A.cm[c].com[1] * py + A.cm[c].com[2] * pz));
   }
 }
 
 // per particle: the ancestors' push-down, the three parts summed, scaled by h,
 // written in the caller's order
 __global__ void k_adj_final(AdjArgs A, double h, double *__restrict__ g_pos3, double *__restrict__ g_mass) {
-  const int64_t n = A.n, nn = A.n_nodes;
+  const int64_t n = A.n;
   const int leaf0 = (int)n - 1;
   for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
     double sx = 0.0, sy = 0.0, sz = 0.0, sb = 0.0;
     int node = n > 1 ? A.parent[leaf0 + k] : -1;
     while (node >= 0) {
-      sx += A.cx[node];
-      sy += A.cx[nn + node];
-      sz += A.cx[2 * nn + node];
-      sb += A.cmass[node];
+      const double2 *r = (const double2 *)(A.c4 + 4 * (int64_t)node);
+      const double2 xy = r[0], zm = r[1];
       node = A.parent[node];
+      sx += xy.x;
+      sy += xy.y;
+      sz += zm.x;
+      sb += zm.y;
     }
     const double m = A.sm[k];
-    const double gx = A.own[k] + A.gx[k] + m * sx;
-    const double gy = A.own[n + k] + A.gx[n + k] + m * sy;
-    const double gz = A.own[2 * n + k] + A.gx[2 * n + k] + m * sz;
-    const double gm = A.gm[k] + sb + A.sx[k] * sx + A.sy[k] * sy + A.sz[k] * sz;
+    const double2 *g4 = (const double2 *)(A.g4 + 4 * k);
+    const double2 xy = g4[0], zm = g4[1];
+    const double gx = A.own[k] + xy.x + m * sx;
+    const double gy = A.own[n + k] + xy.y + m * sy;
+    const double gz = A.own[2 * n + k] + zm.x + m * sz;
+    const double gm = zm.y + sb + A.sx[k] * sx + A.sy[k] * sy + A.sz[k] * sz;
     const int64_t o = A.sid[k];
     g_pos3[o] = h * gx;
     g_pos3[n + o] = h * gy;
@@ -362,8 +378,6 @@ __global__ void k_adj_final(AdjArgs A, double h, double *__restrict__ g_pos3, do
     g_mass[o] = h * gm;
   }
 }
-
-__global__ void k_adj_reset(unsigned long long *q) { *q = 0ull; }
 
 }  // namespace
 
@@ -386,11 +400,9 @@ hipError_t soft_kick_adjoint(p3t_ctx *c, double h, const double *lam_v3, double 
   A.cnt = c->cnt;
   A.lam = c->adj_buf;
   A.own = c->adj_buf + 3 * n;
-  A.gx = c->adj_buf + 6 * n;
-  A.gm = c->adj_buf + 9 * n;
+  A.g4 = c->adj_buf + 6 * n;  // (records of 4 aligned to 16 bytes: 48 n and 80 n bytes in)
   A.n_nodes = (int)(n > 0 ? 2 * n - 1 : 0);
-  A.cx = c->adj_buf + 10 * n;
-  A.cmass = A.cx + 3 * (int64_t)A.n_nodes;
+  A.c4 = c->adj_buf + 10 * n;
   A.n = n;
   A.G = c->P.G;
   A.gamma = c->P.gamma;
@@ -398,11 +410,10 @@ hipError_t soft_kick_adjoint(p3t_ctx *c, double h, const double *lam_v3, double 
   A.queue = &c->cnt->queue[0];
   const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)c->n_cu * 8, (2 * n + 255) / 256));
   hipLaunchKernelGGL(k_adj_prep, dim3(g), dim3(256), 0, s, A, lam_v3);
-  hipLaunchKernelGGL(k_adj_reset, dim3(1), dim3(1), 0, s, A.queue);
   if (c->P.precision == 1)
-    hipLaunchKernelGGL(k_adj_groups<true>, dim3(c->n_cu * 8), dim3(WAVE), 0, s, A);
+    hipLaunchKernelGGL(k_adj_groups<true>, dim3(c->n_cu * ADJ_BLOCKS), dim3(ADJ_W * WAVE), 0, s, A);
   else
-    hipLaunchKernelGGL(k_adj_groups<false>, dim3(c->n_cu * 8), dim3(WAVE), 0, s, A);
+    hipLaunchKernelGGL(k_adj_groups<false>, dim3(c->n_cu * ADJ_BLOCKS), dim3(ADJ_W * WAVE), 0, s, A);
   hipLaunchKernelGGL(k_adj_cell_coeffs, dim3(g), dim3(256), 0, s, A);
   hipLaunchKernelGGL(k_adj_final, dim3(g), dim3(256), 0, s, A, h, g_pos3, g_mass);
   return hipGetLastError();
