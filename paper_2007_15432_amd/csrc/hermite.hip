@@ -13,9 +13,11 @@
 // Clusters are bucketed by size; the buckets up to 64 members run in ONE
 // launch, so the long-running clusters of different sizes overlap instead
 // of queueing:
-//   sizes <= 4: SEG = next power of two lanes per cluster, 64/SEG clusters
-//     per wavefront, one member per lane (seg_body);
-//   sizes 5..64: one wavefront per cluster, one member per lane, the due
+//   sizes <= 4: SEG = next power of two member slots per cluster, several
+//     clusters per wavefront (seg_body);
+//   sizes 5..8: one wavefront per cluster, eight lanes per member, one
+//     partner in each (seg_body<., 3>);
+//   sizes 9..64: one wavefront per cluster, one member per lane, the due
 //     members' partner sums spread over the wavefront (wave_body);
 //   each wavefront runs its own block steps and synchronises only with
 //   itself (LDS is private per wave);
@@ -24,6 +26,7 @@
 //   larger: the percolated-cluster path (device-wide, below).
 // Predicted states are shared through LDS.
 #include <algorithm>
+#include <cfloat>
 #include <climits>
 #include <vector>
 
@@ -43,7 +46,7 @@ constexpr int BIG_T = 256;
 constexpr int N_BUCKETS = HERM_N_BUCKETS;  // SEG 1..64 (7), 256-thread MPT 1, 2, 4 (3), too big (1)
 constexpr int BC_NC = HERM_BC_NC, BC_BAD = HERM_BC_BAD, BC_WORDS = HERM_BC_WORDS;
 constexpr int PK_MEM = HERM_BC_PARKED - HERM_BC_PARK0;  // parked-member word, relative to the park counts
-constexpr int WAVE_BK0 = 3;  // buckets 3..6 (5..64 members): one wavefront per cluster (wave_body)
+constexpr int WAVE_BK0 = 4;  // buckets 4..6 (9..64 members): one member per lane (wave_body)
 // Regions of the fused launch: buckets 0..6, then the clusters of buckets
 // 1..3 that hold a close pair (regions 7..9); dispatched from the last
 // region to the first.
@@ -187,17 +190,15 @@ __device__ __forceinline__ double root_level(double x) { return x > 0.0 ? x * rs
 // Smallest k >= 0 with P 4^-k <= L (k_max + 1 if none), P = dt_soft^2 den,
 // L = eta num >= 0: the level whose squared step does not exceed the
 // squared Aarseth step.  P = 0 (den = 0) gives level 0, as a step of dt_soft.
-// Closed form, without a search loop: for P > L > 0 let e = ilogb(P) -
-// ilogb(L) >= 0; P 4^-k <= L holds for 2k >= e + 1 and fails for 2k <= e - 1,
-// and at 2k = e one exact comparison of the scaled P decides.
+// Closed form, without a search loop: for P > L > 0 let e be the difference
+// of their exponents, e >= 0; P 4^-k <= L holds for 2k >= e + 1 and fails for
+// 2k <= e - 1, and at 2k = e one exact comparison of the scaled P decides.
+// The other cases (and an infinite P, whose exponent field says nothing) are
+// chosen at the end, away from the chain through e.
 __device__ __forceinline__ int level_for_sq(double P, double L, int kmax) {
-  const bool ok = P > L && L > 0.0;
-  // ilogb(inf) is INT_MAX: bounded first; then e >= 2 k_max + 2 already
-  // gives k_max + 1
-  int eP = ilogb(ok ? P : 2.0);
-  eP = eP < 1100 ? eP : 1100;
-  int e = eP - ilogb(ok ? L : 1.0);
-  e = e < 2 * kmax + 2 ? e : 2 * kmax + 2;
+  const int eP = P > DBL_MAX ? 1101 : __builtin_amdgcn_frexp_exp(P);
+  int e = eP - __builtin_amdgcn_frexp_exp(L);
+  e = e < 2 * kmax + 2 ? e : 2 * kmax + 2;  // already gives k_max + 1
   int k = (e + 1) >> 1;
   k += ((e & 1) == 0 && ldexp(P, -e) > L) ? 1 : 0;
   k = k > kmax ? kmax + 1 : k;
@@ -205,11 +206,26 @@ __device__ __forceinline__ int level_for_sq(double P, double L, int kmax) {
   return (P > L) ? k : 0;
 }
 
+// Block times: ticks of dt_soft 2^-40 as whole numbers, or as doubles (exact
+// up to 2^53) where the time sits on the step's dependency chain and fewer
+// instructions lead from the level to the next time.
+__device__ __forceinline__ bool on_doubled_step(int64_t t, int lev) {
+  return (t & (((int64_t)1 << (TICK_BITS - lev + 1)) - 1)) == 0;
+}
+__device__ __forceinline__ double step_ticks(int lev) {  // 2^(TICK_BITS - lev)
+  return __hiloint2double((1023 + TICK_BITS - lev) << 20, 0);
+}
+__device__ __forceinline__ bool on_doubled_step(double t, int lev) {
+  const double q = t * __hiloint2double((1023 - TICK_BITS - 1 + lev) << 20, 0);
+  return q == floor(q);
+}
+
 // corrector + new level for one active member; its step is h = dt_soft 2^-lev
 // (h, 1/h^2, 1/h^3, h^3/6, ... are the level-0 powers scaled by exact
 // powers of two, so no division sits on the step's dependency chain)
+template <typename Time>
 __device__ __forceinline__ void correct(double *x, double *v, double *a0, double *j0, const double *xp, const double *vp,
-                                        const double *a1, const double *j1, double h, int64_t tnew, int &lev,
+                                        const double *a1, const double *j1, double h, Time tnew, int &lev,
                                         const HermArgs &A) {
   double a2[3], a3[3];
   const int l = lev, l2 = l + l, l3 = l2 + l, l4 = l2 + l2, l5 = l4 + l;  // shifts and adds, no multiply
@@ -236,8 +252,7 @@ __device__ __forceinline__ void correct(double *x, double *v, double *a0, double
   const int knew = level_for_sq(A.dt_soft2 * den, num, A.k_max);
   // grow by at most a factor two, and only on a multiple of the doubled
   // step (lev <= k_max <= 40, so the shift stays below 64)
-  const int64_t dbl_mask = ((int64_t)1 << (TICK_BITS - lev + 1)) - 1;
-  const bool grow = lev > 0 && (tnew & dbl_mask) == 0;
+  const bool grow = lev > 0 && on_doubled_step(tnew, lev);
   int k = knew < lev ? (grow ? lev - 1 : lev) : knew;
   if (k > A.k_max) {
     set_flag(A.cnt, P3T_FLAG_KMAX);
@@ -272,6 +287,7 @@ __device__ __forceinline__ int64_t dpp_i64(int64_t v) {
   return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+constexpr int DPP_ROR8 = 0x128, DPP_ROR4 = 0x124;  // rotations of a row by 8 and 4 lanes
 
 // minimum over aligned segments of 2^sl2 lanes (sl2 wave-uniform); every
 // lane of the wave must be active
@@ -284,6 +300,34 @@ __device__ __forceinline__ int64_t seg_min(int64_t v, int sl2) {
   if (sl2 >= 5) { t = __shfl_xor(v, 16, WAVE); v = t < v ? t : v; }
   if (sl2 >= 6) { t = __shfl_xor(v, 32, WAVE); v = t < v ? t : v; }
   return v;
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_time(double v) {
+  return __longlong_as_double((long long)dpp_i64<CTRL>((int64_t)__double_as_longlong(v)));
+}
+__device__ __forceinline__ double seg_min(double v, int sl2) {
+  if (sl2 >= 1) v = fmin(v, dpp_time<DPP_XOR1>(v));
+  if (sl2 >= 2) v = fmin(v, dpp_time<DPP_XOR2>(v));
+  if (sl2 >= 3) v = fmin(v, dpp_time<DPP_HALF_MIRROR>(v));
+  if (sl2 >= 4) v = fmin(v, dpp_time<DPP_MIRROR>(v));
+  if (sl2 >= 5) v = fmin(v, __shfl_xor(v, 16, WAVE));
+  if (sl2 >= 6) v = fmin(v, __shfl_xor(v, 32, WAVE));
+  return v;
+}
+// minimum over the wavefront of a time that the lanes of each aligned eight
+// share: the row's other half, then the other rows by swaps, no LDS
+__device__ __forceinline__ double wave_min_of_eights(double v) {
+  v = fmin(v, dpp_time<DPP_ROR8>(v));
+  uint64_t u = (uint64_t)__double_as_longlong(v);
+  auto lo = __builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)u, false, false);
+  auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+  v = fmin(__longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])),
+           __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1])));
+  u = (uint64_t)__double_as_longlong(v);
+  lo = __builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)u, false, false);
+  hi = __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+  return fmin(__longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])),
+              __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1])));
 }
 // sum over aligned segments of 2^sl2 lanes
 __device__ __forceinline__ double seg_sum(double v, int sl2) {
@@ -360,6 +404,14 @@ __device__ __forceinline__ double lpm_sum(double v, int ll2) {
 // every LPM-th partner and the partial sums are added across them.
 // MODE 0: plain; 1: park clusters still running after A.budget steps;
 // 2: resume parked clusters
+// SL2 = 1 and 3 (two members; five to eight) are the sizes of the longest
+// chains and have code of their own.  Their block steps are bound by the
+// latency of one wavefront's chain of about 300 instructions, two thirds
+// FP64: times as exact doubles, minima and sums by lane moves, every due
+// member's sum formed in the lanes that hold it, no branch around the pair
+// term.  Five and six members took 1.47 us per block step in wave_body and
+// take 0.93 us here (same sums in the same order), and a 1M-particle soft
+// step with a chain of 3,200 such steps 3.95 -> 3.08 ms.
 template <int MODE, int SL2 = -1>
 __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist, int count, int ci0, const Lds &L,
                                          int wbase, int sl2_rt) {
@@ -376,6 +428,9 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
   const int size = c >= 0 ? A.cl_ptr[c + 1] - b : 0;
   const bool mem = sl < size;
   const bool lead = mem && sub == 0;  // the copy that reads and writes memory
+  // 5 to 8 members: every lane has one partner, and the empty slots hold
+  // finite values too, so that the pair term needs no branch
+  const bool put = SL2 == 3 ? sub == 0 : lead;
   const int gid = mem ? A.members[b + sl] : 0;
   const int64_t n = A.n;
   const int me = sb + sl;
@@ -394,7 +449,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
   }
   const double invi = 1.0 / ro;
   wave_sync();
-  if (lead) {
+  if (put) {
     L.pgm[me] = A.G * m;
     L.pinv[me] = invi;
     L.px[me] = x[0];
@@ -419,12 +474,19 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
       const double dx = L.px[q] - x[0], dy = L.py[q] - x[1], dz = L.pz[q] - x[2];
       const double invR = fmin(invi, L.pinv[q]);
       hard_pair(dx, dy, dz, L.pvx[q] - v[0], L.pvy[q] - v[1], L.pvz[q] - v[2], L.pgm[q], invR, A, pa, pj);
-      if (energy && jj > sl) {
+      if (SL2 != 3 && energy && jj > sl) {
         const double r = sqrt(dx * dx + dy * dy + dz * dz);
         e -= m * L.pgm[q] * (1.0 - changeover_W(r * invR, A)) / r;
       }
     }
   }
+  if (SL2 == 3 && lead && energy && !RESUME)
+    for (int jj = sl + 1; jj < size; ++jj) {
+      const int q = sb + jj;
+      const double dx = L.px[q] - x[0], dy = L.py[q] - x[1], dz = L.pz[q] - x[2];
+      const double r = sqrt(dx * dx + dy * dy + dz * dz);
+      e -= m * L.pgm[q] * (1.0 - changeover_W(r * fmin(invi, L.pinv[q]), A)) / r;
+    }
   star_term(x, v, A.GM, a0, j0);
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
@@ -439,11 +501,15 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
   if constexpr (SL2 == 1) {
     pgm_q = dpp_f64<DPP_XOR1>(A.G * m);
     pinv_q = fmin(invi, dpp_f64<DPP_XOR1>(invi));
+  } else if constexpr (SL2 == 3) {
+    pgm_q = L.pgm[sb + sub];
+    pinv_q = fmin(invi, L.pinv[sb + sub]);
   }
-  const int64_t T = (int64_t)1 << TICK_BITS;
+  const bool other = sub < size && sub != sl;  // (SL2 == 3) the partner exists
+  const double T = ldexp(1.0, TICK_BITS);  // (times in ticks as exact doubles)
   const int max_iter = A.max_iter;
   const double tick = A.tick, GM = A.GM;
-  int64_t t = 0;
+  double t = 0.0;
   int nst = 0;  // block steps of this lane's cluster
   if (RESUME && mem) {
 #pragma unroll
@@ -451,7 +517,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
       a0[d] = A.pk.a[d * n + gid];
       j0[d] = A.pk.j[d * n + gid];
     }
-    t = A.pk.t[gid];
+    t = (double)A.pk.t[gid];
     lev = A.pk.lev[gid];
   }
   if (RESUME && c >= 0) {
@@ -460,18 +526,20 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
   }
   bool parked = false;
   const int budget = PARK ? A.budget : INT_MAX;
+  // (one cluster per wavefront counts its parked steps too)
+  const int limit = SL2 == 3 ? max_iter - uniform_first(nst) : max_iter;
+  const int stop = budget < limit ? budget : limit;
   int n_eval = 0;  // block steps in which this lane's member was due (lead copies only)
   for (int it = 0;; ++it) {
-    const int64_t te = mem ? t + ((int64_t)1 << (TICK_BITS - lev)) : LLONG_MAX;
+    const double te = mem ? t + step_ticks(lev) : DBL_MAX;
     // every step divides T and each member's time is a multiple of its
     // step, so a cluster is finished exactly when its earliest next time
     // lies beyond T
-    const int64_t tn = seg_min(te, cl2);
+    const double tn = SL2 == 3 ? wave_min_of_eights(te) : seg_min(te, cl2);
     const bool done = (size == 0) || (tn > T) || parked;
-    if (__all(done)) break;
-    if (it == budget) break;  // uniform
-    if (it >= max_iter) {
-      if (lane == 0) set_flag(A.cnt, P3T_FLAG_NSTEPS);
+    if (__ballot(!done) == 0ull) break;
+    if (it == stop) {  // uniform: the budget, or too many steps
+      if (it < budget && lane == 0) set_flag(A.cnt, P3T_FLAG_NSTEPS);
       break;
     }
     const bool active = mem && !done && te == tn;
@@ -480,7 +548,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
     // every lane predicts (a lane whose cluster is done, or that holds no
     // member, computes a value nobody reads), so no branch is taken here
     {
-      const double dl = (double)(tn - t) * tick;
+      const double dl = (tn - t) * tick;
       const double d2 = dl * dl * 0.5, d3 = dl * dl * dl * (1.0 / 6.0);
       predict(x, v, a0, j0, dl, d2, d3, xp, vp);
     }
@@ -498,7 +566,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
 #pragma unroll
       for (int d = 0; d < 3; ++d) pa[d] = pj[d] = 0.0;
       wave_sync();
-      if (lead) {
+      if (put) {
         L.px[me] = xp[0];
         L.py[me] = xp[1];
         L.pz[me] = xp[2];
@@ -511,7 +579,11 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
       // alone, so independent work is what hides the FP64 latency)
       star_term(xp, vp, GM, a1, j1);
       wave_sync();
-      if (active) {
+      if constexpr (SL2 == 3) {
+        const int q = sb + sub;
+        hard_pair_other(other, L.px[q] - xp[0], L.py[q] - xp[1], L.pz[q] - xp[2], L.pvx[q] - vp[0], L.pvy[q] - vp[1],
+                        L.pvz[q] - vp[2], pgm_q, pinv_q, A, pa, pj);
+      } else if (active) {
         for (int jj = sub; jj < size; jj += LPM) {
           if (jj == sl) continue;
           const int q = sb + jj;
@@ -535,7 +607,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
           j1[d] += pj[d];
         }
       }
-      const double h = (double)(tn - t) * tick;
+      const double h = (tn - t) * tick;
       t = tn;
       correct(x, v, a0, j0, xp, vp, a1, j1, h, t, lev, A);
       n_eval += sub == 0 ? 1 : 0;
@@ -544,8 +616,8 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
   count_work(A, n_eval, size);
   if (PARK) {
     // park the clusters still running: their first lane takes the slots
-    const int64_t te = mem ? t + ((int64_t)1 << (TICK_BITS - lev)) : LLONG_MAX;
-    const int64_t tmin = seg_min(te, cl2);  // every lane takes part
+    const double te = mem ? t + step_ticks(lev) : DBL_MAX;
+    const double tmin = seg_min(te, cl2);  // every lane takes part
     const bool fin = (size == 0) || (tmin > T);
     int64_t slot = LLONG_MAX;
     if (!fin && lic == 0) {
@@ -565,7 +637,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
         A.pk.a[d * n + gid] = a0[d];
         A.pk.j[d * n + gid] = j0[d];
       }
-      A.pk.t[gid] = t;
+      A.pk.t[gid] = (int64_t)t;
       A.pk.lev[gid] = lev;
       A.pk.members[slot + sl] = gid;
       A.pk.flag[gid] = 1;
@@ -588,7 +660,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
                    A.GM * m * rsqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2])
              : 0.0;
     if (mem) {
-      for (int jj = sl + 1 + sub; jj < size; jj += LPM) {
+      for (int jj = SL2 == 3 ? (lead ? sl + 1 : size) : sl + 1 + sub; jj < size; jj += SL2 == 3 ? 1 : LPM) {
         const int q = sb + jj;
         const double dx = L.px[q] - x[0], dy = L.py[q] - x[1], dz = L.pz[q] - x[2];
         const double r = sqrt(dx * dx + dy * dy + dz * dz);
@@ -731,7 +803,7 @@ __device__ __forceinline__ void add_spread(const Lds &L, int wbase, int a, int l
   }
 }
 
-// One wavefront per cluster of 5..64 members (buckets 3..6), one member per
+// One wavefront per cluster of 9..64 members (buckets 4..6), one member per
 // lane.  In a block step usually only a few members are due; their partner
 // sums are spread over the whole wavefront (spread_sums), so a step costs a
 // few pair evaluations per lane instead of size - 1 in the due members'
@@ -1165,7 +1237,6 @@ __device__ __forceinline__ double swap16_add(double a, double b) {
   return __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])) +
          __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
 }
-constexpr int DPP_ROR8 = 0x128, DPP_ROR4 = 0x124;
 __device__ __forceinline__ double row_butterfly(double v) {
   v += dpp_f64<DPP_ROR8>(v);
   v += dpp_f64<DPP_ROR4>(v);
@@ -1544,6 +1615,8 @@ __global__ __launch_bounds__(BIG_T) void k_herm_fused(HermArgs A) {
     wave_body<MODE, COLL>(A, blist, count, ci0, L, wbase, bk);
   else if (bk == 1)
     seg_body<MODE, 1>(A, blist, count, ci0, L, wbase, bk);
+  else if (bk == 3)
+    seg_body<MODE, 3>(A, blist, count, ci0, L, wbase, bk);
   else
     seg_body<MODE>(A, blist, count, ci0, L, wbase, bk);
 }

@@ -1,5 +1,5 @@
-"""Clusters of one workgroup (65 to 1024 members) at the sizes where the
-members per thread, the last wavefront and the number of due members per step
+"""Clusters of one workgroup (65 to 1024 members) and of one wavefront at the
+sizes where the members per thread, the lanes per member, the last wavefront and the number of due members per step
 change, against the oracle: equal block-step counts, states to the 1e-12 of
 the percolated path's test (both sides add the same terms, at most 1024 of
 them in another order; the oracle's own states move by 1.3e-15 when its input moves by
@@ -17,8 +17,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("sizes", [(65, 1, 127, 128, 2, 129), (191, 192, 193, 3, 255, 256), (257, 16, 512, 66),
-                                   (513, 64, 1024)])
-def test_workgroup_clusters(gpu, orc, sizes):
+                                   (513, 64, 1024), (3, 4, 5, 6, 7, 8, 9, 10), (8, 15, 16, 5, 17, 32, 33)])
+def test_cluster_sizes(gpu, orc, sizes):
     d = diskgen.workload("disk2k_equal")
     p = orc.Params(eta=0.02, eta0=0.002)
     ro, _, _ = orc.cutoffs(d.pos, d.vel, d.mass, p)
