@@ -29,7 +29,7 @@ CFLAGS = [
 # hermite.hip: instruction order chosen for independent work between dependent
 # FP64 operations rather than for occupancy (its long chains run on one
 # wavefront per SIMD); the instructions and their results are the same.
-FILE_FLAGS = {"hermite.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
+FILE_FLAGS = {k: ["-mllvm", "-amdgpu-sched-strategy=max-ilp"] for k in ("hermite.hip", "force_split.hip")}
 
 
 def hipcc() -> str:

@@ -169,9 +169,34 @@ __device__ __forceinline__ void test_candidates(const ForceArgs &A, const CandQu
   }
 }
 
+// How a group's particles lie in the lanes.  Whole: number 64 s + lane in slot
+// s, every lane meets every entry of a tile.  Halved (HALF): number 32 s +
+// (lane & 31) in both halves of the wavefront, each half meets its half of
+// the tile.  Per 64 entries that is 64 evaluations per slot whole and 32
+// halved, so 65 to 96 particles cost 3 x 32 halved against 2 x 64 whole, and up
+// to 32 cost 32 against 64; two thirds of the groups of a disk hold 65 to
+// 96.  Force launch, us, whole -> halved where it is less: 2^20 particles,
+// quadrupoles 1325 -> 1184; 200,000, monopoles 225 -> 218; 262,144 281 -> 265.
+// Eight wavefronts per group keep the whole layout: those launches wait for
+// the longest group, not for arithmetic (2,048 particles: 26.7 whole, 29.4
+// halved).  FP64 only: the FP32 sums of the mixed force are formed per tile,
+// and splitting a tile would round them differently.
+template <bool HALF>
+struct Lay {
+  static constexpr int STRIDE = HALF ? 32 : WAVE;
+  static __device__ __forceinline__ int slot(int lane) { return HALF ? lane & 31 : lane; }
+  // entries that each lane loops over in a tile of nt, a multiple of unr
+  static __device__ __forceinline__ int span(int nt, int unr) {
+    return HALF ? ((nt + 1) / 2 + unr - 1) / unr * unr : min(WAVE, (nt + unr - 1) / unr * unr);
+  }
+  // entries of the padded tile, and the first one of this lane
+  static __device__ __forceinline__ int padded(int span) { return HALF ? 2 * span : span; }
+  static __device__ __forceinline__ int first(int lane, int span) { return HALF && lane >= 32 ? span : 0; }
+};
+
 // The near terms of the tiles from list position `from` on, every `step`
 // positions (multiples of WAVE), added to (ax, ay, az).
-template <bool MIXED, int IPL, int UNR>
+template <bool MIXED, int IPL, int UNR, bool HALF>
 __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h, NearTile &T, int lane, int from,
                                            int step, CandQueue &Q, double *ax, double *ay, double *az) {
   int ii[IPL];
@@ -180,7 +205,7 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
   int ro2q[IPL], rch2q[IPL];  // MIXED: bit patterns of the widened FP32 squares
 #pragma unroll
   for (int s = 0; s < IPL; ++s) {
-    const int k = lane + WAVE * s;
+    const int k = Lay<HALF>::slot(lane) + Lay<HALF>::STRIDE * s;
     ii[s] = k < h.count ? h.first + k : -1;
     const int i = ii[s] >= 0 ? ii[s] : h.first;
     // an empty slot sits far from the group and from the padding entries
@@ -204,7 +229,7 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
   int nj = -2;
   auto fetch = [&](int t0) {
     const int nt = min(WAVE, h.n_near - t0);
-    const int ntp = min(WAVE, (nt + UNR - 1) / UNR * UNR);
+    const int ntp = Lay<HALF>::padded(Lay<HALF>::span(nt, UNR));
     if (lane < nt) {
       const int j = Ln[t0 + lane];
       const double r = A.sreach[j];
@@ -226,7 +251,7 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
   if (h.n_near > from) fetch(from);
   for (int t0 = from; t0 < h.n_near; t0 += step) {
     const int nt = min(WAVE, h.n_near - t0);
-    const int ntp = min(WAVE, (nt + UNR - 1) / UNR * UNR);
+    const int span = Lay<HALF>::span(nt, UNR), ntp = Lay<HALF>::padded(span), e0 = Lay<HALF>::first(lane, span);
     tile_sync();
     if (lane < ntp) {
       T.a[lane] = na;
@@ -241,15 +266,15 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
 #pragma unroll
     for (int s = 0; s < IPL; ++s) tx[s] = ty[s] = tz[s] = 0.0f;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
+    for (int half = 0; half < (HALF ? 1 : 2); ++half) {
 #pragma unroll
       for (int s = 0; s < IPL; ++s) cm[half][s] = chg_m[half][s] = 0u;
-      const int lo = half * 32, hi = min(ntp, lo + 32);
+      const int lo = half * 32, hi = min(span, lo + 32);
       for (int jj = lo; jj < hi; jj += UNR) {
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-          const double4 a = T.a[jj + u];
-          const int jidx = T.j[jj + u];
+          const double4 a = T.a[e0 + jj + u];
+          const int jidx = T.j[e0 + jj + u];
           const unsigned bit = 1u << ((jj + u) & 31);
           if constexpr (MIXED) {
             const float4 fj = T.f[jj + u];
@@ -274,7 +299,7 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
               cm[half][s] |= cand ? bit : 0u;
             }
           } else {
-            const double2 b = T.b[jj + u];
+            const double2 b = T.b[e0 + jj + u];
             const long long rch2j = __double_as_longlong(b.y);
 #pragma unroll
             for (int s = 0; s < IPL; ++s) {
@@ -317,7 +342,7 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
     if (A.collect) {
 #pragma unroll
       for (int s = 0; s < IPL; ++s) {
-        unsigned m0 = ii[s] >= 0 ? cm[0][s] : 0u, m1 = ii[s] >= 0 ? cm[1][s] : 0u;
+        unsigned m0 = ii[s] >= 0 ? cm[0][s] : 0u, m1 = !HALF && ii[s] >= 0 ? cm[1][s] : 0u;
         for (;;) {
           const bool has = (m0 | m1) != 0u;
           const unsigned long long bal = __ballot(has);
@@ -328,7 +353,7 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
               m0 &= m0 - 1u;
             else
               m1 &= m1 - 1u;
-            Q.e[nq + popc_below(bal)] = make_int2(ii[s], T.j[q]);
+            Q.e[nq + popc_below(bal)] = make_int2(ii[s], T.j[e0 + q]);
           }
           nq += (int)__popcll(bal);
           if (nq >= WAVE) {
@@ -355,13 +380,13 @@ union FarTile {
   float4 f[WAVE];   // offsets from the group centre, G m
 };
 
-template <bool MIXED, int IPL, int UNR>
+template <bool MIXED, int IPL, int UNR, bool HALF>
 __device__ __forceinline__ void far_group(const ForceArgs &A, const GroupHdr &h, FarTile &T, int lane, int from,
                                           int step, double *ax, double *ay, double *az) {
   double xi[IPL], yi[IPL], zi[IPL];
 #pragma unroll
   for (int s = 0; s < IPL; ++s) {
-    const int k = lane + WAVE * s;
+    const int k = Lay<HALF>::slot(lane) + Lay<HALF>::STRIDE * s;
     const int i = k < h.count ? h.first + k : h.first;
     xi[s] = A.sx[i];
     yi[s] = A.sy[i];
@@ -371,7 +396,7 @@ __device__ __forceinline__ void far_group(const ForceArgs &A, const GroupHdr &h,
   if (!MIXED) {
     for (int t0 = from; t0 < h.n_far; t0 += step) {
       const int nt = min(WAVE, h.n_far - t0);
-      const int ntp = min(WAVE, (nt + UNR - 1) / UNR * UNR);
+      const int span = Lay<HALF>::span(nt, UNR), ntp = Lay<HALF>::padded(span), e0 = Lay<HALF>::first(lane, span);
       tile_sync();
       if (lane < nt) {
         const int j = Lf[t0 + lane];
@@ -380,10 +405,10 @@ __device__ __forceinline__ void far_group(const ForceArgs &A, const GroupHdr &h,
         T.d[lane] = make_double4(h.cx + kDummyOffset, h.cy, h.cz, 0.0);
       }
       tile_sync();
-      for (int jj = 0; jj < ntp; jj += UNR) {
+      for (int jj = 0; jj < span; jj += UNR) {
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-          const double4 a = T.d[jj + u];
+          const double4 a = T.d[e0 + jj + u];
 #pragma unroll
           for (int s = 0; s < IPL; ++s) {
             const double dx = a.x - xi[s], dy = a.y - yi[s], dz = a.z - zi[s];
@@ -510,13 +535,13 @@ __device__ __forceinline__ void cell_acc(R dx, R dy, R dz, R gm, R q0, R q1, R q
   az = fma_r(-qz, rinv5, fma_r(f, dz, az));
 }
 
-template <bool MIXED, bool QUAD, int IPL, int UNR>
+template <bool MIXED, bool QUAD, int IPL, int UNR, bool HALF>
 __device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h, CellTile &T, int lane, int from,
                                            int step, double *ax, double *ay, double *az) {
   double xi[IPL], yi[IPL], zi[IPL];
 #pragma unroll
   for (int s = 0; s < IPL; ++s) {
-    const int k = lane + WAVE * s;
+    const int k = Lay<HALF>::slot(lane) + Lay<HALF>::STRIDE * s;
     const int i = k < h.count ? h.first + k : h.first;
     xi[s] = A.sx[i];
     yi[s] = A.sy[i];
@@ -527,7 +552,7 @@ __device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h
   if (!MIXED) {
     for (int t0 = from; t0 < h.n_cell; t0 += step) {
       const int nt = min(WAVE, h.n_cell - t0);
-      const int ntp = min(WAVE, (nt + UNR - 1) / UNR * UNR);
+      const int span = Lay<HALF>::span(nt, UNR), ntp = Lay<HALF>::padded(span), e0 = Lay<HALF>::first(lane, span);
       tile_sync();
       if (lane < nt) {
         const CellMom c = A.cm[Lc[t0 + lane]];
@@ -544,15 +569,15 @@ __device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h
         }
       }
       tile_sync();
-      for (int jj = 0; jj < ntp; jj += UNR) {
+      for (int jj = 0; jj < span; jj += UNR) {
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-          const double4 a = T.d.a[jj + u];
+          const double4 a = T.d.a[e0 + jj + u];
           double4 qa = make_double4(0.0, 0.0, 0.0, 0.0);
           double2 qb = make_double2(0.0, 0.0);
           if (QUAD) {
-            qa = T.d.qa[jj + u];
-            qb = T.d.qb[jj + u];
+            qa = T.d.qa[e0 + jj + u];
+            qb = T.d.qb[e0 + jj + u];
           }
 #pragma unroll
           for (int s = 0; s < IPL; ++s) {
@@ -638,22 +663,37 @@ __device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h
 // each with a tile of LDS of its own; the wavefronts' sums are added in
 // wavefront order and written in the caller's order.  Deterministic: the same
 // tiles in the same wavefronts whatever the grid.
-template <bool MIXED, bool QUAD, int IPL, int UNR, int W>
+// a + the value of the lane 32 lanes away
+__device__ __forceinline__ double other_half_add(double a) {
+  const uint64_t u = (uint64_t)__double_as_longlong(a);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)u, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+  return __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])) +
+         __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
+}
+
+template <bool MIXED, bool QUAD, int IPL, int UNR, int W, bool HALF = false>
 __device__ __forceinline__ void all_group(const ForceArgs &A, const GroupHdr &h, ForceTile *T, CandQueue *Q,
                                           int lane, int w) {
   double ax[IPL] = {}, ay[IPL] = {}, az[IPL] = {};
   const int nt = (h.n_near + WAVE - 1) / WAVE, ft = (h.n_far + WAVE - 1) / WAVE;
   // first far / cell tile of wavefront w: the tiles are numbered through
   const int f0 = ((w - nt) % W + W) % W, c0 = ((w - nt - ft) % W + W) % W;
-  near_group<MIXED, IPL, UNR>(A, h, T[w].near, lane, WAVE * w, WAVE * W, Q[w], ax, ay, az);
-  far_group<MIXED, IPL, UNR>(A, h, T[w].far, lane, WAVE * f0, WAVE * W, ax, ay, az);
-  cell_group<MIXED, QUAD, IPL, UNR>(A, h, T[w].cell, lane, WAVE * c0, WAVE * W, ax, ay, az);
+  near_group<MIXED, IPL, UNR, HALF>(A, h, T[w].near, lane, WAVE * w, WAVE * W, Q[w], ax, ay, az);
+  far_group<MIXED, IPL, UNR, HALF>(A, h, T[w].far, lane, WAVE * f0, WAVE * W, ax, ay, az);
+  cell_group<MIXED, QUAD, IPL, UNR, HALF>(A, h, T[w].cell, lane, WAVE * c0, WAVE * W, ax, ay, az);
   tile_sync();
 #pragma unroll
   for (int s = 0; s < IPL; ++s) {
-    T[w].sum[0][lane + WAVE * s] = ax[s];
-    T[w].sum[1][lane + WAVE * s] = ay[s];
-    T[w].sum[2][lane + WAVE * s] = az[s];
+    if (HALF) {
+      ax[s] = other_half_add(ax[s]);
+      ay[s] = other_half_add(ay[s]);
+      az[s] = other_half_add(az[s]);
+    }
+    const int k = Lay<HALF>::slot(lane) + Lay<HALF>::STRIDE * s;  // (both halves hold the same)
+    T[w].sum[0][k] = ax[s];
+    T[w].sum[1][k] = ay[s];
+    T[w].sum[2][k] = az[s];
   }
   __syncthreads();
   for (int k = WAVE * w + lane; k < h.count; k += WAVE * W) {
@@ -695,7 +735,11 @@ __global__ __launch_bounds__(WAVE *W, min_waves(UNR)) void k_force_all(ForceArgs
     if (gi >= ngroups) break;
     GroupHdr h;
     if (!group_header(A, gi, h)) continue;
-    if (h.count > WAVE)
+    if (!MIXED && W == 4 && h.count > WAVE && h.count <= 96)
+      all_group<false, QUAD, 3, UNR, W, true>(A, h, T, Q, lane, w);
+    else if (!MIXED && W == 4 && h.count <= 32)
+      all_group<false, QUAD, 1, UNR, W, true>(A, h, T, Q, lane, w);
+    else if (h.count > WAVE)
       all_group<MIXED, QUAD, 2, UNR, W>(A, h, T, Q, lane, w);
     else
       all_group<MIXED, QUAD, 1, UNR, W>(A, h, T, Q, lane, w);
