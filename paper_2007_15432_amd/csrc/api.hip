@@ -119,6 +119,10 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   c->arena.used = 0;
   Arena &A = c->arena;
   c->cnt = A.take<DevCounters>(1);
+  // (with the counters, so that one call clears what is zero between calls)
+  c->row_cnt = A.take<int32_t>(n_cap);
+  c->cl_cnt = A.take<int32_t>(n_cap);
+  c->cl_nc = A.take<int64_t>(2);
   c->bbox_part = A.take<double>(6 * 1024);
   double **soa[11] = {&c->sx, &c->sy, &c->sz, &c->svx, &c->svy, &c->svz, &c->sm, &c->sro, &c->sinv, &c->sreach, &c->srs};
   for (auto p : soa) *p = A.take<double>(n_cap);
@@ -144,11 +148,8 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   c->group_order = A.take<int32_t>(n_cap);
   c->group_cls = A.take<int32_t>(n_cap);
   c->walk_q = A.take<unsigned long long>(WALK_PARTS * WALK_QUEUE_STRIDE);
-  c->row_cnt = A.take<int32_t>(n_cap);
-  c->cl_cnt = A.take<int32_t>(n_cap);
   c->cl_slot = A.take<int32_t>(n_cap);
   c->cl_start = A.take<int32_t>(n_cap);
-  c->cl_nc = A.take<int64_t>(2);
   c->cl_sums = A.take<uint64_t>(scan_sums_need());
   c->uf_parent = A.take<int32_t>(n_cap);
   c->cl_keys = A.take<uint64_t>(n_cap);
@@ -164,11 +165,9 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   c->hs_cl_ptr = A.take<int32_t>(n_cap + 1);
   c->hs_cl_mem = A.take<int32_t>(n_cap + 1);
   if (!c->hs_cl_mem) return fail(c, P3T_ERR_HIP, "arena layout overflow (internal)");
-  HIP_OK(c, hipMemsetAsync(c->cnt, 0, sizeof(DevCounters), c->stream));
   // zero between calls: every pass that counts into them leaves them clear
-  HIP_OK(c, fill_i32(c->row_cnt, 0, n_cap, c->stream));
-  HIP_OK(c, fill_i32(c->cl_cnt, 0, n_cap, c->stream));
-  HIP_OK(c, fill_i32(reinterpret_cast<int32_t *>(c->cl_nc), 0, 4, c->stream));
+  const size_t clear = (size_t)((char *)(c->cl_nc + 2) - (char *)c->cnt);
+  HIP_OK(c, hipMemsetAsync(c->cnt, 0, clear, c->stream));
   c->n_cap = n_cap;
   c->tree_valid = c->force_valid = false;
   c->park_flags_valid = 0;
@@ -505,15 +504,16 @@ p3t_status p3t_get_params(p3t_ctx *c, p3t_params *p) {
 p3t_status p3t_reserve(p3t_ctx *c, int64_t n_max, int64_t nnz_max) {
   if (!c || n_max < 0 || nnz_max < 0) return fail(c, P3T_ERR_ARG, "reserve: bad argument");
   prep_join(c);
-  p3t_status st = ensure_n(c, n_max);
-  if (st != P3T_OK) return st;
-  if ((st = ensure_lists(c, n_max)) != P3T_OK) return st;
-  if (nnz_max > c->pair_cap) {
-    HIP_OK(c, dev_alloc(c->pairs, nnz_max));
-    c->pair_cap = nnz_max;
+  // the pairs first, once, at the size asked for (ensure_lists gives them at least 2 n)
+  const int64_t pairs = std::max(nnz_max, c->pairs ? int64_t(0) : std::max<int64_t>(1 << 16, 2 * n_max));
+  if (pairs > c->pair_cap) {
+    HIP_OK(c, dev_alloc(c->pairs, pairs));
+    c->pair_cap = pairs;
     c->force_valid = false;
   }
-  return P3T_OK;
+  p3t_status st = ensure_n(c, n_max);
+  if (st != P3T_OK) return st;
+  return ensure_lists(c, n_max);
 }
 
 p3t_status p3t_compute_cutoffs(p3t_ctx *c, int64_t n, const double *pos3, const double *vel3, const double *mass,
