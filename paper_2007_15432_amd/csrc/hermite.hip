@@ -314,6 +314,11 @@ __device__ __forceinline__ double seg_min(double v, int sl2) {
   if (sl2 >= 6) v = fmin(v, __shfl_xor(v, 32, WAVE));
   return v;
 }
+// minimum over a row of a time that the lanes of each aligned four share
+__device__ __forceinline__ double row_min_of_fours(double v) {
+  v = fmin(v, dpp_time<DPP_HALF_MIRROR>(v));
+  return fmin(v, dpp_time<DPP_MIRROR>(v));
+}
 // minimum over the wavefront of a time that the lanes of each aligned eight
 // share: the row's other half, then the other rows by swaps, no LDS
 __device__ __forceinline__ double wave_min_of_eights(double v) {
@@ -370,16 +375,13 @@ struct Lds {
 constexpr int BIG_ACT = 128;  // most active members handled lane-parallel
 
 // ---------------------------------------------------------------- small clusters
-// One wavefront (lanes [wbase, wbase + 64) of the LDS arrays) runs 64/SEG
-// clusters; cluster index ci of bucket bk.
-// Lanes of a size bucket bk <= 6: SEG = 2^bk member slots per cluster and
+// Lanes of a size bucket bk <= 3: SEG = 2^bk member slots per cluster and
 // LPM = 2^ll2 lanes per member that share the member's pair loop, so a
-// cluster spans 2^(bk + ll2) lanes.  Small clusters (bk <= 1) keep one lane
-// per member and pack many clusters per wavefront; from four members on,
-// the pair loop, which grows with the cluster, is split over up to eight
-// lanes per member (clusters then fill a whole wavefront or a quarter).
+// cluster spans 2^(bk + ll2) lanes.  One and two members keep one lane per
+// member and pack many clusters per wavefront; from three members on a
+// lane has one partner (clusters then fill a quarter or a whole wavefront).
 __host__ __device__ constexpr int lanes_per_member_log2(int bk) {
-  return bk < 2 ? 0 : (bk < 6 - bk ? bk : 6 - bk);
+  return bk < 2 ? 0 : bk;
 }
 
 // DPP exchange of a double with a fixed lane permutation
@@ -397,28 +399,26 @@ __device__ __forceinline__ double lpm_sum(double v, int ll2) {
 }
 
 // One wavefront (lanes [wbase, wbase + 64) of the LDS arrays) runs the
-// clusters ci0, ci0 + 1, ... of bucket bk; one body serves every bucket (a
-// template per bucket would multiply the kernel's code, and all buckets run
-// side by side in the fused launch, sharing the instruction cache).  The
-// LPM lanes of a member hold identical copies of its state; each evaluates
-// every LPM-th partner and the partial sums are added across them.
+// clusters ci0, ci0 + 1, ... of bucket SL2 <= 3.  The LPM lanes of a member
+// hold identical copies of its state; each evaluates one partner and the
+// terms are added across them.
 // MODE 0: plain; 1: park clusters still running after A.budget steps;
 // 2: resume parked clusters
-// SL2 = 1 and 3 (two members; five to eight) are the sizes of the longest
-// chains and have code of their own.  Their block steps are bound by the
-// latency of one wavefront's chain of about 300 instructions, two thirds
-// FP64: times as exact doubles, minima and sums by lane moves, every due
-// member's sum formed in the lanes that hold it, no branch around the pair
-// term.  Five and six members took 1.47 us per block step in wave_body and
-// take 0.93 us here (same sums in the same order), and a 1M-particle soft
-// step with a chain of 3,200 such steps 3.95 -> 3.08 ms.
-template <int MODE, int SL2 = -1>
+// Clusters of two to eight members have the longest chains, thousands of
+// dependent block steps, bound by the latency of one wavefront's chain of
+// about 300 instructions per step, two thirds of them FP64.  Hence times as
+// exact doubles, minima and sums by lane moves, every due member's sum formed in
+// the lanes that hold it, no branch around the pair term and a copy of the
+// code per bucket.  Block step, us, with one body for all sizes (three or
+// four members) and with one lane per member (five to eight), and here: 1.02
+// -> 0.92, 1.47 -> 0.93; a 1M-particle soft step with a chain of 3,200 steps
+// of five members 3.95 -> 3.08 ms.
+template <int MODE, int SL2>
 __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist, int count, int ci0, const Lds &L,
-                                         int wbase, int sl2_rt) {
-  const int sl2 = SL2 >= 0 ? SL2 : sl2_rt;
+                                         int wbase) {
   constexpr bool RESUME = MODE == 2, PARK = MODE == 1;
-  const int ll2 = lanes_per_member_log2(sl2), cl2 = sl2 + ll2;
-  const int SEG = 1 << sl2, LPM = 1 << ll2;
+  constexpr int sl2 = SL2, ll2 = lanes_per_member_log2(sl2), cl2 = sl2 + ll2;
+  constexpr int SEG = 1 << sl2, LPM = 1 << ll2;
   const int lane = threadIdx.x & (WAVE - 1), cseg = lane >> cl2, lic = lane & ((1 << cl2) - 1);
   const int sl = lic >> ll2, sub = lic & (LPM - 1);
   const int sb = wbase + cseg * SEG;  // LDS slot of the cluster's first member
@@ -428,9 +428,10 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
   const int size = c >= 0 ? A.cl_ptr[c + 1] - b : 0;
   const bool mem = sl < size;
   const bool lead = mem && sub == 0;  // the copy that reads and writes memory
-  // 5 to 8 members: every lane has one partner, and the empty slots hold
+  // 3 to 8 members: every lane has one partner, and the empty slots hold
   // finite values too, so that the pair term needs no branch
-  const bool put = SL2 == 3 ? sub == 0 : lead;
+  constexpr bool ONE = SL2 == 2 || SL2 == 3;
+  const bool put = ONE ? sub == 0 : lead;
   const int gid = mem ? A.members[b + sl] : 0;
   const int64_t n = A.n;
   const int me = sb + sl;
@@ -501,11 +502,11 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
   if constexpr (SL2 == 1) {
     pgm_q = dpp_f64<DPP_XOR1>(A.G * m);
     pinv_q = fmin(invi, dpp_f64<DPP_XOR1>(invi));
-  } else if constexpr (SL2 == 3) {
+  } else if constexpr (ONE) {
     pgm_q = L.pgm[sb + sub];
     pinv_q = fmin(invi, L.pinv[sb + sub]);
   }
-  const bool other = sub < size && sub != sl;  // (SL2 == 3) the partner exists
+  const bool other = sub < size && sub != sl;  // (ONE) the partner exists
   const double T = ldexp(1.0, TICK_BITS);  // (times in ticks as exact doubles)
   const int max_iter = A.max_iter;
   const double tick = A.tick, GM = A.GM;
@@ -535,7 +536,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
     // every step divides T and each member's time is a multiple of its
     // step, so a cluster is finished exactly when its earliest next time
     // lies beyond T
-    const double tn = SL2 == 3 ? wave_min_of_eights(te) : seg_min(te, cl2);
+    const double tn = SL2 == 3 ? wave_min_of_eights(te) : SL2 == 2 ? row_min_of_fours(te) : seg_min(te, cl2);
     const bool done = (size == 0) || (tn > T) || parked;
     if (__ballot(!done) == 0ull) break;
     if (it == stop) {  // uniform: the budget, or too many steps
@@ -565,31 +566,26 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
     } else {
 #pragma unroll
       for (int d = 0; d < 3; ++d) pa[d] = pj[d] = 0.0;
-      wave_sync();
-      if (put) {
-        L.px[me] = xp[0];
-        L.py[me] = xp[1];
-        L.pz[me] = xp[2];
-        L.pvx[me] = vp[0];
-        L.pvy[me] = vp[1];
-        L.pvz[me] = vp[2];
+      if constexpr (ONE) {
+        wave_sync();
+        if (put) {
+          L.px[me] = xp[0];
+          L.py[me] = xp[1];
+          L.pz[me] = xp[2];
+          L.pvx[me] = vp[0];
+          L.pvy[me] = vp[1];
+          L.pvz[me] = vp[2];
+        }
       }
       // the star's term needs only the own predicted state: computed while
       // the exchange through LDS is in flight (one wavefront runs this chain
       // alone, so independent work is what hides the FP64 latency)
       star_term(xp, vp, GM, a1, j1);
-      wave_sync();
-      if constexpr (SL2 == 3) {
+      if constexpr (ONE) {
+        wave_sync();
         const int q = sb + sub;
         hard_pair_other(other, L.px[q] - xp[0], L.py[q] - xp[1], L.pz[q] - xp[2], L.pvx[q] - vp[0], L.pvy[q] - vp[1],
                         L.pvz[q] - vp[2], pgm_q, pinv_q, A, pa, pj);
-      } else if (active) {
-        for (int jj = sub; jj < size; jj += LPM) {
-          if (jj == sl) continue;
-          const int q = sb + jj;
-          hard_pair(L.px[q] - xp[0], L.py[q] - xp[1], L.pz[q] - xp[2], L.pvx[q] - vp[0], L.pvy[q] - vp[1],
-                    L.pvz[q] - vp[2], L.pgm[q], fmin(invi, L.pinv[q]), A, pa, pj);
-        }
       }
     }
     if (ll2 > 0) {  // partial sums of the member's copies (all lanes take part)
@@ -1614,11 +1610,13 @@ __global__ __launch_bounds__(BIG_T) void k_herm_fused(HermArgs A) {
   if (bk >= (COLL ? 1 : WAVE_BK0))
     wave_body<MODE, COLL>(A, blist, count, ci0, L, wbase, bk);
   else if (bk == 1)
-    seg_body<MODE, 1>(A, blist, count, ci0, L, wbase, bk);
+    seg_body<MODE, 1>(A, blist, count, ci0, L, wbase);
+  else if (bk == 2)
+    seg_body<MODE, 2>(A, blist, count, ci0, L, wbase);
   else if (bk == 3)
-    seg_body<MODE, 3>(A, blist, count, ci0, L, wbase, bk);
+    seg_body<MODE, 3>(A, blist, count, ci0, L, wbase);
   else
-    seg_body<MODE>(A, blist, count, ci0, L, wbase, bk);
+    seg_body<MODE, 0>(A, blist, count, ci0, L, wbase);
 }
 
 template <int MPT, int MODE>
