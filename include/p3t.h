@@ -300,9 +300,9 @@ p3t_status p3t_merge_bodies(p3t_ctx *ctx, int64_t n, const int32_t *merged_into,
 
 /* p3t_build_tree followed by p3t_compute_soft_force in one call.  With
  * use_graph = 1 the whole device sequence (bounding box, Morton keys, radix
- * sort, gather, radix tree, moments, groups, walk, longest-first group order,
- * force kernels, neighbour candidates) is captured once into a hipGraph on a
- * private stream and replayed on later calls with the same n, pointers,
+ * sort, gather and tree, moments, walk, longest-first group order, force with
+ * the neighbour candidates) is captured once into a hipGraph on a private
+ * stream and replayed on later calls with the same n, pointers,
  * parameters and launch shapes; the counts that vary between calls (groups,
  * list lengths) stay on the device.  The call then synchronises once to read
  * the counters.  If a list, stack or pair buffer overflowed, the buffers grow

@@ -239,8 +239,9 @@ CloseSrc close_src(p3t_ctx *c) {
 // Enqueues on aux_stream, right behind the evaluation just enqueued on the
 // main stream and before its counters are read, the clusters of the next
 // hard part: labels from the union-find that the evaluation filled, the
-// cluster CSR and the bucket words (copied to pinned host memory).  It runs while the host reads the counters and enqueues the
-// kicks and radii that follow; eval_finish keeps it (prep_confirm) when the
+// cluster CSR and the bucket words (copied to pinned host memory).  It runs
+// while the host reads the counters and enqueues the kicks and radii that
+// follow; eval_finish keeps it (prep_confirm) when the
 // evaluation needs no retry.  p3t_hard_step / p3t_hard_evaluate take the
 // result instead of computing it.
 p3t_status prep_enqueue(p3t_ctx *c) {

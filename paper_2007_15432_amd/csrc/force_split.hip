@@ -176,7 +176,7 @@ __device__ __forceinline__ void test_candidates(const ForceArgs &A, const CandQu
 // halved, so 65 to 96 particles cost 3 x 32 halved against 2 x 64 whole, and up
 // to 32 cost 32 against 64; two thirds of the groups of a disk hold 65 to
 // 96.  Force launch, us, whole -> halved where it is less: 2^20 particles,
-// quadrupoles 1325 -> 1184; 200,000, monopoles 225 -> 218; 262,144 281 -> 265.
+// quadrupoles 1325 -> 1175; 200,000, monopoles 225 -> 209; 262,144 281 -> 261.
 // Eight wavefronts per group keep the whole layout: those launches wait for
 // the longest group, not for arithmetic (2,048 particles: 26.7 whole, 29.4
 // halved).  FP64 only: the FP32 sums of the mixed force are formed per tile,
@@ -711,11 +711,15 @@ __device__ __forceinline__ void all_group(const ForceArgs &A, const GroupHdr &h,
   }
 }
 
-// wavefronts per SIMD that the unroll's registers allow without spills
-constexpr int min_waves(int unr) { return unr <= 2 ? 4 : unr <= 4 ? 3 : 2; }
+// wavefronts per SIMD that the registers allow: FP64 with three slots of half
+// wavefronts needs 167 (unroll 2), and bounded to the 128 of four wavefronts it
+// spilled: 200,000 particles 218 us with four, 209 with three; 2^20 1184 and 1175
+constexpr int min_waves(int unr, bool mixed, int w) {
+  return unr == 2 && !mixed && w == 4 ? 3 : unr <= 2 ? 4 : unr <= 4 ? 3 : 2;
+}
 
 template <bool MIXED, bool QUAD, int UNR, int W>
-__global__ __launch_bounds__(WAVE *W, min_waves(UNR)) void k_force_all(ForceArgs A) {
+__global__ __launch_bounds__(WAVE *W, min_waves(UNR, MIXED, W)) void k_force_all(ForceArgs A) {
   __shared__ ForceTile T[W];
   __shared__ CandQueue Q[W];
   __shared__ int next;

@@ -172,7 +172,7 @@ struct KeyView {
 
 // Into Morton order, and the radix tree over the sorted keys, in one launch
 // (position k: sorted particle k and internal node k).
-//   The particle's record (k_pack) is read once, its rows written.
+//   The particle's packed record (k_morton) is read once, its rows written.
 //   The internal node's key range and split (Karras 2012) go to topo (left,
 // right, first, count: 16 B per node, so that every later pass over the
 // topology reads coalesced 16-B records).  Each node lists its children that
