@@ -58,7 +58,12 @@ template <bool NEAR>
 __device__ __forceinline__ void adj_term(double dx, double dy, double dz, double lx, double ly, double lz, double invR,
                                          bool ok, double g, const AdjArgs &A, double &tx, double &ty, double &tz,
                                          double &s) {
-  if (NEAR) dx = ok ? dx : 1.0;
+  if (NEAR) {  // (lambda, not the factors: whatever it holds, its product here is zero)
+    dx = ok ? dx : 1.0;
+    lx = ok ? lx : 0.0;
+    ly = ok ? ly : 0.0;
+    lz = ok ? lz : 0.0;
+  }
   const double r2 = dx * dx + dy * dy + dz * dz;
   const double rinv = rsqrt_pos(r2);
   const double rinv2 = rinv * rinv;
@@ -69,8 +74,8 @@ __device__ __forceinline__ void adj_term(double dx, double dy, double dz, double
     const double x2 = x * x, omx = 1.0 - x;
     const double K = x2 * x2 * (35.0 + x * (-84.0 + x * (70.0 - 20.0 * x)));
     const double Ky = 140.0 * x2 * x * omx * omx * omx * A.inv1mg;
-    dphi_r = ok ? phi * (Ky * invR - 3.0 * K * rinv) * rinv : 0.0;
-    phi = ok ? phi * K : 0.0;
+    dphi_r = phi * (Ky * invR - 3.0 * K * rinv) * rinv;
+    phi = phi * K;
   } else {
     dphi_r = -3.0 * phi * rinv2;
   }
@@ -259,14 +264,14 @@ __device__ __forceinline__ void adj_group(const AdjArgs &A, AdjLds &S, const Gro
     const int k = (lane & 31) + 32 * s;
     const bool in = k < gcount;
     const int i = in ? first + k : first;
-    const double f = !in ? 0.0 : MIXED ? 1.0 : A.G;
+    const double f = MIXED ? 1.0 : A.G;
     I.id[s] = in ? i : -1;
     I.x[s] = A.sx[i];
     I.y[s] = A.sy[i];
     I.z[s] = A.sz[i];
-    I.lx[s] = f * A.lam[i];
-    I.ly[s] = f * A.lam[n + i];
-    I.lz[s] = f * A.lam[2 * n + i];
+    I.lx[s] = in ? f * A.lam[i] : 0.0;
+    I.ly[s] = in ? f * A.lam[n + i] : 0.0;
+    I.lz[s] = in ? f * A.lam[2 * n + i] : 0.0;
     I.inv[s] = A.sinv[i];
     I.ox[s] = I.oy[s] = I.oz[s] = 0.0;
   }

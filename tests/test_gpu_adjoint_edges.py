@@ -31,3 +31,20 @@ def test_group_sizes(gpu, orc, n, group):
         assert ctx.stats()["n_cell"] > 0
         wx, wm = fd_check(ctx, g, n, T(lam), diskgen.sample_indices(n, 6, 3), gx, gm, 1e-9)
         assert wx < 1e-6 and wm < 1e-6
+
+
+def test_nan_cotangent_stays_with_its_pairs(gpu, orc):
+    """A NaN cotangent of one particle: that particle's mass gradient has no
+    term of its own cotangent (theta = 0), so it stays finite; its partners'
+    and its own position gradients are NaN, as the oracle's."""
+    n, k = 300, 17
+    d = diskgen.workload("disk2k_equal", n)
+    lam = np.random.default_rng(1).normal(size=(3, n))
+    lam[:, k] = np.nan
+    for group in (8, 64, 128):
+        ctx, g, acc, ro, p = setup(gpu, orc, d, theta=0.0, multipole=1, n_group_max=group)
+        gx, gm = ctx.soft_kick_adjoint(T(lam), 0.5)
+        ogx, ogm = orc.soft_adjoint(d.pos, d.mass, ro, lam, p)
+        assert np.array_equal(np.isnan(gx.cpu().numpy()), np.isnan(ogx))
+        assert np.array_equal(np.isnan(gm.cpu().numpy()), np.isnan(ogm))
+        assert np.isfinite(ogm[k])
