@@ -62,11 +62,6 @@ __device__ __forceinline__ bool group_header(const ForceArgs &A, int gi, GroupHd
   return true;
 }
 
-__device__ __forceinline__ int next_gi(const ForceArgs &A, int lane, int iter, int ngroups) {
-  if (A.persistent) return next_group(A.queue, lane);
-  return iter == 0 ? (int)blockIdx.x : ngroups;
-}
-
 // LDS ordering inside one wavefront (each wavefront has tiles of its own): a
 // wave's LDS operations execute in order, so a compiler fence is enough
 // between a write by one lane and a read by another.

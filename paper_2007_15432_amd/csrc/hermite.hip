@@ -305,15 +305,6 @@ template <int CTRL>
 __device__ __forceinline__ double dpp_time(double v) {
   return __longlong_as_double((long long)dpp_i64<CTRL>((int64_t)__double_as_longlong(v)));
 }
-__device__ __forceinline__ double seg_min(double v, int sl2) {
-  if (sl2 >= 1) v = fmin(v, dpp_time<DPP_XOR1>(v));
-  if (sl2 >= 2) v = fmin(v, dpp_time<DPP_XOR2>(v));
-  if (sl2 >= 3) v = fmin(v, dpp_time<DPP_HALF_MIRROR>(v));
-  if (sl2 >= 4) v = fmin(v, dpp_time<DPP_MIRROR>(v));
-  if (sl2 >= 5) v = fmin(v, __shfl_xor(v, 16, WAVE));
-  if (sl2 >= 6) v = fmin(v, __shfl_xor(v, 32, WAVE));
-  return v;
-}
 // minimum over a row of a time that the lanes of each aligned four share
 __device__ __forceinline__ double row_min_of_fours(double v) {
   v = fmin(v, dpp_time<DPP_HALF_MIRROR>(v));
@@ -333,6 +324,14 @@ __device__ __forceinline__ double wave_min_of_eights(double v) {
   hi = __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
   return fmin(__longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])),
               __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1])));
+}
+// earliest time of a cluster of size bucket SL2 <= 3 (seg_body's lanes)
+template <int SL2>
+__device__ __forceinline__ double cluster_min(double t) {
+  if constexpr (SL2 == 1) t = fmin(t, dpp_time<DPP_XOR1>(t));
+  if constexpr (SL2 == 2) t = row_min_of_fours(t);
+  if constexpr (SL2 == 3) t = wave_min_of_eights(t);
+  return t;
 }
 // sum over aligned segments of 2^sl2 lanes
 __device__ __forceinline__ double seg_sum(double v, int sl2) {
@@ -536,7 +535,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
     // every step divides T and each member's time is a multiple of its
     // step, so a cluster is finished exactly when its earliest next time
     // lies beyond T
-    const double tn = SL2 == 3 ? wave_min_of_eights(te) : SL2 == 2 ? row_min_of_fours(te) : seg_min(te, cl2);
+    const double tn = cluster_min<SL2>(te);
     const bool done = (size == 0) || (tn > T) || parked;
     if (__ballot(!done) == 0ull) break;
     if (it == stop) {  // uniform: the budget, or too many steps
@@ -613,7 +612,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
   if (PARK) {
     // park the clusters still running: their first lane takes the slots
     const double te = mem ? t + step_ticks(lev) : DBL_MAX;
-    const double tmin = seg_min(te, cl2);  // every lane takes part
+    const double tmin = cluster_min<SL2>(te);  // every lane takes part
     const bool fin = (size == 0) || (tmin > T);
     int64_t slot = LLONG_MAX;
     if (!fin && lic == 0) {
