@@ -41,7 +41,13 @@ struct GroupHdr {
   long long off;
   int n_cell, n_near, n_far, first, count;
   double cx, cy, cz;
+  double px;  // x of the massless entries that pad a tile
 };
+
+// Padding lies outside the group's box in x, by a distance that survives
+// rounding in any unit of length, so that r > 0 for every particle.  It may lie
+// inside a search reach: it is never a neighbour candidate (see near_group).
+constexpr double kDummyOffset = 1.0e3;
 
 // Reads the list header of the gi-th group (in work order); every field is
 // wave-uniform.  Returns false for a group whose walk overflowed.
@@ -59,6 +65,8 @@ __device__ __forceinline__ bool group_header(const ForceArgs &A, int gi, GroupHd
   h.cx = 0.5 * (A.wn[node].lo[0] + A.wn[node].hi[0]);
   h.cy = 0.5 * (A.wn[node].lo[1] + A.wn[node].hi[1]);
   h.cz = 0.5 * (A.wn[node].lo[2] + A.wn[node].hi[2]);
+  const double hx = A.wn[node].hi[0];
+  h.px = hx + kDummyOffset * (1.0 + fabs(hx));
   return true;
 }
 
@@ -71,7 +79,6 @@ __device__ __forceinline__ void tile_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-constexpr double kDummyOffset = 1.0e3;  // distance of padding entries from the group centre
 constexpr double kTinyR2 = 1.0e-150;     // floor of r^2 in the near kernel (see there)
 // relative margin on reach^2 for neighbour candidates: it covers the rounding
 // of r^2 as computed here, so no pair the exact test keeps is missed
@@ -189,6 +196,9 @@ struct Lay {
   static __device__ __forceinline__ int first(int lane, int span) { return HALF && lane >= 32 ? span : 0; }
 };
 
+// a mask of the lowest k bits (none for k <= 0, all for k >= 32)
+__device__ __forceinline__ unsigned low_bits(int k) { return k >= 32 ? ~0u : k <= 0 ? 0u : (1u << k) - 1u; }
+
 // The near terms of the tiles from list position `from` on, every `step`
 // positions (multiples of WAVE), added to (ax, ay, az).
 template <bool MIXED, int IPL, int UNR, bool HALF>
@@ -203,8 +213,8 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
     const int k = Lay<HALF>::slot(lane) + Lay<HALF>::STRIDE * s;
     ii[s] = k < h.count ? h.first + k : -1;
     const int i = ii[s] >= 0 ? ii[s] : h.first;
-    // an empty slot sits far from the group and from the padding entries
-    xi[s] = ii[s] >= 0 ? A.sx[i] : h.cx - 2.0 * kDummyOffset;
+    // an empty slot sits beyond the padding entries
+    xi[s] = ii[s] >= 0 ? A.sx[i] : 2.0 * h.px - h.cx;
     yi[s] = A.sy[i];
     zi[s] = A.sz[i];
     invi[s] = A.sinv[i];
@@ -236,8 +246,8 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
       }
       nj = j;
     } else if (lane < ntp) {
-      // padding: massless, beyond every reach and every cut-off
-      na = make_double4(h.cx + kDummyOffset, h.cy, h.cz, 0.0);
+      // padding: massless, without a reach or a cut-off of its own
+      na = make_double4(h.px, h.cy, h.cz, 0.0);
       nb = make_double2(1.0, 0.0);
       nf = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
       nj = -2;
@@ -333,11 +343,14 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
         az[s] += (double)tz[s];
       }
     }
-    // hand this tile's candidates to the exact test: one of each lane a round
+    // hand this tile's candidates to the exact test: one of each lane a round.
+    // The padding behind the lane's entries is masked out: it has no particle
+    // index, and a reach of a thousand units of length may cover it.
     if (A.collect) {
+      const unsigned real0 = low_bits(nt - e0), real1 = low_bits(nt - e0 - 32);
 #pragma unroll
       for (int s = 0; s < IPL; ++s) {
-        unsigned m0 = ii[s] >= 0 ? cm[0][s] : 0u, m1 = !HALF && ii[s] >= 0 ? cm[1][s] : 0u;
+        unsigned m0 = ii[s] >= 0 ? cm[0][s] & real0 : 0u, m1 = !HALF && ii[s] >= 0 ? cm[1][s] & real1 : 0u;
         for (;;) {
           const bool has = (m0 | m1) != 0u;
           const unsigned long long bal = __ballot(has);
@@ -397,7 +410,7 @@ __device__ __forceinline__ void far_group(const ForceArgs &A, const GroupHdr &h,
         const int j = Lf[t0 + lane];
         T.d[lane] = make_double4(A.sx[j], A.sy[j], A.sz[j], A.G * A.sm[j]);
       } else if (lane < ntp) {
-        T.d[lane] = make_double4(h.cx + kDummyOffset, h.cy, h.cz, 0.0);
+        T.d[lane] = make_double4(h.px, h.cy, h.cz, 0.0);
       }
       tile_sync();
       for (int jj = 0; jj < span; jj += UNR) {
@@ -435,7 +448,7 @@ __device__ __forceinline__ void far_group(const ForceArgs &A, const GroupHdr &h,
         T.f[lane] = make_float4((float)(A.sx[j] - h.cx), (float)(A.sy[j] - h.cy), (float)(A.sz[j] - h.cz),
                                 (float)(A.G * A.sm[j]));
       } else if (lane < ntp) {
-        T.f[lane] = make_float4((float)kDummyOffset, 0.0f, 0.0f, 0.0f);
+        T.f[lane] = make_float4((float)(h.px - h.cx), 0.0f, 0.0f, 0.0f);
       }
       tile_sync();
       float tx[IPL], ty[IPL], tz[IPL];
@@ -557,7 +570,7 @@ __device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h
           T.d.qb[lane] = make_double2(G * c.q[4], G * c.q[5]);
         }
       } else if (lane < ntp) {
-        T.d.a[lane] = make_double4(h.cx + kDummyOffset, h.cy, h.cz, 0.0);
+        T.d.a[lane] = make_double4(h.px, h.cy, h.cz, 0.0);
         if (QUAD) {
           T.d.qa[lane] = make_double4(0.0, 0.0, 0.0, 0.0);
           T.d.qb[lane] = make_double2(0.0, 0.0);
@@ -607,7 +620,7 @@ __device__ __forceinline__ void cell_group(const ForceArgs &A, const GroupHdr &h
           T.f.qb[lane] = make_float2((float)(G * c.q[4]), (float)(G * c.q[5]));
         }
       } else if (lane < ntp) {
-        T.f.a[lane] = make_float4((float)kDummyOffset, 0.0f, 0.0f, 0.0f);
+        T.f.a[lane] = make_float4((float)(h.px - h.cx), 0.0f, 0.0f, 0.0f);
         if (QUAD) {
           T.f.qa[lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
           T.f.qb[lane] = make_float2(0.0f, 0.0f);
