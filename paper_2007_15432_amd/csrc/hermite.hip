@@ -447,7 +447,7 @@ __device__ __forceinline__ void seg_body(const HermArgs &A, const int32_t *blist
     m = A.mass[gid];
     ro = A.ro[gid];
   }
-  const double invi = 1.0 / ro;
+  const double invi = inv_cutoff(ro);
   wave_sync();
   if (put) {
     L.pgm[me] = A.G * m;
@@ -860,7 +860,7 @@ __device__ __forceinline__ void wave_body(const HermArgs &A, const int32_t *blis
     m = A.mass[gid];
     ro = A.ro[gid];
   }
-  const double invi = 1.0 / ro;
+  const double invi = inv_cutoff(ro);
   const double GM = A.GM, tick = A.tick;
   int mycid = lane;                                        // COLL: composite of this slot
   double eps[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};          // COLL: dissipations (summed on every lane)
@@ -1280,7 +1280,7 @@ __device__ __forceinline__ void big_body(const HermArgs &A, int c, int bk, const
       m[u] = A.mass[gid[u]];
       ro = A.ro[gid[u]];
     }
-    invi[u] = 1.0 / ro;
+    invi[u] = inv_cutoff(ro);
     L.px[k] = x[u][0];
     L.py[k] = x[u][1];
     L.pz[k] = x[u][2];
@@ -2076,7 +2076,7 @@ __global__ __launch_bounds__(HUGE_T) void k_huge_load(HermArgs A, HugeArgs H) {
     const double m = A.mass[g];
     H.m[k] = m;
     H.gm[k] = A.G * m;
-    H.inv[k] = 1.0 / A.ro[g];
+    H.inv[k] = inv_cutoff(A.ro[g]);
     H.t[k] = 0;
     H.e[k] = 0.5 * m * dot3(v, v) - A.GM * m * rsqrt(dot3(x, x));
   }

@@ -81,6 +81,14 @@ __device__ __forceinline__ double rsqrt_pos(double x) {
   return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
+// 1 / r_out, bounded for r_out = 0.  The pair terms multiply it by factors that
+// vanish beyond the cut-off, and by zeros for a particle with itself: 0 times
+// infinity would be a NaN.  A pair takes the smaller of its two.
+__device__ __forceinline__ double inv_cutoff(double ro) {
+  const double i = 1.0 / ro;
+  return i > 1e300 ? 1e300 : i;
+}
+
 __device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)); }
 
 __device__ __forceinline__ int popc_below(unsigned long long mask) {
