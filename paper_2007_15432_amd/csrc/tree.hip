@@ -224,7 +224,7 @@ __global__ __launch_bounds__(GT_T) void k_gather_tree(
         sm[k] = r[6];
         const double o = r[7], s = r[8];
         sro[k] = o;
-        sinv[k] = 1.0 / o;
+        sinv[k] = p3t::inv_cutoff(o);
         sreach[k] = fmax(o, s);
         srs[k] = s;
         sid[k] = i;

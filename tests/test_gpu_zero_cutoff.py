@@ -36,3 +36,22 @@ def test_clusters_with_zero_cutoffs(gpu, orc, sizes):
         assert np.array_equal(nst.cpu().numpy(), ns)
         assert np.abs(pos.cpu().numpy() - xo).max() < 1e-12 and np.abs(vel.cpu().numpy() - vo).max() < 1e-12
     ctx.close()
+
+
+@pytest.mark.parametrize("group", [8, 64, 128])
+def test_adjoint_with_a_zero_cutoff(gpu, orc, group):
+    n = 500
+    d = diskgen.workload("disk2k_equal", n)
+    p = orc.Params()
+    ro, rs, _ = orc.cutoffs(d.pos, d.vel, d.mass, p)
+    ro[17] = 0.0
+    lam = np.random.default_rng(group).normal(size=(3, n))
+    ogx, ogm = orc.soft_adjoint(d.pos, d.mass, ro, lam, p)
+    assert np.isfinite(ogx).all() and np.isfinite(ogm).all()
+    ctx = gpu.Context(gparams(gpu, p, theta=0.0, multipole=1, n_group_max=group, n_leaf_max=8))
+    ctx.build_tree(T(d.pos), T(d.vel), T(d.mass), T(ro), T(rs))
+    ctx.compute_soft_force()
+    gx, gm = ctx.soft_kick_adjoint(T(lam), 0.5)
+    assert np.abs(gx.cpu().numpy() - 0.5 * ogx).max() < 1e-12 * np.abs(0.5 * ogx).max()
+    assert np.abs(gm.cpu().numpy() - 0.5 * ogm).max() < 1e-12 * np.abs(0.5 * ogm).max()
+    ctx.close()
