@@ -130,6 +130,25 @@ __device__ __forceinline__ unsigned long long wave_fetch_add(unsigned long long 
   return (unsigned long long)uniform_lane64((long long)r, from);
 }
 
+// hist[idx] += 1 for the active lanes that have `valid`, one atomic for the
+// lanes that share the first lane's entry, until the first lane left is the only
+// one with its entry; the others then add one by one.  Atomics on one entry
+// queue up, 12 ns each: keys that agree in a digit (a disk in the box of one
+// particle far out, labels of few classes) would wait for a tile's worth of them.
+__device__ __forceinline__ void count_entry(uint32_t *hist, uint32_t idx, bool valid) {
+  const int lane = lane_id();
+  unsigned long long left = __ballot(valid);
+  while (left != 0ull) {  // uniform
+    const int lead = __ffsll((long long)left) - 1;
+    const unsigned long long same = __ballot(idx == (uint32_t)uniform_lane((int)idx, lead)) & left;
+    const int m = (int)__popcll(same);
+    if (m == 1) break;
+    if (lane == lead) atomicAdd(&hist[idx], (uint32_t)m);
+    left &= ~same;
+  }
+  if ((left >> lane) & 1ull) atomicAdd(&hist[idx], 1u);
+}
+
 // Union-find over the neighbour pairs.  The larger root is hooked under the
 // smaller one, so every root stays its component's minimum index.
 __device__ __forceinline__ int uf_load(int32_t *p, int i) {

@@ -116,7 +116,7 @@ __global__ __launch_bounds__(BB_T) void k_morton(int64_t n, const double *__rest
       const uint64_t key = (spread3(u[0]) << 2) | (spread3(u[1]) << 1) | spread3(u[2]);
       keys[i] = key;
       perm[i] = (int32_t)i;
-      if (hist) atomicAdd(&hist[(i / tile) * 256 + (int64_t)(key & 255u)], 1u);
+      if (hist) p3t::count_entry(hist, (uint32_t)(i / tile) * 256u + (uint32_t)(key & 255u), true);
       // the records through LDS: stored lane by lane, every instruction
       // would leave 64 partial lines
       double *r = lrec + PACK * threadIdx.x;

@@ -163,7 +163,7 @@ __global__ __launch_bounds__(RS_T) void k_radix_tile_hist(const uint64_t *__rest
 __global__ __launch_bounds__(256) void k_radix_hist(const uint64_t *__restrict__ kin, int64_t n, int shift, int tile,
                                                     uint32_t *__restrict__ hist) {
   for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
-    atomicAdd(&hist[(k / tile) * 256 + ((unsigned)(kin[k] >> shift) & 255u)], 1u);
+    count_entry(hist, (uint32_t)(k / tile) * 256u + ((unsigned)(kin[k] >> shift) & 255u), true);
 }
 
 // Column d of hist (tile counts of digit d) becomes its exclusive scan, tot[d]
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(RS_T) void k_radix_pass(const uint64_t *__restrict_
     const uint32_t off = gbase[d] + (uint32_t)p - lstart[d];
     kout[off] = k;
     if (VALS) vout[off] = lv[p];
-    if (hist_next) atomicAdd(&hist_next[(off / TILE) * 256u + ((unsigned)(k >> (shift + 8)) & 255u)], 1u);
+    if (hist_next) count_entry(hist_next, (off / TILE) * 256u + ((unsigned)(k >> (shift + 8)) & 255u), true);
   }
 }
 
