@@ -96,8 +96,8 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   total += bytes(n_cap, sizeof(GroupList));
   total += 2 * bytes(n_cap, sizeof(int32_t));                                       // group order, classes
   total += bytes(WALK_PARTS * WALK_QUEUE_STRIDE, sizeof(unsigned long long));       // walk queues
-  total += 4 * bytes(n_cap, sizeof(int32_t));                    // row_cnt, cl_cnt, cl_slot, cl_start
-  total += bytes(2, sizeof(int64_t)) + bytes(scan_sums_need(), sizeof(uint64_t));  // cluster count, scan sums
+  total += 3 * bytes(n_cap, sizeof(int32_t)) + bytes(label_counters_need(n_cap), sizeof(int32_t));  // row_cnt, cl_*
+  total += bytes(3, sizeof(int64_t)) + bytes(scan_sums_need(), sizeof(uint64_t));  // cluster count, scan sums
   total += bytes(n_cap, sizeof(int32_t)) + 2 * bytes(n_cap, sizeof(uint64_t));      // uf, cl keys
   total += bytes(cut_part_need(n_cap), sizeof(double)) + bytes(n_cap, sizeof(int32_t));  // cut-off bins
   total += bytes(n_cap + 4, sizeof(uint8_t));                                                // close flags
@@ -121,8 +121,8 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   c->cnt = A.take<DevCounters>(1);
   // (with the counters, so that one call clears what is zero between calls)
   c->row_cnt = A.take<int32_t>(n_cap);
-  c->cl_cnt = A.take<int32_t>(n_cap);
-  c->cl_nc = A.take<int64_t>(2);
+  c->cl_cnt = A.take<int32_t>(label_counters_need(n_cap));
+  c->cl_nc = A.take<int64_t>(3);
   c->bbox_part = A.take<double>(6 * 1024);
   double **soa[11] = {&c->sx, &c->sy, &c->sz, &c->svx, &c->svy, &c->svz, &c->sm, &c->sro, &c->sinv, &c->sreach, &c->srs};
   for (auto p : soa) *p = A.take<double>(n_cap);
@@ -166,7 +166,7 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   c->hs_cl_mem = A.take<int32_t>(n_cap + 1);
   if (!c->hs_cl_mem) return fail(c, P3T_ERR_HIP, "arena layout overflow (internal)");
   // zero between calls: every pass that counts into them leaves them clear
-  const size_t clear = (size_t)((char *)(c->cl_nc + 2) - (char *)c->cnt);
+  const size_t clear = (size_t)((char *)(c->cl_nc + 3) - (char *)c->cnt);
   HIP_OK(c, hipMemsetAsync(c->cnt, 0, clear, c->stream));
   c->n_cap = n_cap;
   c->tree_valid = c->force_valid = false;
@@ -955,6 +955,7 @@ p3t_status p3t_hard_step(p3t_ctx *c, double *pos3, double *vel3, const double *m
   hipError_t e = prepared ? (hc[HERM_BC_BAD] ? hipErrorInvalidDevicePointer : hipSuccess)
                           : herm_bucket(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, c->cl_nc, hc, close_src(c), true);
   HIP_OK(c, e);
+  if (hc[HERM_BC_UNSORTED]) HIP_OK(c, members_sorted(c, n, c->hs_label, c->hs_cl_mem));
   HIP_OK(c, aux_streams(c));
   HIP_OK(c, herm_launch(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, pos3, vel3, mass, r_out, dt_hard, nullptr, nullptr,
                         steps, hc, 0, 0, c->stream, c->aux_stream, c->aux_ev[0], c->aux_ev[1]));
@@ -1006,6 +1007,7 @@ p3t_status p3t_hard_step_collide(p3t_ctx *c, double *pos3, double *vel3, const d
   hipError_t e = prepared ? (hcw[HERM_BC_BAD] ? hipErrorInvalidDevicePointer : hipSuccess)
                           : herm_bucket(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, c->cl_nc, hcw, close_src(c), true);
   HIP_OK(c, e);
+  if (hcw[HERM_BC_UNSORTED]) HIP_OK(c, members_sorted(c, n, c->hs_label, c->hs_cl_mem));
   HIP_OK(c, aux_streams(c));
   HIP_OK(c, herm_launch(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, pos3, vel3, mass, r_out, dt_hard, nullptr, nullptr,
                         steps, hcw, 0, 0, c->stream, c->aux_stream, c->aux_ev[0], c->aux_ev[1], &hc));
@@ -1133,6 +1135,7 @@ p3t_status p3t_hard_evaluate(p3t_ctx *c, double *pos3, double *vel3, const doubl
                           : herm_bucket(c, n, n, c->hs_cl_ptr, c->hs_cl_mem, c->cl_nc, hc, close_src(c), true);
   if (n_clusters_host) *n_clusters_host = hc[HERM_BC_NC];
   HIP_OK(c, e);
+  if (hc[HERM_BC_UNSORTED]) HIP_OK(c, members_sorted(c, n, c->hs_label, c->hs_cl_mem));
   HIP_OK(c, aux_streams(c));
   const int budget = split ? (slow_log2 < 30 ? 1 << slow_log2 : 1 << 30) : 0;
   if (split) {

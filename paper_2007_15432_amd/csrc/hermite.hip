@@ -1654,7 +1654,7 @@ __device__ __forceinline__ int bucket_of(int size, int cap) {
 
 struct BucketArgs {
   int64_t nc_host;
-  const int64_t *nc_dev;
+  const int64_t *nc_dev;  // (nullable) the count on the device, two words behind it the unsorted flag
   int64_t stride, n;
   int cap;  // clusters above this many members take the percolated-cluster path
   const int32_t *cl_ptr, *members;
@@ -1705,6 +1705,7 @@ __global__ __launch_bounds__(BK_T) void k_bucket(BucketArgs B) {
   const int64_t nc = B.nc_dev ? *B.nc_dev : B.nc_host;  // clusters (at most stride)
   if (blockIdx.x == 0 && t == 0) {
     B.bcount[BC_NC] = (int32_t)nc;
+    if (B.nc_dev) B.bcount[HERM_BC_UNSORTED] = (int32_t)B.nc_dev[2];
     if (B.reset_work) {  // the work counters of this hard part
       B.cnt->n_heval = 0;
       B.cnt->n_hpair = 0;

@@ -17,11 +17,12 @@
 // Cluster CSR by counting: members per label, a scan of (cluster, size) over
 // the labels, members into their cluster's range, ranges sorted.  Most
 // particles are clusters of their own and every cluster starts with its label's
-// particle, so only the others take an atomic and only clusters of three and
-// more need sorting: five short launches, where a radix sort of (label, index)
-// took two or three passes of three launches, a flag pass and a scan.  With the
-// bucket lists of the hard part: 65,536 particles 96 -> 34 us, 2^20 190 ->
-// 75 us; neighbour lists and clusters of 65,536 particles 208 -> 82 us a call.
+// particle, so only the others take a slot and only clusters of three and more
+// need sorting: five short launches.  With the bucket lists of the hard part, a
+// radix sort of (label, index) against this: 65,536 particles 96 -> 34 us, 2^20
+// 190 -> 75 us.  Where many members share a label (a percolated disk, a caller's
+// classes), ordering the members is left to the radix sort after all, whose
+// cost does not depend on the cluster sizes (see CL_WORK).
 #include <algorithm>
 
 #include "p3t_internal.h"
@@ -41,10 +42,39 @@ static inline unsigned g1d(int64_t n, int64_t cap = 65536) {
 //   CL_ROWS: cnt[i] entries in row i
 constexpr int CL_ROOT = 0, CL_ANY = 1, CL_ROWS = 2;
 constexpr int CS_T = 256, CS_CHUNK = 4 * CS_T, CS_BLOCKS = 1024;
+// words behind c->cl_nc: a label was out of range, members are not in order
+constexpr int CL_BAD = 1, CL_UNSORTED = 2;
+// Members ascending in every cluster (k_cl_sort): up to CL_SMALL members by the
+// cluster's thread in place, larger ones one after another by the wavefront
+// that holds their thread, which ranks m members in about m + m^2 / 64 steps.
+// Where a wavefront's clusters add up to more than CL_WORK steps, or a cluster
+// exceeds CL_LARGE members, the members are sorted by label and index instead
+// (members_sorted).  CL_WORK is some ten microseconds, a sixth of that sort's
+// launches.  Without the line, 2^20 particles in 512 classes took 212 ms (the
+// sort alone: see members_sorted) and 65,536 in clusters of 128 took 1.0 ms.
+constexpr int CL_SMALL = 12, CL_WORK = 2048;
+constexpr uint32_t CL_LARGE = 320;  // m + m^2 / 64 <= CL_WORK
+
+// The counter of label or row i.  A caller's labels (CL_ANY) are often small
+// neighbouring numbers, and atomics on one cache line queue up like those on one
+// counter: their counters are dealt to parts of cnt, few of them where the
+// labels of a wavefront's particles may as well be neighbours and their atomics
+// share a line.  2^20 particles in 512 classes 0 to 511, counting launch: 273 us
+// in one part, 165 in 32, 62 in 256 (16 with the tiles below).
+constexpr int64_t CC_WAVE_MAX = 1 << 17;  // up to here k_cl_count, above it k_cl_count_tile
+constexpr int CNT_PARTS = 256;            // at most
 
 template <int KIND>
-__device__ __forceinline__ uint64_t item(const int32_t *__restrict__ label, const int32_t *__restrict__ cnt, int64_t i) {
-  const uint64_t c = (uint32_t)cnt[i];
+__device__ __forceinline__ int64_t counter(int64_t i, int64_t n) {
+  if (KIND != CL_ANY) return i;
+  const int lg = n <= CC_WAVE_MAX ? 4 : 8;
+  return (i & ((1 << lg) - 1)) * ((n + (1 << lg) - 1) >> lg) + (i >> lg);
+}
+
+template <int KIND>
+__device__ __forceinline__ uint64_t item(const int32_t *__restrict__ label, const int32_t *__restrict__ cnt, int64_t i,
+                                         int64_t n) {
+  const uint64_t c = (uint32_t)cnt[counter<KIND>(i, n)];
   if (KIND == CL_ROOT) return label[i] == (int32_t)i ? (1ull << 32) + 1ull + c : 0ull;
   if (KIND == CL_ANY) return c > 0 ? (1ull << 32) + c : 0ull;
   return c;
@@ -67,13 +97,16 @@ __device__ __forceinline__ uint64_t block_sum(uint64_t v, uint64_t *ws) {
   return r;
 }
 
+// (also clears the flag that the launches behind it set, nullable)
 template <int KIND>
 __global__ __launch_bounds__(CS_T) void k_item_sums(int64_t n, int64_t tile, const int32_t *__restrict__ label,
-                                                    const int32_t *__restrict__ cnt, uint64_t *__restrict__ sums) {
+                                                    const int32_t *__restrict__ cnt, uint64_t *__restrict__ sums,
+                                                    int64_t *__restrict__ unsorted) {
   __shared__ uint64_t ws[CS_T / WAVE];
+  if (unsorted && blockIdx.x == 0 && threadIdx.x == 0) *unsorted = 0;
   const int64_t a = (int64_t)blockIdx.x * tile, b = a + tile < n ? a + tile : n;
   uint64_t s = 0;
-  for (int64_t i = a + threadIdx.x; i < b; i += CS_T) s += item<KIND>(label, cnt, i);
+  for (int64_t i = a + threadIdx.x; i < b; i += CS_T) s += item<KIND>(label, cnt, i, n);
   s = block_sum(s, ws);
   if (threadIdx.x == 0) sums[blockIdx.x] = s;
 }
@@ -81,14 +114,16 @@ __global__ __launch_bounds__(CS_T) void k_item_sums(int64_t n, int64_t tile, con
 // Every workgroup adds the sums before its own itself, then scans its tile.
 // Clusters: their first slot into start[] (by label) and cl_ptr[] (by
 // cluster), CL_ROOT also the root into its slot; cnt is left cleared; the
-// cluster count goes to *nc, and clear[0, n_clear) is cleared for the launch
-// that buckets the clusters.  Rows: row_ptr.
+// cluster count goes to *out64, clear[0, n_clear) is cleared for the launch
+// that buckets the clusters, and a cluster above CL_LARGE members sets
+// *unsorted.  Rows: row_ptr.
 template <int KIND>
 __global__ __launch_bounds__(CS_T) void k_item_place(int64_t n, int64_t tile, const int32_t *__restrict__ label,
                                                      int32_t *__restrict__ cnt, const uint64_t *__restrict__ sums,
                                                      int32_t *__restrict__ start, int32_t *__restrict__ cl_ptr,
                                                      int32_t *__restrict__ members, int64_t *__restrict__ out64,
-                                                     int32_t *__restrict__ clear, int n_clear) {
+                                                     int64_t *__restrict__ unsorted, int32_t *__restrict__ clear,
+                                                     int n_clear) {
   __shared__ uint64_t ws[CS_T / WAVE];
   const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE;
   uint64_t run = 0;
@@ -102,7 +137,7 @@ __global__ __launch_bounds__(CS_T) void k_item_place(int64_t n, int64_t tile, co
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int64_t i = c0 + 4 * t + q;
-      v[q] = i < b ? item<KIND>(label, cnt, i) : 0ull;
+      v[q] = i < b ? item<KIND>(label, cnt, i, n) : 0ull;
       s += v[q];
     }
     uint64_t incl = s;
@@ -131,7 +166,8 @@ __global__ __launch_bounds__(CS_T) void k_item_place(int64_t n, int64_t tile, co
         start[i] = o;
         cl_ptr[at >> 32] = o;
         if (KIND == CL_ROOT) members[o] = (int32_t)i;
-        if ((uint32_t)v[q] > (KIND == CL_ROOT ? 1u : 0u)) cnt[i] = 0;
+        if ((uint32_t)v[q] > (KIND == CL_ROOT ? 1u : 0u)) cnt[counter<KIND>(i, n)] = 0;
+        if ((uint32_t)v[q] > CL_LARGE) *unsorted = 1;
       }
       at += v[q];
     }
@@ -153,11 +189,14 @@ static void scan_items(p3t_ctx *c, int64_t n, const int32_t *label, int32_t *cnt
   const int64_t tile = scan_tile(n);
   const unsigned g = (unsigned)((n + tile - 1) / tile);
   uint64_t *sums = reinterpret_cast<uint64_t *>(c->cl_sums);
-  hipLaunchKernelGGL(k_item_sums<KIND>, dim3(g), dim3(CS_T), 0, c->stream, n, tile, label, (const int32_t *)cnt, sums);
+  int64_t *unsorted = KIND == CL_ROWS ? nullptr : c->cl_nc + CL_UNSORTED;
+  hipLaunchKernelGGL(k_item_sums<KIND>, dim3(g), dim3(CS_T), 0, c->stream, n, tile, label, (const int32_t *)cnt, sums,
+                     unsorted);
   hipLaunchKernelGGL(k_item_place<KIND>, dim3(g), dim3(CS_T), 0, c->stream, n, tile, label, cnt, (const uint64_t *)sums,
-                     c->cl_start, cl_ptr, members, out64, clear, n_clear);
+                     c->cl_start, cl_ptr, members, out64, unsorted, clear, n_clear);
 }
 int64_t scan_sums_need() { return CS_BLOCKS; }
+int64_t label_counters_need(int64_t n_cap) { return n_cap + CNT_PARTS; }
 
 // ------------------------------------------------------------------ neighbour CSR
 __global__ void k_pair_count(const int2 *__restrict__ pairs, int64_t np, int32_t *__restrict__ cnt) {
@@ -204,132 +243,199 @@ hipError_t neighbour_csr(p3t_ctx *c, int64_t n, int64_t np, int64_t *row_ptr, in
 }
 
 // ------------------------------------------------------------------ cluster CSR
-// labels from the union-find; every member but the root takes a slot behind it
-__global__ void k_cl_labels(int64_t n, int32_t *uf, int32_t *__restrict__ label, int32_t *__restrict__ cnt,
-                            int32_t *__restrict__ slot) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+// The label of every particle and its slot among those that share it (in any
+// order): from the union-find (CL_ROOT, every member but the root takes a slot
+// behind it) or the caller's labels (CL_ANY, one outside [0, n) is reported).
+// The atomics of one label queue up, 12 ns each, so they are taken for several
+// members at once.  Counting launch, one atomic per member against this: 2^20
+// particles of one label 12 ms -> 14 us, of distinct labels 46 -> 47.
+
+// label of particle i, -1 where no slot is wanted
+template <int KIND>
+__device__ __forceinline__ int slot_label(int64_t i, int64_t n, int32_t *uf, int32_t *__restrict__ label,
+                                          int64_t *__restrict__ bad) {
+  if (i >= n) return -1;
+  if (KIND == CL_ROOT) {
     const int r = uf_find(uf, (int)i);
     label[i] = r;
-    if (r != (int)i) slot[i] = 1 + atomicAdd(&cnt[r], 1);
+    return r != (int)i ? r : -1;
   }
+  const int l = label[i];
+  if ((uint32_t)l < (uint64_t)n) return l;
+  *bad = 1;
+  return -1;
 }
 
-// caller's labels: a slot per member; a label outside [0, n) is reported
-__global__ void k_cl_count(int64_t n, const int32_t *__restrict__ label, int32_t *__restrict__ cnt,
-                           int32_t *__restrict__ slot, int64_t *__restrict__ bad) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const int l = label[i];
-    if ((uint32_t)l < (uint64_t)n)
-      slot[i] = atomicAdd(&cnt[l], 1);
-    else
-      *bad = 1;
+// One atomic per label that the wavefront's first lanes share; as soon as the
+// first lane left is the only one with its label, the others go one by one:
+// many labels, which do not queue up, or few and most of them counted.
+template <int KIND>
+__global__ __launch_bounds__(CS_T) void k_cl_count(int64_t n, int32_t *uf, int32_t *__restrict__ label,
+                                                   int32_t *__restrict__ cnt, int32_t *__restrict__ slot,
+                                                   int64_t *__restrict__ bad) {
+  const int64_t i = (int64_t)blockIdx.x * CS_T + threadIdx.x;
+  const int l = slot_label<KIND>(i, n, uf, label, bad), lane = lane_id();
+  int s = 0;
+  unsigned long long left = __ballot(l >= 0);
+  while (left != 0ull) {  // uniform
+    const int lead = __ffsll((long long)left) - 1;
+    const unsigned long long same = __ballot(l == uniform_lane(l, lead)) & left;
+    const int m = (int)__popcll(same);
+    if (m == 1) break;
+    int base = 0;
+    if (lane == lead) base = atomicAdd(&cnt[counter<KIND>(l, n)], m);
+    base = uniform_lane(base, lead);
+    if ((same >> lane) & 1ull) s = base + popc_below(same);
+    left &= ~same;
+  }
+  if ((left >> lane) & 1ull) s = atomicAdd(&cnt[counter<KIND>(l, n)], 1);
+  if (l >= 0) slot[i] = (KIND == CL_ROOT ? 1 : 0) + s;
+}
+
+// The same by tiles of 4096, whose labels a workgroup counts in an LDS table
+// (at most half full): 1.2 launches of the former for distinct labels of 2^20
+// particles, but 64 labels do not queue up either.
+constexpr int CT_T = 1024, CT_I = 4, CT_SLOTS = 2 * CT_T * CT_I;
+
+template <int KIND>
+__global__ __launch_bounds__(CT_T) void k_cl_count_tile(int64_t n, int32_t *uf, int32_t *__restrict__ label,
+                                                        int32_t *__restrict__ cnt, int32_t *__restrict__ slot,
+                                                        int64_t *__restrict__ bad) {
+  __shared__ int key[CT_SLOTS], val[CT_SLOTS];
+  const int t = threadIdx.x;
+  for (int64_t base = (int64_t)blockIdx.x * (CT_T * CT_I); base < n;
+       base += (int64_t)gridDim.x * (CT_T * CT_I)) {  // uniform
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2 * CT_I; ++q) {
+      key[q * CT_T + t] = -1;
+      val[q * CT_T + t] = 0;
+    }
+    int l[CT_I];
+#pragma unroll
+    for (int q = 0; q < CT_I; ++q) l[q] = slot_label<KIND>(base + q * CT_T + t, n, uf, label, bad);
+    __syncthreads();
+    int at[CT_I], rank[CT_I];  // table entry and place among the tile's members
+#pragma unroll
+    for (int q = 0; q < CT_I; ++q) {
+      if (l[q] < 0) continue;
+      unsigned h = ((unsigned)l[q] * 2654435761u) / (0xffffffffu / CT_SLOTS + 1u);
+      for (;;) {
+        const int k = atomicCAS(&key[h], -1, l[q]);
+        if (k == -1 || k == l[q]) break;
+        h = (h + 1) & (CT_SLOTS - 1);
+      }
+      at[q] = (int)h;
+      rank[q] = atomicAdd(&val[h], 1);
+    }
+    __syncthreads();
+    int k[2 * CT_I], v[2 * CT_I];
+#pragma unroll
+    for (int q = 0; q < 2 * CT_I; ++q) {
+      k[q] = key[q * CT_T + t];
+      v[q] = val[q * CT_T + t];
+    }
+    // (all of them issued before the first is waited for)
+#pragma unroll
+    for (int q = 0; q < 2 * CT_I; ++q)
+      if (k[q] >= 0) v[q] = atomicAdd(&cnt[counter<KIND>(k[q], n)], v[q]);
+#pragma unroll
+    for (int q = 0; q < 2 * CT_I; ++q) val[q * CT_T + t] = v[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < CT_I; ++q)
+      if (l[q] >= 0) slot[base + q * CT_T + t] = (KIND == CL_ROOT ? 1 : 0) + val[at[q]] + rank[q];
   }
 }
 
 template <int KIND>
+static void count_labels(p3t_ctx *c, int64_t n, int32_t *label) {
+  auto go = [&](auto kernel, int64_t g, int t) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)std::min<int64_t>(65536, g)), dim3(t), 0, c->stream, n, c->uf_parent, label,
+                       c->cl_cnt, c->cl_slot, c->cl_nc + CL_BAD);
+  };
+  if (n <= CC_WAVE_MAX)
+    go(k_cl_count<KIND>, (n + CS_T - 1) / CS_T, CS_T);
+  else
+    go(k_cl_count_tile<KIND>, (n + CT_T * CT_I - 1) / (CT_T * CT_I), CT_T);
+}
+
+template <int KIND>
 __global__ void k_cl_fill(int64_t n, const int32_t *__restrict__ label, const int32_t *__restrict__ start,
-                          const int32_t *__restrict__ slot, int32_t *__restrict__ members) {
+                          const int32_t *__restrict__ slot, const int64_t *__restrict__ unsorted,
+                          int32_t *__restrict__ members) {
+  // (the hard part reads its members before they are in order: CL_ROOT fills them in any case)
+  if (KIND == CL_ANY && *unsorted) return;  // uniform: sorted from the labels instead
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const int l = label[i];
     if (KIND == CL_ROOT ? l != (int)i : (uint32_t)l < (uint64_t)n) members[start[l] + slot[i]] = (int32_t)i;
   }
 }
 
-// Members ascending in every cluster.  Up to CL_SMALL members by the
-// cluster's thread in place; up to CL_WAVE by one wavefront that ranks them in
-// LDS; above that (a percolated graph) by the workgroup, which rereads the
-// labels of all particles and compacts those of the cluster.
-constexpr int CL_SMALL = 12, CL_WAVE = 1024;
-
+// members ascending in every cluster (see CL_WORK)
 __global__ __launch_bounds__(CS_T) void k_cl_sort(int64_t n, const int64_t *__restrict__ nc_dev,
-                                                  const int32_t *__restrict__ cl_ptr,
-                                                  const int32_t *__restrict__ label, int32_t *__restrict__ members) {
-  __shared__ int32_t buf[CS_T / WAVE][CL_WAVE];
-  __shared__ int list[CS_T], n_list;
-  __shared__ int wsum[CS_T / WAVE];
-  const int t = threadIdx.x, lane = t & (WAVE - 1), w = uniform_first(t / WAVE);
-  const int64_t nc = *nc_dev;
-  if (t == 0) n_list = 0;
-  __syncthreads();
-  const int64_t c = (int64_t)blockIdx.x * CS_T + t;
-  if (c < nc) {
-    const int a = cl_ptr[c], b = cl_ptr[c + 1];
-    if (b - a > CL_SMALL) {
-      list[atomicAdd(&n_list, 1)] = (int)c;
-    } else {
-      for (int k = a + 1; k < b; ++k) {
-        const int32_t v = members[k];
-        int q = k - 1;
-        while (q >= a && members[q] > v) {
-          members[q + 1] = members[q];
-          --q;
-        }
-        members[q + 1] = v;
+                                                  const int32_t *__restrict__ cl_ptr, int64_t *unsorted,
+                                                  int32_t *__restrict__ members) {
+  __shared__ int32_t buf[CS_T / WAVE][CL_LARGE];
+  const int lane = threadIdx.x & (WAVE - 1), w = uniform_first((int)threadIdx.x / WAVE);
+  // (clusters above CL_LARGE set the flag before this launch)
+  if (uniform_first((int)__hip_atomic_load(unsorted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) return;
+  // consecutive clusters in the lanes; where they hold more than CL_SMALL
+  // members on average, dealt to all wavefronts instead
+  const int64_t nc = *nc_dev, nw = (int64_t)gridDim.x * (CS_T / WAVE), gw = (int64_t)blockIdx.x * (CS_T / WAVE) + w;
+  const int64_t c = nc * CL_SMALL <= n ? gw + lane * nw : gw * WAVE + lane;
+  const int a = c < nc ? cl_ptr[c] : 0, m = c < nc ? cl_ptr[c + 1] - a : 0;
+  if (m <= CL_SMALL) {
+    for (int k = a + 1; k < a + m; ++k) {
+      const int32_t v = members[k];
+      int q = k - 1;
+      while (q >= a && members[q] > v) {
+        members[q + 1] = members[q];
+        --q;
       }
+      members[q + 1] = v;
     }
   }
-  __syncthreads();
-  const int nl = n_list;
-  for (int e = w; e < nl; e += CS_T / WAVE) {  // uniform per wavefront
-    const int a = cl_ptr[list[e]], m = cl_ptr[list[e] + 1] - a;
-    if (m > CL_WAVE) continue;
-    for (int k = lane; k < m; k += WAVE) buf[w][k] = members[a + k];
+  unsigned long long large = __ballot(m > CL_SMALL && m <= (int)CL_LARGE);
+  if (large == 0ull) return;  // uniform
+  if (wave_sum(m > CL_SMALL ? m + m * m / WAVE : 0) > CL_WORK) {
+    if (lane == 0) *unsorted = 1;
+    return;
+  }
+  while (large != 0ull) {
+    const int l = __ffsll((long long)large) - 1;
+    large &= large - 1ull;
+    const int a0 = uniform_lane(a, l), k0 = uniform_lane(m, l);
+    for (int k = lane; k < k0; k += WAVE) buf[w][k] = members[a0 + k];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int k = lane; k < m; k += WAVE) {
+    for (int k = lane; k < k0; k += WAVE) {
       const int32_t v = buf[w][k];
       int r = 0;
-      for (int q = 0; q < m; ++q) r += buf[w][q] < v ? 1 : 0;
-      members[a + r] = v;
+#pragma unroll 8
+      for (int q = 0; q < k0; ++q) r += buf[w][q] < v ? 1 : 0;
+      members[a0 + r] = v;
     }
     __builtin_amdgcn_wave_barrier();
-  }
-  for (int e = 0; e < nl; ++e) {  // uniform over the workgroup
-    const int a = cl_ptr[list[e]], m = cl_ptr[list[e] + 1] - a;
-    if (m <= CL_WAVE) continue;
-    __syncthreads();  // every thread reads the label before a member is rewritten
-    const int l = label[members[a]];
-    __syncthreads();
-    int at = a;
-    for (int64_t i0 = 0; i0 < n; i0 += 4 * CS_T) {
-      int own = 0;
-      bool in[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int64_t i = i0 + 4 * t + q;
-        in[q] = i < n && label[i] == l;
-        own += in[q] ? 1 : 0;
-      }
-      const int incl = wave_incl_scan(own);
-      if (lane == WAVE - 1) wsum[w] = incl;
-      __syncthreads();
-      int o = at + incl - own;
-#pragma unroll
-      for (int q = 0; q < CS_T / WAVE; ++q) {
-        o += q < w ? wsum[q] : 0;
-        at += wsum[q];
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (in[q]) members[o++] = (int32_t)(i0 + 4 * t + q);
-      __syncthreads();
-    }
   }
 }
 
 // The clusters of the last evaluation: labels, cluster CSR and the cluster
 // count (c->cl_nc, on the device).  clear: words to clear on the way (the
-// bucket words).
+// bucket words).  Where c->cl_nc[CL_UNSORTED] ends up set, which the bucket
+// words report as HERM_BC_UNSORTED, the members are not in order:
+// members_sorted.
 hipError_t clusters_pairs(p3t_ctx *c, int64_t n, int32_t *label, int32_t *cl_ptr, int32_t *cl_members,
                           int32_t *clear, int n_clear) {
   hipStream_t s = c->stream;
-  hipLaunchKernelGGL(k_cl_labels, dim3(g1d(n)), dim3(256), 0, s, n, c->uf_parent, label, c->cl_cnt, c->cl_slot);
+  count_labels<CL_ROOT>(c, n, label);
   scan_items<CL_ROOT>(c, n, label, c->cl_cnt, cl_ptr, cl_members, c->cl_nc, clear, n_clear);
   hipLaunchKernelGGL(k_cl_fill<CL_ROOT>, dim3(g1d(n)), dim3(256), 0, s, n, (const int32_t *)label,
-                     (const int32_t *)c->cl_start, (const int32_t *)c->cl_slot, cl_members);
+                     (const int32_t *)c->cl_start, (const int32_t *)c->cl_slot,
+                     (const int64_t *)c->cl_nc + CL_UNSORTED, cl_members);
   hipLaunchKernelGGL(k_cl_sort, dim3((unsigned)((n + CS_T - 1) / CS_T)), dim3(CS_T), 0, s, n,
-                     (const int64_t *)c->cl_nc, (const int32_t *)cl_ptr, (const int32_t *)label, cl_members);
+                     (const int64_t *)c->cl_nc, (const int32_t *)cl_ptr, c->cl_nc + CL_UNSORTED, cl_members);
   return hipGetLastError();
 }
 
@@ -354,13 +460,16 @@ __global__ void k_cl_ptr(int64_t n, const int32_t *__restrict__ flag, const int6
   if (blockIdx.x == 0 && threadIdx.x == 0) cl_ptr[pos[n]] = (int32_t)n;
 }
 
-// Labels outside [0, n) cannot index a count: (label, index) sorted by the
-// low bits that labels of n particles need, neighbours of different label
-// split, as such labels were always treated.
-static hipError_t clusters_sorted(p3t_ctx *c, int64_t n, const int32_t *label, int32_t *cl_ptr, int32_t *cl_members,
-                                  int64_t *n_clusters) {
+// sorted keys (label, index) to members
+__global__ void k_cl_members(int64_t n, const uint64_t *__restrict__ key, int32_t *__restrict__ members) {
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
+    members[k] = (int32_t)(key[k] & 0xffffffffull);
+}
+
+// (label, index) sorted by the low bits that labels of n particles need, in
+// c->cl_keys or c->cl_keys_alt
+static hipError_t sort_labels(p3t_ctx *c, int64_t n, const int32_t *label, uint64_t **sorted) {
   hipStream_t s = c->stream;
-  hipError_t e;
   hipLaunchKernelGGL(k_cl_keys, dim3(g1d(n)), dim3(256), 0, s, n, label, c->cl_keys);
   int bits = 1;
   while ((int64_t(1) << bits) < n) ++bits;
@@ -368,8 +477,27 @@ static hipError_t clusters_sorted(p3t_ctx *c, int64_t n, const int32_t *label, i
   // label bits alone orders by (label, index)
   uint64_t *k = c->cl_keys, *ka = c->cl_keys_alt;
   int32_t *v = nullptr, *va = nullptr;
-  if ((e = radix_sort_pairs(k, v, ka, va, n, 32, 32 + bits, c->radix_hist, c->radix_hist_cap, false, s)) != hipSuccess)
-    return e;
+  const hipError_t e = radix_sort_pairs(k, v, ka, va, n, 32, 32 + bits, c->radix_hist, c->radix_hist_cap, false, s);
+  *sorted = k;
+  return e;
+}
+
+hipError_t members_sorted(p3t_ctx *c, int64_t n, const int32_t *label, int32_t *cl_members) {
+  uint64_t *k = nullptr;
+  const hipError_t e = sort_labels(c, n, label, &k);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_cl_members, dim3(g1d(n)), dim3(256), 0, c->stream, n, (const uint64_t *)k, cl_members);
+  return hipGetLastError();
+}
+
+// Labels outside [0, n) cannot index a count: sorted, neighbours of different
+// label split, as such labels were always treated.
+static hipError_t clusters_sorted(p3t_ctx *c, int64_t n, const int32_t *label, int32_t *cl_ptr, int32_t *cl_members,
+                                  int64_t *n_clusters) {
+  hipStream_t s = c->stream;
+  hipError_t e;
+  uint64_t *k = nullptr;
+  if ((e = sort_labels(c, n, label, &k)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_cl_flags, dim3(g1d(n)), dim3(256), 0, s, n, k, cl_members, c->cl_slot);
   if ((e = scan_i32_to_i64(c->cl_slot, c->node_scan, n, c->scan_tmp, c->scan_tmp_cap, s)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_cl_ptr, dim3(g1d(n)), dim3(256), 0, s, n, c->cl_slot, c->node_scan, cl_ptr);
@@ -384,23 +512,24 @@ hipError_t clusters_csr(p3t_ctx *c, int64_t n, const int32_t *label, int32_t *cl
                         int64_t *n_clusters) {
   hipStream_t s = c->stream;
   hipError_t e;
-  // c->cl_nc[1]: a label was out of range
-  hipLaunchKernelGGL(k_cl_count, dim3(g1d(n)), dim3(256), 0, s, n, label, c->cl_cnt, c->cl_slot, c->cl_nc + 1);
+  count_labels<CL_ANY>(c, n, const_cast<int32_t *>(label));  // (read only)
   scan_items<CL_ANY>(c, n, nullptr, c->cl_cnt, cl_ptr, cl_members, c->cl_nc, nullptr, 0);
   hipLaunchKernelGGL(k_cl_fill<CL_ANY>, dim3(g1d(n)), dim3(256), 0, s, n, label, (const int32_t *)c->cl_start,
-                     (const int32_t *)c->cl_slot, cl_members);
+                     (const int32_t *)c->cl_slot, (const int64_t *)c->cl_nc + CL_UNSORTED, cl_members);
   hipLaunchKernelGGL(k_cl_sort, dim3((unsigned)((n + CS_T - 1) / CS_T)), dim3(CS_T), 0, s, n,
-                     (const int64_t *)c->cl_nc, (const int32_t *)cl_ptr, label, cl_members);
+                     (const int64_t *)c->cl_nc, (const int32_t *)cl_ptr, c->cl_nc + CL_UNSORTED, cl_members);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   int64_t *h = c->host_words;
-  if ((e = hipMemcpyAsync(h, c->cl_nc, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
+  if ((e = hipMemcpyAsync(h, c->cl_nc, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-  if (h[1]) {
-    if ((e = fill_i32(reinterpret_cast<int32_t *>(c->cl_nc + 1), 0, 2, s)) != hipSuccess) return e;
+  *n_clusters = h[0];
+  if (h[CL_BAD]) {
+    if ((e = fill_i32(reinterpret_cast<int32_t *>(c->cl_nc + CL_BAD), 0, 2, s)) != hipSuccess) return e;
     return clusters_sorted(c, n, label, cl_ptr, cl_members, n_clusters);
   }
-  *n_clusters = h[0];
-  return hipSuccess;
+  if (!h[CL_UNSORTED]) return hipSuccess;
+  if ((e = members_sorted(c, n, label, cl_members)) != hipSuccess) return e;
+  return hipStreamSynchronize(s);
 }
 
 }  // namespace p3t

@@ -220,10 +220,10 @@ __device__ __forceinline__ T wave_max(T v) {
 // Hermite bucket-count words (hermite.hip): [0, 11) the buckets, [11, 21)
 // the parked clusters of buckets 0..9, the parked member count, [22, 25)
 // the clusters of buckets 1..3 with a close pair (listed at the end of
-// their bucket's list, apart from the others), then the cluster count and
-// the malformed-input flag.
+// their bucket's list, apart from the others), then the cluster count, the
+// malformed-input flag and the flag of members that are not in order.
 constexpr int HERM_BC_PARK0 = 11, HERM_BC_PARKED = 21, HERM_BC_CLOSE0 = 22, HERM_BC_NC = 28, HERM_BC_BAD = 29,
-              HERM_BC_WORDS = 32;
+              HERM_BC_UNSORTED = 30, HERM_BC_WORDS = 32;
 constexpr int HERM_N_BUCKETS = 11;
 // A neighbour pair counts as close when its free-fall time scale
 // sqrt(r^3 / G(m_i + m_j)) is below dt_soft / CLOSE_RATIO: nearly every
@@ -348,10 +348,10 @@ struct p3t_ctx {
   int64_t scan_tmp_cap = 0;
   int32_t *row_cnt = nullptr;       // per-particle counters (n)
   int32_t *uf_parent = nullptr;     // union-find parents (n), complete with the pairs of the last evaluation
-  int32_t *cl_cnt = nullptr;        // members per label (n; zero between calls, as row_cnt is)
+  int32_t *cl_cnt = nullptr;        // members per label (label_counters_need; zero between calls, as row_cnt is)
   int32_t *cl_slot = nullptr;       // slot of each member in its cluster (n)
   int32_t *cl_start = nullptr;      // first slot of each label's cluster (n)
-  int64_t *cl_nc = nullptr;         // cluster count, out-of-range flag of p3t_clusters
+  int64_t *cl_nc = nullptr;         // cluster count, out-of-range and unsorted flags (nbr.hip)
   uint64_t *cl_sums = nullptr;      // scan scratch (scan_sums_need)
   int64_t *host_words = nullptr;    // pinned host memory: the device counters, small results
   uint64_t *cl_keys = nullptr, *cl_keys_alt = nullptr;  // cluster sort keys (n)
@@ -466,9 +466,13 @@ hipError_t soft_force(p3t_ctx *c, int64_t n_groups, double *acc3, bool frozen = 
 
 // nbr.hip
 int64_t scan_sums_need();
+int64_t label_counters_need(int64_t n_cap);
 hipError_t neighbour_csr(p3t_ctx *c, int64_t n, int64_t np, int64_t *row_ptr, int32_t *col, int32_t *label);
 hipError_t clusters_pairs(p3t_ctx *c, int64_t n, int32_t *label, int32_t *cl_ptr, int32_t *cl_members,
                           int32_t *clear, int n_clear);
+// the members of the clusters of label in ascending order (their cl_ptr is
+// known), for clusters_pairs with HERM_BC_UNSORTED set
+hipError_t members_sorted(p3t_ctx *c, int64_t n, const int32_t *label, int32_t *cl_members);
 hipError_t clusters_csr(p3t_ctx *c, int64_t n, const int32_t *label, int32_t *cl_ptr, int32_t *cl_members,
                         int64_t *n_clusters);
 
