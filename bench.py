@@ -198,7 +198,7 @@ def kernel_rooflines(out, stage, steps, precision):
     the near, far and cell lists: its algorithmic flops (interactions x flops
     per interaction) over its event-timed average launch duration."""
     fp32 = precision == 1
-    ms = stage["ms_near"] / steps
+    ms = sum(stage[k] for k in ("ms_near", "ms_far", "ms_cell", "ms_cand")) / steps
     if ms <= 0.0:
         return {}
     flops = (out["n_near"] * (FLOPS_NEAR_MIXED if fp32 else FLOPS_NEAR) + out["n_far"] * FLOPS_FAR +

@@ -92,10 +92,10 @@ typedef struct {
   int64_t n_pairs;      /* neighbour pairs found (directed, = nnz) */
   int64_t list_entries; /* total interaction-list entries (near + far + cells) */
   double ms_cutoffs, ms_tree, ms_walk, ms_force, ms_neighbour, ms_hermite; /* event-timed phases */
-  /* the force phase by launch (split form; zero for the fused kernel):
-     ms_near the launch over the near, far and cell lists with the exact
-     neighbour test of the candidates (ms_far, ms_cell and ms_cand are zero:
-     they share it) */
+  /* the force phase by class (split form; zero for the fused kernel): near
+     particles with the changeover, far particles, cells, exact neighbour test
+     of the candidates.  They share one launch, whose time is divided in the
+     proportion of the cycles that its wavefronts spent on each */
   double ms_near, ms_far, ms_cell, ms_cand;
   int32_t timing;       /* 1 if the phase times above were measured */
   int32_t n_slow;       /* members of slow clusters in the last p3t_hard_evaluate */

@@ -412,7 +412,7 @@ hipError_t soft_kick_adjoint(p3t_ctx *c, double h, const double *lam_v3, double 
   A.G = c->P.G;
   A.gamma = c->P.gamma;
   A.inv1mg = 1.0 / (1.0 - c->P.gamma);
-  A.queue = &c->cnt->queue[0];
+  A.queue = &c->cnt->queue;
   const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)c->n_cu * 8, (2 * n + 255) / 256));
   hipLaunchKernelGGL(k_adj_prep, dim3(g), dim3(256), 0, s, A, lam_v3);
   if (c->P.precision == 1)

@@ -733,13 +733,15 @@ bool eval_finish(p3t_ctx *c, const DevCounters &h, unsigned *num, p3t_status *st
       }
       c->stats.ms_walk = ev_ms(c, 4, 5);
       c->stats.ms_force = ev_ms(c, 5, 6);
-      if (c->fcfg.split) {
-        // one launch for the three classes and the neighbour test
-        c->stats.ms_near = ev_ms(c, 5, 11);
-        c->stats.ms_far = c->stats.ms_cell = c->stats.ms_cand = 0.0;
-      } else {
-        c->stats.ms_near = c->stats.ms_far = c->stats.ms_cell = c->stats.ms_cand = 0.0;
-      }
+      // one launch for the three classes and the neighbour test: its time in
+      // the proportion of the cycles that its wavefronts spent on each
+      double cycles = 0.0;
+      for (unsigned long long q : h.force_clk) cycles += (double)q;
+      const double ms = c->fcfg.split && cycles > 0.0 ? ev_ms(c, 5, 11) / cycles : 0.0;
+      c->stats.ms_near = ms * (double)h.force_clk[0];
+      c->stats.ms_far = ms * (double)h.force_clk[1];
+      c->stats.ms_cell = ms * (double)h.force_clk[2];
+      c->stats.ms_cand = ms * (double)h.force_clk[3];
     }
     c->tree_timing_pending = 0;
   }

@@ -443,6 +443,7 @@ hipError_t soft_force(p3t_ctx *c, int64_t n_groups_max, double *acc3, bool froze
   A.persistent = c->force_persistent;
   A.ngroups_bound = (int)std::min<int64_t>(n_groups_max, INT32_MAX);
   A.queue = &c->cnt->force_queue;
+  A.clk = nullptr;
   unsigned grid = A.persistent ? (unsigned)c->force_slots : (unsigned)std::max<int64_t>(1, n_groups_max);
   if (c->fcfg.split) return soft_force_split(c, A, (unsigned)std::max<int64_t>(1, n_groups_max), acc3);
   const int ipl = P.n_group_max > WAVE ? 2 : 1;

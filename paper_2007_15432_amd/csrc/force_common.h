@@ -28,6 +28,7 @@ struct ForceArgs {
   unsigned long long *queue;  // persistent-queue head of this launch
   uint8_t *close;             // caller's order: set for both members of a close neighbour pair (nullable)
   double close_k;             // G dt_soft^2 / CLOSE_RATIO^2
+  unsigned long long *clk;    // cycles by class, split form (nullable: not taken)
 };
 
 // Flags both members of the neighbour pair (i, j) (sorted indices) when

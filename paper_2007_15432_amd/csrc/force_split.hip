@@ -37,6 +37,16 @@ namespace p3t {
 
 namespace {
 
+// The time of the force phase by class, where it is asked for (A.clk): each
+// wavefront's cycles in the near, far and cell loops and in the candidate
+// tests, added per workgroup in LDS.  The host divides the launch's time in
+// their proportion.
+enum { CLK_NEAR, CLK_FAR, CLK_CELL, CLK_CAND, CLK_N };
+
+__device__ __forceinline__ unsigned long long clk_now(const ForceArgs &A) {
+  return A.clk ? (unsigned long long)__builtin_readcyclecounter() : 0ull;  // uniform
+}
+
 struct GroupHdr {
   long long off;
   int n_cell, n_near, n_far, first, count;
@@ -203,7 +213,8 @@ __device__ __forceinline__ unsigned low_bits(int k) { return k >= 32 ? ~0u : k <
 // positions (multiples of WAVE), added to (ax, ay, az).
 template <bool MIXED, int IPL, int UNR, bool HALF>
 __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h, NearTile &T, int lane, int from,
-                                           int step, CandQueue &Q, double *ax, double *ay, double *az) {
+                                           int step, CandQueue &Q, double *ax, double *ay, double *az,
+                                           unsigned long long &cand) {
   int ii[IPL];
   int nq = 0;  // candidates waiting, fewer than 64 between tiles
   double xi[IPL], yi[IPL], zi[IPL], invi[IPL], rch2[IPL];
@@ -366,7 +377,9 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
           nq += (int)__popcll(bal);
           if (nq >= WAVE) {
             tile_sync();
+            const unsigned long long c0 = clk_now(A);
             test_candidates(A, Q, WAVE, lane);
+            cand += clk_now(A) - c0;
             const int2 rest = Q.e[WAVE + lane];
             tile_sync();
             Q.e[lane] = rest;
@@ -378,7 +391,9 @@ __device__ __forceinline__ void near_group(const ForceArgs &A, const GroupHdr &h
   }
   if (nq > 0) {
     tile_sync();
+    const unsigned long long c0 = clk_now(A);
     test_candidates(A, Q, nq, lane);
+    cand += clk_now(A) - c0;
   }
 }
 
@@ -682,14 +697,24 @@ __device__ __forceinline__ double other_half_add(double a) {
 
 template <bool MIXED, bool QUAD, int IPL, int UNR, int W, bool HALF = false>
 __device__ __forceinline__ void all_group(const ForceArgs &A, const GroupHdr &h, ForceTile *T, CandQueue *Q,
-                                          int lane, int w) {
+                                          unsigned long long *clk, int lane, int w) {
   double ax[IPL] = {}, ay[IPL] = {}, az[IPL] = {};
   const int nt = (h.n_near + WAVE - 1) / WAVE, ft = (h.n_far + WAVE - 1) / WAVE;
   // first far / cell tile of wavefront w: the tiles are numbered through
   const int f0 = ((w - nt) % W + W) % W, c0 = ((w - nt - ft) % W + W) % W;
-  near_group<MIXED, IPL, UNR, HALF>(A, h, T[w].near, lane, WAVE * w, WAVE * W, Q[w], ax, ay, az);
+  unsigned long long cand = 0;
+  const unsigned long long t0 = clk_now(A);
+  near_group<MIXED, IPL, UNR, HALF>(A, h, T[w].near, lane, WAVE * w, WAVE * W, Q[w], ax, ay, az, cand);
+  const unsigned long long t1 = clk_now(A);
   far_group<MIXED, IPL, UNR, HALF>(A, h, T[w].far, lane, WAVE * f0, WAVE * W, ax, ay, az);
+  const unsigned long long t2 = clk_now(A);
   cell_group<MIXED, QUAD, IPL, UNR, HALF>(A, h, T[w].cell, lane, WAVE * c0, WAVE * W, ax, ay, az);
+  if (A.clk && lane == 0) {
+    atomicAdd(&clk[CLK_NEAR], t1 - t0 - cand);
+    atomicAdd(&clk[CLK_FAR], t2 - t1);
+    atomicAdd(&clk[CLK_CELL], clk_now(A) - t2);
+    atomicAdd(&clk[CLK_CAND], cand);
+  }
   tile_sync();
 #pragma unroll
   for (int s = 0; s < IPL; ++s) {
@@ -730,7 +755,12 @@ template <bool MIXED, bool QUAD, int UNR, int W>
 __global__ __launch_bounds__(WAVE *W, min_waves(UNR, MIXED, W)) void k_force_all(ForceArgs A) {
   __shared__ ForceTile T[W];
   __shared__ CandQueue Q[W];
+  __shared__ unsigned long long clk[CLK_N];
   __shared__ int next;
+  if (A.clk) {  // uniform
+    if (threadIdx.x < CLK_N) clk[threadIdx.x] = 0ull;
+    __syncthreads();
+  }
   const int lane = threadIdx.x & (WAVE - 1), w = uniform_first(threadIdx.x / WAVE);
   const int ngroups = uniform_first(min((int)A.cnt->n_groups, A.ngroups_bound));
   unsigned long long nn = 0, nf = 0, nc = 0;  // this workgroup's interactions, added once at its end
@@ -748,13 +778,13 @@ __global__ __launch_bounds__(WAVE *W, min_waves(UNR, MIXED, W)) void k_force_all
     GroupHdr h;
     if (!group_header(A, gi, h)) continue;
     if (!MIXED && W == 4 && h.count > WAVE && h.count <= 96)
-      all_group<false, QUAD, 3, UNR, W, true>(A, h, T, Q, lane, w);
+      all_group<false, QUAD, 3, UNR, W, true>(A, h, T, Q, clk, lane, w);
     else if (!MIXED && W == 4 && h.count <= 32)
-      all_group<false, QUAD, 1, UNR, W, true>(A, h, T, Q, lane, w);
+      all_group<false, QUAD, 1, UNR, W, true>(A, h, T, Q, clk, lane, w);
     else if (h.count > WAVE)
-      all_group<MIXED, QUAD, 2, UNR, W>(A, h, T, Q, lane, w);
+      all_group<MIXED, QUAD, 2, UNR, W>(A, h, T, Q, clk, lane, w);
     else
-      all_group<MIXED, QUAD, 1, UNR, W>(A, h, T, Q, lane, w);
+      all_group<MIXED, QUAD, 1, UNR, W>(A, h, T, Q, clk, lane, w);
     const unsigned long long ni = (unsigned long long)h.count;
     nn += ni * (unsigned long long)h.n_near - ni;
     nf += ni * (unsigned long long)h.n_far;
@@ -764,6 +794,10 @@ __global__ __launch_bounds__(WAVE *W, min_waves(UNR, MIXED, W)) void k_force_all
     if (nn) atomicAdd(&A.cnt->n_near, nn);
     if (nf) atomicAdd(&A.cnt->n_far, nf);
     if (nc) atomicAdd(&A.cnt->n_cell, nc);
+  }
+  if (A.clk) {  // uniform
+    __syncthreads();
+    if (threadIdx.x < CLK_N) atomicAdd(&A.clk[threadIdx.x], clk[threadIdx.x]);
   }
 }
 
@@ -803,7 +837,8 @@ void launch_all(p3t_ctx *c, const ForceArgs &A, unsigned nonpersistent_grid) {
 template <int UNR>
 hipError_t launch_split(p3t_ctx *c, ForceArgs A, unsigned nonpersistent_grid, double *acc3) {
   A.acc = acc3;
-  A.queue = &c->cnt->queue[0];
+  A.queue = &c->cnt->queue;
+  A.clk = c->timing ? c->cnt->force_clk : nullptr;
   const int64_t groups = c->n / std::max(1, 2 * c->P.n_group_max / 3);
   if (groups < kGroupsWide)
     launch_all<UNR, 8>(c, A, nonpersistent_grid);

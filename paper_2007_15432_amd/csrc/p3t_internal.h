@@ -57,10 +57,10 @@ struct DevCounters {
   unsigned long long n_groups;     // interaction groups
   unsigned long long force_queue;  // persistent force kernel queue head
   unsigned long long n_near, n_far, n_cell;  // interaction counts
-  unsigned long long n_clusters;
   unsigned long long n_chunks;     // subtree roots of the bottom-up moment pass
   unsigned long long n_top;        // nodes above them
-  unsigned long long queue[3];    // persistent queues of the split force kernels
+  unsigned long long queue;       // persistent queue of the split force kernel and the adjoint
+  unsigned long long force_clk[4];  // wavefront cycles of the split force: near, far, cells, candidate tests
   unsigned long long n_pairs_d;   // pairs of the parked members' direct terms (p3t_hard_evaluate)
   unsigned long long n_unbound;   // orbits that are not bound (p3t_kepler_drift)
   unsigned long long n_bad_index; // list entries outside [0, n) (p3t_kepler_drift)

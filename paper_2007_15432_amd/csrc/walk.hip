@@ -234,7 +234,8 @@ __global__ void k_reset_queues(DevCounters *cnt, unsigned long long *__restrict_
   if (t0 < WALK_PARTS) queues[t0 * WALK_QUEUE_STRIDE] = 0;
   if (t0 != 0) return;
   cnt->force_queue = 0;
-  for (int k = 0; k < 3; ++k) cnt->queue[k] = 0;
+  cnt->queue = 0;
+  for (int k = 0; k < 4; ++k) cnt->force_clk[k] = 0;
   cnt->pool_cursor = 0;
   cnt->n_pairs = 0;
   cnt->n_near = 0;
