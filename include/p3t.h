@@ -397,7 +397,9 @@ p3t_status p3t_set_timing(p3t_ctx *ctx, int32_t on);
                       candidates tested 64 at a time; 0: one fused kernel.
      force_unroll     j-loop unroll of the split kernels: 1, 2, 4 or 8.
      force_persistent 1: persistent grids that take groups from a queue in
-                      longest-list-first order; 0: one workgroup per group.
+                      longest-list-first order; 0: a workgroup per group
+                      (several groups each where there are many more groups
+                      than n / (2/3 n_group_max)).
      waves_per_cu     persistent grid of the split kernels in wavefronts per
                       compute unit (1..64; capped by the kernel's occupancy).
      walk_waves_per_cu persistent grid of the walk (1..64).
