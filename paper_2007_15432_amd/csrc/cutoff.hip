@@ -195,7 +195,9 @@ __global__ __launch_bounds__(CUT_BT) void k_cut_bins(CutIn I, const double *__re
       __syncthreads();
     }
   }
-  const int L = CUT_BT / nbins;  // threads per bin (at least four)
+  // threads per bin, at least four; their partials are added one after another,
+  // so no more than 64 (one bin, 1,000 particles: 41 -> 32 us a call)
+  const int L = CUT_BT / nbins < WAVE ? CUT_BT / nbins : WAVE;
   const int k = t / L, q0 = t - k * L;
   double s = 0.0;
   if (k < nbins)
