@@ -71,7 +71,12 @@ hipError_t dev_alloc(T *&p, int64_t count) {
     if (e != hipSuccess) return e;
   }
   if (count <= 0) count = 1;
-  return hipMalloc((void **)&p, (size_t)count * sizeof(T));
+  const hipError_t e = hipMalloc((void **)&p, (size_t)count * sizeof(T));
+  if (e != hipSuccess) {
+    p = nullptr;
+    (void)hipGetLastError();  // reported by the caller, not by the next launch
+  }
+  return e;
 }
 
 // (re)allocate the arena for n_cap particles
@@ -508,9 +513,10 @@ p3t_status p3t_reserve(p3t_ctx *c, int64_t n_max, int64_t nnz_max) {
   // the pairs first, once, at the size asked for (ensure_lists gives them at least 2 n)
   const int64_t pairs = std::max(nnz_max, c->pairs ? int64_t(0) : std::max<int64_t>(1 << 16, 2 * n_max));
   if (pairs > c->pair_cap) {
+    c->force_valid = false;  // the pairs are gone, also if there is no room for the new ones
+    c->pair_cap = 0;
     HIP_OK(c, dev_alloc(c->pairs, pairs));
     c->pair_cap = pairs;
-    c->force_valid = false;
   }
   p3t_status st = ensure_n(c, n_max);
   if (st != P3T_OK) return st;
