@@ -173,6 +173,9 @@ p3t_status alloc_arena(p3t_ctx *c, int64_t n_cap) {
   // zero between calls: every pass that counts into them leaves them clear
   const size_t clear = (size_t)((char *)(c->cl_nc + 3) - (char *)c->cnt);
   HIP_OK(c, hipMemsetAsync(c->cnt, 0, clear, c->stream));
+  if (!c->clear_ev) HIP_OK(c, hipEventCreateWithFlags(&c->clear_ev, hipEventDisableTiming));
+  HIP_OK(c, hipEventRecord(c->clear_ev, c->stream));
+  c->clear_pending = 1;
   c->n_cap = n_cap;
   c->tree_valid = c->force_valid = false;
   c->park_flags_valid = 0;
@@ -478,6 +481,7 @@ p3t_status p3t_destroy(p3t_ctx *c) {
     if (e) (void)hipEventDestroy(e);
   for (auto &e : c->prep_ev)
     if (e) (void)hipEventDestroy(e);
+  if (c->clear_ev) (void)hipEventDestroy(c->clear_ev);
   if (c->host_words) (void)hipHostFree(c->host_words);
   delete c;
   return P3T_OK;
@@ -487,7 +491,22 @@ p3t_status p3t_set_stream(p3t_ctx *c, void *stream) {
   if (!c) return P3T_ERR_ARG;
   // a pending cluster preparation stays valid: every later call makes the
   // (new) stream wait for it before using its scratch
-  c->stream = (hipStream_t)stream;
+  const hipStream_t s = (hipStream_t)stream;
+  if (s != c->stream && c->clear_pending) {
+    // the counters of the arena may still have to be cleared on the stream it
+    // was allocated on: this one waits for that (the host, if it cannot)
+    const hipError_t q = hipEventQuery(c->clear_ev);
+    if (q == hipSuccess)
+      c->clear_pending = 0;
+    else {
+      (void)hipGetLastError();
+      if (hipStreamWaitEvent(s, c->clear_ev, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        HIP_OK(c, hipEventSynchronize(c->clear_ev));
+      }
+    }
+  }
+  c->stream = s;
   return P3T_OK;
 }
 

@@ -273,6 +273,8 @@ struct p3t_ctx {
 
   // arena (particles, tree, groups, scratch) and separately grown buffers
   p3t::Arena arena;
+  hipEvent_t clear_ev = nullptr;    // the arena's counters are clear
+  int clear_pending = 0;            // that event has not been seen to have happened
   int32_t *pool = nullptr;          // list pool
   int32_t *slot_lists = nullptr;    // walk temp lists (walk_slots * 3 * slot_cap_list)
   int32_t *slot_stack = nullptr;    // walk stacks (walk_slots * slot_cap_stack)
