@@ -1684,8 +1684,10 @@ constexpr int N_CATS = N_BUCKETS + 3;
 constexpr int BK_T = 256;
 
 // Bucket lists in one launch: a workgroup takes 256 BK_I clusters (one per
-// thread up to 2^18 clusters, so that a small batch still fills the chip; four
-// above, where the atomics on the counters add up), counts them
+// thread up to 2^16 clusters, so that a small batch still fills the chip; four
+// above, where the atomics on the counters add up: hard part of single
+// particles, one against four, 65,536 clusters 37 and 38 us, 131,072 42 and 41,
+// 262,144 51 and 46, 2^20 104 and 73), counts them
 // per category in LDS, reserves its share of every list with one atomic per
 // category and writes its entries (in cluster order within the chunk; the
 // order between chunks, on which nothing but the dispatch order depends, is
@@ -1831,7 +1833,7 @@ hipError_t herm_bucket_enqueue(p3t_ctx *c, hipStream_t s, int64_t n, int64_t nc,
   auto go = [&](auto kernel, int chunk) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)std::max<int64_t>(1, (nc + chunk - 1) / chunk)), dim3(BK_T), 0, s, B);
   };
-  if (nc <= (1 << 18))
+  if (nc <= (1 << 16))
     go(k_bucket<1>, BK_T);
   else
     go(k_bucket<4>, 4 * BK_T);

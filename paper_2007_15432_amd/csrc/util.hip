@@ -121,20 +121,24 @@ hipError_t scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, int64_t *
 // The pass's tile histogram (hist[tile][digit]) is complete when it starts.
 // Up to RS_CHAIN keys the pass before, which knows where each key lands, adds
 // the key's next digit to it (the first one comes with the keys): one launch
-// per pass.  More keys make that an atomic per key too many (2^20 keys: 41 us a
-// pass), and a launch of its own counts each tile in LDS.  Up to RS_SELF tiles
-// every workgroup sums the histogram's columns itself (256 rows of 1 KB, 3 us);
-// more tiles take one launch more per pass that scans the columns.
-//   48-bit keys with values, all passes (one histogram, one column or row scan
-// and one scatter per pass of 2048-key tiles before): 2048 keys 82 -> 34 us,
-// 65,536 116 -> 47, 262,144 105 -> 85, 2^20 144 -> 119.
+// per pass.  More keys make that an atomic per key too many, and a launch of its
+// own counts each tile in LDS.  Up to RS_SELF tiles every workgroup sums the
+// histogram's columns itself (256 rows of 1 KB, 3 us); more tiles take one
+// launch more per pass that scans the columns.
+//   48-bit keys with values, all passes, us: 2,048 keys 34, 65,536 46, 262,144
+// 68, 2^20 118 (one histogram, one column or row scan and one scatter per pass of
+// 2048-key tiles: 82, 116, 105, 144).  The lines, both sides in us: chained
+// against counted 65,537 keys 46 and 50, 98,304 62 and 61, 131,072 60 and 55;
+// columns summed against scanned 2^20 118 and 135, 1,250,000 159 and 158, 2^21
+// 204 and 187; tiles below.
 constexpr int RS_T = 1024, RS_W = RS_T / WAVE;
 constexpr int RS_SELF = 256;
-constexpr int64_t RS_CHAIN = 1 << 18;
+constexpr int64_t RS_CHAIN = 3 << 15;
 
-// keys per thread: tiles of 1024 keys keep 65,536 keys on 64 workgroups, tiles
-// of 4096 keep the columns of 2^20 keys at RS_SELF rows
-static int radix_items(int64_t n) { return n <= (1 << 16) ? 1 : n <= (1 << 18) ? 2 : 4; }
+// keys per thread: small tiles while the chip is not full (tiles of 1024, 2048
+// and 4096 keys: 131,072 keys 55, 59 and 83 us, 262,144 72, 68 and 80, 2^19 -, 89
+// and 93), and at most RS_SELF of them up to 2^20 keys
+static int radix_items(int64_t n) { return n <= (1 << 17) ? 1 : n <= (1 << 19) ? 2 : 4; }
 
 RadixPlan radix_plan(int64_t n) {
   RadixPlan p;
