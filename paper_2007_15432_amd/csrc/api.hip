@@ -249,8 +249,8 @@ CloseSrc close_src(p3t_ctx *c) {
 // hard part: labels from the union-find that the evaluation filled, the
 // cluster CSR and the bucket words (copied to pinned host memory).  It runs
 // while the host reads the counters and enqueues the kicks and radii that
-// follow; eval_finish keeps it (prep_confirm) when the
-// evaluation needs no retry.  p3t_hard_step / p3t_hard_evaluate take the
+// follow; eval_finish keeps it (prep_state 1) when the evaluation needs no
+// retry.  p3t_hard_step / p3t_hard_evaluate take the
 // result instead of computing it.
 p3t_status prep_enqueue(p3t_ctx *c) {
   const int64_t n = c->n;
@@ -616,7 +616,7 @@ p3t_status grow_for_retry(p3t_ctx *c, const DevCounters &h) {
     if ((int64_t)h.n_pairs > c->pair_cap) {
       const int64_t cap = (int64_t)h.n_pairs + (int64_t)h.n_pairs / 4 + 1024;
       HIP_OK(c, dev_alloc(c->pairs, cap));
-        c->pair_cap = cap;
+      c->pair_cap = cap;
     }
   }
   return P3T_OK;

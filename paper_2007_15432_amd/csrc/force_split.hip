@@ -29,8 +29,9 @@
 //
 // Bound by VALU issue.  One launch instead of one per class and a scatter:
 // the i-particles are read once, the sums written once, and the classes fill
-// each other's tails; tree + walk + force at 2^20 particles 2069 -> 1818 us
-// mixed, 2509 -> 2299 us FP64, at 65,536 592 -> 447 and 658 -> 473.
+// each other's tails; by itself this took tree + walk + force at 2^20 particles
+// from 2069 to 1818 us mixed and 2509 to 2299 us FP64, at 65,536 from 592 to 447
+// and 658 to 473 (now FORCE20).
 #include "force_common.h"
 
 namespace p3t {

@@ -1623,8 +1623,8 @@ __global__ __launch_bounds__(BIG_T) void k_herm_big(HermArgs A, int bk) {
   __shared__ double lds[8][BIG_T * MPT];
   __shared__ int64_t shi[BIG_T / WAVE];
   __shared__ double shd[BIG_T / WAVE];
-  // the lane-parallel partner loop needs 6.6 KB more LDS, which the
-  // 1024-member variant does not have within 64 KB per workgroup
+  // the lane-parallel partner loop needs 6.6 KB more LDS; the variant for 513
+  // to 1024 members does without (it has not been tried there)
   constexpr int NACT = MPT <= 2 ? BIG_ACT : 1;
   __shared__ int act[NACT];
   __shared__ double res[6 * NACT];

@@ -315,7 +315,7 @@ struct p3t_ctx {
   int tree_timing_pending = 0;  // the last tree build recorded its events
   int graphed = 0;            // the last evaluation replayed the captured graph
   struct {
-    int split = 1;         // 1: one kernel per interaction class, 0: the fused kernel
+    int split = 1;         // 1: a loop per interaction class in one launch, 0: the fused kernel
     int unroll = 2;         // j-loop unroll of the split kernel (1, 2, 4, 8)
     int waves_per_cu = 16;  // its persistent grid: waves per CU (capped by occupancy)
   } fcfg;

@@ -19,15 +19,20 @@
 // per-wavefront device memory behind them for the groups that need more.  Every
 // write is bounds-checked; an overflow marks the group (offset -1) and sets a
 // status bit so that the host can grow and retry.
-//   Bound by a chain of about 30 frontiers per group, each the load of up to
-// 64 scattered node records and some 200 VALU instructions (more wavefronts
-// per CU than eight change nothing).  With the stack and lists in device
-// memory, a store waited for per frontier, and the particles written one by
-// one to a scratch list first, 2^20 particles took 359 us, 65,536 65, 2048
-// 43; now 199, 31 and 16.  The groups are dealt in eight contiguous
-// parts of the Morton order, a part to the workgroups of one XCD (blockIdx mod
-// 8), whose L2 then serves one region of the tree; a wavefront whose part is
-// done takes groups of the others.
+//   A group is a chain of about 30 frontiers, each the load of up to 64
+// scattered node records and some 200 VALU instructions.  Up to about six
+// wavefronts per CU the latency of that chain bounds the walk (2^20 particles,
+// with the order of the groups: 757 us with one, 414 with two, 252 with four,
+// 220 with six), beyond that the throughput of the node tests: 211 with eight or
+// ten, and with half the LDS, so that 22 fit instead of 11, 215 with eight, 209
+// with eighteen.  65,536 particles have three groups per CU: the chain alone.
+// With the stack and lists in device memory, a store waited for per frontier,
+// and the particles written one by one to a scratch list first, 2^20 particles
+// took 359 us, 65,536 65, 2048 43; now 199, 31 and 16.
+//   The group list is cut into eight parts, a part to the workgroups of one XCD
+// (blockIdx mod 8), whose L2 then serves one region of the tree: the list is
+// roughly in Morton order (that of the arrival of the workgroups that filled
+// it).  A wavefront whose part is done takes groups of the others.
 #include "p3t_internal.h"
 
 namespace p3t {
