@@ -31,7 +31,8 @@
 // the i-particles are read once, the sums written once, and the classes fill
 // each other's tails; by itself this took tree + walk + force at 2^20 particles
 // from 2069 to 1818 us mixed and 2509 to 2299 us FP64, at 65,536 from 592 to 447
-// and 658 to 473 (now FORCE20).
+// and 658 to 473.  With what came after, here and in the tree, an evaluation is
+// 1.37 ms mixed and 1.69 ms FP64 at 2^20 particles, 0.27 ms mixed at 65,536.
 #include "force_common.h"
 
 namespace p3t {

@@ -83,11 +83,11 @@ __device__ __forceinline__ double rsqrt_pos(double x) {
 
 // 1 / r_out, bounded for r_out = 0.  The pair terms multiply it by factors that
 // vanish beyond the cut-off, and by zeros for a particle with itself: 0 times
-// infinity would be a NaN.  A pair takes the smaller of its two.
-__device__ __forceinline__ double inv_cutoff(double ro) {
-  const double i = 1.0 / ro;
-  return i > 1e300 ? 1e300 : i;
-}
+// infinity would be a NaN.  A pair takes the smaller of its two.  The sum rounds
+// to r_out itself for every radius above 1e-284.  A compare and a select on the
+// quotient gave the Hermite kernels another allocation of registers and a block
+// step at 2^20 particles 3.87 ms instead of 3.79.
+__device__ __forceinline__ double inv_cutoff(double ro) { return 1.0 / (ro + 1e-300); }
 
 __device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)); }
 
